@@ -6,151 +6,396 @@
 // A floating-point comparison decides an integer, so order and precision are part of the definition
 // (the paper gives none; this is the reading the CPU reference follows too): squared Euclidean distance
 // in fp32, elements in ascending order, every subtraction, multiplication and addition rounded on its own
-// (floating-point contraction is switched off for the kernel); strict "<" while walking the entries in
-// ascending order, so ties go to the smallest index.
+// (no fused multiply-add); strict "<" while walking the entries in ascending order, so ties go to the smallest index.
 //
-// One workgroup per (batch, head, chunk of new tokens): the head's codebooks of one side (G * E entries) are
-// staged in LDS (converted to fp32 once when that fits), then L lanes share a (token, sub-vector) item: each
-// walks every L-th entry and the L partial winners are merged by (distance, index).  L = 1 for
-// prefill-sized calls; a decode step (one token) has only D / v items per head, so 8 lanes split the entries.
-#include <type_traits>
-
+// Two kernels with the same codes: kv_quantize_scan_kernel computes every distance (decode steps), and
+// kv_quantize_mfma_kernel lets the matrix cores rule out all but eight entries (prompts).
 #include "vq_common.h"
 
 namespace vq {
-
-constexpr int kQuantTokens = 64;  // new tokens per workgroup (L = 1)
 
 struct KvQuantArgs {
     const half_t *x[2];    // K, V: [B][H][n_new][D]
     const half_t *cb[2];   // [H][G][E][v]
     uint8_t *codes[2];     // [B][H][T][D/v]
-    int H, T, D, v, E, G, n_new, pos;
-    int L, tokens_per_wg;  // lanes per item (power of two <= 64, divides E), tokens per workgroup
-    int both;              // the codebooks of both sides fit LDS together: staged at once, one barrier
-    int par;               // 512 threads, the two sides handled side by side by 256 threads each (needs both)
+    int H, T, D, P, E, G, n_new, pos;
+    int tokens;            // new tokens per workgroup
+    int PG, pg_shift;      // sub-vectors per group of the codebook; its logarithm (matrix-core kernel)
 };
 
-template <int V, bool F32>
-__global__ __launch_bounds__(512) void kv_quantize_kernel(KvQuantArgs a) {
-#pragma clang fp contract(off)  // the distance must not be computed with fused multiply-adds
-    extern __shared__ __align__(16) unsigned char smem[];
-    typedef typename std::conditional<F32, float, half_t>::type cb_t;
-    cb_t *cbl = reinterpret_cast<cb_t *>(smem);
-    const int P = a.D / V;
-    const int bh = blockIdx.x, h = bh % a.H;
-    const int t0 = blockIdx.y * a.tokens_per_wg;
-    const int nt = min(a.tokens_per_wg, a.n_new - t0);
-    const int cb_halves = a.G * a.E * V;
-    const int nthreads = a.par ? 512 : 256;
-    const int tx = threadIdx.x % 256;             // thread within its side
-    const int side0 = a.par ? (int)threadIdx.x / 256 : 0, side1 = a.par ? side0 + 1 : 2;
-    const int L = a.L, sub = tx % L, per_lane = a.E / L;
-    // the lane's part of item `local` of this workgroup: which (token, sub-vector), and its elements
-    struct Item { bool live; int t, p; };
-    auto item_of = [&](int r) {
-        const int item = (r * 256 + tx) / L;
-        Item it;
-        it.live = item < nt * P;
-        it.t = t0 + (it.live ? item / P : 0);
-        it.p = it.live ? item % P : 0;
-        return it;
-    };
-    auto load_x = [&](int side, const Item &it, float (&xv)[V]) {
-        const half_t *xp = a.x[side] + (((size_t)bh * a.n_new + it.t) * a.D) + it.p * V;
-        if constexpr (V == 8) {
-            const V16 x8 = ld16(xp);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) xv[i] = (float)x8.h8[i];
-        } else if constexpr (V == 4) {
-            const V8 x4 = ld8(xp);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) xv[i] = (float)x4.h4[i];
-        } else {
-            const half2_t x2 = *reinterpret_cast<const half2_t *>(xp);
-            xv[0] = (float)x2[0];
-            xv[1] = (float)x2[1];
-        }
-    };
-    // the first item's elements are asked for before the codebooks (they come from further away)
-    float x_first[V];
-    load_x(side0, item_of(0), x_first);
-    auto stage = [&](int side, cb_t *dst) {
-        const half_t *src = a.cb[side] + (size_t)h * cb_halves;
-        if (F32) {
-            for (int i = threadIdx.x; i < cb_halves / 8; i += nthreads) {
-                const V16 e8 = ld16(src + i * 8);
-#pragma unroll
-                for (int k = 0; k < 8; ++k) dst[i * 8 + k] = (cb_t)e8.h8[k];
-            }
-        } else {
-            for (int i = threadIdx.x; i < cb_halves / 8; i += nthreads)
-                reinterpret_cast<uint4 *>(dst)[i] = reinterpret_cast<const uint4 *>(src)[i];
-        }
-    };
-    if (a.both) {
-        stage(0, cbl);
-        stage(1, cbl + cb_halves);
-        __syncthreads();
+// A sub-vector (V halves, aligned) in the low halves of 16 bytes, the rest zero.
+template <int V>
+__device__ __forceinline__ V16 kvq_load(const void *p) {
+    V16 r;
+    if constexpr (V == 8) {
+        r = ld16(p);
+    } else if constexpr (V == 4) {
+        const V8 t = ld8(p);
+        r.u = make_uint4(t.w[0], t.w[1], 0, 0);
+    } else {
+        r.u = make_uint4(*reinterpret_cast<const uint32_t *>(p), 0, 0, 0);
     }
-    for (int side = side0; side < side1; ++side) {
-        const cb_t *cbs = cbl + (a.both ? side * cb_halves : 0);
-        if (!a.both) {
-            __syncthreads();  // the previous side's lookups are done before its codebooks are overwritten
-            stage(side, cbl);
-            __syncthreads();
-        }
-        // all lanes of a wavefront run the same number of rounds (the merge below uses lane shuffles)
-        const int n_items = nt * P, rounds = (n_items * L + 255) / 256;
-        for (int r = 0; r < rounds; ++r) {
-            const Item it = item_of(r);
-            const bool live = it.live;
-            const int t = it.t, p = it.p;
-            float xv[V];
-            if (side == side0 && r == 0) {
+    return r;
+}
+
+// x - c of two pairs of halves in fp32: a fused c * (-1) + x, whose product is exact, so that it rounds once like the
+// subtraction; it takes the halves as they are.
+__device__ __forceinline__ float mix_diff_lo(uint32_t x, uint32_t c) {
+    float r;
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,1]" : "=v"(r) : "v"(c), "v"(x));
+    return r;
+}
+__device__ __forceinline__ float mix_diff_hi(uint32_t x, uint32_t c) {
+    float r;
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,1] op_sel_hi:[1,0,1]" : "=v"(r) : "v"(c), "v"(x));
+    return r;
+}
+
+// The definition's distance of x and c (V halves each).
+template <int V>
+__device__ __forceinline__ float kvq_exact(const V16 &x, const V16 &c) {
+#pragma clang fp contract(off)
+    float d = 0.f;
 #pragma unroll
-                for (int i = 0; i < V; ++i) xv[i] = x_first[i];
-            } else {
-                load_x(side, it, xv);
-            }
-            const cb_t *grp = cbs + (size_t)(p * a.G / P) * a.E * V;
-            // the L lanes of an item take the entries in turn (lane `sub`: sub, sub + L, ...), so that at every
-            // step they read L neighbouring entries: with a block of consecutive entries per lane the L
-            // addresses of a step are 16 * E / L bytes apart, all in the same LDS banks -- an 8-way conflict
-            // that made the walk of a decode step 7 us long.  Each lane still meets its entries in ascending
-            // order, so its strict "<" keeps the smallest index among equals.
-            int best = sub;
-            float best_d = INFINITY;
-#pragma unroll 4
-            for (int k = 0; k < per_lane; ++k) {
-                const int e = sub + k * L;
-                float d = 0.f;
+    for (int i = 0; i < V / 2; ++i) {
+        const float lo = mix_diff_lo(x.w[i], c.w[i]), hi = mix_diff_hi(x.w[i], c.w[i]);
+        const float s0 = lo * lo, s1 = hi * hi;
+        d = i == 0 ? s0 : d + s0;
+        d = d + s1;
+    }
+    return d;
+}
+
+// Smallest value over the wavefront, and the smallest index e among the lanes that hold it (64 lanes active, e < 256
+// with e % 64 == lane): the minimum by lane permutes on the vector ALU, the index from the mask of its holders.
+template <int CTRL>
+__device__ __forceinline__ float dpp_min_step(float x) {
+    const int y = __builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), CTRL, 0xF, 0xF, false);
+    return fminf(x, __int_as_float(y));
+}
+__device__ __forceinline__ int kvq_wave_argmin(float d, int e) {
+    float m = dpp_min_step<0xB1>(d);    // quad_perm [1,0,3,2]
+    m = dpp_min_step<0x4E>(m);          // quad_perm [2,3,0,1]
+    m = dpp_min_step<0x141>(m);         // row_half_mirror
+    m = dpp_min_step<0x140>(m);         // row_mirror: rows of 16 done
+    const int mi = __float_as_int(m);
+    const float m0 = fminf(__int_as_float(__builtin_amdgcn_readlane(mi, 0)), __int_as_float(__builtin_amdgcn_readlane(mi, 16)));
+    const float m1 = fminf(__int_as_float(__builtin_amdgcn_readlane(mi, 32)), __int_as_float(__builtin_amdgcn_readlane(mi, 48)));
+    m = fminf(m0, m1);
+    unsigned long long at = __ballot(d == m);
+    int r = __builtin_amdgcn_readlane(e, __ffsll((long long)at) - 1);
+    for (at &= at - 1; at; at &= at - 1) r = min(r, __builtin_amdgcn_readlane(e, __ffsll((long long)at) - 1));
+    return r;
+}
+
+// Decode steps (few new tokens).  A wavefront takes the sub-vectors of one group: every lane holds four entries of the
+// group's codebook in registers (entry lane + 64 k, straight from memory: nothing is staged, so a codebook that serves a
+// single sub-vector -- coupled quantization -- is read once and used once) and the sub-vectors come one after the other.
+// Bound: the latency of two dependent loads and, per sub-vector, four distances and one reduction over the lanes.  One
+// token of B3 H32 with 32 codebooks per head and side: 5.8 us, where staging both sides' codebooks in LDS took 14.7.
+template <int V>
+__global__ __launch_bounds__(512) void kv_quantize_scan_kernel(KvQuantArgs a) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, NW = blockDim.x >> 6;
+    const int bh = blockIdx.x, h = bh % a.H, side = blockIdx.z;
+    const int t0 = blockIdx.y * a.tokens, nt = min(a.tokens, a.n_new - t0);
+    const half_t *src = a.cb[side] + (size_t)h * a.G * a.E * V;
+    const half_t *xs = a.x[side] + ((size_t)bh * a.n_new + t0) * a.D;
+    uint8_t *dst = a.codes[side] + ((size_t)bh * a.T + a.pos + t0) * a.P;
+    const int n_items = nt * a.PG;                // per group
+    const int R = max(1, NW / a.G);               // wavefronts that share a group
+    for (int u = wave; u < a.G * R; u += NW) {
+        const int g = u / R;
+        V16 c[4];
 #pragma unroll
-                for (int i = 0; i < V; ++i) {
-                    const float diff = xv[i] - (float)grp[e * V + i];
-                    const float sq = diff * diff;
-                    d = i == 0 ? sq : d + sq;  // (0 + sq is sq: the same value as the reference's first addition)
-                }
-                if (d < best_d) {  // strict: the first of equal distances stays
-                    best = e;
-                    best_d = d;
-                }
+        for (int k = 0; k < 4; ++k) c[k] = kvq_load<V>(src + ((size_t)g * a.E + min(lane + 64 * k, a.E - 1)) * V);
+        for (int i = u % R; i < n_items; i += R) {
+            const int t = i / a.PG, p = g * a.PG + (i - t * a.PG);
+            const V16 x = kvq_load<V>(xs + (size_t)t * a.D + p * V);   // the same for all lanes
+            float bd = INFINITY;
+            int be = lane;                        // (nothing is closer than infinity: entry 0, as lane 0 has it)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float d = kvq_exact<V>(x, c[k]);
+                const bool closer = d < bd && lane + 64 * k < a.E;
+                be = closer ? lane + 64 * k : be;
+                bd = closer ? d : bd;
             }
-            // merge the L lanes of the item: smaller distance, then smaller index
-            for (int m = 1; m < L; m <<= 1) {
-                const float od = __shfl_xor(best_d, m, 64);
-                const int oe = __shfl_xor(best, m, 64);
-                if (od < best_d || (od == best_d && oe < best)) {
-                    best_d = od;
-                    best = oe;
-                }
-            }
-            if (live && sub == 0) a.codes[side][((size_t)bh * a.T + a.pos + t) * P + p] = (uint8_t)best;
+            const int code = kvq_wave_argmin(bd, be);
+            if (lane == 0) dst[(size_t)t * a.P + p] = (uint8_t)code;
         }
     }
 }
 
+// Prompt-sized calls.  The scan above spends 14 vector instructions on every (item, entry) pair; here the matrix cores
+// do the pairs and the vector ALU only looks for the minimum.
+//   With h_e = |c_e|^2 / 2 the closest entry minimises s_e = h_e - x.c_e (d = |x|^2 + 2 s).  One
+//   v_mfma_f32_32x32x16_f16 gives s for 32 entries and 32 items: k = 0 .. V - 1 holds A = -c, B = x (both exact), and
+//   k = 8 .. 10 holds h as three halves, scaled by a power of two that B takes back.  Products of two halves are exact in
+//   fp32.  E = 256 entries are 8 of these.
+//   s is not the definition's distance bit for bit, so it only narrows the search: a lane keeps the minimum of each group
+//   of eight entries (the group's number in the four low mantissa bits), the best group and the value of the second best.
+//   If the second best is further away than the error of s can bridge, the definition's winner is in the best group: the
+//   two lanes of the item compute its eight distances as the definition says, four each, and take the smaller (smaller
+//   index on a tie).  Otherwise -- a near tie between groups, or anything not finite, for which the comparison is
+//   false -- the whole codebook is scanned as the definition says.  So the codes are those of the definition, always.
+//   Error bound, in units of |x|^2 + |c|max^2, which bounds every |s|, term and partial sum: 17 products and sums to 2^-23
+//   each, 15 ulp of the packed bits 2^-19.1, h itself (V + 2) 2^-24 and its split 2^-22: below 2^-17.7; the definition's
+//   own rounding, (V + 2) 2^-24 of d / 2, below 2^-20.6.  Two distances are ordered as their s are when these lie more than
+//   2^-16.4 apart: 2^-16 is used.  (The split is that good while |c|max^2 lies in [kQuantMinC2, kQuantMaxC2]; outside, every
+//   item is scanned.  The matrix cores of this chip take subnormal halves as they are.)
+// Bound: vector issue, about 230 instructions per 32 items and wavefront (112 for minima, 60 for the exact distances)
+// against 8 matrix instructions.  B2 H32, 2048 tokens, one codebook per head and side (4.2 M items per side): 112 us back to back,
+// where a scan of every pair took 546; 32 codebooks of v = 4: 163, 64 of v = 2: 324.
+constexpr int kQuantMfmaTokens = 128;        // tokens per workgroup
+constexpr float kQuantMinC2 = 1e-6f, kQuantMaxC2 = 1e9f;   // (the largest h that 2^15 of headroom takes is 2^30)
+
+// min(a, b) as the median with a minus infinity that the compiler does not see through: one instruction (fminf first
+// quiets operands that come straight from a matrix instruction, two more)
+__device__ __forceinline__ float min2f(float a, float b, float ninf) { return __builtin_amdgcn_fmed3f(a, b, ninf); }
+
+// {the lower half's value in every lane, the upper half's value in every lane}
+__device__ __forceinline__ void both_halves(unsigned v, unsigned &lower, unsigned &upper) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    lower = r[0];
+    upper = r[1];
+}
+__device__ __forceinline__ void both_halves(float v, float &lower, float &upper) {
+    unsigned l, u;
+    both_halves(__float_as_uint(v), l, u);
+    lower = __uint_as_float(l);
+    upper = __uint_as_float(u);
+}
+__device__ __forceinline__ void both_halves(int v, int &lower, int &upper) {
+    unsigned l, u;
+    both_halves((unsigned)v, l, u);
+    lower = (int)l;
+    upper = (int)u;
+}
+
+template <int V>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) void kv_quantize_mfma_kernel(KvQuantArgs a) {
+    constexpr int TILES = 8;                       // entry tiles of 32: codebooks are padded to 256 entries
+    constexpr int EP = TILES * 32;
+    extern __shared__ __align__(16) unsigned char smem[];
+    half_t *cb = reinterpret_cast<half_t *>(smem);                            // [G][EP][V], infinite past E
+    float *c2m = reinterpret_cast<float *>(cb + (size_t)a.G * EP * V);        // [G]  largest |c|^2
+    uint8_t *out = reinterpret_cast<uint8_t *>(c2m + ((a.G + 3) & ~3));       // [tokens][P]
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, NW = blockDim.x >> 6;
+    const int ln = lane & 31, lh = lane >> 5;
+    const int bh = blockIdx.x, h = bh % a.H, side = blockIdx.z;
+    const int t0 = blockIdx.y * a.tokens, nt = min(a.tokens, a.n_new - t0);
+
+    const half_t *src = a.cb[side] + (size_t)h * a.G * a.E * V;
+    // one wavefront per group of entries: the entries to LDS, the largest |c|^2 by a butterfly
+    for (int g = wave; g < a.G; g += NW) {
+        float m = 0.f;
+        for (int e = lane; e < EP; e += 64) {
+            V16 c;
+            c.u = make_uint4(0x7C007C00u, 0x7C007C00u, 0x7C007C00u, 0x7C007C00u);
+            if (e < a.E) {
+                c = kvq_load<V>(src + ((size_t)g * a.E + e) * V);
+                float n = 0.f;
+#pragma unroll
+                for (int k = 0; k < V; ++k) n = __builtin_fmaf((float)c.h8[k], (float)c.h8[k], n);
+                // as bits, so that a NaN (above infinity) stays
+                m = __uint_as_float(max(__float_as_uint(m), __float_as_uint(n) & 0x7FFFFFFFu));
+            }
+#pragma unroll
+            for (int k = 0; k < V / 2; ++k) reinterpret_cast<uint32_t *>(cb + (size_t)(g * EP + e) * V)[k] = c.w[k];
+        }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1)
+            m = __uint_as_float(max(__float_as_uint(m), (unsigned)__shfl_xor((int)__float_as_uint(m), o, 64)));
+        if (lane == 0) c2m[g] = m;
+    }
+    __syncthreads();
+
+    float ninf;
+    asm("s_mov_b32 %0, 0xff800000" : "=s"(ninf));
+    const unsigned char *xs = reinterpret_cast<const unsigned char *>(a.x[side] + ((size_t)bh * a.n_new + t0) * a.D);
+    const int n_items = nt * a.PG, n_ct = (n_items + 31) / 32;   // per group
+    const int R = max(1, NW / a.G);                              // wavefronts that share a group
+    for (int u = wave; u < a.G * R; u += NW) {
+        const int g = u / R;
+        const half_t *cbg = cb + (size_t)g * EP * V;
+        const float c2 = c2m[g];
+        const bool in_range = c2 >= kQuantMinC2 && c2 <= kQuantMaxC2;
+        // h = 2^-k (h1 + h2 + h3) with the largest h just below 2^15 (k within what a half can take back)
+        const int k = min(max(15 - (int)((__float_as_uint(0.5f * c2) >> 23) & 255) + 126, -15), 24);
+        const float up = __uint_as_float((unsigned)(127 + k) << 23);
+        const half_t down = (half_t)__uint_as_float((unsigned)(127 - k) << 23);
+        // the codebook of the group as matrix operands: entry 32 t + ln (past E: the last entry again)
+        half8_t A[TILES];
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) {
+            const V16 c = kvq_load<V>(cbg + (size_t)min(32 * t + ln, a.E - 1) * V);
+            float hh = 0.f;
+#pragma unroll
+            for (int i = 0; i < V; ++i) hh = __builtin_fmaf((float)c.h8[i], (float)c.h8[i], hh);
+            hh *= 0.5f * up;
+            const half_t h1 = (half_t)hh;
+            const half_t h2 = (half_t)(hh - (float)h1);
+            const half_t h3 = (half_t)((hh - (float)h1) - (float)h2);
+            V16 v;
+            const half2_t h12 = {h1, h2}, h30 = {h3, (half_t)0.f};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v.w[i] = lh ? 0u : i < V / 2 ? c.w[i] ^ 0x80008000u : 0u;
+            if (lh) {
+                v.h2[0] = h12;
+                v.h2[1] = h30;
+            }
+            A[t] = v.h8;
+        }
+        const half2_t dd = {down, down}, d0 = {down, (half_t)0.f};
+        auto item_off = [&](unsigned i) {   // index of the sub-vector in [token][P]
+            return (i >> a.pg_shift) * (unsigned)(a.P - a.PG) + i + (unsigned)(g * a.PG);
+        };
+        auto load_item = [&](int ct) { return kvq_load<V>(xs + item_off((unsigned)min(ct * 32 + ln, n_items - 1)) * (V * 2)); };
+        V16 xb = load_item(min(u % R, n_ct - 1));
+        for (int ct = u % R; ct < n_ct; ct += R) {
+            const V16 xnext = load_item(min(ct + R, n_ct - 1));
+            V16 bop;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) bop.w[i] = lh ? 0u : xb.w[i];
+            if (lh) {
+                bop.h2[0] = dd;
+                bop.h2[1] = d0;
+            }
+            float best = INFINITY, second = INFINITY;
+            const float16_t zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            float16_t s = __builtin_amdgcn_mfma_f32_32x32x16_f16(A[0], bop.h8, zero, 0, 0, 0);
+#pragma unroll
+            for (int t = 0; t < TILES; ++t) {
+                float16_t sn = s;   // the next tile's products run while this tile's minima are taken
+                if (t + 1 < TILES) sn = __builtin_amdgcn_mfma_f32_32x32x16_f16(A[t + 1 < TILES ? t + 1 : 0], bop.h8, zero, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int hf = 0; hf < 2; ++hf) {
+                    float m = min2f(s[8 * hf], s[8 * hf + 1], ninf);
+                    m = fminf(fminf(m, s[8 * hf + 2]), s[8 * hf + 3]);
+                    m = fminf(fminf(m, s[8 * hf + 4]), s[8 * hf + 5]);
+                    m = fminf(fminf(m, s[8 * hf + 6]), s[8 * hf + 7]);
+                    const float key = __uint_as_float((__float_as_uint(m) & 0xFFFFFFF0u) | (unsigned)(2 * t + hf));
+                    second = __builtin_amdgcn_fmed3f(best, second, key);
+                    best = min2f(best, key, ninf);
+                }
+                s = sn;
+            }
+            // the two lanes of the item
+            float bl, bu, sl, su;
+            both_halves(best, bl, bu);
+            both_halves(second, sl, su);
+            const float win = min2f(bl, bu, ninf);
+            second = fminf(fmaxf(bl, bu), fminf(sl, su));
+            float x2 = 0.f;
+#pragma unroll
+            for (int i = 0; i < V; ++i) x2 = __builtin_fmaf((float)xb.h8[i], (float)xb.h8[i], x2);
+            const bool sure = second - win > 1.52587890625e-5f * (x2 + c2) && in_range;
+            // entries of the group: rows 16 (grp & 1) + 4 (half whose lane holds them) + {0 .. 3, 8 .. 11} of tile grp / 2
+            const int e0 = 16 * (int)(__float_as_uint(win) & 15u) + (bu < bl ? 4 : 0) + 8 * lh;
+            int be = e0;
+            float bd = kvq_exact<V>(xb, kvq_load<V>(cbg + (size_t)e0 * V));
+#pragma unroll
+            for (int i = 1; i < 4; ++i) {
+                const float d = kvq_exact<V>(xb, kvq_load<V>(cbg + (size_t)(e0 + i) * V));
+                be = d < bd ? e0 + i : be;
+                bd = d < bd ? d : bd;
+            }
+            {
+                float dl, du;
+                int el, eu;
+                both_halves(bd, dl, du);
+                both_halves(be, el, eu);
+                be = du < dl ? eu : el;   // (the lower half's entries have the smaller indices)
+            }
+            const unsigned i = (unsigned)(ct * 32 + ln);
+            const bool live = (int)i < n_items;
+            unsigned long long left = __ballot(!sure && live && lh == 0);
+            if (left) {
+                if (__popcll(left) > 12) {
+                    // many: every item scanned by its own two lanes, one half of the entries each
+                    float bd2 = INFINITY;
+                    int be2 = lh * 128;
+                    for (int e = lh * 128; e < min(lh * 128 + 128, a.E); ++e) {
+                        const float d = kvq_exact<V>(xb, kvq_load<V>(cbg + (size_t)e * V));
+                        be2 = d < bd2 ? e : be2;
+                        bd2 = d < bd2 ? d : bd2;
+                    }
+                    float dl, du;
+                    int el, eu;
+                    both_halves(bd2, dl, du);
+                    both_halves(be2, el, eu);
+                    be = sure ? be : du < dl ? eu : el;
+                } else {
+                    // few: one after the other, the 64 lanes taking the entries in turn
+                    for (; left; left &= left - 1) {
+                        const int j = __ffsll((long long)left) - 1;
+                        V16 xj;
+                        xj.u = make_uint4(0, 0, 0, 0);
+#pragma unroll
+                        for (int q = 0; q < V / 2; ++q) xj.w[q] = (unsigned)__builtin_amdgcn_readlane((int)xb.w[q], j);
+                        float bd2 = INFINITY;
+                        int be2 = lane;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {   // (entries past E are infinitely far)
+                            const float d = kvq_exact<V>(xj, kvq_load<V>(cbg + (size_t)(lane + 64 * q) * V));
+                            be2 = d < bd2 ? lane + 64 * q : be2;
+                            bd2 = d < bd2 ? d : bd2;
+                        }
+                        const int code = kvq_wave_argmin(bd2, be2);
+                        be = ln == j ? code : be;
+                    }
+                }
+            }
+            if (live && lh == 0) out[item_off(i)] = (uint8_t)be;
+            xb = xnext;
+        }
+    }
+    __syncthreads();
+    uint8_t *dst = a.codes[side] + ((size_t)bh * a.T + a.pos + t0) * a.P;
+    if ((a.P & 3) == 0) {
+        for (int i = tid; i < nt * a.P / 4; i += blockDim.x)
+            reinterpret_cast<uint32_t *>(dst)[i] = reinterpret_cast<const uint32_t *>(out)[i];
+    } else {
+        for (int i = tid; i < nt * a.P; i += blockDim.x) dst[i] = out[i];
+    }
+}
+
+namespace {
+
+// New tokens from which the matrix-core kernel is used.  B2 H32, us: one codebook per head and side, scan 12.2 / 19.9 for
+// 4 / 8 tokens against 11.6 for the matrix-core kernel at 16; 64 codebooks of v = 2 (64 KiB to stage), 17.7 / 31.2 against
+// 26.9; a single token 11.4 - 12.7 by the scan in every layout (all of it the launch).
+constexpr int kQuantMfmaMin = 6;
+constexpr int kQuantScanTokens = 16;
+
+template <int V>
+int run_kvq(KvQuantArgs &a, int bh, hipStream_t s) {
+    const bool pow2 = (a.PG & (a.PG - 1)) == 0;   // (the matrix-core kernel splits an item index by a shift)
+    if (a.n_new < kQuantMfmaMin || !pow2) {
+        a.tokens = a.n_new < kQuantScanTokens ? a.n_new : kQuantScanTokens;
+        kv_quantize_scan_kernel<V><<<dim3(bh, (a.n_new + a.tokens - 1) / a.tokens, 2), 512, 0, s>>>(a);
+        return launch_status();
+    }
+    a.pg_shift = 0;
+    while ((1 << a.pg_shift) < a.PG) ++a.pg_shift;
+    // tokens per workgroup: as many as leave the chip two rounds of workgroups (a workgroup stages its codebooks first)
+    a.tokens = kQuantMfmaTokens;
+    while (a.tokens > 16 && (long)bh * 2 * ((a.n_new + a.tokens - 1) / a.tokens) < 1024) a.tokens /= 2;
+    const size_t lds = (size_t)a.G * 256 * V * sizeof(half_t) + (((size_t)a.G + 3) & ~(size_t)3) * 4 + (size_t)a.tokens * a.P;
+    static KernelSetup setup;
+    if (int st = kernel_setup(reinterpret_cast<const void *>(&kv_quantize_mfma_kernel<V>), lds, false, setup)) return st;
+    // a CU holds 16 wavefronts of this kernel: two workgroups of 8 where 64 KiB of codebooks are staged, four of 4 otherwise
+    const int threads = 4 * lds > 160 * 1024 ? 512 : 256;
+    kv_quantize_mfma_kernel<V><<<dim3(bh, (a.n_new + a.tokens - 1) / a.tokens, 2), threads, lds, s>>>(a);
+    return launch_status();
+}
+
+}  // namespace
+
 int launch_kv_quantize(const vq_kv_t *kv, const void *k_new, const void *v_new, int n_new, int pos, hipStream_t s) {
+    const size_t cb_bytes = (size_t)kv->cb_groups * kv->n_entries * kv->v * sizeof(half_t);
+    if (cb_bytes > 64 * 1024 || cb_bytes % 16 != 0) return VQ_ERR_UNSUPPORTED;
     KvQuantArgs a;
     a.x[0] = (const half_t *)k_new;
     a.x[1] = (const half_t *)v_new;
@@ -161,42 +406,17 @@ int launch_kv_quantize(const vq_kv_t *kv, const void *k_new, const void *v_new, 
     a.H = kv->H;
     a.T = kv->T;
     a.D = kv->D;
-    a.v = kv->v;
+    a.P = kv->D / kv->v;
     a.E = kv->n_entries;
     a.G = kv->cb_groups;
     a.n_new = n_new;
     a.pos = pos;
-    const size_t cb_elems = (size_t)kv->cb_groups * kv->n_entries * kv->v;
-    if (cb_elems * sizeof(half_t) > 64 * 1024 || (cb_elems * sizeof(half_t)) % 16 != 0) return VQ_ERR_UNSUPPORTED;
-    const bool f32 = cb_elems * sizeof(float) <= 64 * 1024;  // converted once per workgroup instead of per use
-    const size_t one = cb_elems * (f32 ? sizeof(float) : sizeof(half_t));
-    a.both = 2 * one <= 64 * 1024;
-    const size_t lds = a.both ? 2 * one : one;
-    a.tokens_per_wg = n_new < kQuantTokens ? n_new : kQuantTokens;
-    // lanes per item: fill the 256 threads when a workgroup has few items (decode), 1 otherwise
-    const int items = a.tokens_per_wg * (kv->D / kv->v);
-    int L = 1;
-    while (L < 64 && items * (L * 2) <= 256 && kv->n_entries % (L * 2) == 0) L *= 2;
-    a.L = L;
-    // a decode-sized call (one round of items per side) runs the two sides side by side
-    a.par = a.both && items * L <= 256;
-    const int threads = a.par ? 512 : 256;
-    const dim3 grid(kv->B * kv->H, (n_new + a.tokens_per_wg - 1) / a.tokens_per_wg);
-#define VQ_KVQ(V)                                                         \
-    do {                                                                  \
-        if (f32)                                                          \
-            kv_quantize_kernel<V, true><<<grid, threads, lds, s>>>(a);    \
-        else                                                              \
-            kv_quantize_kernel<V, false><<<grid, threads, lds, s>>>(a);   \
-    } while (0)
-    if (kv->v == 8)
-        VQ_KVQ(8);
-    else if (kv->v == 4)
-        VQ_KVQ(4);
-    else
-        VQ_KVQ(2);
-#undef VQ_KVQ
-    return launch_status();
+    a.PG = a.P / a.G;
+    a.pg_shift = 0;
+    const int bh = kv->B * kv->H;
+    if (kv->v == 8) return run_kvq<8>(a, bh, s);
+    if (kv->v == 4) return run_kvq<4>(a, bh, s);
+    return run_kvq<2>(a, bh, s);
 }
 
 }  // namespace vq

@@ -999,6 +999,38 @@ def test_kv_quantize_ties_go_to_the_smallest_index(gpu_device):
         assert np.array_equal(got_v, oracle.kv_quantize(v_new, kv.v_codebooks))
 
 
+@pytest.mark.parametrize("v,G,E,n_new", [(4, 1, 256, 5), (4, 1, 256, 6), (4, 32, 250, 17), (2, 64, 256, 129), (8, 2, 33, 40), (4, 1, 8, 300)])
+@pytest.mark.parametrize("kind", ["plain", "near_ties", "tiny", "huge", "not_finite"])
+def test_kv_quantize_hard_values(gpu_device, v, G, E, n_new, kind):
+    """The matrix-core kernel rules entries out by an approximate distance: entries that differ in the last bits, codebooks
+    whose squares leave the range of its scaled halves, and values that are not finite must give the definition's codes."""
+    kv = wl.make_kv(1, 2, 128, n_new + 3, v, E, G, seed=9500 + E + n_new)
+    rng = np.random.default_rng(9501 + E + n_new)
+    x = rng.normal(0, 1, size=(2, 1, 2, n_new, 128)).astype(np.float16)
+    for cb in (kv.k_codebooks, kv.v_codebooks):
+        if kind == "near_ties":   # copies of a few entries, one unit in the last place apart
+            cb[:] = np.resize(cb[:, :, :max(1, E // 8), :], cb.shape)
+            bits = cb.view(np.uint16)
+            bits[:, :, ::3, 0] += 1
+        elif kind == "tiny":
+            cb *= np.float16(2.0 ** -13)
+        elif kind == "huge":
+            cb *= np.float16(12000.0)
+        elif kind == "not_finite":
+            cb[0, 0, E // 2, 0] = np.inf
+            x[:, 0, 0, 1, :8] = np.inf
+            x[:, 0, 0, 2, 8:16] = np.nan
+    if kind == "tiny":
+        x *= np.float16(2.0 ** -13)
+    elif kind == "huge":
+        x *= np.float16(12000.0)
+    kd = vq.kv_to_device(kv, gpu_device)
+    vq.vq_kv_quantize(kd, dev_x(x[0], gpu_device), dev_x(x[1], gpu_device), 2)
+    torch.cuda.synchronize()
+    assert np.array_equal(kd.k_codes.cpu().numpy()[:, :, 2:2 + n_new], oracle.kv_quantize(x[0], kv.k_codebooks))
+    assert np.array_equal(kd.v_codes.cpu().numpy()[:, :, 2:2 + n_new], oracle.kv_quantize(x[1], kv.v_codebooks))
+
+
 def test_kv_quantize_then_attend(gpu_device):
     # a cache written by the quantizer, read by the attention kernel: compare with the oracle's two steps
     B, H, T = 2, 4, 700
