@@ -285,13 +285,14 @@ size_t vq_gemv_sequence_streams_workspace(const vq_gemv_call_t *calls, int n_cal
  * Second kind of list: weights with SMALL codebooks in the canonical layout (no re-tiled codes; uint8 codes, v = 8,
  * one or two additive codebooks of <= 256 entries, K a multiple of 64 in [512, 12288]; Sec. II-A residual
  * quantization, Sec. III-C VQ-gemv).  All problems of the list must be of this kind and have the same number of
- * codebooks (a mix: VQ_ERR_UNSUPPORTED).  One launch: a workgroup per compute unit holds 16 copies of every entry
- * of the current problem's codebooks in LDS, one per bank column, so that the random entry reads of a wavefront never
- * collide; groups of workgroups work on different problems at the same time and re-stage between problems while
- * the next problem's codes are already in flight.  No partial sums, no second launch: ws holds only the problem
- * table.  Outputs are within the gemv tolerance of the definition but not bit-identical to vq_gemv's (another
- * summation order); repeated runs give identical bits.  vq_gemv_pipeline_status reports 0 (this kernel has no waits
- * it could give up).
+ * codebooks (a mix: VQ_ERR_UNSUPPORTED).  One launch, a persistent workgroup per compute unit.  Long lists: the products
+ * of a slice of x with all entries are formed in LDS once and looked up, one 4-byte read and one addition per code, as
+ * 128 bytes of every row stream by.  Short ones: LDS holds 16 copies of every entry of the current problem's codebooks,
+ * one per bank column, so that the random entry reads of a wavefront never collide; groups of workgroups work on
+ * different problems at the same time and re-stage between problems while the next problem's codes are already in
+ * flight.  No partial sums, no second launch: ws holds only the problem table.  Outputs are within the gemv tolerance
+ * of the definition but not bit-identical to vq_gemv's (another summation order); repeated runs give identical bits.
+ * vq_gemv_pipeline_status reports 0 (these kernels have no waits they could give up).
  */
 typedef struct vq_gemv_pipeline vq_gemv_pipeline_t;
 size_t vq_gemv_pipeline_workspace(const vq_gemv_call_t *calls, int n_calls);

@@ -240,10 +240,12 @@ int vq_gemv_sequence(const vq_gemv_call_t *calls, int n_calls, void *ws, size_t 
 }
 
 // A pipeline is one of two kinds, after its weights: re-tiled codes of a large codebook (the persistent two-image
-// kernel), or canonical uint8 codes with small codebooks (the kernel that holds 16 LDS copies of every entry).
+// kernel), or canonical uint8 codes with small codebooks (a table of products in LDS for long lists, 16 LDS copies of
+// every entry for short ones).
 struct vq_gemv_pipeline {
     GemvPipeline *impl;
     GemvReplicaList *rep;
+    GemvLutList *lut;
 };
 
 // 1 if every problem can run on the small-codebook kernel, 0 if none can (or some weight is re-tiled), < 0 on a
@@ -275,6 +277,10 @@ static int count_problems(const vq_gemv_call_t *calls, int n_calls) {
     return n;
 }
 
+static size_t small_codebook_workspace(const vq_gemv_call_t *calls, int n_calls) {
+    return gemv_lut_worth(calls, n_calls) ? gemv_lut_list_workspace(calls, n_calls) : gemv_replica_list_workspace(count_problems(calls, n_calls));
+}
+
 static int check_pipeline_calls(const vq_gemv_call_t *calls, int n_calls) {
     if (!calls) return VQ_ERR_NULL;
     if (n_calls < 1) return VQ_ERR_SHAPE;
@@ -288,7 +294,7 @@ static int check_pipeline_calls(const vq_gemv_call_t *calls, int n_calls) {
 
 size_t vq_gemv_pipeline_workspace(const vq_gemv_call_t *calls, int n_calls) {
     const int rep = replica_calls(calls, n_calls);
-    if (rep == 1) return gemv_replica_list_workspace(count_problems(calls, n_calls));
+    if (rep == 1) return small_codebook_workspace(calls, n_calls);
     if (rep < 0 || check_pipeline_calls(calls, n_calls) != VQ_OK) return 0;
     return gemv_pipeline_workspace(calls, n_calls);
 }
@@ -301,15 +307,17 @@ int vq_gemv_pipeline_create(const vq_gemv_call_t *calls, int n_calls, void *ws, 
     if (rep < 0) return rep;
     if (rep == 0)
         if (int st = check_pipeline_calls(calls, n_calls)) return st;
-    const size_t need = rep ? gemv_replica_list_workspace(count_problems(calls, n_calls)) : gemv_pipeline_workspace(calls, n_calls);
+    const size_t need = rep ? small_codebook_workspace(calls, n_calls) : gemv_pipeline_workspace(calls, n_calls);
     if (!ws || ws_bytes < need) return VQ_ERR_WORKSPACE;
     if (((uintptr_t)ws & 255) != 0) return VQ_ERR_ALIGN;
     vq_gemv_pipeline *h = new (std::nothrow) vq_gemv_pipeline;
     if (!h) return VQ_ERR_LAUNCH;
     h->impl = nullptr;
     h->rep = nullptr;
-    const int st = rep ? gemv_replica_list_create(calls, n_calls, ws, static_cast<hipStream_t>(stream), &h->rep)
-                       : gemv_pipeline_create(calls, n_calls, ws, static_cast<hipStream_t>(stream), &h->impl);
+    h->lut = nullptr;
+    const int st = rep && gemv_lut_worth(calls, n_calls) ? gemv_lut_list_create(calls, n_calls, ws, static_cast<hipStream_t>(stream), &h->lut)
+                   : rep ? gemv_replica_list_create(calls, n_calls, ws, static_cast<hipStream_t>(stream), &h->rep)
+                         : gemv_pipeline_create(calls, n_calls, ws, static_cast<hipStream_t>(stream), &h->impl);
     if (st != VQ_OK) {
         delete h;
         return st;
@@ -319,14 +327,15 @@ int vq_gemv_pipeline_create(const vq_gemv_call_t *calls, int n_calls, void *ws, 
 }
 
 int vq_gemv_pipeline_run(const vq_gemv_pipeline_t *p, void *stream) {
-    if (!p || (!p->impl && !p->rep)) return VQ_ERR_NULL;
+    if (!p || (!p->impl && !p->rep && !p->lut)) return VQ_ERR_NULL;
+    if (p->lut) return launch_gemv_lut_list(p->lut, static_cast<hipStream_t>(stream));
     if (p->rep) return launch_gemv_replica_list(p->rep, static_cast<hipStream_t>(stream));
     return launch_gemv_pipeline(p->impl, static_cast<hipStream_t>(stream));
 }
 
 int vq_gemv_pipeline_status(const vq_gemv_pipeline_t *p, void *stream, int *status) {
-    if (!p || (!p->impl && !p->rep) || !status) return VQ_ERR_NULL;
-    if (p->rep) {   // (that kernel has no waits it could give up)
+    if (!p || (!p->impl && !p->rep && !p->lut) || !status) return VQ_ERR_NULL;
+    if (!p->impl) {   // (those kernels have no waits they could give up)
         *status = 0;
         return hipStreamSynchronize(static_cast<hipStream_t>(stream)) == hipSuccess ? VQ_OK : VQ_ERR_LAUNCH;
     }
@@ -337,6 +346,7 @@ void vq_gemv_pipeline_destroy(vq_gemv_pipeline_t *p) {
     if (!p) return;
     if (p->impl) gemv_pipeline_destroy(p->impl);
     if (p->rep) gemv_replica_list_destroy(p->rep);
+    if (p->lut) gemv_lut_list_destroy(p->lut);
     delete p;
 }
 

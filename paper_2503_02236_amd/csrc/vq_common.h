@@ -125,6 +125,13 @@ size_t gemv_replica_list_workspace(int n);
 int gemv_replica_list_create(const vq_gemv_call_t *calls, int n_calls, void *ws, hipStream_t s, GemvReplicaList **out);
 void gemv_replica_list_destroy(GemvReplicaList *h);
 int launch_gemv_replica_list(const GemvReplicaList *h, hipStream_t s);
+// the same lists when they are long: products of x with the entries from a table in LDS (gemv_lut.hip)
+struct GemvLutList;
+bool gemv_lut_worth(const vq_gemv_call_t *calls, int n_calls);
+size_t gemv_lut_list_workspace(const vq_gemv_call_t *calls, int n_calls);
+int gemv_lut_list_create(const vq_gemv_call_t *calls, int n_calls, void *ws, hipStream_t s, GemvLutList **out);
+void gemv_lut_list_destroy(GemvLutList *h);
+int launch_gemv_lut_list(const GemvLutList *h, hipStream_t s);
 int launch_attn_decode(const vq_kv_t *kv, const void *q, float sm_scale, void *out, void *ws, hipStream_t s);
 // channel-parallel variant for caches with one codebook per channel sub-space (attn_channel.hip)
 bool attn_channel_supported(const vq_kv_t *kv);

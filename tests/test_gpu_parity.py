@@ -503,6 +503,51 @@ def test_gemv_pipeline_small_codebook_list_of_forty(gpu_device):
     _small_codebook_list(gpu_device, 2, specs, 9600, [range(40), range(33)])
 
 
+@pytest.mark.parametrize("R,count,shapes", [
+    (2, 192, [(1400, 1088), (1024, 2112), (512, 512), (129, 576), (1, 512), (1300, 1408), (8, 1024)]),
+    (1, 192, [(1400, 1088), (1024, 2112), (512, 512), (129, 576), (1, 512), (1300, 1408), (8, 1024)]),
+    (2, 48, [(2100, 12288), (2100, 11008), (700, 4096)]),         # rows of 2752 bytes: even and odd rows dealt apart
+    (2, 48, [(8300, 1088), (1100, 1088)]),                        # rows of 272 bytes: every eighth row
+    (1, 48, [(4200, 1280), (16500, 576), (300, 12288)]),          # every fourth (160 bytes), every sixteenth (72)
+])
+def test_gemv_pipeline_long_small_codebook_lists(gpu_device, R, count, shapes):
+    """Lists long enough for the kernel that looks products up in a table: rows that end inside a slice of 64 (or 128)
+    positions, fewer rows than a step's 128, one row, rows and codes that start inside a 128-byte line, small codebooks, no
+    scale; the same bits on a second run, and entries that no code uses may hold anything."""
+    calls, ref = [], []
+    for i in range(count):
+        N, K = shapes[i % len(shapes)]
+        E = (256, 250, 16)[i % 3]
+        w = wl.make_weight(N, K, 8, 8, R, E, 0.01, seed=12000 + 100 * R + i, with_scale=(i % 4 != 0))
+        if E == 256 and N > 1:
+            w.codes[...] = w.codes % 255
+            w.codebooks[:, 255, :] = np.float16("nan")
+        x = wl.make_activations(1, w.K, seed=12500 + i)
+        wd = vq.weight_to_device(w, gpu_device)
+        if i % 5 == 1:      # codes that do not start at a line
+            flat = torch.zeros(wd.codes.numel() + 16, dtype=torch.uint8, device=gpu_device)
+            flat[16:] = wd.codes.reshape(-1)
+            wd.codes = flat[16:].view(wd.codes.shape)
+        calls.append([(wd, dev_x(x, gpu_device), torch.full((1, N), 5.0, dtype=torch.float16, device=gpu_device))])
+        ref.append((w, x))
+    pipe = vq.GemvPipeline(calls)
+    # (the table of the kernel for short lists is smaller than this)
+    assert vq.lib().vq_gemv_pipeline_workspace(pipe.seq.arr, pipe.seq.n) > 72 * 256
+    first = []
+    for rep in range(2):
+        assert pipe.run() == 0
+        torch.cuda.synchronize()
+        for i, (c, (w, x)) in enumerate(zip(calls, ref)):
+            y = c[0][2]
+            if rep == 0:
+                assert_close(y, oracle.gemv(w.codes, w.codebooks, w.scale, x), f"long list member {i}: {w.N}x{w.K} R={R}")
+                first.append(y.clone())
+            else:
+                assert torch.equal(y, first[i]), i
+            y.fill_(3.0)
+    pipe.close()
+
+
 def test_gemv_pipeline_small_codebook_nan_entries_unused(gpu_device):
     """Entries that no code uses are never multiplied into a result: with NaN in them the outputs stay finite and
     equal those with zeros there (a lane past the end of a ragged row computes with codes that are not its own;
