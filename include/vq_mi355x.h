@@ -95,8 +95,7 @@ typedef struct vq_gemv_pack_t {
  * entries (the exact sum rounded once), which is the same value whenever the fp32 sum is exact, i.e. always
  * unless the two entries' exponents lie more than 13 apart (then it can differ by one fp16 ulp on a tie).
  * With per-tile codebooks (cb_tile_n, cb_tile_k > 0) `codebooks` above is the set of the tile that holds
- * (n, j*v).  Re-tiled gemv codes (gemv_pack), hot_entries and the fused small-M matrix-core path of vq_gemm
- * apply to per-tensor codebooks only.
+ * (n, j*v).  Re-tiled gemv codes (gemv_pack) and hot_entries apply to per-tensor codebooks only.
  */
 typedef struct vq_weight_t {
     int N, K;              /* output / input features; K % v == 0 */
@@ -309,7 +308,8 @@ void vq_gemv_pipeline_destroy(vq_gemv_pipeline_t *p);
  * X: device fp16 [M][K]; Y: device fp16 [M][N]; M >= 1.
  * ws: vq_gemm_workspace(w, M) bytes.  For M > 256 that is N*K*2: the weight is dequantized once per
  * call into ws (fp16, the same bits vq_dequant returns) and multiplied by a dense matrix-core kernel;
- * for smaller M the dequantization is fused into the matrix-core loop and no workspace is needed.
+ * for smaller M the dequantization is fused into the matrix-core loop and no workspace is needed
+ * (a small product of more than 256 tokens may leave ws unused).
  */
 int vq_gemm(const vq_weight_t *w, const void *X, int M, void *Y,
             void *ws, size_t ws_bytes, void *stream);

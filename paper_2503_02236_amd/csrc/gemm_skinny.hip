@@ -1,0 +1,530 @@
+// Products of a VQ weight with a few to a few hundred tokens in ONE pass over the codes, on the matrix cores of gfx950:
+// vq_gemm for 17 .. 256 tokens and more where the product is small, vq_gemv for several tokens of a codebook that does
+// not fit LDS and for nearly 16 of one that does.
+// Operation: VQ-LLM (arXiv 2503.02236) Sec. III-C; dequantization of Sec. II-A in front of the matrix instruction.
+//
+// What bounds it: every workgroup reads its share of X from L2 (41 bytes per clock and CU) and looks up one entry per
+// code, from LDS (5.5 per clock and CU) or, for a 2^16-entry codebook, from L2 (0.44).  A workgroup owns 16 RT weight
+// rows x 16 CT tokens; each of its wavefronts computes that whole tile over its own part of K, so inside a workgroup
+// nothing is looked up or read twice, no barrier stands in the main loop, and the partial tiles meet in LDS once at
+// the end.  16 RT trades X traffic (N / 16 RT workgroups read all of X), 16 CT lookups (M / 16 CT workgroups look up
+// the same codes): skinny_tile() weighs the two.
+//
+// Operands: v_mfma_f32_16x16x32_f16, A = 16 weight rows (a lane's operand is 8 consecutive k of its row = one v = 8
+// entry or two v = 4 entries, straight from the codebook), B = 16 tokens.  Both want lane l to hold row l % 16, which is
+// the worst order for a load: neighbouring lanes on different lines, 16 bytes of each (measured: 13 bytes of X per clock
+// and CU, however deep the prefetch).  So X is loaded as whole contiguous pieces of token rows (8 lanes a line), written
+// to a small LDS area of the wavefront's own and read back as operands: N = K = 4096, two codebooks, 77 tokens 21.2 ->
+// 13.0 us, 256 tokens 25.2 -> 18.4.  A lane loads 16 bytes of codes, the four lanes of a row 64 consecutive bytes; a
+// 4 x 4 transposition of the dwords over the four lanes (v_permlane32_swap, v_permlane16_swap) gives step i the i-th 16
+// bytes of the 64, one dword per lane, which makes the X of a step contiguous.
+//
+// Measured (N = K = 4096 unless said; before: 16 tokens a launch from LDS codebooks, a 256-token tile from L2 ones):
+// two 256-entry codebooks, 77 tokens 37.8 -> 12.9 us, 256 tokens 120 -> 18.6; 12-bit codes, 77 tokens 40.8 -> 15.4; 2^16
+// entries, 32 tokens 160 -> 14.7, 256 tokens 175 -> 32; N = 11008, 8 tokens 62.5 -> 30.5 (two passes of gathers before,
+// one now: 0.37 per clock and CU).
+#include <algorithm>
+#include <type_traits>
+
+#include "vq_common.h"
+
+namespace vq {
+
+namespace {
+
+typedef float float4v_t __attribute__((ext_vector_type(4)));
+
+struct SkinnyArgs {
+    const void *codes;
+    const half_t *cb, *scale, *x;
+    half_t *y;
+    int N, K, M, E;
+    int ops;   // MFMA operands (8 consecutive k) per row
+    int nit;   // wavefront iterations over K
+    int tiles_k, tile_ops, tile_n;   // per-tile codebooks: sets per row of tiles, operands per tile, rows per tile (0: per tensor)
+    int groups_m;                    // workgroups along the tokens
+};
+
+// Code load of a lane and iteration: 16 bytes, 8 for single uint8 codes (rows are multiples of 8 bytes only), 12-byte
+// words of 8 codes for packed 12-bit codes.
+template <typename CodeT, int V, int R>
+struct SkinnyShape {
+    static constexpr int BITS = (int)sizeof(CodeT) * 8;
+    static constexpr int LB = R * (int)sizeof(CodeT) == 1 ? 8 : 16;
+};
+template <int V, int R>
+struct SkinnyShape<Code12, V, R> {
+    static constexpr int BITS = 12;
+    static constexpr int LB = 12;
+};
+
+// Code number q (static) of the lane's code words.
+template <typename CodeT>
+__device__ __forceinline__ unsigned skinny_code(const V16 &cd, int q) {
+    return sizeof(CodeT) == 1 ? (cd.w[q >> 2] >> (8 * (q & 3))) & 0xFFu : (cd.w[q >> 1] >> (16 * (q & 1))) & 0xFFFFu;
+}
+template <>
+__device__ __forceinline__ unsigned skinny_code<Code12>(const V16 &cd, int q) {
+    const int bit = 12 * q, wi = bit >> 5, sh = bit & 31;
+    unsigned v = cd.w[wi] >> sh;
+    if (sh > 20) v |= cd.w[wi + 1] << (32 - sh);
+    return v & 0xFFFu;
+}
+
+__device__ __forceinline__ void swap32(uint32_t &a, uint32_t &b) {   // upper half of a <-> lower half of b
+    const auto t = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = t[0];
+    b = t[1];
+}
+__device__ __forceinline__ void swap16(uint32_t &a, uint32_t &b) {   // odd rows of 16 lanes of a <-> even rows of b
+    const auto t = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = t[0];
+    b = t[1];
+}
+
+constexpr int skinny_max_waves(bool l2, int rt, int ct) { return !l2 && rt * ct <= 2 ? 16 : 8; }
+
+// Operands of an X unit: two (a line of 128 bytes per token), or as many as a lane's dword holds.
+constexpr int skinny_unit(int mpi, int opd) { return opd > 2 ? opd : mpi < 2 ? mpi : 2; }
+// Units in flight: up to 64 registers (32 where the accumulators or 16 wavefronts take the rest), a divisor of the
+// units per iteration.
+constexpr int skinny_depth(int epi, int u, bool l2, int rt, int ct) {
+    int d = (rt * ct >= 16 || skinny_max_waves(l2, rt, ct) == 16 ? 8 : 16) / u;
+    while (epi % d) --d;
+    return d;
+}
+
+// L2CB: entries are gathered from global memory (L2); otherwise the codebooks are staged in LDS.
+template <typename CodeT, int V, int R, bool L2CB, int RT, int CT>
+__global__ __launch_bounds__(64 * skinny_max_waves(L2CB, RT, CT)) void gemm_skinny_kernel(SkinnyArgs a) {
+    constexpr int BITS = SkinnyShape<CodeT, V, R>::BITS, LB = SkinnyShape<CodeT, V, R>::LB;
+    constexpr int CPO = 8 / V;                         // entries side by side in an operand
+    constexpr int MPI = LB * 8 / (BITS * R * CPO);     // operands per lane and iteration
+    static_assert(MPI * BITS * R * CPO == LB * 8, "whole operands per code load");
+    static_assert(R <= 2, "operands are summed in fp16 (one rounding)");
+    constexpr bool TR = LB != 12 && BITS * R * CPO <= 32;   // whole operands per dword: transpose
+    constexpr int NS = TR ? LB / 4 : 1, OPD = MPI / NS;     // steps per iteration, operands per step
+    // X goes through LDS in units of U operands (32 U k) x 16 tokens, private to the wavefront.  D units per lane are
+    // in flight in registers.
+    constexpr int U = skinny_unit(MPI, OPD), NU = MPI / U, SEGS = 4 * U, EPI = NU * CT;
+    constexpr int D = skinny_depth(EPI, U, L2CB, RT, CT);
+    static_assert(D <= EPI && MPI % U == 0 && EPI % D == 0 && (!L2CB || NU % 2 == 0), "slots are the same in every iteration");
+
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, nwaves = blockDim.x >> 6;
+    const int r = lane & 15, g = lane >> 4;
+    const int n0 = (blockIdx.x / a.groups_m) * 16 * RT, m0 = (blockIdx.x % a.groups_m) * 16 * CT;
+    const int row_bytes = a.ops * CPO * R * BITS / 8;
+    const int slot = !TR || NS == 4 ? g : ((g & 1) << 1) | (g >> 1);   // (two dwords: one swap, lanes 1 and 2 of a row change places)
+
+    const unsigned char *crow[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t)   // rows past the end are computed and dropped
+        crow[t] = reinterpret_cast<const unsigned char *>(a.codes) + (size_t)min(n0 + 16 * t + r, a.N - 1) * row_bytes;
+    // X loads: instruction j of a unit covers 64 / SEGS tokens, whole contiguous rows of SEGS 16-byte segments
+    const int xseg = lane % SEGS, xtok = lane / SEGS;
+    uint32_t xrow[CT][U];   // byte offsets (gemm_skinny_supported bounds K)
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int j = 0; j < U; ++j) xrow[c][j] = (uint32_t)min(m0 + 16 * c + j * (64 / SEGS) + xtok, a.M - 1) * (uint32_t)(a.K * 2);
+
+    // Loads carry no condition: a lane past the end of its row reads the row's last bytes, and what it makes of them
+    // is zeroed (both operands: an infinity there must not meet a zero).
+    auto load_codes = [&](int it, int t, V16 &cd) {
+        const unsigned char *p = crow[t] + min((it * 4 + g) * LB, row_bytes - LB);
+        if (LB == 16) {
+            cd = ld16(p);
+        } else if (LB == 12) {
+            const uint32_t *c3 = reinterpret_cast<const uint32_t *>(p);
+            cd.w[0] = c3[0];
+            cd.w[1] = c3[1];
+            cd.w[2] = c3[2];
+            cd.w[3] = 0;
+        } else {
+            const V8 c8 = ld8(p);
+            cd.w[0] = c8.w[0];
+            cd.w[1] = c8.w[1];
+            cd.w[2] = cd.w[3] = 0;
+        }
+    };
+    auto transpose = [&](V16 &cd) {
+        if (TR && NS == 4) {
+            swap32(cd.w[0], cd.w[2]);
+            swap32(cd.w[1], cd.w[3]);
+            swap16(cd.w[0], cd.w[1]);
+            swap16(cd.w[2], cd.w[3]);
+        } else if (TR && NS == 2) {
+            swap32(cd.w[0], cd.w[1]);
+        }
+    };
+    // position (in operands) of this lane's operand o of an iteration
+    auto op_index = [&](int it, int o) { return it * 4 * MPI + ((o / OPD) * 4 + slot) * OPD + o % OPD; };
+    const int cb_bytes = L2CB ? 0 : (R * a.E * V * 2 * a.tiles_k + 15) & ~15;
+    unsigned char *stage = smem + cb_bytes + wave * (U * 1024);
+    // slot of 16-byte segment `seg` of token `tok` of a unit: the 16 tokens of a pass over the banks get different ones
+    auto stage_off = [&](int tok, int seg) {
+        const int swz = U == 2 ? (tok ^ (tok >> 3)) & 7 : tok & (SEGS < 16 ? SEGS - 1 : 15);
+        return tok * (SEGS * 16) + ((seg ^ swz) << 4);
+    };
+    auto load_x = [&](int it, int e, V16 (&xb)[U]) {   // unit e / CT, token tile e % CT
+        const uint32_t k = min((it * NU + e / CT) * SEGS + xseg, a.ops - 1) * 16;
+#pragma unroll
+        for (int j = 0; j < U; ++j) xb[j] = ld16(reinterpret_cast<const unsigned char *>(a.x) + (xrow[e % CT][j] + k));
+    };
+    // registers -> LDS -> operands (a wavefront's LDS operations are carried out in order: one buffer is enough)
+    auto stage_x = [&](const V16 (&xb)[U], half8_t (&xo)[U]) {
+#pragma unroll
+        for (int j = 0; j < U; ++j) *reinterpret_cast<uint4 *>(stage + stage_off(j * (64 / SEGS) + xtok, xseg)) = xb[j].u;
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+            xo[q] = *reinterpret_cast<const half8_t *>(stage + stage_off(r, ((q / OPD) * 4 + slot) * OPD + q % OPD));
+    };
+    const half_t *cbl = reinterpret_cast<const half_t *>(smem);
+    const int set_halves = R * a.E * V;
+    auto entry = [&](unsigned idx, int set) {   // entry idx of the concatenated codebooks (LDS) or of the codebook (L2)
+        V16 e;
+        e.u = make_uint4(0, 0, 0, 0);
+        if (L2CB) {
+            const unsigned char *p = reinterpret_cast<const unsigned char *>(a.cb) + idx * (unsigned)(V * 2);
+            if (V == 8) {
+                e = ld16(p);
+            } else {
+                const V8 t = ld8(p);
+                e.w[0] = t.w[0];
+                e.w[1] = t.w[1];
+            }
+        } else {
+            const half_t *p = cbl + set + idx * V;
+            if (V == 8) {
+                e = ld16(p);
+            } else {
+                const V8 t = ld8(p);
+                e.w[0] = t.w[0];
+                e.w[1] = t.w[1];
+            }
+        }
+        return e;
+    };
+    auto load_entries = [&](int it, int u, const V16 (&cd)[RT], V16 (&ev)[U][RT][CPO][R]) {
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int o = u * U + q;
+            int set = 0;
+            if (!L2CB && a.tiles_k > 1) set = min(op_index(it, o) / a.tile_ops, a.tiles_k - 1) * set_halves;
+#pragma unroll
+            for (int t = 0; t < RT; ++t)
+#pragma unroll
+                for (int h = 0; h < CPO; ++h)
+#pragma unroll
+                    for (int rr = 0; rr < R; ++rr)
+                        ev[q][t][h][rr] = entry(rr * a.E + skinny_code<CodeT>(cd[t], (o * CPO + h) * R + rr), set);
+        }
+    };
+
+    // codes of this iteration, of the next one and of the one after that (a wavefront whose iterations have run out
+    // repeats the last one and does not use it)
+    V16 cd[RT], cn[RT], cf[RT];
+    V16 xr[D][U];
+    V16 er[L2CB ? 2 : 1][U][RT][CPO][R];
+    const int first = min(wave, a.nit - 1);
+#pragma unroll
+    for (int t = 0; t < RT; ++t) load_codes(first, t, cd[t]);
+#pragma unroll
+    for (int t = 0; t < RT; ++t) load_codes(min(wave + nwaves, a.nit - 1), t, cn[t]);
+#pragma unroll
+    for (int e = 0; e < D; ++e) load_x(first, e, xr[e]);
+    // scales of the rows that this lane writes at the end, as raw halves (row tile wave % RT; else read there)
+    half_t sc4[4];
+    {
+        const half_t *sp = a.scale ? a.scale : a.x;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sc4[i] = sp[a.scale ? min(n0 + 16 * (wave % RT) + 4 * g + i, a.N - 1) : 0];
+    }
+    if (!L2CB) {
+        const half_t *src = a.cb + (a.tile_n > 0 ? (size_t)(n0 / a.tile_n) * a.tiles_k * set_halves : 0);
+        const int n16 = set_halves * a.tiles_k / 8;
+        for (int i = tid; i < n16; i += blockDim.x) reinterpret_cast<uint4 *>(smem)[i] = reinterpret_cast<const uint4 *>(src)[i];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int t = 0; t < RT; ++t) transpose(cd[t]);
+    if (L2CB) load_entries(first, 0, cd, er[0]);
+
+    float4v_t acc[RT][CT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) acc[t][c] = float4v_t{0.f, 0.f, 0.f, 0.f};
+
+    half8_t xo[U];
+    {   // element 0 is staged ahead, and so is every next element before the current one is multiplied
+        stage_x(xr[0], xo);
+        load_x(D < EPI ? first : min(first + nwaves, a.nit - 1), D % EPI, xr[0]);
+    }
+    for (int it = wave; it < a.nit; it += nwaves) {
+        const int nx = min(it + nwaves, a.nit - 1);
+        const bool tail = (it + 1) * 4 * MPI > a.ops;   // some lanes of this iteration are past the end of the row
+#pragma unroll
+        for (int t = 0; t < RT; ++t) load_codes(min(it + 2 * nwaves, a.nit - 1), t, cf[t]);
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            if (L2CB) {
+                if (u + 1 == NU) {
+#pragma unroll
+                    for (int t = 0; t < RT; ++t) {
+                        cd[t] = cn[t];
+                        transpose(cd[t]);
+                    }
+                }
+                load_entries(u + 1 < NU ? it : nx, (u + 1) % NU, cd, er[(u + 1) & 1]);
+            } else {
+                load_entries(it, u, cd, er[0]);
+            }
+            // the operands: one entry, or the fp16 sum of two (one rounding, that of their fp32 sum)
+            V16 op[U][RT];
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+#pragma unroll
+                for (int t = 0; t < RT; ++t) {
+                    const V16 (&e)[CPO][R] = er[L2CB ? u & 1 : 0][q][t];
+#pragma unroll
+                    for (int h = 0; h < CPO; ++h) {
+#pragma unroll
+                        for (int p = 0; p < V / 2; ++p) {
+                            half2_t s = e[h][0].h2[p];
+                            if (R == 2) s += e[h][R - 1].h2[p];
+                            op[q][t].h2[h * (V / 2) + p] = s;
+                        }
+                    }
+                }
+            }
+            if (tail) {
+#pragma unroll
+                for (int q = 0; q < U; ++q)
+                    if (op_index(it, u * U + q) >= a.ops) {
+#pragma unroll
+                        for (int t = 0; t < RT; ++t) op[q][t].u = make_uint4(0, 0, 0, 0);
+                    }
+            }
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                const int e = u * CT + c;
+                half8_t xc[U];
+#pragma unroll
+                for (int q = 0; q < U; ++q) xc[q] = xo[q];
+                stage_x(xr[(e + 1) % D], xo);
+                {
+                    const int f = e + 1 + D;   // element f of this iteration, or of one of the next two
+                    load_x(f < EPI ? it : f < 2 * EPI ? nx : min(it + 2 * nwaves, a.nit - 1), f % EPI, xr[(e + 1) % D]);
+                }
+                if (tail) {
+#pragma unroll
+                    for (int q = 0; q < U; ++q)
+                        if (op_index(it, u * U + q) >= a.ops) xc[q] = half8_t{0, 0, 0, 0, 0, 0, 0, 0};
+                }
+#pragma unroll
+                for (int q = 0; q < U; ++q)
+#pragma unroll
+                    for (int t = 0; t < RT; ++t) acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(op[q][t].h8, xc[q], acc[t][c], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            if (!L2CB) {
+                cd[t] = cn[t];
+                transpose(cd[t]);
+            }
+            cn[t] = cf[t];
+        }
+    }
+
+    // partial tiles -> LDS [tile][wavefront][lane] (over the codebooks), added in wavefront order, tile t by wavefront t
+    // mod the wavefronts.  Lane (r, g) of a tile holds token r, rows 4 g + 0..3.
+    float4v_t *red = reinterpret_cast<float4v_t *>(smem);
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int t = 0; t < RT; ++t) red[((c * RT + t) * nwaves + wave) * 64 + lane] = acc[t][c];
+    __syncthreads();
+    for (int i = wave; i < RT * CT; i += nwaves) {
+        float4v_t sum = red[(i * nwaves) * 64 + lane];
+        for (int w = 1; w < nwaves; ++w) sum += red[(i * nwaves + w) * 64 + lane];
+        const int t = i % RT, m = m0 + 16 * (i / RT) + r, n = n0 + 16 * t + 4 * g;
+        if (m >= a.M) continue;
+        half4_t o;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float sc = !a.scale ? 1.f : t == wave % RT ? (float)sc4[j] : (float)a.scale[min(n + j, a.N - 1)];
+            o[j] = (half_t)(sum[j] * sc);
+        }
+        half_t *yp = a.y + (size_t)m * a.N + n;
+        if ((a.N & 3) == 0) {
+            if (n < a.N) *reinterpret_cast<half4_t *>(yp) = o;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (n + j < a.N) yp[j] = o[j];
+        }
+    }
+}
+
+constexpr size_t kSkinnyLds = 160 * 1024, kSkinnyLdsCodebook = 128 * 1024;
+template <typename CodeT, int V, int R>
+constexpr int skinny_unit_of() {
+    constexpr int BITS = SkinnyShape<CodeT, V, R>::BITS, LB = SkinnyShape<CodeT, V, R>::LB, CPO = 8 / V;
+    constexpr int MPI = LB * 8 / (BITS * R * CPO);
+    return skinny_unit(MPI, LB != 12 && BITS * R * CPO <= 32 ? MPI / (LB / 4) : MPI);
+}
+
+template <typename CodeT, int V, int R, bool L2CB, int RT, int CT>
+int run_tile(const vq_weight_t *w, const half_t *x, int M, half_t *y, hipStream_t s) {
+    constexpr int MPI = SkinnyShape<CodeT, V, R>::LB * 8 / (SkinnyShape<CodeT, V, R>::BITS * R * (8 / V));
+    SkinnyArgs a;
+    a.codes = w->codes;
+    a.cb = (const half_t *)w->codebooks;
+    a.scale = (const half_t *)w->scale;
+    a.x = x;
+    a.y = y;
+    a.N = w->N;
+    a.K = w->K;
+    a.M = M;
+    a.E = w->n_entries;
+    a.ops = w->K / 8;
+    a.nit = (a.ops + 4 * MPI - 1) / (4 * MPI);
+    a.tile_n = w->cb_tile_n;
+    a.tiles_k = w->cb_tile_n > 0 ? w->K / w->cb_tile_k : 1;
+    a.tile_ops = w->cb_tile_n > 0 ? w->cb_tile_k / 8 : 1;
+    a.groups_m = (M + 16 * CT - 1) / (16 * CT);
+    constexpr size_t kUnit = 1024 * skinny_unit_of<CodeT, V, R>();
+    const size_t cb_bytes = L2CB ? 0 : ((size_t)R * a.E * V * 2 * a.tiles_k + 15) & ~(size_t)15;
+    int waves = std::min(a.nit, skinny_max_waves(L2CB, RT, CT));
+    while (waves > 1 && cb_bytes + waves * kUnit > kSkinnyLds) waves = (waves + 1) / 2;
+    const size_t lds = std::max(cb_bytes + waves * kUnit, (size_t)RT * CT * waves * 1024);
+    static KernelSetup setup;
+    if (int st = kernel_setup(reinterpret_cast<const void *>(&gemm_skinny_kernel<CodeT, V, R, L2CB, RT, CT>), lds, false, setup)) return st;
+    const long grid = (long)((w->N + 16 * RT - 1) / (16 * RT)) * a.groups_m;
+    gemm_skinny_kernel<CodeT, V, R, L2CB, RT, CT><<<(int)grid, waves * 64, lds, s>>>(a);
+    return launch_status();
+}
+
+// The tiles that are built, {RT, CT}.
+struct SkinnyTile { int rt, ct; };
+constexpr SkinnyTile kLdsTiles[] = {{1, 1}, {1, 2}, {2, 2}, {2, 4}, {4, 4}};   // ({1, 4} was never the best)
+constexpr SkinnyTile kL2Tiles[] = {{1, 1}, {1, 2}, {1, 4}, {2, 4}, {1, 8}, {2, 8}};
+
+// Estimated clocks of a launch: a workgroup's lookups (3.5 per clock from LDS, 0.35 from L2) and X (41 bytes per clock)
+// plus its start and end, times the rounds of workgroups over 256 CUs.  From LDS a second round is a whole one, later
+// ones fill in; from L2 all workgroups share the dies' L2s, so fewer than 256 of them are not that much faster.
+// The constants were fitted to 210 measured shapes (six formats, N 256 .. 11008, M 17 .. 256) x 6 tiles: the tile that
+// this picks takes 0.5 % more than the best one on average and 17 % more at worst.
+int skinny_tile(const vq_weight_t *w, int M, bool l2, double *clocks = nullptr) {
+    int best = 0;
+    double best_cost = 1e300;
+    for (int i = 0; i < (l2 ? 6 : 5); ++i) {
+        const SkinnyTile t = l2 ? kL2Tiles[i] : kLdsTiles[i];
+        if (w->cb_tile_n > 0 && w->cb_tile_n % (16 * t.rt) != 0) continue;
+        if (w->code_bits == 12 && t.rt == 4) continue;   // (four operands per lane and unit: does not fit the registers)
+        const double r = (double)(((long)w->N + 16 * t.rt - 1) / (16 * t.rt)) * ((M + 16 * t.ct - 1) / (16 * t.ct)) / 256;
+        const double rounds = l2 ? (r <= 1 ? std::max(0.7, r) : r + 0.3) : r <= 1 ? 1.0 : r <= 2 ? 2.0 : r + 0.3;
+        const double lookups = 16.0 * t.rt * (w->K / w->v) * w->n_codebooks / (l2 ? 0.35 : 3.5);
+        const double cost = rounds * (lookups + 16.0 * t.ct * w->K * 2 / 41 + 2000);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = i;
+        }
+    }
+    if (clocks) *clocks = best_cost;
+    return best;
+}
+
+template <typename CodeT, int V, int R>
+int run_lds(int tile, const vq_weight_t *w, const half_t *x, int M, half_t *y, hipStream_t s) {
+    switch (tile) {
+        case 0: return run_tile<CodeT, V, R, false, 1, 1>(w, x, M, y, s);
+        case 1: return run_tile<CodeT, V, R, false, 1, 2>(w, x, M, y, s);
+        case 2: return run_tile<CodeT, V, R, false, 2, 2>(w, x, M, y, s);
+        case 3: return run_tile<CodeT, V, R, false, 2, 4>(w, x, M, y, s);
+        default:
+            if constexpr (!std::is_same<CodeT, Code12>::value) return run_tile<CodeT, V, R, false, 4, 4>(w, x, M, y, s);
+            return VQ_ERR_UNSUPPORTED;
+    }
+}
+template <int V>
+int run_l2(int tile, const vq_weight_t *w, const half_t *x, int M, half_t *y, hipStream_t s) {
+    switch (tile) {
+        case 0: return run_tile<uint16_t, V, 1, true, 1, 1>(w, x, M, y, s);
+        case 1: return run_tile<uint16_t, V, 1, true, 1, 2>(w, x, M, y, s);
+        case 2: return run_tile<uint16_t, V, 1, true, 1, 4>(w, x, M, y, s);
+        case 3: return run_tile<uint16_t, V, 1, true, 2, 4>(w, x, M, y, s);
+        case 4: return run_tile<uint16_t, V, 1, true, 1, 8>(w, x, M, y, s);
+        default: return run_tile<uint16_t, V, 1, true, 2, 8>(w, x, M, y, s);
+    }
+}
+
+bool codebooks_fit_lds(const vq_weight_t *w) {
+    const size_t sets = w->cb_tile_n > 0 ? w->K / w->cb_tile_k : 1;
+    return sets * w->n_codebooks * w->n_entries * w->v * 2 <= kSkinnyLdsCodebook;
+}
+
+int run_skinny(int tile, const vq_weight_t *w, const half_t *x, int M, half_t *y, hipStream_t s) {
+    if (!codebooks_fit_lds(w)) return w->v == 8 ? run_l2<8>(tile, w, x, M, y, s) : run_l2<4>(tile, w, x, M, y, s);
+#define VQ_SK(CodeT)                                                                                              \
+    if (w->v == 8) return w->n_codebooks == 1 ? run_lds<CodeT, 8, 1>(tile, w, x, M, y, s) : run_lds<CodeT, 8, 2>(tile, w, x, M, y, s); \
+    return w->n_codebooks == 1 ? run_lds<CodeT, 4, 1>(tile, w, x, M, y, s) : run_lds<CodeT, 4, 2>(tile, w, x, M, y, s);
+    if (w->code_bits == 8) { VQ_SK(uint8_t) }
+    if (w->code_bits == 12) { VQ_SK(Code12) }
+    VQ_SK(uint16_t)
+#undef VQ_SK
+}
+
+}  // namespace
+
+// One or two codebooks, whole code loads per row (16-byte aligned rows; 8 bytes for single uint8 codes, 12-byte words
+// for 12-bit codes), codebooks of whole 16-byte pieces that fit LDS -- or one uint16 codebook of any size, from L2.
+bool gemm_skinny_supported(const vq_weight_t *w) {
+    const int R = w->n_codebooks;
+    if (R != 1 && R != 2) return false;
+    const int lb = w->code_bits == 12 ? 12 : R * w->code_bits == 8 ? 8 : 16;
+    const long row_bits = (long)(w->K / w->v) * R * w->code_bits;
+    if (w->K <= 0 || w->K % 8 != 0 || w->N <= 0 || w->N > (1 << 26) || row_bits % (lb * 8) != 0 || w->K > (1 << 22)) return false;   // (256 tokens: byte offsets into X of 32 bits)
+    if (codebooks_fit_lds(w)) return (R * w->n_entries * w->v * 2) % 16 == 0;
+    return w->cb_tile_n == 0 && R == 1 && w->code_bits == 16;
+}
+
+// More than 256 tokens: against the two-stage product, whose time is one round of 256 x 128 tiles after another, however
+// few tiles a round has (about 20 K + 5500 clocks), after writing the weight once (0.0017 clocks an element + 3500).
+// Measured with two 256-entry codebooks, two-stage / here: N = 256, K = 1024, 1024 tokens 19.0 / 5.6 us; N = 1024,
+// K = 4096, 1024 tokens 49.8 / 19.5; N = K = 4096, 384 tokens 63.1 / 34.5, 1024 tokens 60.5 / 67.6; N = 11008, 272 tokens
+// 77.8 / 67.8, 384 tokens 78.3 / 83.5; 2^16 entries, N = 1024, 1024 tokens 50.6 / 31.8, N = 4096, 384 tokens 59.7 / 60.3.
+// The estimates are good to 20 %, so this one has to be that much lower.
+bool gemm_skinny_wins(const vq_weight_t *w, int M) {
+    if (!gemm_skinny_supported(w) || (long)M * w->K >= (1L << 31)) return false;   // (byte offsets into X of 32 bits)
+    double here;
+    skinny_tile(w, M, !codebooks_fit_lds(w), &here);
+    const double rounds = (((long)((M + 255) / 256) * ((w->N + 127) / 128)) + 255) / 256;
+    return here < 0.8 * (rounds * (20.0 * w->K + 5500) + 0.0017 * w->N * w->K + 3500);
+}
+
+// Where vq_gemv (1 .. 16 tokens) runs here.
+// A codebook that does not fit LDS: the row kernel gathers every entry once per 4 tokens (and per token beyond 256 code
+// chunks a row), this one once.  v = 8 from two tokens on (N = K = 4096: 13.1 / 11.7 us; 16 tokens 67.4 / 12.4; one token
+// 12.0 / 11.8 at 4096 rows but 26.9 / 28.9 at 11008), v = 4 from five on (4 tokens 21.0 / 20.4, at 11008 rows 48.0 / 53.3;
+// 8 tokens 41.2 / 20.6).  Not where the caller says that the front of the codebook is hot: that part is kept in LDS.
+// LDS codebooks: the matrix-core gemv reads X in operand order, which costs it 0.1 .. 0.4 us per token; from 14 tokens on
+// this kernel is ahead where one round of workgroups covers the rows (16 tokens, N = 4096, K = 11008, two codebooks
+// 13.6 / 11.2; 8 tokens 10.3 / 10.9) and K is long enough to fill its wavefronts (K = 256: 3.6 / 4.0; 16 tokens of 11008
+// rows: 15.0 / 18.4).
+bool gemm_skinny_for_gemv(const vq_weight_t *w, int bs) {
+    if (!gemm_skinny_supported(w)) return false;
+    if (codebooks_fit_lds(w)) return bs >= 14 && w->K >= 2048 && w->N <= 16 * 256;
+    if (gemv_mfma_supported(w)) return false;
+    return bs >= (w->v == 8 ? 2 : 5) || w->K / (8 * w->v) > 256;
+}
+
+int launch_gemm_skinny(const vq_weight_t *w, const void *x, int M, void *y, hipStream_t s) {
+    return run_skinny(skinny_tile(w, M, !codebooks_fit_lds(w)), w, (const half_t *)x, M, (half_t *)y, s);
+}
+
+}  // namespace vq

@@ -267,7 +267,8 @@ template <typename CodeT, int V, int R, bool LDSCB>
 int run_rows_bs(const vq_weight_t *w, const half_t *x, int bs, half_t *y, hipStream_t s) {
     constexpr int KPC = (16 / ((int)sizeof(CodeT) * R)) * V;
     constexpr int BSMAX = KPC >= 128 ? 2 : 4;  // keeps the activation fragment within 128 registers
-    if (bs == 1) return run_rows<CodeT, V, R, LDSCB, 1>(w, x, bs, y, s);
+    // (several tokens of one uint16 codebook of 8-vectors: gemm_skinny.hip)
+    if (bs == 1 || (sizeof(CodeT) == 2 && V == 8 && R == 1 && !LDSCB)) return run_rows<CodeT, V, R, LDSCB, 1>(w, x, bs, y, s);
     if (bs == 2 || BSMAX == 2) return run_rows<CodeT, V, R, LDSCB, 2>(w, x, bs, y, s);
     return run_rows<CodeT, V, R, LDSCB, BSMAX>(w, x, bs, y, s);
 }
@@ -329,6 +330,7 @@ int launch_gemv_rows(const vq_weight_t *w, const void *x, int bs, void *y, hipSt
         fill_zero_kernel<<<(int)((n + 255) / 256), 256, 0, s>>>(yp, n);
         return launch_status();
     }
+    if (gemm_skinny_for_gemv(w, bs)) return launch_gemm_skinny(w, x, bs, y, s);
     if (gemv_mfma_supported(w)) return launch_gemv_mfma(w, x, bs, y, s);  // codebooks in LDS, matrix cores
     if (w->cb_tile_n > 0 || w->code_bits == 12) return VQ_ERR_UNSUPPORTED;  // those formats exist on that path only
     if (w->code_bits == 8) return w->v == 8 ? dispatch<uint8_t, 8>(w, xp, bs, yp, s) : dispatch<uint8_t, 4>(w, xp, bs, yp, s);

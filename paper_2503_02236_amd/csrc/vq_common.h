@@ -114,6 +114,11 @@ int launch_gemv_mfma(const vq_weight_t *w, const void *x, int bs, void *y, hipSt
 int launch_gemv_generic(const vq_weight_t *w, const void *x, int bs, void *y, hipStream_t s);
 int launch_gemm(const vq_weight_t *w, const void *X, int M, void *Y, void *ws, hipStream_t s);
 size_t gemm_workspace(const vq_weight_t *w, int M);
+// a few to a few hundred tokens in one pass over the codes (gemm_skinny.hip)
+bool gemm_skinny_supported(const vq_weight_t *w);
+bool gemm_skinny_wins(const vq_weight_t *w, int M);
+bool gemm_skinny_for_gemv(const vq_weight_t *w, int bs);
+int launch_gemm_skinny(const vq_weight_t *w, const void *x, int M, void *y, hipStream_t s);
 int launch_gemm_dense(const half_t *A, const half_t *B, const half_t *scale, half_t *C, int M, int N, int K,
                       hipStream_t s);
 bool gemv_mfma_batch_supported(const vq_weight_t *const *w, int count);

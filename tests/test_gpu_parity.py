@@ -770,6 +770,59 @@ def test_gemm_config4_full_size_sampled_columns(gpu_device, N, v):
     assert torch.isfinite(Y.float()).all()
 
 
+# The two-stage product at ragged sizes: three and four codebooks always take it, at any size (one K block, N of one and
+# of two tiles, rows of Y 16-byte aligned and not, two to five M tiles).
+@pytest.mark.parametrize("M,N,K,v,bits,R", [(300, 130, 256, 8, 8, 4), (1025, 64, 64, 8, 8, 4), (700, 200, 320, 8, 8, 3), (257, 136, 128, 4, 8, 4),
+                                            (257, 520, 256, 4, 16, 3)])
+def test_gemm_two_stage_ragged(gpu_device, M, N, K, v, bits, R):
+    w = wl.make_weight(N, K, v, bits, R, 200, 0.02 / R, seed=4760 + M)
+    X = wl.make_activations(M, K, seed=4761 + M)
+    Y = vq.vq_gemm(vq.weight_to_device(w, gpu_device), dev_x(X, gpu_device))
+    assert_close(Y, oracle.gemm(w.codes, w.codebooks, w.scale, X), f"gemm two-stage {M}x{N}x{K} R{R}")
+
+
+# One pass over the codes for 17 .. 256 tokens: every tile of the kernel ({weight rows} x {tokens} of a workgroup: 16 x 16,
+# 16 x 32, 32 x 32, 32 x 64, 64 x 64 from LDS; 16 x 16 .. 32 x 128 from L2) at ragged N, M and K, several iterations per
+# wavefront among them.  Codes are in range, so the bound is that of the other products (fp16 operands, fp32 sums).
+@pytest.mark.parametrize("N,K,M", [(33, 64, 17), (37, 1216, 18), (20, 2304, 256), (2051, 192, 17), (2051, 320, 33), (4099, 192, 33),
+                                   (8195, 64, 17), (8200, 320, 63), (131, 320, 401)])
+@pytest.mark.parametrize("v,bits,R,E", [(8, 8, 1, 256), (8, 8, 2, 200), (4, 8, 1, 256), (4, 8, 2, 256), (8, 12, 2, 4096), (8, 12, 1, 4096),
+                                        (4, 12, 2, 512), (8, 16, 2, 2048), (4, 16, 1, 1000), (4, 16, 2, 256)])
+def test_gemm_skinny_lds_codebooks(gpu_device, N, K, M, v, bits, R, E):
+    w = wl.make_weight(N, K, v, bits, R, E, 0.02 / R, seed=4800 + N + K, with_scale=(N + R) % 2 == 0)
+    X = wl.make_activations(M, K, seed=4801 + M)
+    Y = vq.vq_gemm(vq.weight_to_device(w, gpu_device), dev_x(X, gpu_device))
+    assert_close(Y, oracle.gemm(ocodes(w), w.codebooks, w.scale, X), f"skinny gemm {M}x{N}x{K} v{v} b{bits} R{R}")
+
+
+@pytest.mark.parametrize("v", [8, 4])
+@pytest.mark.parametrize("N,K,M", [(33, 64, 17), (37, 1216, 2), (64, 8320, 5), (1500, 192, 17), (1500, 320, 33), (1029, 64, 129),
+                                   (2051, 192, 129), (4099, 64, 17), (515, 1024, 256), (130, 320, 8), (130, 320, 16), (131, 320, 401)])
+def test_gemm_skinny_l2_codebook(gpu_device, N, K, M, v):
+    w = wl.make_weight(N, K, v, 16, 1, 65536, 0.02, seed=4850 + N + K, with_scale=N % 2 == 1)
+    X = wl.make_activations(M, K, seed=4851 + M)
+    wd = vq.weight_to_device(w, gpu_device)
+    Y = vq.vq_gemm(wd, dev_x(X, gpu_device)) if M > 16 else vq.vq_gemv(wd, dev_x(X, gpu_device))
+    assert_close(Y, oracle.gemm(w.codes, w.codebooks, w.scale, X), f"skinny gemm {M}x{N}x{K} v{v} 2^16")
+
+
+@pytest.mark.parametrize("bits,E,M", [(8, 256, 20), (16, 65536, 20), (16, 65536, 3)])
+def test_gemm_skinny_infinities_at_the_end_of_a_row(gpu_device, bits, E, M):
+    # K = 192 leaves half of an iteration past the end of every row; there the last codes and activations are read again,
+    # and an infinity among them must not meet a zero
+    w = wl.make_weight(40, 192, 8, bits, 1, E, 0.02, seed=4890, with_scale=False)
+    w.codes[:, -1, 0] = 7
+    w.codes[:, :-1, 0][w.codes[:, :-1, 0] == 7] = 8
+    w.codebooks[0, 7] = np.float16(0.01)
+    X = wl.make_activations(M, 192, seed=4891)
+    X[1, -1] = np.float16(np.inf)
+    wd = vq.weight_to_device(w, gpu_device)
+    Y = (vq.vq_gemm(wd, dev_x(X, gpu_device)) if M > 16 else vq.vq_gemv(wd, dev_x(X, gpu_device))).float().cpu().numpy()
+    assert np.isposinf(Y[1]).all()
+    rest = np.delete(np.arange(M), 1)
+    assert_close(torch.from_numpy(Y[rest]), oracle.gemm(w.codes, w.codebooks, None, X[rest]), "other tokens")
+
+
 def test_gemm_rows_match_gemv(gpu_device):
     # the prefill product of a few tokens and the decode product of the same tokens agree to tolerance
     w = wl.make_weight(256, 1024, 8, 16, 1, 65536, 0.02, seed=4600)
