@@ -866,6 +866,33 @@ def test_attn_small_full_compare(gpu_device, B, H, T, v, G, ragged):
     assert_close(run_attn(kv, gpu_device, sm), oracle_attn(kv, sm), f"attn B{B} H{H} T{T} v{v} G{G}")
 
 
+# p V on the matrix cores (two items per workgroup, v = 4): one codebook per head with copies in LDS, and 32 codebooks; odd
+# numbers of items and of token ranges, one and two tokens past a 32-token unit, flat and sharp softmax (weights from 1 down
+# to far below the smallest half), and a V codebook with an infinity and a NaN that some tokens use.
+@pytest.mark.parametrize("sharp", [1.0, 6.0])
+@pytest.mark.parametrize("B,H,T,G", [(13, 32, 33, 1), (16, 24, 290, 1), (3, 32, 1500, 32), (9, 32, 97, 32), (3, 32, 2050, 32)])
+def test_attn_matrix_core_values(gpu_device, B, H, T, G, sharp):
+    kv = wl.make_kv(B, H, 128, T, 4, 256, G, seed=5300 + T, ragged=sharp > 1)
+    kv.q = (kv.q * np.float16(sharp)).astype(np.float16)
+    sm = 1.0 / np.sqrt(128.0)
+    assert_close(run_attn(kv, gpu_device, sm), oracle_attn(kv, sm), f"attn B{B} H{H} T{T} G{G} x{sharp}")
+
+
+@pytest.mark.parametrize("B,H,T,G", [(16, 24, 290, 1), (3, 32, 1500, 32)])
+def test_attn_matrix_core_values_with_infinities(gpu_device, B, H, T, G):
+    kv = wl.make_kv(B, H, 128, T, 4, 256, G, seed=5350 + T)
+    kv.v_codes[kv.v_codes == 7] = 8
+    kv.v_codes[kv.v_codes == 9] = 8
+    kv.v_codebooks[3, 0, 7, 1] = np.float16(-np.inf)      # element 1 of entry 7, head 3
+    kv.v_codebooks[5, 0, 9, 2] = np.float16(np.nan)       # an entry that no token uses
+    kv.v_codes[1, 3, T - 20, 0] = 7                       # channel 1 of batch entry 1, head 3
+    want = oracle_attn(kv, 1.0 / np.sqrt(128.0))
+    got = run_attn(kv, gpu_device, 1.0 / np.sqrt(128.0)).float().cpu().numpy()
+    assert want[1, 3, 1] == -np.inf and got[1, 3, 1] == -np.inf
+    want[1, 3, 1] = got[1, 3, 1] = 0
+    assert_close(torch.from_numpy(got), want, "all other channels")
+
+
 def test_attn_two_sequences_per_workgroup_odd_batch_and_empty_sequences(gpu_device):
     # 32 codebooks per head and side: pairs of batch entries share a workgroup; the batch is odd, one
     # sequence is empty and one stops inside the first token range while its partner goes on
