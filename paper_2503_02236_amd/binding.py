@@ -131,7 +131,8 @@ def status_str(status: int) -> str:
 
 
 def _stream() -> int:
-    return int(torch.cuda.current_stream().cuda_stream)
+    """The current HIP stream of the current device, without building a stream object (1 us of a 10 us call)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dev(t: Optional[torch.Tensor], name: str, dtype=None) -> Optional[int]:
@@ -143,7 +144,7 @@ def _dev(t: Optional[torch.Tensor], name: str, dtype=None) -> Optional[int]:
         raise ValueError(f"{name} must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
-    return int(t.data_ptr())
+    return t.data_ptr()
 
 
 @dataclass
@@ -162,10 +163,10 @@ class VQWeightDev:
     cb_tile: Optional[tuple] = None              # (tile_n, tile_k): codebooks [N/tile_n][K/tile_k][R][E][v]
 
     def desc(self, use_pack: bool = True) -> vq_weight_t:
-        R, E, v = self.codebooks.shape[-3:]
+        shape = self.codebooks.shape
         tn, tk = self.cb_tile if self.cb_tile else (0, 0)
         code_dt = torch.uint16 if self.code_bits == 16 else torch.uint8   # 12-bit codes: packed bytes
-        d = vq_weight_t(self.N, self.K, self.v, self.code_bits, R, E,
+        d = vq_weight_t(self.N, self.K, self.v, self.code_bits, shape[-3], shape[-2],
                         _dev(self.codes, "codes", code_dt), _dev(self.codebooks, "codebooks", torch.float16),
                         _dev(self.scale, "scale", torch.float16), None, int(self.hot_entries), int(tn), int(tk))
         if use_pack and self.pack is not None:
@@ -274,9 +275,11 @@ def _check(status: int, where: str):
         raise VQError(status, where)
 
 
-def _workspace(nbytes: int, device, ws: Optional[torch.Tensor]):
+def _workspace(device, ws: Optional[torch.Tensor], query, *args):
+    """The caller's workspace, or one of the size that ``query(*args)`` names (asked only then)."""
     if ws is not None:
         return ws, _dev(ws, "ws"), ws.numel() * ws.element_size()
+    nbytes = query(*args)
     if nbytes == 0:
         return None, None, 0
     ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
@@ -293,10 +296,10 @@ def vq_gemv(w: VQWeightDev, x: torch.Tensor, y: Optional[torch.Tensor] = None,
     """y[bs][N] = scale * (x[bs][K] @ dequant(W)^T) on the current stream."""
     bs = x.shape[0]
     if y is None:
-        y = torch.empty((bs, w.N), dtype=torch.float16, device=x.device)
-    d = w.desc()
-    ws_t, ws_p, ws_n = _workspace(int(lib().vq_gemv_workspace(ctypes.byref(d), bs)), x.device, ws)
-    _check(lib().vq_gemv(ctypes.byref(d), _dev(x, "x", torch.float16), bs, _dev(y, "y", torch.float16),
+        y = x.new_empty((bs, w.N))     # (x has to be fp16: checked below)
+    d, l = ctypes.byref(w.desc()), lib()
+    ws_t, ws_p, ws_n = _workspace(x.device, ws, l.vq_gemv_workspace, d, bs)
+    _check(l.vq_gemv(d, _dev(x, "x", torch.float16), bs, _dev(y, "y", torch.float16),
                          ws_p, ws_n, _stream()), "vq_gemv")
     return y
 
@@ -333,7 +336,7 @@ def vq_gemv_batch(ws_list, xs, ys=None, ws: Optional[torch.Tensor] = None):
     if ys is None:
         ys = [torch.empty((1, w.N), dtype=torch.float16, device=x.device) for w, x in zip(ws_list, xs)]
     call = GemvBatch(ws_list, xs, ys)
-    ws_t, ws_p, ws_n = _workspace(call.workspace(), xs[0].device, ws)
+    ws_t, ws_p, ws_n = _workspace(xs[0].device, ws, call.workspace)
     _check(call.run(ws_p, ws_n), "vq_gemv_batch")
     return ys
 
@@ -426,7 +429,7 @@ def vq_gemv_sequence(calls, ws: Optional[torch.Tensor] = None):
 
     ``calls``: list of lists of (VQWeightDev, x, y).  Returns the marshalled sequence (its y tensors are filled)."""
     seq = GemvSequence(calls)
-    ws_t, ws_p, ws_n = _workspace(seq.workspace(), calls[0][0][1].device, ws)
+    ws_t, ws_p, ws_n = _workspace(calls[0][0][1].device, ws, seq.workspace)
     _check(seq.run(ws_p, ws_n), "vq_gemv_sequence")
     return seq
 
@@ -441,10 +444,10 @@ def vq_gemm(w: VQWeightDev, X: torch.Tensor, Y: Optional[torch.Tensor] = None,
     """Y[M][N] = scale * (X[M][K] @ dequant(W)^T) on the current stream (matrix cores)."""
     M = X.shape[0]
     if Y is None:
-        Y = torch.empty((M, w.N), dtype=torch.float16, device=X.device)
-    d = w.desc()
-    ws_t, ws_p, ws_n = _workspace(int(lib().vq_gemm_workspace(ctypes.byref(d), M)), X.device, ws)
-    _check(lib().vq_gemm(ctypes.byref(d), _dev(X, "X", torch.float16), M, _dev(Y, "Y", torch.float16),
+        Y = X.new_empty((M, w.N))      # (X has to be fp16: checked below)
+    d, l = ctypes.byref(w.desc()), lib()
+    ws_t, ws_p, ws_n = _workspace(X.device, ws, l.vq_gemm_workspace, d, M)
+    _check(l.vq_gemm(d, _dev(X, "X", torch.float16), M, _dev(Y, "Y", torch.float16),
                          ws_p, ws_n, _stream()), "vq_gemm")
     return Y
 
@@ -459,9 +462,9 @@ def vq_attn_decode(kv: VQKVDev, q: torch.Tensor, sm_scale: float, out: Optional[
     """out[B][H][D] = softmax(sm_scale * q K^T) V over the VQ cache, on the current stream."""
     if out is None:
         out = torch.empty_like(q)
-    d = kv.desc()
-    ws_t, ws_p, ws_n = _workspace(int(lib().vq_attn_decode_workspace(ctypes.byref(d))), q.device, ws)
-    _check(lib().vq_attn_decode(ctypes.byref(d), _dev(q, "q", torch.float16), float(sm_scale),
+    d, l = ctypes.byref(kv.desc()), lib()
+    ws_t, ws_p, ws_n = _workspace(q.device, ws, l.vq_attn_decode_workspace, d)
+    _check(l.vq_attn_decode(d, _dev(q, "q", torch.float16), float(sm_scale),
                                 _dev(out, "out", torch.float16), ws_p, ws_n, _stream()), "vq_attn_decode")
     return out
 
@@ -471,9 +474,9 @@ def vq_attn_decode_channel_parallel(kv: VQKVDev, q: torch.Tensor, sm_scale: floa
     """The same product by the channel-parallel dataflow (caches with one codebook per channel sub-space)."""
     if out is None:
         out = torch.empty_like(q)
-    d = kv.desc()
-    ws_t, ws_p, ws_n = _workspace(int(lib().vq_attn_decode_channel_parallel_workspace(ctypes.byref(d))), q.device, ws)
-    _check(lib().vq_attn_decode_channel_parallel(ctypes.byref(d), _dev(q, "q", torch.float16), float(sm_scale),
+    d, l = ctypes.byref(kv.desc()), lib()
+    ws_t, ws_p, ws_n = _workspace(q.device, ws, l.vq_attn_decode_channel_parallel_workspace, d)
+    _check(l.vq_attn_decode_channel_parallel(d, _dev(q, "q", torch.float16), float(sm_scale),
                                                  _dev(out, "out", torch.float16), ws_p, ws_n, _stream()),
            "vq_attn_decode_channel_parallel")
     return out
