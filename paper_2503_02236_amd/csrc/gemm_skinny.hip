@@ -493,17 +493,17 @@ bool gemm_skinny_supported(const vq_weight_t *w) {
     return w->cb_tile_n == 0 && R == 1 && w->code_bits == 16;
 }
 
-// More than 256 tokens: against the two-stage product, whose time is one round of 256 x 128 tiles after another, however
-// few tiles a round has (about 20 K + 5500 clocks), after writing the weight once (0.0017 clocks an element + 3500).
-// Measured with two 256-entry codebooks, two-stage / here: N = 256, K = 1024, 1024 tokens 19.0 / 5.6 us; N = 1024,
-// K = 4096, 1024 tokens 49.8 / 19.5; N = K = 4096, 384 tokens 63.1 / 34.5, 1024 tokens 60.5 / 67.6; N = 11008, 272 tokens
-// 77.8 / 67.8, 384 tokens 78.3 / 83.5; 2^16 entries, N = 1024, 1024 tokens 50.6 / 31.8, N = 4096, 384 tokens 59.7 / 60.3.
+// More than 256 tokens: against the two-stage product, whose time is one round of tiles after another, however few tiles a
+// round has (256 x 128 tiles: about 20 K + 5500 clocks), after writing the weight once (0.0017 clocks an element + 3500).
+// Measured with two 256-entry codebooks, two-stage / here: N = 256, K = 1024, 1024 tokens 13.0 / 5.8 us; N = 1024,
+// K = 4096, 1024 tokens 35.7 / 20.0; N = K = 4096, 384 tokens 48.2 / 34.8, 1024 tokens 51.4 / 67.6; N = 11008, 272 tokens
+// 75.0 / 66.2, 384 tokens 75.7 / 83.5; 2^16 entries, N = 1024, 1024 tokens 36.9 / 31.8, N = 4096, 384 tokens 45.4 / 60.3.
 // The estimates are good to 20 %, so this one has to be that much lower.
 bool gemm_skinny_wins(const vq_weight_t *w, int M) {
     if (!gemm_skinny_supported(w) || (long)M * w->K >= (1L << 31)) return false;   // (byte offsets into X of 32 bits)
     double here;
     skinny_tile(w, M, !codebooks_fit_lds(w), &here);
-    const double rounds = (((long)((M + 255) / 256) * ((w->N + 127) / 128)) + 255) / 256;
+    const double rounds = gemm_dense_rounds(M, w->N, nullptr);
     return here < 0.8 * (rounds * (20.0 * w->K + 5500) + 0.0017 * w->N * w->K + 3500);
 }
 

@@ -119,6 +119,7 @@ bool gemm_skinny_supported(const vq_weight_t *w);
 bool gemm_skinny_wins(const vq_weight_t *w, int M);
 bool gemm_skinny_for_gemv(const vq_weight_t *w, int bs);
 int launch_gemm_skinny(const vq_weight_t *w, const void *x, int M, void *y, hipStream_t s);
+double gemm_dense_rounds(int M, int N, bool *small);
 int launch_gemm_dense(const half_t *A, const half_t *B, const half_t *scale, half_t *C, int M, int N, int K,
                       hipStream_t s);
 bool gemv_mfma_batch_supported(const vq_weight_t *const *w, int count);

@@ -771,9 +771,9 @@ def test_gemm_config4_full_size_sampled_columns(gpu_device, N, v):
 
 
 # The two-stage product at ragged sizes: three and four codebooks always take it, at any size (one K block, N of one and
-# of two tiles, rows of Y 16-byte aligned and not, two to five M tiles).
+# of two tiles, rows of Y 16-byte aligned and not, two to five M tiles; the last two sizes take the larger tile).
 @pytest.mark.parametrize("M,N,K,v,bits,R", [(300, 130, 256, 8, 8, 4), (1025, 64, 64, 8, 8, 4), (700, 200, 320, 8, 8, 3), (257, 136, 128, 4, 8, 4),
-                                            (257, 520, 256, 4, 16, 3)])
+                                            (257, 520, 256, 4, 16, 3), (1990, 3013, 64, 8, 8, 3), (1990, 3016, 192, 8, 8, 4)])
 def test_gemm_two_stage_ragged(gpu_device, M, N, K, v, bits, R):
     w = wl.make_weight(N, K, v, bits, R, 200, 0.02 / R, seed=4760 + M)
     X = wl.make_activations(M, K, seed=4761 + M)
