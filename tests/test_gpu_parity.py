@@ -36,6 +36,17 @@ def dev_x(x, device):
 
 # ---------------------------------------------------------------- dequantized tiles: bit exact
 
+# weights large enough for the kernel with eight sub-vectors per thread (a ragged last workgroup each): the fp16 tile is the
+# fp32 one rounded, bit for bit
+@pytest.mark.parametrize("N,K,v,bits,R,E", [(2051, 4160, 8, 16, 1, 65536), (2051, 4160, 8, 8, 2, 256), (1031, 4160, 4, 16, 1, 65536),
+                                            (1031, 4160, 4, 8, 2, 256), (2051, 4160, 8, 12, 2, 4096), (1031, 4160, 4, 12, 1, 4096),
+                                            (2051, 4160, 8, 16, 2, 3000)])
+def test_dequant_large_fp16_is_the_rounded_fp32_tile(gpu_device, N, K, v, bits, R, E):
+    wd = vq.weight_to_device(wl.make_weight(N, K, v, bits, R, E, 0.02, seed=60 + v + bits + R), gpu_device)
+    half, full = vq.vq_dequant(wd, out_fp32=False), vq.vq_dequant(wd, out_fp32=True)
+    assert torch.equal(half.view(torch.int16), full.to(torch.float16).view(torch.int16))
+
+
 @pytest.mark.parametrize("N,K,v,bits,R,E,sigma", [
     (256, 256, 8, 8, 1, 256, 0.02),        # config 1
     (96, 4096, 8, 16, 1, 65536, 0.02),     # config 2 codebook, a slab of rows
