@@ -18,7 +18,7 @@
 //   (Sec. III-B, Fig. 6) is deferred to one sum over lanes at the very end, so dequantized values never travel
 //   through LDS.
 // Measured (B = 16, H = 32, T = 4096, one codebook per head and side, 134 MB of codes): vector ALU 34.2 us, matrix cores
-// 31.3 us (4.3 TB/s).  The vector ALU issued 99 instructions per 16 tokens, half of them for p V, now about 50; what is
+// 31.3 us with the codes in the last-level cache, 36.6 / 35.1 and 34.2 / 34.2 from HBM on two cards.  The vector ALU issued 99 instructions per 16 tokens, half of them for p V, now about 50; what is
 // left is the chain of a tile: codes -> entries -> scores -> maximum -> weights -> p V with 4 wavefronts per SIMD.
 // Only ~130 registers per lane are needed, so 16 wavefronts per CU hide the gather latency.
 // Codebooks live in LDS (2 KB each for one codebook per head and side).
