@@ -515,10 +515,11 @@ bool gemm_skinny_wins(const vq_weight_t *w, int M) {
 // LDS codebooks: the matrix-core gemv reads X in operand order, which costs it 0.1 .. 0.4 us per token; from 14 tokens on
 // this kernel is ahead where one round of workgroups covers the rows (16 tokens, N = 4096, K = 11008, two codebooks
 // 13.6 / 11.2; 8 tokens 10.3 / 10.9) and K is long enough to fill its wavefronts (K = 256: 3.6 / 4.0; 16 tokens of 11008
-// rows: 15.0 / 18.4).
+// rows: 15.0 / 18.4).  Not for 12-bit codes, which have no transposition (16 tokens with cold caches, N = K = 4096: 10.1 /
+// 10.7).
 bool gemm_skinny_for_gemv(const vq_weight_t *w, int bs) {
     if (!gemm_skinny_supported(w)) return false;
-    if (codebooks_fit_lds(w)) return bs >= 14 && w->K >= 2048 && w->N <= 16 * 256;
+    if (codebooks_fit_lds(w)) return bs >= 14 && w->code_bits != 12 && w->K >= 2048 && w->N <= 16 * 256;
     if (gemv_mfma_supported(w)) return false;
     return bs >= (w->v == 8 ? 2 : 5) || w->K / (8 * w->v) > 256;
 }
