@@ -374,10 +374,14 @@ __global__ __launch_bounds__(kAttnWaves * 64 * SEQ) __attribute__((amdgpu_waves_
         // ---- V on the matrix cores.  The K operand comes first, so a score lands with token = accumulator row: lane
         // (r, g) holds the scores of tokens 16 s + 4 g + 0..3 of every step s -- the 8 slots (s, i) of its part of the
         // reduction axis in the second product.  Row r of that product's first operand carries slot r % 8 only: each
-        // lane forms one weight, as an fp16 value (rows 0..7) or as what the fp16 value leaves of the fp32 one, times
-        // 2^11 (rows 8..15), so a weight keeps 22 bits and more; the 16 rows are added at the very end.  The 7 zeros
-        // of a row meet other tokens' values, which is why V is staged without infinities.
+        // lane forms one weight times 2^15, as an fp16 value (rows 0..7) or as what the fp16 value leaves of the fp32
+        // one, times 2^12 (rows 8..15); the 16 rows are added at the very end.  A weight (1 at most) so keeps 23 bits, the
+        // precision of its exponential, down to 2^-29, and is off by 2^-52 at most below that; both sums, p V and that of
+        // the weights, take the same value.  (With weights up to 1 and 2^11 those below 2^-36 were zero in p V alone: 31
+        // tokens of 2^-38 and V = 60000 beside one of weight 1 gave 0 where 7e-6 is right.)  The 7 zeros of a row meet
+        // other tokens' values, which is why V is staged without infinities.
         constexpr int NU = NS / 2 > 0 ? NS / 2 : 1;   // units of 32 tokens per tile
+        constexpr float kWeightUp = 32768.f, kRestUp = 4096.f;
         const int slot = tok & 7;
         const bool lo_row = tok >= 8;
         const unsigned half_shift = 16u * (slot & 1);
@@ -425,11 +429,11 @@ __global__ __launch_bounds__(kAttnWaves * 64 * SEQ) __attribute__((amdgpu_waves_
 
 #pragma unroll
             for (int u = 0; u < NU; ++u) {
-                const float p_t = sc[u] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sc[u] - m_run);
-                lsum += p_t;
+                const float p_t = (sc[u] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sc[u] - m_run)) * kWeightUp;
                 const half_t p_hi = (half_t)p_t;
-                const half_t p_lo = (half_t)((p_t - (float)p_hi) * 2048.f);
-                const unsigned bits = (unsigned)__builtin_bit_cast(unsigned short, lo_row ? p_lo : p_hi) << half_shift;
+                const half_t part = lo_row ? (half_t)((p_t - (float)p_hi) * kRestUp) : p_hi;
+                lsum += (float)part;   // (the sum of the weights as they are used)
+                const unsigned bits = (unsigned)__builtin_bit_cast(unsigned short, part) << half_shift;
                 V16 pop;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) pop.w[j] = bits & keep[j];
@@ -453,10 +457,10 @@ __global__ __launch_bounds__(kAttnWaves * 64 * SEQ) __attribute__((amdgpu_waves_
             tile_step(it, kA, vA, kB);
             if (it + 1 < ntiles) tile_step(it + 1, kB, vB, kA);
         }
-        lsum = wave_sum(lsum) * 0.5f;   // two lanes per token
+        lsum = wave_sum(lsum * (lo_row ? 1.f / (kWeightUp * kRestUp) : 1.f / kWeightUp));
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            float o = ((acc[q][0] + acc[q][1]) + (acc[q][2] + acc[q][3])) * (g < 2 ? 1.f : 1.f / 2048.f);
+            float o = ((acc[q][0] + acc[q][1]) + (acc[q][2] + acc[q][3])) * (g < 2 ? 1.f / kWeightUp : 1.f / (kWeightUp * kRestUp));
             o += __shfl_xor(o, 16, 64);
             o += __shfl_xor(o, 32, 64);
             // column tok of operand q: channel 4 (its code's position) + tok % 4 for v = 4

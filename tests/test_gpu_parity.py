@@ -904,6 +904,26 @@ def test_attn_matrix_core_values_with_infinities(gpu_device, B, H, T, G):
     assert_close(torch.from_numpy(got), want, "all other channels")
 
 
+@pytest.mark.parametrize("B,H,T,G", [(16, 24, 290, 1), (9, 32, 97, 32), (3, 32, 2050, 32)])
+@pytest.mark.parametrize("bits", [20, 30, 34, 38])
+def test_attn_small_weights_of_large_values(gpu_device, B, H, T, G, bits):
+    """In every run of 32 tokens one takes nearly all of the softmax and holds zeros in every fourth channel; the others
+    have weights of 2^-bits and hold 60000 there, so those channels are sums of the small weights alone.  A weight may be
+    off by 2^-23 of itself (two halves), by 2^-52 of the largest (where the smaller half ends) and by the rounding of its
+    exponent's argument (about 2^6, to 24 bits: 2^-18); the output by one rounding to half."""
+    kv = wl.make_kv(B, H, 128, T, 4, 256, G, seed=5380 + T)
+    sm = 1.0 / np.sqrt(128.0)
+    kv.q[:] = 1
+    kv.k_codes[:], kv.v_codes[:] = 1, 1
+    kv.k_codes[:, :, 7::32], kv.v_codes[:, :, 7::32] = 0, 0
+    kv.k_codebooks[:, :, 0], kv.k_codebooks[:, :, 1] = 0, np.float16(-bits * np.log(2.0) / (128 * sm))
+    kv.v_codebooks[:, :, 0], kv.v_codebooks[:, :, 1] = np.float16([0, 0.5, -1, 2]), np.float16([60000, 1, 3, -2])
+    want = oracle_attn(kv, sm)
+    got = run_attn(kv, gpu_device, sm).double().cpu().numpy()
+    bound = (2.0 ** -11 + 2.0 ** -17) * np.abs(want) + 2.0 ** -25 + 32 * 60000 * 2.0 ** -52
+    assert (np.abs(got - want) <= bound).all(), (want[0, 0, 0], got[0, 0, 0])
+
+
 def test_attn_two_sequences_per_workgroup_odd_batch_and_empty_sequences(gpu_device):
     # 32 codebooks per head and side: pairs of batch entries share a workgroup; the batch is odd, one
     # sequence is empty and one stops inside the first token range while its partner goes on
