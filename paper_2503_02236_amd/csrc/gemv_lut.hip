@@ -144,7 +144,8 @@ __global__ __launch_bounds__(kLutThreads) void gemv_lut_kernel(const LutSegment 
         rq_turn = 0;
         rq_base = rq.codes;
         const int at = rq_slice * kSliceBytes + q * 16;
-        // (a lane before the row or past it reads the row's first codes; what it looks up is dropped)
+        // (a lane before the row or past it, or one half of it where R = 1, reads the row's first codes; what it looks up
+        // is dropped)
         rq_col = inside(rq, at) ? at : rq.lead;
         rq_second = (inside(rq, at + 8) ? at + 8 : rq.lead) - rq_col;
         rq_off = rq_col + (uint32_t)((8 * wave + row) * rq.stride);
@@ -194,7 +195,8 @@ __global__ __launch_bounds__(kLutThreads) void gemv_lut_kernel(const LutSegment 
     LutSegment sg;
     half8_t ent;                        // A operand: 32 entries of the wavefront (codebook wave / 8, entries 32 (wave % 8) ..)
     int seg = seg0, slice = 0;
-    bool whole = true, in_row = true;   // the slice lies in the row; the lane's chunk does
+    bool whole = true;                  // the slice lies in the row
+    bool in_row[2] = {true, true};      // the halves of the lane's chunk do (R = 2: both or none)
     lds_f32_t *acc = nullptr;           // row sums of the segment, behind x
     lds_f32_t *acc_lane = nullptr;      // where the lane's current row lies
 
@@ -237,7 +239,8 @@ __global__ __launch_bounds__(kLutThreads) void gemv_lut_kernel(const LutSegment 
         lut_barrier();
         const int at = s * kSliceBytes;
         whole = inside(sg, at) && inside(sg, at + kSliceBytes - 1);
-        in_row = inside(sg, at + q * 16) || (R == 1 && inside(sg, at + q * 16 + 8));
+        in_row[0] = inside(sg, at + q * 16);
+        in_row[1] = R == 1 ? inside(sg, at + q * 16 + 8) : in_row[0];
         acc_lane = acc + 8 * wave + row;
     };
     // Waits for all but the requests made after this one (anything else in flight is older, or makes the wait stricter).
@@ -263,6 +266,10 @@ __global__ __launch_bounds__(kLutThreads) void gemv_lut_kernel(const LutSegment 
 #pragma unroll
             for (int r = 0; r < 2; ++r)
                 v[2 * t + r] = *(lds_f32_t *)(uintptr_t)__builtin_amdgcn_perm(kc[t >> 1], w[t >> 1], sel[t & 1][r]);
+        if (R == 1 && !whole) {      // (uniform; not by a zero of x: the row's first code may name an infinity)
+#pragma unroll
+            for (int t = 0; t < 16; ++t) v[t] = in_row[t >> 3] ? v[t] : 0.f;
+        }
         float s0 = v[0], s1 = v[1];
 #pragma unroll
         for (int t = 1; t < 8; ++t) {
@@ -270,7 +277,7 @@ __global__ __launch_bounds__(kLutThreads) void gemv_lut_kernel(const LutSegment 
             s1 += v[2 * t + 1];
         }
         float s = s0 + s1;
-        if (!whole) s = in_row ? s : 0.f;
+        if (R == 2 && !whole) s = in_row[0] ? s : 0.f;
         s = lut_dpp_add<0xB1>(s);    // quad_perm [1,0,3,2]
         s = lut_dpp_add<0x4E>(s);    // quad_perm [2,3,0,1]
         s = lut_dpp_add<0x141>(s);   // row_half_mirror: all eight lanes of the row

@@ -559,6 +559,36 @@ def test_gemv_pipeline_long_small_codebook_lists(gpu_device, R, count, shapes):
     pipe.close()
 
 
+@pytest.mark.parametrize("R", [1, 2])
+def test_gemv_pipeline_long_list_infinite_entry_at_the_start_of_a_row(gpu_device, R):
+    """A lane whose 16 code bytes lie partly outside its row looks up the row's first codes in place of the missing ones.
+    Where the first code names an infinite entry, the row is +-inf, and no zero of the padding may turn that into a NaN:
+    rows of 72 (144) bytes, whose ends lie 8 (0) bytes into a chunk of 16, dealt as one run of rows and as every
+    sixteenth (eighth)."""
+    calls, ref = [], []
+    for i in range(48):
+        N = (16500, 700)[i % 2]
+        w = wl.make_weight(N, 576, 8, 8, R, 256, 0.01, seed=12700 + i, with_scale=(i % 4 != 0))
+        w.codes[w.codes == 7] = 8
+        w.codes[3::5, 0, R - 1] = 7
+        w.codebooks[R - 1, 7, 2] = np.float16(np.inf)
+        x = wl.make_activations(1, w.K, seed=12800 + i)
+        wd = vq.weight_to_device(w, gpu_device)
+        calls.append([(wd, dev_x(x, gpu_device), torch.zeros((1, N), dtype=torch.float16, device=gpu_device))])
+        ref.append((w, x))
+    pipe = vq.GemvPipeline(calls)
+    assert vq.lib().vq_gemv_pipeline_workspace(pipe.seq.arr, pipe.seq.n) > 72 * 256     # (a long list)
+    assert pipe.run() == 0
+    torch.cuda.synchronize()
+    for i, (c, (w, x)) in enumerate(zip(calls, ref)):
+        got = c[0][2].float().cpu().numpy()[0]
+        want = oracle.gemv(w.codes, w.codebooks, w.scale, x)[0]
+        inf = np.arange(w.N) % 5 == 3
+        assert np.array_equal(np.isinf(want), inf) and np.array_equal(got[inf], want[inf].astype(np.float32)), i
+        assert_close(torch.from_numpy(got[~inf]), want[~inf], f"finite rows of member {i}, R={R}")
+    pipe.close()
+
+
 def test_gemv_pipeline_small_codebook_nan_entries_unused(gpu_device):
     """Entries that no code uses are never multiplied into a result: with NaN in them the outputs stay finite and
     equal those with zeros there (a lane past the end of a ragged row computes with codes that are not its own;
