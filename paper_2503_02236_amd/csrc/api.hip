@@ -292,11 +292,20 @@ static int check_pipeline_calls(const vq_gemv_call_t *calls, int n_calls) {
     return VQ_OK;
 }
 
+// Bytes of workspace a checked list needs, 0 where the host is out of memory (lists are planned in host vectors, whose
+// exceptions must not pass a C entry point).
+static size_t pipeline_workspace(const vq_gemv_call_t *calls, int n_calls, bool rep) {
+    try {
+        return rep ? small_codebook_workspace(calls, n_calls) : gemv_pipeline_workspace(calls, n_calls);
+    } catch (const std::bad_alloc &) {
+        return 0;
+    }
+}
+
 size_t vq_gemv_pipeline_workspace(const vq_gemv_call_t *calls, int n_calls) {
     const int rep = replica_calls(calls, n_calls);
-    if (rep == 1) return small_codebook_workspace(calls, n_calls);
-    if (rep < 0 || check_pipeline_calls(calls, n_calls) != VQ_OK) return 0;
-    return gemv_pipeline_workspace(calls, n_calls);
+    if (rep < 0 || (rep == 0 && check_pipeline_calls(calls, n_calls) != VQ_OK)) return 0;
+    return pipeline_workspace(calls, n_calls, rep == 1);
 }
 
 int vq_gemv_pipeline_create(const vq_gemv_call_t *calls, int n_calls, void *ws, size_t ws_bytes, void *stream,
@@ -307,7 +316,8 @@ int vq_gemv_pipeline_create(const vq_gemv_call_t *calls, int n_calls, void *ws, 
     if (rep < 0) return rep;
     if (rep == 0)
         if (int st = check_pipeline_calls(calls, n_calls)) return st;
-    const size_t need = rep ? small_codebook_workspace(calls, n_calls) : gemv_pipeline_workspace(calls, n_calls);
+    const size_t need = pipeline_workspace(calls, n_calls, rep == 1);
+    if (!need) return VQ_ERR_LAUNCH;
     if (!ws || ws_bytes < need) return VQ_ERR_WORKSPACE;
     if (((uintptr_t)ws & 255) != 0) return VQ_ERR_ALIGN;
     vq_gemv_pipeline *h = new (std::nothrow) vq_gemv_pipeline;
@@ -315,9 +325,14 @@ int vq_gemv_pipeline_create(const vq_gemv_call_t *calls, int n_calls, void *ws, 
     h->impl = nullptr;
     h->rep = nullptr;
     h->lut = nullptr;
-    const int st = rep && gemv_lut_worth(calls, n_calls) ? gemv_lut_list_create(calls, n_calls, ws, static_cast<hipStream_t>(stream), &h->lut)
-                   : rep ? gemv_replica_list_create(calls, n_calls, ws, static_cast<hipStream_t>(stream), &h->rep)
-                         : gemv_pipeline_create(calls, n_calls, ws, static_cast<hipStream_t>(stream), &h->impl);
+    int st;
+    try {
+        st = rep && gemv_lut_worth(calls, n_calls) ? gemv_lut_list_create(calls, n_calls, ws, static_cast<hipStream_t>(stream), &h->lut)
+             : rep ? gemv_replica_list_create(calls, n_calls, ws, static_cast<hipStream_t>(stream), &h->rep)
+                   : gemv_pipeline_create(calls, n_calls, ws, static_cast<hipStream_t>(stream), &h->impl);
+    } catch (const std::bad_alloc &) {
+        st = VQ_ERR_LAUNCH;
+    }
     if (st != VQ_OK) {
         delete h;
         return st;

@@ -3,6 +3,8 @@ and rejects bad arguments before anything is launched."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -418,3 +420,50 @@ def test_binding_refuses_host_tensors():
     wd = vq.VQWeightDev(w.N, w.K, w.v, w.code_bits, torch.from_numpy(w.codes), torch.from_numpy(w.codebooks), None)
     with pytest.raises(ValueError):
         vq.vq_gemv(wd, torch.from_numpy(x))
+
+
+def test_gemv_pipeline_reports_a_failed_host_allocation(tmp_path):
+    """The plan of a list is made in host vectors: where one of their allocations fails, the entry points say so instead of
+    letting the exception end a C caller's program.  The n-th allocation fails, for every n until a call gets through."""
+    shim = tmp_path / "new.cpp"
+    shim.write_text("""#include <cstdlib>
+#include <new>
+extern "C" { long new_fails_in = -1; }
+void *operator new(std::size_t n) {
+    if (new_fails_in >= 0 && new_fails_in-- == 0) throw std::bad_alloc();
+    if (void *p = std::malloc(n ? n : 1)) return p;
+    throw std::bad_alloc();
+}
+""")
+    subprocess.run(["g++", "-shared", "-fPIC", "-O1", str(shim), "-o", str(tmp_path / "libnew.so")], check=True)
+    code = """
+import ctypes, sys
+shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)      # in front of libvqmi, whose operator new it becomes
+fails_in = ctypes.c_long.in_dll(shim, "new_fails_in")
+import paper_2503_02236_amd as vq
+from paper_2503_02236_amd.binding import vq_gemv_call_t, vq_weight_t
+P, n = 0x10000, 64
+w = vq_weight_t(1400, 1088, 8, 8, 2, 256, P, P, None, None)
+ptr = (ctypes.POINTER(vq_weight_t) * 1)(ctypes.pointer(w))
+xy = (ctypes.c_void_p * 1)(P)
+calls = (vq_gemv_call_t * n)()
+for c in calls:
+    c.w, c.x, c.y, c.count = ctypes.cast(ptr, type(c.w)), ctypes.cast(xy, type(c.x)), ctypes.cast(xy, type(c.y)), 1
+lib, h = vq.lib(), ctypes.c_void_p()
+query = lambda: lib.vq_gemv_pipeline_workspace(calls, n)
+create = lambda: lib.vq_gemv_pipeline_create(calls, n, None, 0, None, ctypes.byref(h))
+need = query()
+assert need > 72 * 256          # (a list for the kernel that deals out segments)
+for call, failed, good in ((query, 0, need), (create, -6, -5)):
+    for k in range(100000):
+        fails_in.value = k
+        got = call()
+        left, fails_in.value = fails_in.value, -1
+        if left >= 0:           # not reached: the call made k allocations and got through
+            assert got == good and k > 5, (got, k)
+            break
+        assert got == failed and not h.value, (got, k)
+print("done")
+"""
+    r = subprocess.run([sys.executable, "-c", code, str(tmp_path / "libnew.so")], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.strip() == "done", r.stderr[-2000:]
