@@ -467,9 +467,14 @@ bool codebooks_fit_lds(const vq_weight_t *w) {
     const size_t sets = w->cb_tile_n > 0 ? w->K / w->cb_tile_k : 1;
     return sets * w->n_codebooks * w->n_entries * w->v * 2 <= kSkinnyLdsCodebook;
 }
+// Entries from LDS: the codebooks fit, and their sets are whole 16-byte pieces (an odd number of 8-byte entries is not;
+// one uint16 codebook of those is looked up in L2 like a large one).
+bool entries_from_lds(const vq_weight_t *w) {
+    return codebooks_fit_lds(w) && (w->n_codebooks * w->n_entries * w->v * 2) % 16 == 0;
+}
 
 int run_skinny(int tile, const vq_weight_t *w, const half_t *x, int M, half_t *y, hipStream_t s) {
-    if (!codebooks_fit_lds(w)) return w->v == 8 ? run_l2<8>(tile, w, x, M, y, s) : run_l2<4>(tile, w, x, M, y, s);
+    if (!entries_from_lds(w)) return w->v == 8 ? run_l2<8>(tile, w, x, M, y, s) : run_l2<4>(tile, w, x, M, y, s);
 #define VQ_SK(CodeT)                                                                                              \
     if (w->v == 8) return w->n_codebooks == 1 ? run_lds<CodeT, 8, 1>(tile, w, x, M, y, s) : run_lds<CodeT, 8, 2>(tile, w, x, M, y, s); \
     return w->n_codebooks == 1 ? run_lds<CodeT, 4, 1>(tile, w, x, M, y, s) : run_lds<CodeT, 4, 2>(tile, w, x, M, y, s);
@@ -482,15 +487,14 @@ int run_skinny(int tile, const vq_weight_t *w, const half_t *x, int M, half_t *y
 }  // namespace
 
 // One or two codebooks, whole code loads per row (16-byte aligned rows; 8 bytes for single uint8 codes, 12-byte words
-// for 12-bit codes), codebooks of whole 16-byte pieces that fit LDS -- or one uint16 codebook of any size, from L2.
+// for 12-bit codes), codebooks that can be staged in LDS -- or one uint16 codebook of any size, from L2.
 bool gemm_skinny_supported(const vq_weight_t *w) {
     const int R = w->n_codebooks;
     if (R != 1 && R != 2) return false;
     const int lb = w->code_bits == 12 ? 12 : R * w->code_bits == 8 ? 8 : 16;
     const long row_bits = (long)(w->K / w->v) * R * w->code_bits;
     if (w->K <= 0 || w->K % 8 != 0 || w->N <= 0 || w->N > (1 << 26) || row_bits % (lb * 8) != 0 || w->K > (1 << 22)) return false;   // (256 tokens: byte offsets into X of 32 bits)
-    if (codebooks_fit_lds(w)) return (R * w->n_entries * w->v * 2) % 16 == 0;
-    return w->cb_tile_n == 0 && R == 1 && w->code_bits == 16;
+    return entries_from_lds(w) || (w->cb_tile_n == 0 && R == 1 && w->code_bits == 16);
 }
 
 // More than 256 tokens: against the two-stage product, whose time is one round of tiles after another, however few tiles a
@@ -502,7 +506,7 @@ bool gemm_skinny_supported(const vq_weight_t *w) {
 bool gemm_skinny_wins(const vq_weight_t *w, int M) {
     if (!gemm_skinny_supported(w) || (long)M * w->K >= (1L << 31)) return false;   // (byte offsets into X of 32 bits)
     double here;
-    skinny_tile(w, M, !codebooks_fit_lds(w), &here);
+    skinny_tile(w, M, !entries_from_lds(w), &here);
     const double rounds = gemm_dense_rounds(M, w->N, nullptr);
     return here < 0.8 * (rounds * (20.0 * w->K + 5500) + 0.0017 * w->N * w->K + 3500);
 }
@@ -519,13 +523,13 @@ bool gemm_skinny_wins(const vq_weight_t *w, int M) {
 // 10.7).
 bool gemm_skinny_for_gemv(const vq_weight_t *w, int bs) {
     if (!gemm_skinny_supported(w)) return false;
-    if (codebooks_fit_lds(w)) return bs >= 14 && w->code_bits != 12 && w->K >= 2048 && w->N <= 16 * 256;
+    if (codebooks_fit_lds(w)) return entries_from_lds(w) && bs >= 14 && w->code_bits != 12 && w->K >= 2048 && w->N <= 16 * 256;
     if (gemv_mfma_supported(w)) return false;
     return bs >= (w->v == 8 ? 2 : 5) || w->K / (8 * w->v) > 256;
 }
 
 int launch_gemm_skinny(const vq_weight_t *w, const void *x, int M, void *y, hipStream_t s) {
-    return run_skinny(skinny_tile(w, M, !codebooks_fit_lds(w)), w, (const half_t *)x, M, (half_t *)y, s);
+    return run_skinny(skinny_tile(w, M, !entries_from_lds(w)), w, (const half_t *)x, M, (half_t *)y, s);
 }
 
 }  // namespace vq

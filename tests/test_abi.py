@@ -467,3 +467,20 @@ print("done")
 """
     r = subprocess.run([sys.executable, "-c", code, str(tmp_path / "libnew.so")], cwd=ROOT, capture_output=True, text=True)
     assert r.returncode == 0 and r.stdout.strip() == "done", r.stderr[-2000:]
+
+
+def internal(name, *args):
+    """A bool of the library's own routing functions (C++ names, exported but not part of the ABI)."""
+    f = getattr(vq.lib(), name)
+    f.restype = ctypes.c_bool
+    return f(*args)
+
+
+@pytest.mark.parametrize("E", [1, 1000, 1001, 16383, 16385])
+def test_one_uint16_codebook_of_any_number_of_entries_takes_the_one_pass_product(E):
+    """17 .. 256 tokens: an odd number of 8-byte entries cannot be staged in LDS in 16-byte pieces and is looked up in L2."""
+    w = weight(N=4096, K=4096, v=4, code_bits=16, n_entries=E)
+    assert internal("_ZN2vq21gemm_skinny_supportedEPK11vq_weight_t", ctypes.byref(w))
+    # (vq_gemv keeps such a weight where it fits LDS on the row kernel)
+    if E % 2 and E < 16384:
+        assert not any(internal("_ZN2vq20gemm_skinny_for_gemvEPK11vq_weight_ti", ctypes.byref(w), bs) for bs in range(1, 17))

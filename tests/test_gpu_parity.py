@@ -847,6 +847,15 @@ def test_gemm_skinny_l2_codebook(gpu_device, N, K, M, v):
     assert_close(Y, oracle.gemm(w.codes, w.codebooks, w.scale, X), f"skinny gemm {M}x{N}x{K} v{v} 2^16")
 
 
+@pytest.mark.parametrize("E", [1, 1001, 16383])      # odd: no whole 16-byte pieces, so not staged in LDS
+@pytest.mark.parametrize("N,K,M", [(37, 1216, 18), (1500, 320, 33), (2051, 192, 129), (515, 1024, 256), (131, 320, 401)])
+def test_gemm_skinny_odd_codebook(gpu_device, N, K, M, E):
+    w = wl.make_weight(N, K, 4, 16, 1, E, 0.02, seed=4870 + N + E, with_scale=N % 2 == 1)
+    X = wl.make_activations(M, K, seed=4871 + M)
+    Y = vq.vq_gemm(vq.weight_to_device(w, gpu_device), dev_x(X, gpu_device))
+    assert_close(Y, oracle.gemm(w.codes, w.codebooks, w.scale, X), f"skinny gemm {M}x{N}x{K} v4 E{E}")
+
+
 @pytest.mark.parametrize("bits,E,M", [(8, 256, 20), (16, 65536, 20), (16, 65536, 3)])
 def test_gemm_skinny_infinities_at_the_end_of_a_row(gpu_device, bits, E, M):
     # K = 192 leaves half of an iteration past the end of every row; there the last codes and activations are read again,
