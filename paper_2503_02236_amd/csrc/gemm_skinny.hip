@@ -370,6 +370,11 @@ __global__ __launch_bounds__(64 * skinny_max_waves(L2CB, RT, CT)) void gemm_skin
     }
 }
 
+// Elements of X of one launch: its kernel holds byte offsets into X in 32 bits.  At least 512 tokens (K <= 2^22), whole
+// tiles of every kind.
+constexpr long kSkinnyMaxX = 1L << 31;
+int skinny_max_tokens(int K) { return (int)std::min(1L << 30, (kSkinnyMaxX - 1) / K / 128 * 128); }
+
 constexpr size_t kSkinnyLds = 160 * 1024, kSkinnyLdsCodebook = 128 * 1024;
 template <typename CodeT, int V, int R>
 constexpr int skinny_unit_of() {
@@ -502,9 +507,9 @@ bool gemm_skinny_supported(const vq_weight_t *w) {
 // Measured with two 256-entry codebooks, two-stage / here: N = 256, K = 1024, 1024 tokens 13.0 / 5.8 us; N = 1024,
 // K = 4096, 1024 tokens 35.7 / 20.0; N = K = 4096, 384 tokens 48.2 / 34.8, 1024 tokens 51.4 / 67.6; N = 11008, 272 tokens
 // 75.0 / 66.2, 384 tokens 75.7 / 83.5; 2^16 entries, N = 1024, 1024 tokens 36.9 / 31.8, N = 4096, 384 tokens 45.4 / 60.3.
-// The estimates are good to 20 %, so this one has to be that much lower.
+// The estimates are good to 20 %, so this one has to be that much lower.  (A supported weight with K % 64 == 0.)
 bool gemm_skinny_wins(const vq_weight_t *w, int M) {
-    if (!gemm_skinny_supported(w) || (long)M * w->K >= (1L << 31)) return false;   // (byte offsets into X of 32 bits)
+    if ((long)M * w->K >= kSkinnyMaxX) return false;
     double here;
     skinny_tile(w, M, !entries_from_lds(w), &here);
     const double rounds = gemm_dense_rounds(M, w->N, nullptr);
@@ -529,7 +534,14 @@ bool gemm_skinny_for_gemv(const vq_weight_t *w, int bs) {
 }
 
 int launch_gemm_skinny(const vq_weight_t *w, const void *x, int M, void *y, hipStream_t s) {
-    return run_skinny(skinny_tile(w, M, !entries_from_lds(w)), w, (const half_t *)x, M, (half_t *)y, s);
+    const half_t *xp = (const half_t *)x;
+    half_t *yp = (half_t *)y;
+    const int most = skinny_max_tokens(w->K);   // of a launch; the rest in further ones
+    for (int m = 0; m < M; m += most) {
+        const int n = std::min(most, M - m);
+        if (int st = run_skinny(skinny_tile(w, n, !entries_from_lds(w)), w, xp + (size_t)m * w->K, n, yp + (size_t)m * w->N, s)) return st;
+    }
+    return VQ_OK;
 }
 
 }  // namespace vq

@@ -112,6 +112,7 @@ int launch_gemv_rows(const vq_weight_t *w, const void *x, int bs, void *y, hipSt
 bool gemv_mfma_supported(const vq_weight_t *w);
 int launch_gemv_mfma(const vq_weight_t *w, const void *x, int bs, void *y, hipStream_t s);
 int launch_gemv_generic(const vq_weight_t *w, const void *x, int bs, void *y, hipStream_t s);
+bool gemm_one_pass(const vq_weight_t *w, int M);
 int launch_gemm(const vq_weight_t *w, const void *X, int M, void *Y, void *ws, hipStream_t s);
 size_t gemm_workspace(const vq_weight_t *w, int M);
 // a few to a few hundred tokens in one pass over the codes (gemm_skinny.hip)

@@ -484,3 +484,16 @@ def test_one_uint16_codebook_of_any_number_of_entries_takes_the_one_pass_product
     # (vq_gemv keeps such a weight where it fits LDS on the row kernel)
     if E % 2 and E < 16384:
         assert not any(internal("_ZN2vq20gemm_skinny_for_gemvEPK11vq_weight_ti", ctypes.byref(w), bs) for bs in range(1, 17))
+
+
+@pytest.mark.parametrize("kw", [dict(v=8, code_bits=12, n_codebooks=2, n_entries=4096), dict(v=4, code_bits=16, n_entries=65536),
+                                dict(v=4, code_bits=8, n_codebooks=2), dict(v=8, code_bits=16, n_codebooks=2, n_entries=2048)])
+def test_more_than_256_tokens_without_a_two_stage_product_take_one_pass(kw):
+    """K % 64 == 32: the two-stage product does not exist, and 16 tokens a launch would read all codes again and again."""
+    one_pass = lambda w, M: internal("_ZN2vq13gemm_one_passEPK11vq_weight_ti", ctypes.byref(w), M)  # noqa: E731
+    for M in (17, 256, 257, 2048, 1 << 20):
+        assert one_pass(weight(N=4096, K=4128, **kw), M), M
+        assert vq.lib().vq_gemm_workspace(ctypes.byref(weight(N=4096, K=4128, **kw)), M) == 0
+    assert not one_pass(weight(N=4096, K=4128, **kw), 16)
+    # with both ways open a large product keeps the two stages
+    assert not one_pass(weight(N=4096, K=4096, **kw), 2048) and one_pass(weight(N=4096, K=4096, **kw), 256)

@@ -847,6 +847,32 @@ def test_gemm_skinny_l2_codebook(gpu_device, N, K, M, v):
     assert_close(Y, oracle.gemm(w.codes, w.codebooks, w.scale, X), f"skinny gemm {M}x{N}x{K} v{v} 2^16")
 
 
+# more than 256 tokens where the two-stage product does not exist (K % 64 == 32)
+@pytest.mark.parametrize("N,K,M", [(130, 96, 257), (37, 1248, 300), (515, 4128, 1025)])
+@pytest.mark.parametrize("v,bits,R,E", [(8, 12, 2, 4096), (4, 16, 1, 65536), (4, 8, 2, 256), (8, 16, 2, 2048)])
+def test_gemm_skinny_many_tokens_half_a_block_of_k(gpu_device, N, K, M, v, bits, R, E):
+    w = wl.make_weight(N, K, v, bits, R, E, 0.02 / R, seed=4880 + N + K)
+    X = wl.make_activations(M, K, seed=4881 + M)
+    Y = vq.vq_gemm(vq.weight_to_device(w, gpu_device), dev_x(X, gpu_device))
+    assert_close(Y, oracle.gemm(ocodes(w), w.codebooks, w.scale, X), f"skinny gemm {M}x{N}x{K} v{v} b{bits} R{R}")
+
+
+def test_gemm_skinny_x_beyond_32_bit_offsets(gpu_device):
+    # 513 tokens of K = 2^22 - 32: byte offsets into X fit 32 bits for 512 tokens, so the last one goes in a second launch
+    N, K, M = 16, (1 << 22) - 32, 513
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(4895)
+    codes = torch.randint(0, 256, (N, K // 4, 2), generator=g, device=gpu_device, dtype=torch.uint8)
+    cb = (torch.randn((2, 256, 4), generator=g, device=gpu_device) * 0.001).to(torch.float16)
+    w = vq.VQWeightDev(N, K, 4, 8, codes, cb, None)
+    X = torch.randn((M, K), generator=g, device=gpu_device, dtype=torch.float16)
+    Y = vq.vq_gemm(w, X).double().cpu().numpy()
+    W = vq.vq_dequant(w, out_fp32=False).float()
+    for m in (0, 255, 511, 512):
+        want = (W * X[m].float()).sum(1, dtype=torch.float64).cpu().numpy()
+        assert np.linalg.norm(Y[m] - want) <= 2e-3 * np.linalg.norm(want), m
+
+
 @pytest.mark.parametrize("E", [1, 1001, 16383])      # odd: no whole 16-byte pieces, so not staged in LDS
 @pytest.mark.parametrize("N,K,M", [(37, 1216, 18), (1500, 320, 33), (2051, 192, 129), (515, 1024, 256), (131, 320, 401)])
 def test_gemm_skinny_odd_codebook(gpu_device, N, K, M, E):
