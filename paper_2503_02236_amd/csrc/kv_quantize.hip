@@ -20,7 +20,8 @@ struct KvQuantArgs {
     uint8_t *codes[2];     // [B][H][T][D/v]
     int H, T, D, P, E, G, n_new, pos;
     int tokens;            // new tokens per workgroup
-    int PG, pg_shift;      // sub-vectors per group of the codebook; its logarithm (matrix-core kernel)
+    int PG;                // sub-vectors per group of the codebook
+    unsigned pg_inverse;   // kvq_inverse(PG) (matrix-core kernel)
 };
 
 // A sub-vector (V halves, aligned) in the low halves of 16 bytes, the rest zero.
@@ -147,6 +148,17 @@ __global__ __launch_bounds__(512) void kv_quantize_scan_kernel(KvQuantArgs a) {
 // against 8 matrix instructions.  B2 H32, 2048 tokens, one codebook per head and side (4.2 M items per side): 112 us back to back,
 // where a scan of every pair took 546; 32 codebooks of v = 4: 163, 64 of v = 2: 324.
 constexpr int kQuantMfmaTokens = 128;        // tokens per workgroup
+// i / PG for the items of a workgroup (i < 128 PG, PG <= 128) by a 24-bit product and a shift: with m = ceil(2^21 / PG) the
+// excess i (m PG - 2^21) stays below 2^14 * 2^7 = 2^21, and the product below 2^29.
+constexpr unsigned kvq_inverse(int PG) { return ((1u << 21) + PG - 1) / PG; }
+constexpr unsigned kvq_quotient(unsigned i, unsigned inverse) { return (i * inverse) >> 21; }
+constexpr bool kvq_quotient_exact() {
+    for (unsigned PG = 1; PG <= 128; ++PG)
+        for (unsigned t = 0; t < 128; ++t)   // (between two multiples the quotient cannot fall)
+            if (kvq_quotient(t * PG, kvq_inverse((int)PG)) != t || kvq_quotient(t * PG + PG - 1, kvq_inverse((int)PG)) != t) return false;
+    return true;
+}
+static_assert(kQuantMfmaTokens <= 128 && kvq_quotient_exact(), "");
 constexpr float kQuantMinC2 = 1e-6f, kQuantMaxC2 = 1e9f;   // (the largest h that 2^15 of headroom takes is 2^30)
 
 // min(a, b) as the median with a minus infinity that the compiler does not see through: one instruction (fminf first
@@ -248,12 +260,15 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
         }
         const half2_t dd = {down, down}, d0 = {down, (half_t)0.f};
         auto item_off = [&](unsigned i) {   // index of the sub-vector in [token][P]
-            return (i >> a.pg_shift) * (unsigned)(a.P - a.PG) + i + (unsigned)(g * a.PG);
+            return __umul24(__umul24(i, a.pg_inverse) >> 21, (unsigned)(a.P - a.PG)) + i + (unsigned)(g * a.PG);   // (kvq_quotient)
         };
-        auto load_item = [&](int ct) { return kvq_load<V>(xs + item_off((unsigned)min(ct * 32 + ln, n_items - 1)) * (V * 2)); };
-        V16 xb = load_item(min(u % R, n_ct - 1));
+        auto lane_off = [&](int ct) { return item_off((unsigned)min(ct * 32 + ln, n_items - 1)); };
+        auto load_item = [&](unsigned off) { return kvq_load<V>(xs + off * (V * 2)); };
+        unsigned off = lane_off(min(u % R, n_ct - 1));
+        V16 xb = load_item(off);
         for (int ct = u % R; ct < n_ct; ct += R) {
-            const V16 xnext = load_item(min(ct + R, n_ct - 1));
+            const unsigned off_next = lane_off(min(ct + R, n_ct - 1));
+            const V16 xnext = load_item(off_next);
             V16 bop;
 #pragma unroll
             for (int i = 0; i < 4; ++i) bop.w[i] = lh ? 0u : xb.w[i];
@@ -308,8 +323,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
                 both_halves(be, el, eu);
                 be = du < dl ? eu : el;   // (the lower half's entries have the smaller indices)
             }
-            const unsigned i = (unsigned)(ct * 32 + ln);
-            const bool live = (int)i < n_items;
+            const bool live = ct * 32 + ln < n_items;
             unsigned long long left = __ballot(!sure && live && lh == 0);
             if (left) {
                 if (__popcll(left) > 12) {
@@ -347,8 +361,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
                     }
                 }
             }
-            if (live && lh == 0) out[item_off(i)] = (uint8_t)be;
+            if (live && lh == 0) out[off] = (uint8_t)be;
             xb = xnext;
+            off = off_next;
         }
     }
     __syncthreads();
@@ -361,24 +376,23 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     }
 }
 
-namespace {
-
 // New tokens from which the matrix-core kernel is used.  B2 H32, us: one codebook per head and side, scan 12.2 / 19.9 for
 // 4 / 8 tokens against 11.6 for the matrix-core kernel at 16; 64 codebooks of v = 2 (64 KiB to stage), 17.7 / 31.2 against
 // 26.9; a single token 11.4 - 12.7 by the scan in every layout (all of it the launch).
 constexpr int kQuantMfmaMin = 6;
+bool kv_quantize_on_matrix_cores(int n_new) { return n_new >= kQuantMfmaMin; }
 constexpr int kQuantScanTokens = 16;
+
+namespace {
 
 template <int V>
 int run_kvq(KvQuantArgs &a, int bh, hipStream_t s) {
-    const bool pow2 = (a.PG & (a.PG - 1)) == 0;   // (the matrix-core kernel splits an item index by a shift)
-    if (a.n_new < kQuantMfmaMin || !pow2) {
+    if (!kv_quantize_on_matrix_cores(a.n_new)) {
         a.tokens = a.n_new < kQuantScanTokens ? a.n_new : kQuantScanTokens;
         kv_quantize_scan_kernel<V><<<dim3(bh, (a.n_new + a.tokens - 1) / a.tokens, 2), 512, 0, s>>>(a);
         return launch_status();
     }
-    a.pg_shift = 0;
-    while ((1 << a.pg_shift) < a.PG) ++a.pg_shift;
+    a.pg_inverse = kvq_inverse(a.PG);
     // tokens per workgroup: as many as leave the chip two rounds of workgroups (a workgroup stages its codebooks first)
     a.tokens = kQuantMfmaTokens;
     while (a.tokens > 16 && (long)bh * 2 * ((a.n_new + a.tokens - 1) / a.tokens) < 1024) a.tokens /= 2;
@@ -412,7 +426,7 @@ int launch_kv_quantize(const vq_kv_t *kv, const void *k_new, const void *v_new, 
     a.n_new = n_new;
     a.pos = pos;
     a.PG = a.P / a.G;
-    a.pg_shift = 0;
+    a.pg_inverse = 0;
     const int bh = kv->B * kv->H;
     if (kv->v == 8) return run_kvq<8>(a, bh, s);
     if (kv->v == 4) return run_kvq<4>(a, bh, s);

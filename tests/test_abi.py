@@ -497,3 +497,9 @@ def test_more_than_256_tokens_without_a_two_stage_product_take_one_pass(kw):
     assert not one_pass(weight(N=4096, K=4128, **kw), 16)
     # with both ways open a large product keeps the two stages
     assert not one_pass(weight(N=4096, K=4096, **kw), 2048) and one_pass(weight(N=4096, K=4096, **kw), 256)
+
+
+def test_kv_quantize_of_prompts_runs_on_the_matrix_cores():
+    for n_new in (6, 17, 128, 4096):
+        assert internal("_ZN2vq27kv_quantize_on_matrix_coresEi", n_new)
+    assert not internal("_ZN2vq27kv_quantize_on_matrix_coresEi", 1)

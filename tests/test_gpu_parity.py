@@ -1252,6 +1252,26 @@ def test_kv_quantize_hard_values(gpu_device, v, G, E, n_new, kind):
     assert np.array_equal(kd.v_codes.cpu().numpy()[:, :, 2:2 + n_new], oracle.kv_quantize(x[1], kv.v_codebooks))
 
 
+# head sizes other than 128: sub-vectors per group that are no power of two, one sub-vector per group, and the most LDS that
+# staged codebooks take (D = 256: 128 KiB); a last workgroup that is not full
+@pytest.mark.parametrize("D,v,G,E", [(96, 4, 1, 256), (96, 8, 4, 256), (80, 8, 2, 250), (192, 2, 32, 256), (40, 2, 5, 200), (24, 8, 3, 256),
+                                     (8, 8, 1, 256), (256, 4, 1, 256), (256, 8, 32, 64), (256, 2, 128, 128)])
+@pytest.mark.parametrize("n_new", [1, 7, 300])
+def test_kv_quantize_head_sizes(gpu_device, D, v, G, E, n_new):
+    rng = np.random.default_rng(9600 + D + v + n_new)
+    B, H, T, P = 1, 3, n_new + 5, D // v
+    cb = rng.normal(0, 1, size=(2, H, G, E, v)).astype(np.float16)
+    x = rng.normal(0, 1, size=(2, B, H, n_new, D)).astype(np.float16)
+    codes = [torch.full((B, H, T, P), 255, dtype=torch.uint8, device=gpu_device) for _ in range(2)]
+    kd = vq.VQKVDev(B, H, D, T, v, codes[0], codes[1], dev_x(cb[0], gpu_device), dev_x(cb[1], gpu_device))
+    vq.vq_kv_quantize(kd, dev_x(x[0], gpu_device), dev_x(x[1], gpu_device), 4)
+    torch.cuda.synchronize()
+    for side in range(2):
+        got = codes[side].cpu().numpy()
+        assert np.array_equal(got[:, :, 4:4 + n_new], oracle.kv_quantize(x[side], cb[side])), side
+        assert (got[:, :, :4] == 255).all() and (got[:, :, 4 + n_new:] == 255).all(), side
+
+
 def test_kv_quantize_then_attend(gpu_device):
     # a cache written by the quantizer, read by the attention kernel: compare with the oracle's two steps
     B, H, T = 2, 4, 700
