@@ -8,8 +8,11 @@
 // in fp32, elements in ascending order, every subtraction, multiplication and addition rounded on its own
 // (no fused multiply-add); strict "<" while walking the entries in ascending order, so ties go to the smallest index.
 //
-// Two kernels with the same codes: kv_quantize_scan_kernel computes every distance (decode steps), and
-// kv_quantize_mfma_kernel lets the matrix cores rule out all but eight entries (prompts).
+// Three kernels with the same codes: kv_quantize_scan_kernel computes every distance, a wavefront per sub-vector (decode
+// steps), kv_quantize_small_kernel does so with a lane per sub-vector (small codebooks), and kv_quantize_mfma_kernel lets the
+// matrix cores rule out all but eight entries (prompts).
+#include <algorithm>
+
 #include "vq_common.h"
 
 namespace vq {
@@ -127,6 +130,55 @@ __global__ __launch_bounds__(512) void kv_quantize_scan_kernel(KvQuantArgs a) {
     }
 }
 
+// Small codebooks (E v <= 64).  A thread takes a sub-vector position of TOK tokens at a time and walks over the entries in
+// LDS; groups lie an entry more than their length apart, so that lanes of different groups read different banks.  Bound:
+// vector issue, about 4 + 2.5 V instructions per (item, entry); the matrix-core kernel spends 100 or more on an item
+// whatever E is.
+template <int V, int TOK>
+__global__ __launch_bounds__(256) void kv_quantize_small_kernel(KvQuantArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    half_t *cb = reinterpret_cast<half_t *>(smem);   // [G][E + 1][V]
+    const int tid = threadIdx.x;
+    const int bh = blockIdx.x, h = bh % a.H, side = blockIdx.z;
+    const int t0 = blockIdx.y * a.tokens, nt = min(a.tokens, a.n_new - t0);
+    const int rows = 256 / a.P;                      // tokens side by side
+    const int row = tid / a.P, p = tid - row * a.P, g = p / a.PG;
+    const half_t *src = a.cb[side] + (size_t)h * a.G * a.E * V;
+    const half_t *xs = a.x[side] + ((size_t)bh * a.n_new + t0) * a.D + p * V;
+    uint8_t *dst = a.codes[side] + ((size_t)bh * a.T + a.pos + t0) * a.P + p;
+    for (int i = tid; i < a.G * a.E; i += blockDim.x) {
+        const V16 c = kvq_load<V>(src + (size_t)i * V);
+#pragma unroll
+        for (int k = 0; k < V / 2; ++k) reinterpret_cast<uint32_t *>(cb + (size_t)(i + i / a.E) * V)[k] = c.w[k];
+    }
+    __syncthreads();
+    if (row >= rows) return;
+    const half_t *grp = cb + (size_t)g * (a.E + 1) * V;
+    for (int t = row; t < nt; t += rows * TOK) {
+        V16 x[TOK];
+        float bd[TOK];
+        int be[TOK];
+#pragma unroll
+        for (int k = 0; k < TOK; ++k) {
+            x[k] = kvq_load<V>(xs + (size_t)min(t + k * rows, nt - 1) * a.D);
+            bd[k] = INFINITY;
+            be[k] = 0;
+        }
+        for (int e = 0; e < a.E; ++e) {
+            const V16 c = kvq_load<V>(grp + (size_t)e * V);
+#pragma unroll
+            for (int k = 0; k < TOK; ++k) {
+                const float d = kvq_exact<V>(x[k], c);
+                be[k] = d < bd[k] ? e : be[k];
+                bd[k] = d < bd[k] ? d : bd[k];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < TOK; ++k)
+            if (t + k * rows < nt) dst[(size_t)(t + k * rows) * a.P] = (uint8_t)be[k];
+    }
+}
+
 // Prompt-sized calls.  The scan above spends 14 vector instructions on every (item, entry) pair; here the matrix cores
 // do the pairs and the vector ALU only looks for the minimum.
 //   With h_e = |c_e|^2 / 2 the closest entry minimises s_e = h_e - x.c_e (d = |x|^2 + 2 s).  One
@@ -184,10 +236,10 @@ __device__ __forceinline__ void both_halves(int v, int &lower, int &upper) {
     upper = (int)u;
 }
 
-template <int V>
+// TILES: tiles of 32 entries, 1, 2, 4 or 8, the fewest that hold E; codebooks are padded to that.
+template <int V, int TILES>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) void kv_quantize_mfma_kernel(KvQuantArgs a) {
-    constexpr int TILES = 8;                       // entry tiles of 32: codebooks are padded to 256 entries
-    constexpr int EP = TILES * 32;
+    constexpr int EP = 32 * TILES;
     extern __shared__ __align__(16) unsigned char smem[];
     half_t *cb = reinterpret_cast<half_t *>(smem);                            // [G][EP][V], infinite past E
     float *c2m = reinterpret_cast<float *>(cb + (size_t)a.G * EP * V);        // [G]  largest |c|^2
@@ -236,11 +288,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
         const int k = min(max(15 - (int)((__float_as_uint(0.5f * c2) >> 23) & 255) + 126, -15), 24);
         const float up = __uint_as_float((unsigned)(127 + k) << 23);
         const half_t down = (half_t)__uint_as_float((unsigned)(127 - k) << 23);
-        // the codebook of the group as matrix operands: entry 32 t + ln (past E: the last entry again)
+        // the codebook of the group as matrix operands: entry 32 t + ln.  Past E: the first entry of the same group of eight
+        // once more, which changes no minimum (a group without entries: the last entry again)
         half8_t A[TILES];
 #pragma unroll
         for (int t = 0; t < TILES; ++t) {
-            const V16 c = kvq_load<V>(cbg + (size_t)min(32 * t + ln, a.E - 1) * V);
+            int e = ln;
+            if (32 * t + 32 > a.E) e = 32 * t + ln < a.E ? ln : min(ln & 20, a.E - 1 - 32 * t);   // (uniform)
+            const V16 c = kvq_load<V>(cbg + (32 * t + e) * V);
             float hh = 0.f;
 #pragma unroll
             for (int i = 0; i < V; ++i) hh = __builtin_fmaf((float)c.h8[i], (float)c.h8[i], hh);
@@ -290,7 +345,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
                     m = fminf(fminf(m, s[8 * hf + 2]), s[8 * hf + 3]);
                     m = fminf(fminf(m, s[8 * hf + 4]), s[8 * hf + 5]);
                     m = fminf(fminf(m, s[8 * hf + 6]), s[8 * hf + 7]);
-                    const float key = __uint_as_float((__float_as_uint(m) & 0xFFFFFFF0u) | (unsigned)(2 * t + hf));
+                    float key = __uint_as_float((__float_as_uint(m) & 0xFFFFFFF0u) | (unsigned)(2 * t + hf));
+                    // (a group whose first row, 16 hf + 4 lh, is past E has no entries and is never the closest; of 256 or
+                    // nearly 256 the few such groups may tie with the last entry instead, which is cheaper)
+                    if (TILES < 8) key = 32 * t + 16 * hf + 4 * lh < a.E ? key : 3e38f;
                     second = __builtin_amdgcn_fmed3f(best, second, key);
                     best = min2f(best, key, ninf);
                 }
@@ -307,7 +365,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
             for (int i = 0; i < V; ++i) x2 = __builtin_fmaf((float)xb.h8[i], (float)xb.h8[i], x2);
             const bool sure = second - win > 1.52587890625e-5f * (x2 + c2) && in_range;
             // entries of the group: rows 16 (grp & 1) + 4 (half whose lane holds them) + {0 .. 3, 8 .. 11} of tile grp / 2
-            const int e0 = 16 * (int)(__float_as_uint(win) & 15u) + (bu < bl ? 4 : 0) + 8 * lh;
+            const int e0 = 16 * (int)(__float_as_uint(win) & (2u * TILES - 1u)) + (bu < bl ? 4 : 0) + 8 * lh;
             int be = e0;
             float bd = kvq_exact<V>(xb, kvq_load<V>(cbg + (size_t)e0 * V));
 #pragma unroll
@@ -352,7 +410,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
                         int be2 = lane;
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {   // (entries past E are infinitely far)
-                            const float d = kvq_exact<V>(xj, kvq_load<V>(cbg + (size_t)(lane + 64 * q) * V));
+                            if (64 * q >= EP) break;
+                            const float d = kvq_exact<V>(xj, kvq_load<V>(cbg + (size_t)min(lane + 64 * q, EP - 1) * V));
                             be2 = d < bd2 ? lane + 64 * q : be2;
                             bd2 = d < bd2 ? d : bd2;
                         }
@@ -380,13 +439,43 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 // 4 / 8 tokens against 11.6 for the matrix-core kernel at 16; 64 codebooks of v = 2 (64 KiB to stage), 17.7 / 31.2 against
 // 26.9; a single token 11.4 - 12.7 by the scan in every layout (all of it the launch).
 constexpr int kQuantMfmaMin = 6;
+// Prompts (B2 H32, 2048 tokens), us, all pairs as before / matrix cores with every codebook padded to 256 entries / padded to a
+// power of two of tiles / small kernel: v = 4, one group, 8 entries 48 / 350 / 63 / 30; 16 59 / 268 / 57 / 50; 24 76 / 192 / 58 / 72;
+// 64 158 / 146 / 66 / 184; v = 8, 8 entries 31 / 267 / 42 / 27; 16 49 / 203 / 42 / 48; v = 2, 64 groups, 16 entries 231 / 356 / 115 /
+// 55; 32 891 / 305 / 118 / 100; 64 1774 / 279 / 140 / 192.
+bool kv_quantize_small_codebook(int E, int v) { return E * v <= 64; }
 bool kv_quantize_on_matrix_cores(int n_new) { return n_new >= kQuantMfmaMin; }
 constexpr int kQuantScanTokens = 16;
 
 namespace {
 
+template <int V, int TILES>
+int run_kvq_mfma(const KvQuantArgs &a, int bh, hipStream_t s) {
+    const size_t lds = (size_t)a.G * 32 * TILES * V * sizeof(half_t) + (((size_t)a.G + 3) & ~(size_t)3) * 4 + (size_t)a.tokens * a.P;
+    static KernelSetup setup;
+    if (int st = kernel_setup(reinterpret_cast<const void *>(&kv_quantize_mfma_kernel<V, TILES>), lds, false, setup)) return st;
+    // a CU holds 16 wavefronts of this kernel: two workgroups of 8 where 64 KiB of codebooks are staged, four of 4 otherwise
+    const int threads = 4 * lds > 160 * 1024 ? 512 : 256;
+    kv_quantize_mfma_kernel<V, TILES><<<dim3(bh, (a.n_new + a.tokens - 1) / a.tokens, 2), threads, lds, s>>>(a);
+    return launch_status();
+}
+
+// TOK = 4 saves the lookups of an entry for three of four tokens (v = 8 is bound by its distances: 27.1 us with one token at a
+// time, 28.0 with four, for 8 entries; v = 4 34.3 / 30.3).
+template <int V, int TOK>
+int run_kvq_small(KvQuantArgs &a, int bh, hipStream_t s) {
+    a.tokens = std::min(a.n_new, 128);
+    const size_t lds = (size_t)a.G * (a.E + 1) * V * sizeof(half_t);
+    kv_quantize_small_kernel<V, TOK><<<dim3(bh, (a.n_new + a.tokens - 1) / a.tokens, 2), 256, lds, s>>>(a);   // (16.5 KiB at most)
+    return launch_status();
+}
+
 template <int V>
 int run_kvq(KvQuantArgs &a, int bh, hipStream_t s) {
+    if (kv_quantize_small_codebook(a.E, V)) {
+        if (V <= 4 && a.n_new >= 4 * (256 / a.P)) return run_kvq_small<V, 4>(a, bh, s);
+        return run_kvq_small<V, 1>(a, bh, s);
+    }
     if (!kv_quantize_on_matrix_cores(a.n_new)) {
         a.tokens = a.n_new < kQuantScanTokens ? a.n_new : kQuantScanTokens;
         kv_quantize_scan_kernel<V><<<dim3(bh, (a.n_new + a.tokens - 1) / a.tokens, 2), 512, 0, s>>>(a);
@@ -396,13 +485,10 @@ int run_kvq(KvQuantArgs &a, int bh, hipStream_t s) {
     // tokens per workgroup: as many as leave the chip two rounds of workgroups (a workgroup stages its codebooks first)
     a.tokens = kQuantMfmaTokens;
     while (a.tokens > 16 && (long)bh * 2 * ((a.n_new + a.tokens - 1) / a.tokens) < 1024) a.tokens /= 2;
-    const size_t lds = (size_t)a.G * 256 * V * sizeof(half_t) + (((size_t)a.G + 3) & ~(size_t)3) * 4 + (size_t)a.tokens * a.P;
-    static KernelSetup setup;
-    if (int st = kernel_setup(reinterpret_cast<const void *>(&kv_quantize_mfma_kernel<V>), lds, false, setup)) return st;
-    // a CU holds 16 wavefronts of this kernel: two workgroups of 8 where 64 KiB of codebooks are staged, four of 4 otherwise
-    const int threads = 4 * lds > 160 * 1024 ? 512 : 256;
-    kv_quantize_mfma_kernel<V><<<dim3(bh, (a.n_new + a.tokens - 1) / a.tokens, 2), threads, lds, s>>>(a);
-    return launch_status();
+    if (a.E <= 32) return run_kvq_mfma<V, 1>(a, bh, s);
+    if (a.E <= 64) return run_kvq_mfma<V, 2>(a, bh, s);
+    if (a.E <= 128) return run_kvq_mfma<V, 4>(a, bh, s);
+    return run_kvq_mfma<V, 8>(a, bh, s);
 }
 
 }  // namespace

@@ -503,3 +503,6 @@ def test_kv_quantize_of_prompts_runs_on_the_matrix_cores():
     for n_new in (6, 17, 128, 4096):
         assert internal("_ZN2vq27kv_quantize_on_matrix_coresEi", n_new)
     assert not internal("_ZN2vq27kv_quantize_on_matrix_coresEi", 1)
+    # but for codebooks so small that comparing all entries is less work
+    small = lambda E, v: internal("_ZN2vq26kv_quantize_small_codebookEii", E, v)  # noqa: E731
+    assert small(16, 4) and small(8, 8) and small(32, 2) and not small(17, 4) and not small(16, 8) and not small(256, 2)

@@ -1220,7 +1220,8 @@ def test_kv_quantize_ties_go_to_the_smallest_index(gpu_device):
         assert np.array_equal(got_v, oracle.kv_quantize(v_new, kv.v_codebooks))
 
 
-@pytest.mark.parametrize("v,G,E,n_new", [(4, 1, 256, 5), (4, 1, 256, 6), (4, 32, 250, 17), (2, 64, 256, 129), (8, 2, 33, 40), (4, 1, 8, 300)])
+@pytest.mark.parametrize("v,G,E,n_new", [(4, 1, 256, 5), (4, 1, 256, 6), (4, 32, 250, 17), (2, 64, 256, 129), (8, 2, 33, 40), (4, 1, 8, 300),
+                                          (4, 1, 30, 70), (8, 2, 10, 40), (2, 64, 60, 40), (4, 32, 120, 40)])
 @pytest.mark.parametrize("kind", ["plain", "near_ties", "tiny", "huge", "not_finite"])
 def test_kv_quantize_hard_values(gpu_device, v, G, E, n_new, kind):
     """The matrix-core kernel rules entries out by an approximate distance: entries that differ in the last bits, codebooks
@@ -1255,7 +1256,11 @@ def test_kv_quantize_hard_values(gpu_device, v, G, E, n_new, kind):
 # head sizes other than 128: sub-vectors per group that are no power of two, one sub-vector per group, and the most LDS that
 # staged codebooks take (D = 256: 128 KiB); a last workgroup that is not full
 @pytest.mark.parametrize("D,v,G,E", [(96, 4, 1, 256), (96, 8, 4, 256), (80, 8, 2, 250), (192, 2, 32, 256), (40, 2, 5, 200), (24, 8, 3, 256),
-                                     (8, 8, 1, 256), (256, 4, 1, 256), (256, 8, 32, 64), (256, 2, 128, 128)])
+                                     (8, 8, 1, 256), (256, 4, 1, 256), (256, 8, 32, 64), (256, 2, 128, 128),
+                                     # fewer entries: one, two and four tiles of 32 with groups of eight that are partly or
+                                     # wholly empty; a lane per sub-vector (E v <= 64)
+                                     (128, 4, 1, 18), (128, 8, 2, 9), (96, 2, 16, 40), (128, 4, 1, 66), (128, 2, 64, 100), (128, 8, 4, 128),
+                                     (128, 4, 1, 16), (96, 8, 12, 7), (256, 2, 128, 32), (128, 4, 32, 2), (40, 2, 5, 24), (128, 8, 1, 1)])
 @pytest.mark.parametrize("n_new", [1, 7, 300])
 def test_kv_quantize_head_sizes(gpu_device, D, v, G, E, n_new):
     rng = np.random.default_rng(9600 + D + v + n_new)
