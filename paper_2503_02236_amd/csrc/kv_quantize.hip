@@ -9,7 +9,7 @@
 // (no fused multiply-add); strict "<" while walking the entries in ascending order, so ties go to the smallest index.
 //
 // Three kernels with the same codes: kv_quantize_scan_kernel computes every distance, a wavefront per sub-vector (decode
-// steps), kv_quantize_small_kernel does so with a lane per sub-vector (small codebooks), and kv_quantize_mfma_kernel lets the
+// steps), kv_quantize_lane_kernel does so with a lane per sub-vector or a few (small codebooks), and kv_quantize_mfma_kernel lets the
 // matrix cores rule out all but eight entries (prompts).
 #include <algorithm>
 
@@ -25,6 +25,7 @@ struct KvQuantArgs {
     int tokens;            // new tokens per workgroup
     int PG;                // sub-vectors per group of the codebook
     unsigned pg_inverse;   // kvq_inverse(PG) (matrix-core kernel)
+    int log_lanes;         // lanes that share an item (kv_quantize_lane_kernel)
 };
 
 // A sub-vector (V halves, aligned) in the low halves of 16 bytes, the rest zero.
@@ -130,52 +131,82 @@ __global__ __launch_bounds__(512) void kv_quantize_scan_kernel(KvQuantArgs a) {
     }
 }
 
-// Small codebooks (E v <= 64).  A thread takes a sub-vector position of TOK tokens at a time and walks over the entries in
-// LDS; groups lie an entry more than their length apart, so that lanes of different groups read different banks.  Bound:
-// vector issue, about 4 + 2.5 V instructions per (item, entry); the matrix-core kernel spends 100 or more on an item
-// whatever E is.
+// Small codebooks, and medium ones with few items.  A lane takes an item and walks over the entries in LDS, TOK items (of the
+// same position in different tokens) at a time; where a workgroup has few items, 2^log_lanes lanes share one, each taking every
+// 2^log_lanes-th entry.  Groups lie an entry more than their length apart, so that lanes of different groups read different
+// banks.  Bound: vector issue, about 4 + 2.5 V instructions per (item, entry); the matrix-core kernel spends 100 or more on
+// an item whatever E is.
 template <int V, int TOK>
-__global__ __launch_bounds__(256) void kv_quantize_small_kernel(KvQuantArgs a) {
+__global__ __launch_bounds__(256) void kv_quantize_lane_kernel(KvQuantArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     half_t *cb = reinterpret_cast<half_t *>(smem);   // [G][E + 1][V]
     const int tid = threadIdx.x;
     const int bh = blockIdx.x, h = bh % a.H, side = blockIdx.z;
     const int t0 = blockIdx.y * a.tokens, nt = min(a.tokens, a.n_new - t0);
-    const int rows = 256 / a.P;                      // tokens side by side
-    const int row = tid / a.P, p = tid - row * a.P, g = p / a.PG;
     const half_t *src = a.cb[side] + (size_t)h * a.G * a.E * V;
-    const half_t *xs = a.x[side] + ((size_t)bh * a.n_new + t0) * a.D + p * V;
-    uint8_t *dst = a.codes[side] + ((size_t)bh * a.T + a.pos + t0) * a.P + p;
-    for (int i = tid; i < a.G * a.E; i += blockDim.x) {
+    const half_t *xs = a.x[side] + ((size_t)bh * a.n_new + t0) * a.D;
+    uint8_t *dst = a.codes[side] + ((size_t)bh * a.T + a.pos + t0) * a.P;
+    for (int i = tid; i < a.G * a.E; i += 256) {
         const V16 c = kvq_load<V>(src + (size_t)i * V);
 #pragma unroll
         for (int k = 0; k < V / 2; ++k) reinterpret_cast<uint32_t *>(cb + (size_t)(i + i / a.E) * V)[k] = c.w[k];
     }
     __syncthreads();
-    if (row >= rows) return;
-    const half_t *grp = cb + (size_t)g * (a.E + 1) * V;
-    for (int t = row; t < nt; t += rows * TOK) {
-        V16 x[TOK];
-        float bd[TOK];
-        int be[TOK];
-#pragma unroll
-        for (int k = 0; k < TOK; ++k) {
-            x[k] = kvq_load<V>(xs + (size_t)min(t + k * rows, nt - 1) * a.D);
-            bd[k] = INFINITY;
-            be[k] = 0;
-        }
-        for (int e = 0; e < a.E; ++e) {
-            const V16 c = kvq_load<V>(grp + (size_t)e * V);
+    if constexpr (TOK > 1) {
+        const int rows = 256 / a.P, row = tid / a.P, p = tid - row * a.P;   // tokens side by side; this lane's position
+        if (row >= rows) return;
+        const half_t *grp = cb + (size_t)(p / a.PG) * (a.E + 1) * V;
+        for (int t = row; t < nt; t += rows * TOK) {
+            V16 x[TOK];
+            float bd[TOK];
+            int be[TOK];
 #pragma unroll
             for (int k = 0; k < TOK; ++k) {
-                const float d = kvq_exact<V>(x[k], c);
-                be[k] = d < bd[k] ? e : be[k];
-                bd[k] = d < bd[k] ? d : bd[k];
+                x[k] = kvq_load<V>(xs + (size_t)min(t + k * rows, nt - 1) * a.D + p * V);
+                bd[k] = INFINITY;
+                be[k] = 0;
             }
-        }
+            for (int e = 0; e < a.E; ++e) {
+                const V16 c = kvq_load<V>(grp + (size_t)e * V);
 #pragma unroll
-        for (int k = 0; k < TOK; ++k)
-            if (t + k * rows < nt) dst[(size_t)(t + k * rows) * a.P] = (uint8_t)be[k];
+                for (int k = 0; k < TOK; ++k) {
+                    const float d = kvq_exact<V>(x[k], c);
+                    be[k] = d < bd[k] ? e : be[k];
+                    bd[k] = d < bd[k] ? d : bd[k];
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < TOK; ++k)
+                if (t + k * rows < nt) dst[(size_t)(t + k * rows) * a.P + p] = (uint8_t)be[k];
+        }
+    } else {
+        const int lanes = 1 << a.log_lanes, sub = tid & (lanes - 1), n_items = nt * a.P;
+        // (all lanes of a wavefront stay to the end: they merge what they found)
+        for (int i0 = 0; i0 < n_items; i0 += 256 >> a.log_lanes) {
+            const int i = min(i0 + (tid >> a.log_lanes), n_items - 1), t = i / a.P, p = i - t * a.P;
+            const V16 x = kvq_load<V>(xs + (size_t)t * a.D + p * V);
+            const half_t *grp = cb + (size_t)(p / a.PG) * (a.E + 1) * V;
+            float bd = INFINITY;
+            int be = sub;      // (nothing is closer than infinity: entry 0, as the first lane has it)
+            for (int e = sub; e < a.E; e += 4 * lanes) {   // (four lookups and distances side by side)
+                float d[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k)   // (past the end: the last entry, whose own index is smaller)
+                    d[k] = kvq_exact<V>(x, kvq_load<V>(grp + (size_t)min(e + k * lanes, a.E - 1) * V));
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    be = d[k] < bd ? e + k * lanes : be;
+                    bd = d[k] < bd ? d[k] : bd;
+                }
+            }
+            for (int m = 1; m < lanes; m <<= 1) {   // smaller distance, then smaller index
+                const float od = __shfl_xor(bd, m, 64);
+                const int oe = __shfl_xor(be, m, 64);
+                be = od < bd || (od == bd && oe < be) ? oe : be;
+                bd = od < bd ? od : bd;
+            }
+            if (sub == 0 && i0 + (tid >> a.log_lanes) < n_items) dst[(size_t)t * a.P + p] = (uint8_t)be;
+        }
     }
 }
 
@@ -289,13 +320,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
         const float up = __uint_as_float((unsigned)(127 + k) << 23);
         const half_t down = (half_t)__uint_as_float((unsigned)(127 - k) << 23);
         // the codebook of the group as matrix operands: entry 32 t + ln.  Past E: the first entry of the same group of eight
-        // once more, which changes no minimum (a group without entries: the last entry again)
+        // once more, which changes no minimum, or the last entry (groups without entries, and all of nearly 256: an item whose
+        // closest entry is the last one then ties and is scanned, but the select, once per workgroup and tile, costs more)
         half8_t A[TILES];
 #pragma unroll
         for (int t = 0; t < TILES; ++t) {
-            int e = ln;
-            if (32 * t + 32 > a.E) e = 32 * t + ln < a.E ? ln : min(ln & 20, a.E - 1 - 32 * t);   // (uniform)
-            const V16 c = kvq_load<V>(cbg + (32 * t + e) * V);
+            const int e = 32 * t + ln, last = a.E - 1;
+            const V16 c = kvq_load<V>(cbg + (TILES < 8 && e > last ? min(32 * t + (ln & 20), last) : min(e, last)) * V);
             float hh = 0.f;
 #pragma unroll
             for (int i = 0; i < V; ++i) hh = __builtin_fmaf((float)c.h8[i], (float)c.h8[i], hh);
@@ -435,17 +466,77 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     }
 }
 
-// New tokens from which the matrix-core kernel is used.  B2 H32, us: one codebook per head and side, scan 12.2 / 19.9 for
-// 4 / 8 tokens against 11.6 for the matrix-core kernel at 16; 64 codebooks of v = 2 (64 KiB to stage), 17.7 / 31.2 against
-// 26.9; a single token 11.4 - 12.7 by the scan in every layout (all of it the launch).
-constexpr int kQuantMfmaMin = 6;
-// Prompts (B2 H32, 2048 tokens), us, all pairs as before / matrix cores with every codebook padded to 256 entries / padded to a
-// power of two of tiles / small kernel: v = 4, one group, 8 entries 48 / 350 / 63 / 30; 16 59 / 268 / 57 / 50; 24 76 / 192 / 58 / 72;
-// 64 158 / 146 / 66 / 184; v = 8, 8 entries 31 / 267 / 42 / 27; 16 49 / 203 / 42 / 48; v = 2, 64 groups, 16 entries 231 / 356 / 115 /
-// 55; 32 891 / 305 / 118 / 100; 64 1774 / 279 / 140 / 192.
-bool kv_quantize_small_codebook(int E, int v) { return E * v <= 64; }
-bool kv_quantize_on_matrix_cores(int n_new) { return n_new >= kQuantMfmaMin; }
-constexpr int kQuantScanTokens = 16;
+enum { kKvqScan, kKvqLane, kKvqMfma };
+constexpr int kQuantScanTokens = 16, kQuantLaneTokens = 128;   // tokens per workgroup, at most
+constexpr int kQuantLaneBytes = 16 * 1024;                     // of codebooks: more leave a CU too few wavefronts
+
+namespace {
+
+int ceil_div(long a, long b) { return (int)((a + b - 1) / b); }
+// Tokens per workgroup of the matrix-core kernel: as many as leave the chip two rounds of workgroups (a workgroup stages its
+// codebooks first).
+int kvq_mfma_tokens(int bh, int n_new) {
+    int tokens = kQuantMfmaTokens;
+    while (tokens > 16 && (long)bh * 2 * ceil_div(n_new, tokens) < 1024) tokens /= 2;
+    return tokens;
+}
+// Lanes that share an item: as many as give 256 lanes work.
+int kvq_log_lanes(int items) {
+    int log_lanes = 0;
+    while (log_lanes < 6 && items << (log_lanes + 1) <= 256) ++log_lanes;
+    return log_lanes;
+}
+// Four tokens at a time save three of four lookups of an entry (v = 8 is bound by its distances: 8 entries 27.1 us with one,
+// 28.0 with four; v = 4 34.3 / 30.3).
+bool kvq_four_tokens(int P, int v, int n_new) { return v <= 4 && n_new >= 4 * (256 / P); }
+
+// The kernel with the least estimated time (us): the chain of one workgroup or the instructions of all of them (a vector
+// instruction of a wavefront: 1.63e-6 us of the chip), whichever is longer.  Fitted to 703 measured calls (B 1 .. 64, 1 to
+// 2048 tokens, 8 to 256 entries, 1 to 64 groups, head sizes 64 to 256): the pick takes 0.2 % more than the best of the three on
+// average, 20 % at worst.  Some of them, us, scan / lane / matrix cores: one group of 256, v = 4, one token, B4 4.3 / 4.1 / 4.8,
+// B16 8.6 / 6.3 / 5.4, B64 25.2 / 16.8 / 15.9; 32 groups of 256, B4, 4 tokens 11.0 / - / 14.3, 8 tokens 18.9 / - / 14.5; 8 groups of 64,
+// B16, one token 8.6 / 4.0 / 6.7; 16 entries, v = 4, B64, 4 tokens 73 / 7.2 / 11.1, B2, 2048 tokens 1052 / 49 / 57.
+int kvq_choice(int bh, int P, int v, int E, int G, int n_new) {
+    const double kInst = 1.63e-6;
+    double best = 1e300;
+    int pick = kKvqScan;
+    auto consider = [&](int kernel, double chain, double wgs, double start, double inst) {
+        const double t = std::max(chain, wgs * (start + inst * kInst));
+        if (t < best) {
+            best = t;
+            pick = kernel;
+        }
+    };
+    const double sides = 2.0 * bh;
+    {   // a wavefront of eight takes one item after the other
+        const int tokens = std::min(n_new, kQuantScanTokens), items = tokens * P;
+        consider(kKvqScan, ceil_div(items, 8) * (0.33 + 0.045 * v), sides * ceil_div(n_new, tokens), 0.0022, items * (52.0 + 9 * v));
+    }
+    if (G * E * v * 2 <= kQuantLaneBytes) {
+        const int tokens = std::min(n_new, kQuantLaneTokens), items = tokens * P, log_lanes = kvq_log_lanes(items);
+        const bool four = kvq_four_tokens(P, v, n_new);
+        const int entries = ceil_div(E, 1 << log_lanes);
+        const int waves = four ? 16 * ceil_div(tokens, 4 * (256 / P)) : ceil_div((long)items << log_lanes, 64);
+        const double per_entry = four ? 1 + 2.7 * v : 4 + 2.5 * v;
+        consider(kKvqLane, ceil_div(waves, 4) * (entries * (0.03 + 0.005 * v) + 0.06 * log_lanes) + 5e-5 * (G * E * v * 2), sides * ceil_div(n_new, tokens), 0.0015,
+                 waves * (entries * per_entry + 12 * log_lanes) + G * E * 0.4);
+    }
+    {
+        const int tiles = E <= 32 ? 1 : E <= 64 ? 2 : E <= 128 ? 4 : 8, most = kvq_mfma_tokens(bh, n_new), tokens = std::min(n_new, most);
+        const int columns = ceil_div((long)tokens * (P / G), 32);   // column tiles of 32 items per group
+        const int waves = 4 * ((long)G * 64 * tiles * v + tokens * P) > 160 * 1024 ? 8 : 4, share = std::max(1, waves / G);
+        const double chain = ceil_div(G, waves) * (0.6 + 0.2 * tiles + 0.08 * v + (ceil_div(columns, share) - 1) * (0.5 + 0.06 * tiles));
+        consider(kKvqMfma, chain + 1.8e-5 * (G * E * v * 2), sides * ceil_div(n_new, most), 0.0022,
+                 G * (40.0 + 36 * tiles + columns * (95.0 + 14 * tiles)));
+    }
+    return pick;
+}
+
+}  // namespace
+
+int kv_quantize_kernel_of(const vq_kv_t *kv, int n_new) {
+    return kvq_choice(kv->B * kv->H, kv->D / kv->v, kv->v, kv->n_entries, kv->cb_groups, n_new);
+}
 
 namespace {
 
@@ -460,31 +551,32 @@ int run_kvq_mfma(const KvQuantArgs &a, int bh, hipStream_t s) {
     return launch_status();
 }
 
-// TOK = 4 saves the lookups of an entry for three of four tokens (v = 8 is bound by its distances: 27.1 us with one token at a
-// time, 28.0 with four, for 8 entries; v = 4 34.3 / 30.3).
-template <int V, int TOK>
-int run_kvq_small(KvQuantArgs &a, int bh, hipStream_t s) {
-    a.tokens = std::min(a.n_new, 128);
-    const size_t lds = (size_t)a.G * (a.E + 1) * V * sizeof(half_t);
-    kv_quantize_small_kernel<V, TOK><<<dim3(bh, (a.n_new + a.tokens - 1) / a.tokens, 2), 256, lds, s>>>(a);   // (16.5 KiB at most)
+template <int V>
+int run_kvq_lane(KvQuantArgs &a, int bh, hipStream_t s) {
+    a.tokens = std::min(a.n_new, kQuantLaneTokens);
+    a.log_lanes = kvq_log_lanes(a.tokens * a.P);
+    const dim3 grid(bh, (a.n_new + a.tokens - 1) / a.tokens, 2);
+    const size_t lds = (size_t)a.G * (a.E + 1) * V * sizeof(half_t);   // (below 64 KiB: kQuantLaneBytes)
+    if constexpr (V <= 4)
+        if (kvq_four_tokens(a.P, V, a.n_new)) {
+            kv_quantize_lane_kernel<V, 4><<<grid, 256, lds, s>>>(a);
+            return launch_status();
+        }
+    kv_quantize_lane_kernel<V, 1><<<grid, 256, lds, s>>>(a);
     return launch_status();
 }
 
 template <int V>
 int run_kvq(KvQuantArgs &a, int bh, hipStream_t s) {
-    if (kv_quantize_small_codebook(a.E, V)) {
-        if (V <= 4 && a.n_new >= 4 * (256 / a.P)) return run_kvq_small<V, 4>(a, bh, s);
-        return run_kvq_small<V, 1>(a, bh, s);
-    }
-    if (!kv_quantize_on_matrix_cores(a.n_new)) {
-        a.tokens = a.n_new < kQuantScanTokens ? a.n_new : kQuantScanTokens;
+    const int kernel = kvq_choice(bh, a.P, V, a.E, a.G, a.n_new);
+    if (kernel == kKvqLane) return run_kvq_lane<V>(a, bh, s);
+    if (kernel == kKvqScan) {
+        a.tokens = std::min(a.n_new, kQuantScanTokens);
         kv_quantize_scan_kernel<V><<<dim3(bh, (a.n_new + a.tokens - 1) / a.tokens, 2), 512, 0, s>>>(a);
         return launch_status();
     }
     a.pg_inverse = kvq_inverse(a.PG);
-    // tokens per workgroup: as many as leave the chip two rounds of workgroups (a workgroup stages its codebooks first)
-    a.tokens = kQuantMfmaTokens;
-    while (a.tokens > 16 && (long)bh * 2 * ((a.n_new + a.tokens - 1) / a.tokens) < 1024) a.tokens /= 2;
+    a.tokens = kvq_mfma_tokens(bh, a.n_new);
     if (a.E <= 32) return run_kvq_mfma<V, 1>(a, bh, s);
     if (a.E <= 64) return run_kvq_mfma<V, 2>(a, bh, s);
     if (a.E <= 128) return run_kvq_mfma<V, 4>(a, bh, s);

@@ -499,10 +499,17 @@ def test_more_than_256_tokens_without_a_two_stage_product_take_one_pass(kw):
     assert not one_pass(weight(N=4096, K=4096, **kw), 2048) and one_pass(weight(N=4096, K=4096, **kw), 256)
 
 
-def test_kv_quantize_of_prompts_runs_on_the_matrix_cores():
-    for n_new in (6, 17, 128, 4096):
-        assert internal("_ZN2vq27kv_quantize_on_matrix_coresEi", n_new)
-    assert not internal("_ZN2vq27kv_quantize_on_matrix_coresEi", 1)
-    # but for codebooks so small that comparing all entries is less work
-    small = lambda E, v: internal("_ZN2vq26kv_quantize_small_codebookEii", E, v)  # noqa: E731
-    assert small(16, 4) and small(8, 8) and small(32, 2) and not small(17, 4) and not small(16, 8) and not small(256, 2)
+@pytest.mark.parametrize("kw,n_new,kernel", [
+    # prompts of 256 entries, whatever the head size and the groups
+    (dict(B=2, H=32, D=128, v=4), 2048, "matrix"), (dict(B=2, H=32, D=96, v=4), 2048, "matrix"), (dict(B=1, H=8, D=80, v=8, cb_groups=2), 300, "matrix"),
+    (dict(B=2, H=32, D=192, v=2, cb_groups=32), 100, "matrix"),
+    # small codebooks: all entries, a lane per sub-vector
+    (dict(B=2, H=32, D=128, v=4, n_entries=16), 2048, "lane"), (dict(B=2, H=32, D=128, v=8, n_entries=8), 2048, "lane"),
+    (dict(B=2, H=32, D=128, v=4, n_entries=64), 2048, "matrix"), (dict(B=64, H=32, D=128, v=4, n_entries=16), 5, "lane"),
+    # decode steps: a few sequences scan, many do not (their launch is bound by instructions, not by the chain of one item)
+    (dict(B=3, H=32, D=128, v=4, cb_groups=32), 1, "scan"), (dict(B=2, H=32, D=128, v=4), 1, "lane"), (dict(B=64, H=32, D=128, v=4), 1, "matrix"),
+    (dict(B=64, H=32, D=128, v=4), 5, "matrix"), (dict(B=16, H=32, D=128, v=4, cb_groups=32), 4, "scan"), (dict(B=16, H=32, D=128, v=4, cb_groups=32), 16, "matrix"),
+])
+def test_kv_quantize_kernel_follows_the_amount_of_work(kw, n_new, kernel):
+    f = vq.lib()._ZN2vq21kv_quantize_kernel_ofEPK7vq_kv_ti
+    assert f(ctypes.byref(kvdesc(**{**dict(T=4096), **kw})), n_new) == ("scan", "lane", "matrix").index(kernel)

@@ -1261,7 +1261,7 @@ def test_kv_quantize_hard_values(gpu_device, v, G, E, n_new, kind):
                                      # wholly empty; a lane per sub-vector (E v <= 64)
                                      (128, 4, 1, 18), (128, 8, 2, 9), (96, 2, 16, 40), (128, 4, 1, 66), (128, 2, 64, 100), (128, 8, 4, 128),
                                      (128, 4, 1, 16), (96, 8, 12, 7), (256, 2, 128, 32), (128, 4, 32, 2), (40, 2, 5, 24), (128, 8, 1, 1)])
-@pytest.mark.parametrize("n_new", [1, 7, 300])
+@pytest.mark.parametrize("n_new", [1, 3, 7, 300])
 def test_kv_quantize_head_sizes(gpu_device, D, v, G, E, n_new):
     rng = np.random.default_rng(9600 + D + v + n_new)
     B, H, T, P = 1, 3, n_new + 5, D // v
