@@ -84,8 +84,12 @@ __device__ __forceinline__ void swap16(uint32_t &a, uint32_t &b) {   // odd rows
 
 constexpr int skinny_max_waves(bool l2, int rt, int ct) { return !l2 && rt * ct <= 2 ? 16 : 8; }
 
-// Operands of an X unit: two (a line of 128 bytes per token), or as many as a lane's dword holds.
-constexpr int skinny_unit(int mpi, int opd) { return opd > 2 ? opd : mpi < 2 ? mpi : 2; }
+// Operands of an X unit: two (a line of 128 bytes per token where a lane's operands of a step are one or two), four where a
+// step has four or eight.  All eight of one 12-bit codebook would be 456 bytes of scratch per lane (N = K = 4096, 17 / 77 / 256
+// tokens 46.9 / 33.7 / 65.9 us, with four 12.2 / 16.8 / 31.4).  With four the {1, 2} tiles and {4, 4} spill up to ten loop
+// constants: units of two (K = 11008, 32 tokens 14.6 -> 18.3) or constants formed again for every unit (two 12-bit
+// codebooks, 32 tokens 8.3 -> 10.5) spill none and take longer.
+constexpr int skinny_unit(int mpi, int opd) { return opd > 2 ? 4 : mpi < 2 ? mpi : 2; }
 // Units in flight: up to 64 registers (32 where the accumulators or 16 wavefronts take the rest), a divisor of the
 // units per iteration.
 constexpr int skinny_depth(int epi, int u, bool l2, int rt, int ct) {
@@ -117,13 +121,14 @@ __global__ __launch_bounds__(64 * skinny_max_waves(L2CB, RT, CT)) void gemm_skin
     const int row_bytes = a.ops * CPO * R * BITS / 8;
     const int slot = !TR || NS == 4 ? g : ((g & 1) << 1) | (g >> 1);   // (two dwords: one swap, lanes 1 and 2 of a row change places)
 
-    const unsigned char *crow[RT];
+    const unsigned char *cbase = reinterpret_cast<const unsigned char *>(a.codes) + (size_t)n0 * row_bytes;
+    uint32_t crow[RT];
 #pragma unroll
     for (int t = 0; t < RT; ++t)   // rows past the end are computed and dropped
-        crow[t] = reinterpret_cast<const unsigned char *>(a.codes) + (size_t)min(n0 + 16 * t + r, a.N - 1) * row_bytes;
+        crow[t] = (uint32_t)(min(n0 + 16 * t + r, a.N - 1) - n0) * (uint32_t)row_bytes;
     // X loads: instruction j of a unit covers 64 / SEGS tokens, whole contiguous rows of SEGS 16-byte segments
     const int xseg = lane % SEGS, xtok = lane / SEGS;
-    uint32_t xrow[CT][U];   // byte offsets (gemm_skinny_supported bounds K)
+    uint32_t xrow[CT][U];   // byte offsets (kSkinnyMaxX)
 #pragma unroll
     for (int c = 0; c < CT; ++c)
 #pragma unroll
@@ -132,7 +137,7 @@ __global__ __launch_bounds__(64 * skinny_max_waves(L2CB, RT, CT)) void gemm_skin
     // Loads carry no condition: a lane past the end of its row reads the row's last bytes, and what it makes of them
     // is zeroed (both operands: an infinity there must not meet a zero).
     auto load_codes = [&](int it, int t, V16 &cd) {
-        const unsigned char *p = crow[t] + min((it * 4 + g) * LB, row_bytes - LB);
+        const unsigned char *p = cbase + (crow[t] + (uint32_t)min((it * 4 + g) * LB, row_bytes - LB));
         if (LB == 16) {
             cd = ld16(p);
         } else if (LB == 12) {
@@ -167,8 +172,14 @@ __global__ __launch_bounds__(64 * skinny_max_waves(L2CB, RT, CT)) void gemm_skin
         const int swz = U == 2 ? (tok ^ (tok >> 3)) & 7 : tok & (SEGS < 16 ? SEGS - 1 : 15);
         return tok * (SEGS * 16) + ((seg ^ swz) << 4);
     };
+    // A unit is whole steps of the four lanes of a row (their operands lie side by side), or a part of one step (U of the OPD
+    // operands of each of the four lanes).
+    constexpr bool PART = U < OPD;
+    static_assert(PART ? OPD % U == 0 : U % OPD == 0, "units and steps");
+    const int xlane = PART ? (xseg / U) * OPD + xseg % U : xseg;
     auto load_x = [&](int it, int e, V16 (&xb)[U]) {   // unit e / CT, token tile e % CT
-        const uint32_t k = min((it * NU + e / CT) * SEGS + xseg, a.ops - 1) * 16;
+        const int u = e / CT, first = PART ? u * U / OPD * (4 * OPD) + u * U % OPD : u * SEGS;
+        const uint32_t k = min(it * (4 * MPI) + first + xlane, a.ops - 1) * 16;
 #pragma unroll
         for (int j = 0; j < U; ++j) xb[j] = ld16(reinterpret_cast<const unsigned char *>(a.x) + (xrow[e % CT][j] + k));
     };
@@ -178,7 +189,7 @@ __global__ __launch_bounds__(64 * skinny_max_waves(L2CB, RT, CT)) void gemm_skin
         for (int j = 0; j < U; ++j) *reinterpret_cast<uint4 *>(stage + stage_off(j * (64 / SEGS) + xtok, xseg)) = xb[j].u;
 #pragma unroll
         for (int q = 0; q < U; ++q)
-            xo[q] = *reinterpret_cast<const half8_t *>(stage + stage_off(r, ((q / OPD) * 4 + slot) * OPD + q % OPD));
+            xo[q] = *reinterpret_cast<const half8_t *>(stage + stage_off(r, PART ? slot * U + q : ((q / OPD) * 4 + slot) * OPD + q % OPD));
     };
     const half_t *cbl = reinterpret_cast<const half_t *>(smem);
     const int set_halves = R * a.E * V;

@@ -169,6 +169,23 @@ def test_gemv_replica_gathers_form_one_block_and_nothing_lives_in_scratch(tmp_pa
     assert checked == 2
 
 
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
+def test_gemm_skinny_keeps_its_operands_in_registers(tmp_path):
+    """Every tile that is built for every format: a few registers of loop constants may be spilled (measured: forming them
+    again costs more), operands may not (one 12-bit codebook once had 456 bytes per lane of them)."""
+    out = tmp_path / "gemm_skinny.s"
+    cmd = [HIPCC, "-O3", "-std=c++17", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang",
+           "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "--cuda-device-only", "-S",
+           os.path.join(CSRC, "gemm_skinny.hip"), "-o", str(out)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    scratch = {m.group(1): int(m.group(2)) for m in re.finditer(
+        r"\.amdhsa_kernel (\S*gemm_skinny_kernel\S*)\n.*?\.amdhsa_private_segment_fixed_size (\d+)", out.read_text(), re.S)}
+    assert len(scratch) == 12 * 5 - 4 + 2 * 6     # LDS tiles (4 x 4 not for 12-bit codes), tiles with the codebook in L2
+    assert max(scratch.values()) <= 48, {k: v for k, v in scratch.items() if v > 48}
+    assert sum(v > 0 for v in scratch.values()) <= 6
+
+
 def _asm_loads_touched_in_flight(text):
     """Registers that asm loads (between ASMSTART / ASMEND) have been asked to fill, followed along every path of a kernel's
     compiled code until an s_waitcnt vmcnt that covers them: the instructions that touch one before that."""
