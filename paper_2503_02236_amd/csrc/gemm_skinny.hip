@@ -534,12 +534,17 @@ bool gemm_skinny_wins(const vq_weight_t *w, int M) {
 // 8 tokens 41.2 / 20.6).  Not where the caller says that the front of the codebook is hot: that part is kept in LDS.
 // LDS codebooks: the matrix-core gemv reads X in operand order, which costs it 0.1 .. 0.4 us per token; from 14 tokens on
 // this kernel is ahead where one round of workgroups covers the rows (16 tokens, N = 4096, K = 11008, two codebooks
-// 13.6 / 11.2; 8 tokens 10.3 / 10.9) and K is long enough to fill its wavefronts (K = 256: 3.6 / 4.0; 16 tokens of 11008
-// rows: 15.0 / 18.4).  Not for 12-bit codes, which have no transposition (16 tokens with cold caches, N = K = 4096: 10.1 /
-// 10.7).
+// 13.6 / 11.2; 8 tokens 10.3 / 10.9; 16 tokens of 11008 rows 15.0 / 18.4) and K is long enough to fill its wavefronts.  Its
+// time over the other's with 14 .. 16 tokens, N = 256 .. 4096: v = 8, K = 1024 1.00 .. 1.04, 2048 0.93 .. 1.03, 4096 0.83 .. 1.01; v = 4
+// with uint16 codes, K = 1024 1.04 .. 1.07, 2048 0.96 .. 1.01; with uint8 codes, one codebook, 2048 1.01 .. 1.06, 4096 0.84 .. 0.90, two,
+// 2048 1.02 .. 1.07, 4096 0.98 .. 1.04, 6400 0.87 .. 0.94.  Not for 12-bit codes, which have no transposition (16 tokens with cold
+// caches, N = K = 4096: 10.1 / 10.7).
 bool gemm_skinny_for_gemv(const vq_weight_t *w, int bs) {
     if (!gemm_skinny_supported(w)) return false;
-    if (codebooks_fit_lds(w)) return entries_from_lds(w) && bs >= 14 && w->code_bits != 12 && w->K >= 2048 && w->N <= 16 * 256;
+    if (codebooks_fit_lds(w)) {
+        const int long_k = w->v == 8 || w->code_bits == 16 ? 2048 : w->n_codebooks == 1 ? 4096 : 5120;
+        return entries_from_lds(w) && bs >= 14 && w->code_bits != 12 && w->K >= long_k && w->N <= 16 * 256;
+    }
     if (gemv_mfma_supported(w)) return false;
     return bs >= (w->v == 8 ? 2 : 5) || w->K / (8 * w->v) > 256;
 }

@@ -513,3 +513,12 @@ def test_more_than_256_tokens_without_a_two_stage_product_take_one_pass(kw):
 def test_kv_quantize_kernel_follows_the_amount_of_work(kw, n_new, kernel):
     f = vq.lib()._ZN2vq21kv_quantize_kernel_ofEPK7vq_kv_ti
     assert f(ctypes.byref(kvdesc(**{**dict(T=4096), **kw})), n_new) == ("scan", "lane", "matrix").index(kernel)
+
+
+def test_gemv_takes_the_faster_of_two_kernels_at_the_lines_between_them():
+    """Routes on both sides of a line; each was measured as the faster one there."""
+    for_gemv = lambda bs, **kw: internal("_ZN2vq20gemm_skinny_for_gemvEPK11vq_weight_ti", ctypes.byref(weight(**kw)), bs)  # noqa: E731
+    assert for_gemv(16, N=4096, K=11008, n_codebooks=2) and not for_gemv(13, N=4096, K=11008, n_codebooks=2)
+    assert not for_gemv(16, N=11008, K=4096, n_codebooks=2) and not for_gemv(16, N=4096, K=1024)
+    assert for_gemv(14, N=1024, K=2048) and not for_gemv(14, N=1024, K=2048, v=4) and for_gemv(14, N=1024, K=4096, v=4)
+    assert not for_gemv(14, N=4096, K=4096, v=4, n_codebooks=2) and for_gemv(14, N=3000, K=6400, v=4, n_codebooks=2)
