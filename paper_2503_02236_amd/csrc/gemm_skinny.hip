@@ -415,12 +415,20 @@ int run_tile(const vq_weight_t *w, const half_t *x, int M, half_t *y, hipStream_
     a.groups_m = (M + 16 * CT - 1) / (16 * CT);
     constexpr size_t kUnit = 1024 * skinny_unit_of<CodeT, V, R>();
     const size_t cb_bytes = L2CB ? 0 : ((size_t)R * a.E * V * 2 * a.tiles_k + 15) & ~(size_t)15;
-    int waves = std::min(a.nit, skinny_max_waves(L2CB, RT, CT));
+    const long grid = (long)((w->N + 16 * RT - 1) / (16 * RT)) * a.groups_m;
+    constexpr int kMaxWaves = skinny_max_waves(L2CB, RT, CT);
+    auto lds_of = [&](int n) { return std::max(cb_bytes + n * kUnit, (size_t)RT * CT * n * 1024); };
+    // a wavefront per iteration over K
+    int waves = std::min(a.nit, kMaxWaves);
     while (waves > 1 && cb_bytes + waves * kUnit > kSkinnyLds) waves = (waves + 1) / 2;
-    const size_t lds = std::max(cb_bytes + waves * kUnit, (size_t)RT * CT * waves * 1024);
+    // and more where a short K leaves few of them to stage the codebooks (one wavefront: 20 us for 128 KiB), unless that takes
+    // the place of other workgroups
+    auto per_cu = [&](int n) { return std::min((int)(kSkinnyLds / lds_of(n)), kMaxWaves / n); };
+    for (int n = std::min((int)(cb_bytes / 8192), kMaxWaves); n > waves; --n)
+        if (lds_of(n) <= kSkinnyLds && (grid <= 256 || per_cu(n) == per_cu(waves))) waves = n;
+    const size_t lds = lds_of(waves);
     static KernelSetup setup;
     if (int st = kernel_setup(reinterpret_cast<const void *>(&gemm_skinny_kernel<CodeT, V, R, L2CB, RT, CT>), lds, false, setup)) return st;
-    const long grid = (long)((w->N + 16 * RT - 1) / (16 * RT)) * a.groups_m;
     gemm_skinny_kernel<CodeT, V, R, L2CB, RT, CT><<<(int)grid, waves * 64, lds, s>>>(a);
     return launch_status();
 }
@@ -434,8 +442,9 @@ constexpr SkinnyTile kL2Tiles[] = {{1, 1}, {1, 2}, {1, 4}, {2, 4}, {1, 8}, {2, 8
 // plus its start and end, times the rounds of workgroups over 256 CUs.  From LDS a second round is a whole one, later
 // ones fill in; from L2 all workgroups share the dies' L2s, so fewer than 256 of them are not that much faster.
 // The constants were fitted to 210 measured shapes (six formats, N 256 .. 11008, M 17 .. 256) x 6 tiles: the tile that
-// this picks takes 0.5 % more than the best one on average and 17 % more at worst.
-int skinny_tile(const vq_weight_t *w, int M, bool l2, double *clocks = nullptr) {
+// this picks takes 0.5 % more than the best one on average and 17 % more at worst.  Staging of the codebooks, the same for every
+// tile, counts only in the estimate (*clocks).
+int skinny_tile(const vq_weight_t *w, int M, bool l2, double staging = 0, double *clocks = nullptr) {
     int best = 0;
     double best_cost = 1e300;
     for (int i = 0; i < (l2 ? 6 : 5); ++i) {
@@ -445,7 +454,7 @@ int skinny_tile(const vq_weight_t *w, int M, bool l2, double *clocks = nullptr) 
         const double r = (double)(((long)w->N + 16 * t.rt - 1) / (16 * t.rt)) * ((M + 16 * t.ct - 1) / (16 * t.ct)) / 256;
         const double rounds = l2 ? (r <= 1 ? std::max(0.7, r) : r + 0.3) : r <= 1 ? 1.0 : r <= 2 ? 2.0 : r + 0.3;
         const double lookups = 16.0 * t.rt * (w->K / w->v) * w->n_codebooks / (l2 ? 0.35 : 3.5);
-        const double cost = rounds * (lookups + 16.0 * t.ct * w->K * 2 / 41 + 2000);
+        const double cost = rounds * (lookups + 16.0 * t.ct * w->K * 2 / 41 + 2000 + staging);
         if (cost < best_cost) {
             best_cost = cost;
             best = i;
@@ -518,11 +527,15 @@ bool gemm_skinny_supported(const vq_weight_t *w) {
 // Measured with two 256-entry codebooks, two-stage / here: N = 256, K = 1024, 1024 tokens 13.0 / 5.8 us; N = 1024,
 // K = 4096, 1024 tokens 35.7 / 20.0; N = K = 4096, 384 tokens 48.2 / 34.8, 1024 tokens 51.4 / 67.6; N = 11008, 272 tokens
 // 75.0 / 66.2, 384 tokens 75.7 / 83.5; 2^16 entries, N = 1024, 1024 tokens 36.9 / 31.8, N = 4096, 384 tokens 45.4 / 60.3.
-// The estimates are good to 20 %, so this one has to be that much lower.  (A supported weight with K % 64 == 0.)
+// Every workgroup stages the codebooks (41 bytes per clock): 4096 12-bit codes, N = 1000, K = 512, 1024 tokens 15.0 / 17.2.
+// The estimates are good to 20 %, so this one has to be that much lower: over 1056 measured calls (11 formats, 12 weights, 257 to
+// 2048 tokens) the pick takes 1.8 % more than the better of the two.  (A supported weight with K % 64 == 0.)
 bool gemm_skinny_wins(const vq_weight_t *w, int M) {
     if ((long)M * w->K >= kSkinnyMaxX) return false;
     double here;
-    skinny_tile(w, M, !entries_from_lds(w), &here);
+    const bool l2 = !entries_from_lds(w);
+    const size_t sets = w->cb_tile_n > 0 ? w->K / w->cb_tile_k : 1;
+    skinny_tile(w, M, l2, l2 ? 0 : sets * w->n_codebooks * w->n_entries * w->v * 2 / 41.0, &here);
     const double rounds = gemm_dense_rounds(M, w->N, nullptr);
     return here < 0.8 * (rounds * (20.0 * w->K + 5500) + 0.0017 * w->N * w->K + 3500);
 }

@@ -522,3 +522,9 @@ def test_gemv_takes_the_faster_of_two_kernels_at_the_lines_between_them():
     assert not for_gemv(16, N=11008, K=4096, n_codebooks=2) and not for_gemv(16, N=4096, K=1024)
     assert for_gemv(14, N=1024, K=2048) and not for_gemv(14, N=1024, K=2048, v=4) and for_gemv(14, N=1024, K=4096, v=4)
     assert not for_gemv(14, N=4096, K=4096, v=4, n_codebooks=2) and for_gemv(14, N=3000, K=6400, v=4, n_codebooks=2)
+
+
+def test_staging_of_large_codebooks_counts_in_the_choice_of_the_product():
+    one_pass = lambda M, **kw: internal("_ZN2vq13gemm_one_passEPK11vq_weight_ti", ctypes.byref(weight(**kw)), M)  # noqa: E731
+    big = dict(code_bits=12, n_codebooks=2, n_entries=4096)      # 128 KiB of codebooks to stage in every workgroup
+    assert one_pass(1024, N=1000, K=512, n_codebooks=2) and not one_pass(1024, N=1000, K=512, **big) and one_pass(257, N=1000, K=512, **big)
