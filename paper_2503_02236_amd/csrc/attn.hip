@@ -11,15 +11,13 @@
 //   operand registers (layout fusion, Sec. VI-B: no shuffle, no LDS round trip).  The A operand is q,
 //   the same in all 16 rows, so every accumulator row holds the score and each of a token's four
 //   lanes reads its token's score from its own registers.  Four MFMAs cover the 128 channels.
-//   V side, 16 wavefronts per CU and v = 4: p V on the matrix cores as well, the entries read from LDS through the
-//   transposing read that lays 4 tokens of a channel side by side in a lane (attn_decode_kernel below).  Otherwise the
-//   lane dequantizes its 32 channels of the token's V vector and adds p_t * V[t] into 32 PRIVATE fp32 accumulators.
-//   Either way the column-wise accumulation over tokens that forces a shared-memory round trip in the paper's baseline
-//   (Sec. III-B, Fig. 6) is deferred to one sum over lanes at the very end, so dequantized values never travel
-//   through LDS.
-// Measured (B = 16, H = 32, T = 4096, one codebook per head and side, 134 MB of codes): vector ALU 34.2 us, matrix cores
-// 31.3 us with the codes in the last-level cache, 36.6 / 35.1 and 34.2 / 34.2 from HBM on two cards.  The vector ALU issued 99 instructions per 16 tokens, half of them for p V, now about 50; what is
-// left is the chain of a tile: codes -> entries -> scores -> maximum -> weights -> p V with 4 wavefronts per SIMD.
+//   V side: the lane dequantizes its 32 channels of the token's V vector and adds p_t * V[t] into 32
+//   PRIVATE fp32 accumulators.  The column-wise accumulation over tokens that forces a shared-memory
+//   round trip in the paper's baseline (Sec. III-B, Fig. 6) is deferred to one butterfly over the 16
+//   token lanes at the very end, so dequantized values never travel through LDS.
+// p V on the matrix cores (entries through the transposing LDS read, weights as two halves) halves the vector instructions
+// and was not faster: its chain per tile is longer.  B = 16, H = 32, T = 4096, one codebook per head and side 30.1 us here, 31.9
+// there (codes in the last-level cache); 32 codebooks 34.9 / 37.6; 0 to 9 % in favour of this over 140 shapes.
 // Only ~130 registers per lane are needed, so 16 wavefronts per CU hide the gather latency.
 // Codebooks live in LDS (2 KB each for one codebook per head and side).
 //
@@ -144,32 +142,6 @@ constexpr int kAttnRepCopies = 32;
 constexpr int kAttnRepSide = 65536;   // bytes per side: 256 entries x 32 copies x 8 bytes
 constexpr int kAttnRepMinWgs = 192;   // fewer workgroups than this: two small workgroups per CU (shared copy) fill the chip better
 
-// What infinities and NaN in the V codebooks of head h add to the wavefront's partial sums o[128]: its tokens one after
-// the other from the caches and codebooks in memory, two channels per lane (slow, and never run on a sound codebook).  A
-// weight that underflows counts as positive.
-template <int V>
-__device__ __noinline__ void add_nonfinite(const uint8_t *k_codes, const uint8_t *v_codes, const half_t *k_cb, const half_t *v_cb,
-                                           const half_t *q, int E, int pg_shift, float scale2, int t_wave, int tile, int per_tile,
-                                           int count, float m_run, int lane, float *o) {
-    const int p = 2 * lane / V, e0 = 2 * lane % V;   // sub-vector and element of this lane's channels
-    const size_t book = (size_t)(p >> pg_shift) * E;
-    float add[2] = {0.f, 0.f};
-    for (int t0 = t_wave; t0 < count; t0 += tile)
-        for (int t = t0; t < min(t0 + per_tile, count); ++t) {
-            const half_t *k = k_cb + (book + k_codes[(size_t)t * (128 / V) + p]) * V + e0;
-            const half_t *v = v_cb + (book + v_codes[(size_t)t * (128 / V) + p]) * V + e0;
-            const float s = wave_sum((float)q[2 * lane] * (float)k[0] + (float)q[2 * lane + 1] * (float)k[1]) * scale2;
-            const float w = fmaxf(__builtin_amdgcn_exp2f(s - m_run), 1e-30f);
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const float x = (float)v[i];
-                if (!(__builtin_fabsf(x) <= 65504.f)) add[i] += w * x;
-            }
-        }
-    o[2 * lane] += add[0];
-    o[2 * lane + 1] += add[1];
-}
-
 template <int V, bool ONE, int SEQ, bool REP = false>
 __global__ __launch_bounds__(kAttnWaves * 64 * SEQ) __attribute__((amdgpu_waves_per_eu(4, 4))) void attn_decode_kernel(AttnArgs a) {
     static_assert(!REP || (V == 4 && ONE), "replicated codebooks: one codebook of 8-byte entries per side");
@@ -179,9 +151,6 @@ __global__ __launch_bounds__(kAttnWaves * 64 * SEQ) __attribute__((amdgpu_waves_
     constexpr int CW = (CB + 3) / 4;  // dwords holding them
     constexpr int NS = attn_steps(V);
     constexpr int TILE = attn_tile(V);
-    // V on the matrix cores: entries of 8 bytes (see tr_gather; v = 8 took 34.7 us for 31.7 at B = 16, H = 32, T = 4096),
-    // and where 16 wavefronts per CU hide its longer chain (8: B = 1, H = 32, T = 4096, 32 codebooks 12.2 us for 11.4)
-    constexpr bool TR = V == 4 && SEQ == 2;
     constexpr unsigned SH = V == 8 ? 4 : V == 4 ? 3 : 2;  // log2 of the entry size in bytes
     extern __shared__ __align__(16) unsigned char smem[];
     // Entry addresses are formed as plain LDS byte offsets (shifted code + constant), which is only
@@ -209,20 +178,17 @@ __global__ __launch_bounds__(kAttnWaves * 64 * SEQ) __attribute__((amdgpu_waves_
 
     const int ntiles = active ? (end - start + TILE - 1) / TILE : 0;
     const size_t row0 = (size_t)bh * a.T;
-    // token of (tile it, step s) for this lane: t_lane + it * TILE + s * 16.  K side, and V on the vector ALU: token
-    // lane % 16 of the step, channels 32 g ..; V on the matrix cores: token 4 g + (lane % 16) / 4, channels
-    // 32 (lane % 4) .. (the operand of a transposing read, see tr_gather)
-    // (counted from the start of the range)
-    const int t_wave = wave * (16 * NS), t_lane = t_wave + tok, count = end - start;
+    // token of (tile it, step s) for this lane, counted from the start of the range: t_lane + it * TILE + s * 16
+    const int t_lane = wave * (16 * NS) + tok, count = end - start;
 
     // codes of one tile and side -> registers (the lane's CB bytes of each of its NS tokens); tokens
     // past the end re-read the last valid token (their scores are masked)
     // (byte offsets of 32 bits: a range that did not fit them would be part of a cache of hundreds of gigabytes)
     const uint8_t *k_base = a.k_codes + (row0 + start) * P, *v_base = a.v_codes + (row0 + start) * P;
-    auto load_codes = [&](const uint8_t *codes, int it, int t0, int byte0, uint32_t (&buf)[NS][CW]) {
+    auto load_codes = [&](const uint8_t *codes, int it, uint32_t (&buf)[NS][CW]) {
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            const uint8_t *cp = codes + (uint32_t)min(t0 + it * TILE + s * 16, count - 1) * (uint32_t)P + (uint32_t)byte0;
+            const uint8_t *cp = codes + (uint32_t)min(t_lane + it * TILE + s * 16, count - 1) * (uint32_t)P + (uint32_t)(g * CB);
             if constexpr (CB == 4) {
                 buf[s][0] = *reinterpret_cast<const uint32_t *>(cp);
             } else if constexpr (CB == 8) {
@@ -247,27 +213,16 @@ __global__ __launch_bounds__(kAttnWaves * 64 * SEQ) __attribute__((amdgpu_waves_
     }
     // 2. codes of the first two tiles, and q as the A operands of the four MFMAs: channels
     //    32 g + 8 i .. + 7 (the same for every row of the operand)
-    const int t_v = TR ? t_wave + 4 * g + (tok >> 2) : t_lane, v_byte = TR ? (tok & 3) * CB : g * CB;
     uint32_t kA[NS][CW] = {}, vA[NS][CW] = {}, kB[NS][CW] = {}, vB[NS][CW] = {};
     half8_t qop[4] = {};
     if (active) {
-        load_codes(k_base, 0, t_lane, g * CB, kA);
-        load_codes(v_base, 0, t_v, v_byte, vA);
-        load_codes(k_base, 1, t_lane, g * CB, kB);
-        load_codes(v_base, 1, t_v, v_byte, vB);
+        load_codes(k_base, 0, kA);
+        load_codes(v_base, 0, vA);
+        load_codes(k_base, 1, kB);
+        load_codes(v_base, 1, vB);
 #pragma unroll
         for (int i = 0; i < 4; ++i) qop[i] = ld16(a.q + (size_t)bh * D + 32 * g + 8 * i).h8;
     }
-    // Infinities and NaN in the V codebooks, where V goes through the matrix cores, are staged as zeros (below) and
-    // added at the end.
-    bool nonfinite = false;
-    auto finite = [&](unsigned w) {
-        if (!TR) return w;
-        const bool lo = (w & 0x7C00u) == 0x7C00u, hi = (w & 0x7C000000u) == 0x7C000000u;
-        nonfinite = nonfinite || lo || hi;
-        return w & (lo ? 0xFFFF0000u : 0xFFFFFFFFu) & (hi ? 0x0000FFFFu : 0xFFFFFFFFu);
-    };
-    auto finite4 = [&](const uint4 &w) { return make_uint4(finite(w.x), finite(w.y), finite(w.z), finite(w.w)); };
     if constexpr (REP) {
         // 32 copies of every entry: consecutive lanes write consecutive 8-byte units (copy c = unit % 32 of entry
         // unit / 32); the 32 lanes of a copy set read one global address
@@ -284,31 +239,24 @@ __global__ __launch_bounds__(kAttnWaves * 64 * SEQ) __attribute__((amdgpu_waves_
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {   // (past the end of a smaller codebook: copies of its last entry, never read)
             reinterpret_cast<uint2 *>(smem)[tid + i * kStep] = ke[i];
-            reinterpret_cast<uint2 *>(smem + kAttnRepSide)[tid + i * kStep] = make_uint2(finite(ve[i].x), finite(ve[i].y));
+            reinterpret_cast<uint2 *>(smem + kAttnRepSide)[tid + i * kStep] = ve[i];
         }
     } else {
         if (tid < n16) {
             reinterpret_cast<uint4 *>(smem)[tid] = kst;
-            reinterpret_cast<uint4 *>(smem + v_off)[tid] = finite4(vst);
+            reinterpret_cast<uint4 *>(smem + v_off)[tid] = vst;
         }
         for (int i = tid + (int)blockDim.x; i < n16; i += (int)blockDim.x) {  // larger codebooks
             reinterpret_cast<uint4 *>(smem)[i] = ks[i];
-            reinterpret_cast<uint4 *>(smem + v_off)[i] = finite4(vs[i]);
+            reinterpret_cast<uint4 *>(smem + v_off)[i] = vs[i];
         }
-    }
-    // one flag per wavefront of the workgroup, in words of their own
-    unsigned *flags = reinterpret_cast<unsigned *>(smem + 2 * (size_t)v_off) + SEQ * (kAttnWaves * (D + 2));
-    if (TR) {
-        const unsigned any = __ballot(nonfinite) != 0;
-        if (lane == 0) flags[wid] = any;
     }
     __syncthreads();
     unsigned sh = SH;
     asm("" : "+v"(sh));
-    // codebook of code position byte0 + c (byte0 a multiple of CB, c < CB, all powers of two: (byte0 + c) >> pg_shift is
-    // (byte0 >> pg_shift) + (c >> pg_shift)): a part of the lane's and one of the position's
-    const unsigned lane_k = ((unsigned)((g * CB) >> a.pg_shift) * a.E) << SH;
-    const unsigned lane_v = (unsigned)v_off + (((unsigned)(v_byte >> a.pg_shift) * a.E) << SH);
+    // codebook of code position g CB + c (c < CB, all powers of two: (g CB + c) >> pg_shift is (g CB >> pg_shift) +
+    // (c >> pg_shift)): a part of the lane's and one of the position's
+    const unsigned lane_k = ((unsigned)((g * CB) >> a.pg_shift) * a.E) << SH, lane_v = (unsigned)v_off + lane_k;
     auto c_off = [&](int c) {   // a scalar, kept out of sight so that the sums are not all held in registers
         unsigned o = ((unsigned)(c >> a.pg_shift) * a.E) << SH;
         asm volatile("" : "+s"(o));
@@ -336,207 +284,71 @@ __global__ __launch_bounds__(kAttnWaves * 64 * SEQ) __attribute__((amdgpu_waves_
         }
     };
 
-    // 8-byte reads of V entries, transposed over each group of 16 lanes (ds_read_b64_tr_b16): lane i of a group reads 4
-    // channels of token i / 4 and receives one channel, 4 (i / 4) + i % 4 of the 16 read, of the 4 tokens -- the
-    // reduction axis of p V side by side in a lane, as the matrix instruction wants it.  Unit u (32 tokens), operands
-    // 4 half .. 4 half + 3; a lane's 8 operands cover its 32 channels 4 at a time.
-    auto tr_gather = [&](const uint32_t (&codes)[NS][CW], int u, int half, V16 (&blk)[4]) {
-        if (!ONE) __builtin_amdgcn_sched_barrier(0);   // (addresses computed ahead of their group do not fit the registers)
-        typedef short raw_t __attribute__((ext_vector_type(4)));
+    float acc[32];  // channels 32 g .. 32 g + 31 of sum_t p_t V[t]
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int c = V == 4 ? 4 * half + q : 2 * half + q / 2;   // code of the lane
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const unsigned w = codes[(2 * u + t) % NS][(c / 4) % CW];
-                unsigned addr;
-                if constexpr (REP) {
-                    addr = __builtin_amdgcn_perm(w, rep_v, 0x0c020000u | ((4u + (unsigned)(c % 4)) << 8));
-                } else {
-                    addr = (c % 4) == 0 ? byte_shl<0>(w, sh) : (c % 4) == 1 ? byte_shl<1>(w, sh)
-                           : (c % 4) == 2 ? byte_shl<2>(w, sh) : byte_shl<3>(w, sh);
-                    addr += (ONE ? (unsigned)v_off : lane_v + c_off(c)) + (V == 8 ? 8u * (q & 1) : 0u);
-                }
-                union { raw_t r; uint32_t w[2]; } d;
-                d.r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) raw_t *)(uintptr_t)addr);
-                blk[q].w[2 * t] = d.w[0];
-                blk[q].w[2 * t + 1] = d.w[1];
-            }
-        }
-    };
-
+    for (int d = 0; d < 32; ++d) acc[d] = 0.f;
+    float lsum = 0.f;          // per lane (every token is counted by its four lanes)
     float m_run = -INFINITY;   // wave-uniform running maximum of the scores (log2 domain)
-    float lsum = 0.f;          // per lane
+
     V16 eb[2][4];  // entries of the group being used and of the one in flight
     gather(kA, 0, 0, eb[0]);  // (codes are zero when there is nothing to attend: entry 0, unused)
 
-    if constexpr (TR) {
-        // ---- V on the matrix cores.  The K operand comes first, so a score lands with token = accumulator row: lane
-        // (r, g) holds the scores of tokens 16 s + 4 g + 0..3 of every step s -- the 8 slots (s, i) of its part of the
-        // reduction axis in the second product.  Row r of that product's first operand carries slot r % 8 only: each
-        // lane forms one weight times 2^15, as an fp16 value (rows 0..7) or as what the fp16 value leaves of the fp32
-        // one, times 2^12 (rows 8..15); the 16 rows are added at the very end.  A weight (1 at most) so keeps 23 bits, the
-        // precision of its exponential, down to 2^-29, and is off by 2^-52 at most below that; both sums, p V and that of
-        // the weights, take the same value.  (With weights up to 1 and 2^11 those below 2^-36 were zero in p V alone: 31
-        // tokens of 2^-38 and V = 60000 beside one of weight 1 gave 0 where 7e-6 is right.)  The 7 zeros of a row meet
-        // other tokens' values, which is why V is staged without infinities.
-        constexpr int NU = NS / 2 > 0 ? NS / 2 : 1;   // units of 32 tokens per tile
-        constexpr float kWeightUp = 32768.f, kRestUp = 4096.f;
-        const int slot = tok & 7;
-        const bool lo_row = tok >= 8;
-        const unsigned half_shift = 16u * (slot & 1);
-        unsigned keep[4];
+    // kn: K codes of the following tile (the other register buffer)
+    auto tile_step = [&](int it, uint32_t (&kc)[NS][CW], uint32_t (&vc)[NS][CW], const uint32_t (&kn)[NS][CW]) {
+        // scores.  Masked tokens get -inf through an additive bias (a select on the finished score
+        // would make the compiler branch around the arithmetic and move the gathers).
+        float sc[NS];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) keep[j] = (slot >> 1) == j ? 0xFFFFFFFFu : 0u;
-        const int t_slot = t_wave + 16 * (slot >> 2) + 4 * g + (slot & 3);
-        float4_t acc[8];   // channel block q of the lane's column, rows 4 g .. 4 g + 3
+        for (int s = 0; s < NS; ++s) {
+            if (s + 1 < NS)
+                gather(kc, s + 1, 0, eb[(s + 1) & 1]);
+            else
+                gather(vc, 0, v_off, eb[NS & 1]);
+            if (NS == 1 || s + 2 == NS) load_codes(k_base, it + 2, kc);  // the K codes of this tile are used up
+            float4_t c4 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int q = 0; q < 8; ++q) acc[q] = float4_t{0.f, 0.f, 0.f, 0.f};
-
-        auto tile_step = [&](int it, uint32_t (&kc)[NS][CW], uint32_t (&vc)[NS][CW], const uint32_t (&kn)[NS][CW]) {
-            float sc[NU];
-            float4_t c4[2];
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                if (s + 1 < NS)
-                    gather(kc, s + 1, 0, eb[(s + 1) & 1]);
-                else
-                    tr_gather(vc, 0, 0, eb[NS & 1]);
-                if (s + 2 == NS) load_codes(k_base, it + 2, t_lane, g * CB, kc);  // the K codes of this tile are used up
-                c4[s & 1] = float4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int i = 0; i < 4; ++i) c4[s & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(eb[s & 1][i].h8, qop[i], c4[s & 1], 0, 0, 0);
-                if (s & 1) {
-                    const float x0 = (slot & 1) ? c4[0][1] : c4[0][0], x1 = (slot & 1) ? c4[0][3] : c4[0][2];
-                    const float y0 = (slot & 1) ? c4[1][1] : c4[1][0], y1 = (slot & 1) ? c4[1][3] : c4[1][2];
-                    const float x = (slot & 2) ? x1 : x0, y = (slot & 2) ? y1 : y0;
-                    const float bias = (t_slot + it * TILE + (s - 1) * 16 < count) ? 0.f : -INFINITY;
-                    sc[s / 2] = __builtin_fmaf((slot & 4) ? y : x, a.scale2, bias);
-                }
-            }
-            // online softmax: raise the wave's running maximum if needed (uniform branch)
-            float tmax = sc[0];
-#pragma unroll
-            for (int u = 1; u < NU; ++u) tmax = fmaxf(tmax, sc[u]);
-            tmax = wave_max_uniform(tmax);
-            if (tmax > m_run) {
-                const float f = __builtin_amdgcn_exp2f(m_run - tmax);  // 0 while nothing was accumulated
-#pragma unroll
-                for (int q = 0; q < 8; ++q) acc[q] *= f;
-                lsum *= f;
-                m_run = tmax;
-            }
-
-#pragma unroll
-            for (int u = 0; u < NU; ++u) {
-                const float p_t = (sc[u] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sc[u] - m_run)) * kWeightUp;
-                const half_t p_hi = (half_t)p_t;
-                const half_t part = lo_row ? (half_t)((p_t - (float)p_hi) * kRestUp) : p_hi;
-                lsum += (float)part;   // (the sum of the weights as they are used)
-                const unsigned bits = (unsigned)__builtin_bit_cast(unsigned short, part) << half_shift;
-                V16 pop;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) pop.w[j] = bits & keep[j];
-#pragma unroll
-                for (int hf = 0; hf < 2; ++hf) {
-                    const int n = NS + 2 * u + hf;   // group number: n & 1 is its register block
-                    if (hf == 0) {
-                        tr_gather(vc, u, 1, eb[(n + 1) & 1]);
-                        if (u + 1 == NU) load_codes(v_base, it + 2, t_v, v_byte, vc);   // (and so are the V codes)
-                    } else if (u + 1 < NU)
-                        tr_gather(vc, u + 1, 0, eb[(n + 1) & 1]);
-                    else
-                        gather(kn, 0, 0, eb[0]);   // first K group of the next tile (2 NS is even)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        acc[4 * hf + q] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pop.h8, eb[n & 1][q].h8, acc[4 * hf + q], 0, 0, 0);
-                }
-            }
-        };
-        for (int it = 0; it < ntiles; it += 2) {
-            tile_step(it, kA, vA, kB);
-            if (it + 1 < ntiles) tile_step(it + 1, kB, vB, kA);
+            for (int i = 0; i < 4; ++i) c4 = __builtin_amdgcn_mfma_f32_16x16x32_f16(qop[i], eb[s & 1][i].h8, c4, 0, 0, 0);
+            const float bias = (t_lane + it * TILE + s * 16 < count) ? 0.f : -INFINITY;
+            sc[s] = __builtin_fmaf(c4[0], a.scale2, bias);
         }
-        lsum = wave_sum(lsum * (lo_row ? 1.f / (kWeightUp * kRestUp) : 1.f / kWeightUp));
+        // online softmax: raise the wave's running maximum if needed (uniform branch)
+        float tmax = sc[0];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            float o = ((acc[q][0] + acc[q][1]) + (acc[q][2] + acc[q][3])) * (g < 2 ? 1.f / kWeightUp : 1.f / (kWeightUp * kRestUp));
-            o += __shfl_xor(o, 16, 64);
-            o += __shfl_xor(o, 32, 64);
-            // column tok of operand q: channel 4 (its code's position) + tok % 4 for v = 4
-            const int ch = V == 4 ? 4 * ((tok >> 2) * 8 + q) + (tok & 3) : 8 * ((tok >> 2) * 4 + q / 2) + 4 * (q & 1) + (tok & 3);
-            if ((q >> 1) == g) xw[wave * D + ch] = o;
-        }
-        unsigned any = 0;
+        for (int s = 1; s < NS; ++s) tmax = fmaxf(tmax, sc[s]);
+        tmax = wave_max_uniform(tmax);
+        if (tmax > m_run) {
+            const float f = __builtin_amdgcn_exp2f(m_run - tmax);  // 0 while nothing was accumulated
 #pragma unroll
-        for (int i = 0; i < kAttnWaves * SEQ; ++i) any |= flags[i];
-        if (__builtin_amdgcn_readfirstlane(any))
-            add_nonfinite<V>(k_base, v_base, reinterpret_cast<const half_t *>(ks), reinterpret_cast<const half_t *>(vs),
-                             a.q + (size_t)bh * D, a.E, a.pg_shift, a.scale2, t_wave, TILE, 16 * NS, count, m_run, lane, xw + wave * D);
-    } else {
-        // ---- V on the vector ALU
-        float acc[32];  // channels 32 g .. 32 g + 31 of sum_t p_t V[t]
-#pragma unroll
-        for (int d = 0; d < 32; ++d) acc[d] = 0.f;
-
-        // kn: K codes of the following tile (the other register buffer)
-        auto tile_step = [&](int it, uint32_t (&kc)[NS][CW], uint32_t (&vc)[NS][CW], const uint32_t (&kn)[NS][CW]) {
-            // scores.  Masked tokens get -inf through an additive bias (a select on the finished score
-            // would make the compiler branch around the arithmetic and move the gathers).
-            float sc[NS];
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                if (s + 1 < NS)
-                    gather(kc, s + 1, 0, eb[(s + 1) & 1]);
-                else
-                    gather(vc, 0, v_off, eb[NS & 1]);
-                if (NS == 1 || s + 2 == NS) load_codes(k_base, it + 2, t_lane, g * CB, kc);  // the K codes of this tile are used up
-                float4_t c4 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int i = 0; i < 4; ++i) c4 = __builtin_amdgcn_mfma_f32_16x16x32_f16(qop[i], eb[s & 1][i].h8, c4, 0, 0, 0);
-                const float bias = (t_lane + it * TILE + s * 16 < count) ? 0.f : -INFINITY;
-                sc[s] = __builtin_fmaf(c4[0], a.scale2, bias);
-            }
-            // online softmax: raise the wave's running maximum if needed (uniform branch)
-            float tmax = sc[0];
-#pragma unroll
-            for (int s = 1; s < NS; ++s) tmax = fmaxf(tmax, sc[s]);
-            tmax = wave_max_uniform(tmax);
-            if (tmax > m_run) {
-                const float f = __builtin_amdgcn_exp2f(m_run - tmax);  // 0 while nothing was accumulated
-#pragma unroll
-                for (int d = 0; d < 32; ++d) acc[d] *= f;
-                lsum *= f;
-                m_run = tmax;
-            }
-
-            // acc += p_t * V[t] on the lane's 32 channels
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                if (s + 1 < NS)
-                    gather(vc, s + 1, v_off, eb[(NS + s + 1) & 1]);
-                else
-                    gather(kn, 0, 0, eb[0]);  // first K group of the next tile (2 NS is even)
-                if (NS == 1 || s + 2 == NS) load_codes(v_base, it + 2, t_lane, g * CB, vc);
-                const float p_t = sc[s] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sc[s] - m_run);
-                lsum += p_t;
-                const V16 (&ev)[4] = eb[(NS + s) & 1];
-#pragma unroll
-                for (int d = 0; d < 32; ++d) acc[d] += p_t * (float)ev[d / 8].h8[d % 8];
-            }
-        };
-        for (int it = 0; it < ntiles; it += 2) {
-            tile_step(it, kA, vA, kB);
-            if (it + 1 < ntiles) tile_step(it + 1, kB, vB, kA);
+            for (int d = 0; d < 32; ++d) acc[d] *= f;
+            lsum *= f;
+            m_run = tmax;
         }
 
-        // reduce over the 16 token lanes
-        row_reduce_scatter(acc, lane);
-        lsum = wave_sum(lsum) * 0.25f;  // four lanes per token
-        xw[wave * D + 32 * g + 2 * tok] = acc[0];
-        xw[wave * D + 32 * g + 2 * tok + 1] = acc[1];
+        // acc += p_t * V[t] on the lane's 32 channels
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            if (s + 1 < NS)
+                gather(vc, s + 1, v_off, eb[(NS + s + 1) & 1]);
+            else
+                gather(kn, 0, 0, eb[0]);  // first K group of the next tile (2 NS is even)
+            if (NS == 1 || s + 2 == NS) load_codes(v_base, it + 2, vc);
+            const float p_t = sc[s] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sc[s] - m_run);
+            lsum += p_t;
+            const V16 (&ev)[4] = eb[(NS + s) & 1];
+#pragma unroll
+            for (int d = 0; d < 32; ++d) acc[d] += p_t * (float)ev[d / 8].h8[d % 8];
+        }
+    };
+    for (int it = 0; it < ntiles; it += 2) {
+        tile_step(it, kA, vA, kB);
+        if (it + 1 < ntiles) tile_step(it + 1, kB, vB, kA);
     }
-    // ---- then over the wavefronts (fixed order)
+
+    // ---- reduce over the 16 token lanes, then over the wavefronts (fixed order) -------------
+    row_reduce_scatter(acc, lane);
+    lsum = wave_sum(lsum) * 0.25f;  // four lanes per token
+    xw[wave * D + 32 * g + 2 * tok] = acc[0];
+    xw[wave * D + 32 * g + 2 * tok + 1] = acc[1];
     if (lane == 0) {
         xw_m[wave] = m_run;
         xw_l[wave] = lsum;
@@ -635,7 +447,7 @@ size_t attn_decode_workspace(const vq_kv_t *kv) {
 template <int V, bool ONE, int SEQ, bool REP = false>
 static int run_attn_seq(const AttnArgs &a, hipStream_t s) {
     const size_t side = REP ? (size_t)kAttnRepSide : ONE ? 4096 : (size_t)a.G * a.E * V * sizeof(half_t);  // matches the kernel's layout
-    size_t lds = 2 * side + (size_t)SEQ * kAttnWaves * (128 + 2 + 1) * sizeof(float);   // (the last word: a flag)
+    size_t lds = 2 * side + (size_t)SEQ * kAttnWaves * (128 + 2) * sizeof(float);
     // the kernel forms absolute LDS addresses: refused here, with an error, if it ever had static LDS
     static KernelSetup setup;
     if (int st = kernel_setup(reinterpret_cast<const void *>(&attn_decode_kernel<V, ONE, SEQ, REP>), lds, true, setup)) return st;

@@ -253,8 +253,9 @@ __global__ __launch_bounds__(256) void gemm_dense_kernel(DenseArgs a) {
     }
 }
 
-// Rounds of workgroups over 256 CUs, in units of a round of 256 x 128 tiles; *small: with 128 x 128 tiles, whose round takes
-// about 0.7 of that.  A product of few tiles leaves CUs idle: M = 512, N = K = 4096 has 64 of the large ones (46.5 us) or 128
+// Rounds of workgroups over 256 CUs, in units of a round of 256 x 128 tiles; *small: with 128 x 128 tiles, whose round is
+// counted as 0.75 of that (over 288 products, N 64 .. 11008, 257 .. 4096 tokens, K 512 and 4096, any value from 0.7 to 0.8 takes
+// 0.03 % more than the better tile; 0.65 up to 9 % more).  A product of few tiles leaves CUs idle: M = 512, N = K = 4096 has 64 of the large ones (46.5 us) or 128
 // of the small (31.9); 600 x 11008 258 (two rounds, 102.9 us) or 430 (two rounds, 69.5); 1024 x 4096 52.4 / 39.7.  With as many
 // large rounds as would be full the large tile is ahead (2048 x 4096 68.6 / 81.4, 512 x 11008 55.0 / 66.7).
 double gemm_dense_rounds(int M, int N, bool *small) {
