@@ -140,7 +140,6 @@ __device__ __forceinline__ unsigned byte_shl(unsigned w, unsigned sh) {
 // permute: (code << 8) | lane constant, the V side's constant carrying its base of 64 KiB.
 constexpr int kAttnRepCopies = 32;
 constexpr int kAttnRepSide = 65536;   // bytes per side: 256 entries x 32 copies x 8 bytes
-constexpr int kAttnRepMinWgs = 192;   // fewer workgroups than this: two small workgroups per CU (shared copy) fill the chip better
 
 template <int V, bool ONE, int SEQ, bool REP = false>
 __global__ __launch_bounds__(kAttnWaves * 64 * SEQ) __attribute__((amdgpu_waves_per_eu(4, 4))) void attn_decode_kernel(AttnArgs a) {
@@ -457,16 +456,28 @@ static int run_attn_seq(const AttnArgs &a, hipStream_t s) {
     return launch_status();
 }
 
+// Replicated codebooks: no bank conflicts, but 128 KiB to fill and only one workgroup (two items) per CU.  Worth it for long
+// ranges in whole rounds of workgroups, and where a shared copy has conflicts (many entries).  H = 32 unless said, 256 entries,
+// us, shared copy / copies: 16 x 4096 tokens 31.6 / 30.1, 16 x 8192 56.6 / 54.1, 8 x 16000 58.2 / 55.1; B32 H8 8192 34.6 / 33.4; but 16 x
+// 3001 26.4 / 26.6, 16 x 300 8.3 / 10.2, 32 x 64 10.6 / 16.0, 5 x 16000 (320 workgroups) 46.2 / 58.7, 3 x 4096 17.6 / 24.0; 64 entries, 16 x
+// 4096 29.5 / 29.8.  (S, tc: attn_split)
+static bool attn_copies(const vq_kv_t *kv, int S, int tc) {
+    const long long items = (long long)kv->B * S, wgs = (items + 1) / 2 * kv->H, rounds = (wgs + 255) / 256;
+    return kv->cb_groups == 1 && kv->v == 4 && kv->n_entries > 128 && tc >= 4096 && items >= 2 && 20 * wgs >= 19 * 256 * rounds;
+}
+
+bool attn_replicated(const vq_kv_t *kv) {
+    int S, tc, seq;
+    attn_split(kv, &S, &tc, &seq);
+    return attn_copies(kv, S, tc);
+}
+
 template <int V, bool ONE>
-static int run_attn(const AttnArgs &a, int seq, hipStream_t s) {
+static int run_attn(const AttnArgs &a, int seq, bool copies, hipStream_t s) {
     if constexpr (!ONE)
         if (seq == 2) return run_attn_seq<V, false, 2>(a, s);
-    if constexpr (ONE && V == 4) {
-        // replicated codebooks (no bank conflicts) where pairs of sequences give every compute unit a workgroup:
-        // 128 KiB of LDS per workgroup, so exactly one fits
-        const long long wgs = (long long)((a.B + 1) / 2) * a.H * a.S;
-        if (a.B >= 2 && a.E * kAttnRepCopies * 8 <= kAttnRepSide && wgs >= kAttnRepMinWgs) return run_attn_seq<4, true, 2, true>(a, s);
-    }
+    if constexpr (ONE && V == 4)
+        if (copies) return run_attn_seq<4, true, 2, true>(a, s);
     return run_attn_seq<V, ONE, 1>(a, s);
 }
 
@@ -496,10 +507,10 @@ int launch_attn_decode(const vq_kv_t *kv, const void *q, float sm_scale, void *o
         if ((1 << sh) != pg) return VQ_ERR_UNSUPPORTED;
         a.pg_shift = sh;
     }
-    const bool one = kv->cb_groups == 1;
-    if (kv->v == 8) return one ? run_attn<8, true>(a, seq, s) : run_attn<8, false>(a, seq, s);
-    if (kv->v == 4) return one ? run_attn<4, true>(a, seq, s) : run_attn<4, false>(a, seq, s);
-    return one ? run_attn<2, true>(a, seq, s) : run_attn<2, false>(a, seq, s);
+    const bool one = kv->cb_groups == 1, copies = attn_copies(kv, a.S, a.tc);
+    if (kv->v == 8) return one ? run_attn<8, true>(a, seq, copies, s) : run_attn<8, false>(a, seq, copies, s);
+    if (kv->v == 4) return one ? run_attn<4, true>(a, seq, copies, s) : run_attn<4, false>(a, seq, copies, s);
+    return one ? run_attn<2, true>(a, seq, copies, s) : run_attn<2, false>(a, seq, copies, s);
 }
 
 }  // namespace vq

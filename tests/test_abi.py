@@ -528,3 +528,14 @@ def test_staging_of_large_codebooks_counts_in_the_choice_of_the_product():
     one_pass = lambda M, **kw: internal("_ZN2vq13gemm_one_passEPK11vq_weight_ti", ctypes.byref(weight(**kw)), M)  # noqa: E731
     big = dict(code_bits=12, n_codebooks=2, n_entries=4096)      # 128 KiB of codebooks to stage in every workgroup
     assert one_pass(1024, N=1000, K=512, n_codebooks=2) and not one_pass(1024, N=1000, K=512, **big) and one_pass(257, N=1000, K=512, **big)
+
+
+@pytest.mark.parametrize("kw,copies", [
+    (dict(B=16, H=32, T=4096), True), (dict(B=8, H=32, T=8192), True), (dict(B=33, H=30, T=4096), True),   # whole rounds of long ranges
+    (dict(B=3, H=32, T=1500), False),        # 160 workgroups (pairs of batch entries would be 192)
+    (dict(B=5, H=32, T=16000), False),       # a round of 256 workgroups and one of 64
+    (dict(B=32, H=32, T=64), False), (dict(B=16, H=32, T=3001), False),          # more to stage than to attend
+    (dict(B=16, H=32, T=4096, n_entries=64), False), (dict(B=16, H=32, T=4096, cb_groups=32), False), (dict(B=16, H=32, T=4096, v=8), False),
+])
+def test_attn_copies_of_a_codebook_are_for_long_ranges_in_whole_rounds(kw, copies):
+    assert internal("_ZN2vq15attn_replicatedEPK7vq_kv_t", ctypes.byref(kvdesc(**kw))) == copies

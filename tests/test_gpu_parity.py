@@ -4,6 +4,8 @@ on the same seeded inputs.
 Bars: dequantized tiles bit-exact; products and attention within relative L2 <= 2e-3 and
 max-abs <= 1e-2 * RMS(oracle output) of the un-rounded fp64 oracle.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -1016,6 +1018,20 @@ def test_attn_replicated_codebooks(gpu_device, B, H, T, E, lens):
     assert torch.equal(out, run_attn(kv, gpu_device, sm))
     if lens is not None and 0 in lens:
         assert (out[lens.index(0)] == 0).all()
+
+
+# Shapes at which the copies are used: one and two ranges per sequence, an odd number of items; most sequences short or empty
+@pytest.mark.parametrize("B,H,T,lens", [(16, 32, 4096, [4096, 0, 1, 33, 300, 31]), (8, 32, 8192, [5000, 0, 4097, 70]), (33, 30, 4096, [1500, 64, 0, 7])])
+def test_attn_replicated_codebooks_of_long_ranges(gpu_device, B, H, T, lens):
+    kv = wl.make_kv(B, H, 128, T, 4, 250, 1, seed=7150 + B)
+    kv.seq_lens = np.array([lens[b] if b < len(lens) else 0 for b in range(B - 1)] + [200], dtype=np.int32)
+    kd = vq.kv_to_device(kv, gpu_device)
+    assert vq.lib()._ZN2vq15attn_replicatedEPK7vq_kv_t(ctypes.byref(kd.desc())) & 0xFF
+    sm = 1.0 / np.sqrt(128.0)
+    out = vq.vq_attn_decode(kd, dev_x(kv.q, gpu_device), sm)
+    torch.cuda.synchronize()
+    assert_close(out, oracle_attn(kv, sm), f"attn replicated B{B} H{H} T{T}")
+    assert (out[1 if lens[1] == 0 else 2] == 0).all()
 
 
 def test_attn_zero_length_sequence_and_sharp_softmax(gpu_device):
