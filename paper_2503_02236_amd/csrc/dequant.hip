@@ -1,6 +1,8 @@
 // Test-hook kernels: the dequantized operand itself (VQ-LLM Sec. II-A, dequantization:
 // look up one entry per residual codebook, add them element-wise, concatenate sub-vectors),
 // plus two streaming probes used to calibrate bandwidth measurements.
+#include <type_traits>
+
 #include "vq_common.h"
 
 namespace vq {
@@ -100,15 +102,25 @@ __global__ __launch_bounds__(256) void dequant_half_kernel(const void *__restric
 template <typename CodeT, int V>
 static void run_dequant_half(const vq_weight_t *w, half_t *W, long n_vec, hipStream_t s) {
     const long blocks = (n_vec + 256 * kDequantUnroll - 1) / (256 * kDequantUnroll);
-    if (w->n_codebooks == 1)
-        dequant_half_kernel<CodeT, V, 1><<<(int)blocks, 256, 0, s>>>(w->codes, (const half_t *)w->codebooks, W, n_vec, w->n_entries);
-    else
+    if (w->n_codebooks == 1) {
+        if constexpr (!std::is_same<CodeT, Code12>::value || V == 4)   // (dequant_in_eights)
+            dequant_half_kernel<CodeT, V, 1><<<(int)blocks, 256, 0, s>>>(w->codes, (const half_t *)w->codebooks, W, n_vec, w->n_entries);
+    } else {
         dequant_half_kernel<CodeT, V, 2><<<(int)blocks, 256, 0, s>>>(w->codes, (const half_t *)w->codebooks, W, n_vec, w->n_entries);
+    }
+}
+
+// Where the kernel above runs.  Not for one 12-bit codebook of 8-vectors, the one format that it slows down (N = K = 4096, plain
+// kernel / eights: 11.9 / 14.1 us, N = 11008 27.3 / 28.3; two codebooks 18.0 / 16.9, 4-vectors 16.2 / 15.2; why was not established).
+bool dequant_in_eights(const vq_weight_t *w) {
+    const long n_vec = (long)w->N * (w->K / w->v);
+    return w->cb_tile_n == 0 && w->n_codebooks <= 2 && !(w->code_bits == 12 && w->v == 8 && w->n_codebooks == 1) &&
+           n_vec >= 512L * 256 * kDequantUnroll && n_vec < (1L << 40);
 }
 
 int launch_dequant(const vq_weight_t *w, void *W, int out_fp32, hipStream_t s) {
     long n_vec = (long)w->N * (w->K / w->v);
-    if (!out_fp32 && w->cb_tile_n == 0 && w->n_codebooks <= 2 && n_vec >= 512L * 256 * kDequantUnroll && n_vec < (1L << 40)) {
+    if (!out_fp32 && dequant_in_eights(w)) {
         half_t *o = (half_t *)W;
         if (w->code_bits == 8) w->v == 8 ? run_dequant_half<uint8_t, 8>(w, o, n_vec, s) : run_dequant_half<uint8_t, 4>(w, o, n_vec, s);
         else if (w->code_bits == 12) w->v == 8 ? run_dequant_half<Code12, 8>(w, o, n_vec, s) : run_dequant_half<Code12, 4>(w, o, n_vec, s);

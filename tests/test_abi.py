@@ -539,3 +539,9 @@ def test_staging_of_large_codebooks_counts_in_the_choice_of_the_product():
 ])
 def test_attn_copies_of_a_codebook_are_for_long_ranges_in_whole_rounds(kw, copies):
     assert internal("_ZN2vq15attn_replicatedEPK7vq_kv_t", ctypes.byref(kvdesc(**kw))) == copies
+
+
+def test_dequantization_in_eights_is_for_the_formats_it_is_faster_for():
+    eights = lambda **kw: internal("_ZN2vq17dequant_in_eightsEPK11vq_weight_t", ctypes.byref(weight(**{**dict(N=4096, K=4096), **kw})))  # noqa: E731
+    assert eights() and eights(code_bits=16, n_entries=65536) and eights(code_bits=12, n_codebooks=2) and eights(code_bits=12, v=4)
+    assert not eights(code_bits=12) and not eights(N=300, K=1024) and not eights(n_codebooks=3)
