@@ -427,10 +427,12 @@ struct GemvLutList {
 //   memory latency after the previous slice's) or kLutStepUs per step, whichever is more.
 //   gemv_replica.hip: a group of workgroups takes its problems one after the other, kRepProblemUs for each and kRepItemUs
 //   per item (512 positions of a row) of a wavefront.
-// Decoder blocks of Llama-7B shape, two codebooks, this kernel against that one, us: 1 block 55 / 25, 2 57 / 54, 4 68 / 93,
-// 8 98 / 148, 32 290 / 481; half the width: 1 block 31 / 17, 4 33 / 44, 32 107 / 221; one codebook: 4 blocks 55 / 60, 32
-// 194 / 303; an eighth of the width, two codebooks: 16 blocks 11 / 43.  A list that is short both ways (kLutMinBytes of
-// codes, kLutMinProblems) stays with that kernel, whose bits do not depend on the list.
+// Decoder blocks of Llama-7B shape, this kernel against that one, us: two codebooks, 1 block 55 / 26, 2 57 / 50, 4 66 / 84, 8 86 / 136,
+// 32 278 / 475; half the width 1 block 31 / 16, 4 33 / 41, 32 89 / 205; an eighth 16 blocks 11 / 42.  One codebook, 3 blocks 48 / 58, 4
+// 55 / 57, 8 70 / 81, 12 109 / 134, 32 186 / 291; half the width 3 blocks 26 / 30, 8 34 / 41, 32 69 / 136; a quarter 8 blocks 16 / 26; an
+// eighth 11 / 18.  The estimates are good to a few per cent, and this kernel must be ahead by more (few rows and a long K: 100 x
+// 512 x 12288, two codebooks, 68 / 64, 48 x 1024 x 11008 68 / 54): over 184 lists none that takes it is slower for it.  A list that is
+// short both ways (kLutMinBytes of codes, kLutMinProblems) stays with that kernel, whose bits do not depend on the list.
 constexpr double kLutMinBytes = 16 << 20, kLutStartUs = 6, kLutSegmentUs = 2, kLutSliceUs[2] = {3.9, 2.3}, kLutStepUs = 0.6;
 constexpr int kLutMinProblems = 48;
 constexpr double kRepStartUs = 4, kRepProblemUs = 3.5, kRepItemUs[2] = {0.6, 1.0};
@@ -459,7 +461,7 @@ bool gemv_lut_worth(const vq_gemv_call_t *calls, int n_calls) {
             t += kRepProblemUs + kRepItemUs[R - 1] * ((w[k]->N * groups + 255) / 256) * ((w[k]->K + 4095) / 4096) / 16;
         there = std::max(there, t);
     }
-    return here < there;
+    return here < 0.95 * there;
 }
 
 // Segments: at most one more per workgroup than the problems need by themselves.

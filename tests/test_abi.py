@@ -545,3 +545,16 @@ def test_dequantization_in_eights_is_for_the_formats_it_is_faster_for():
     eights = lambda **kw: internal("_ZN2vq17dequant_in_eightsEPK11vq_weight_t", ctypes.byref(weight(**{**dict(N=4096, K=4096), **kw})))  # noqa: E731
     assert eights() and eights(code_bits=16, n_entries=65536) and eights(code_bits=12, n_codebooks=2) and eights(code_bits=12, v=4)
     assert not eights(code_bits=12) and not eights(N=300, K=1024) and not eights(n_codebooks=3)
+
+
+@pytest.mark.parametrize("n,N,K,R,table", [(100, 512, 12288, 2, False), (48, 1024, 11008, 2, False), (48, 4096, 4096, 2, True),
+                                           (48, 4096, 4096, 1, True), (48, 16000, 512, 1, True), (3, 1000, 1088, 2, False)])
+def test_lists_take_the_table_kernel_where_it_is_ahead(n, N, K, R, table):
+    """Measured: few rows of a long K are not faster from a table of products, which is formed anew for every slice of K."""
+    from paper_2503_02236_amd.binding import vq_gemv_call_t
+    w = weight(N=N, K=K, n_codebooks=R)
+    ptr, xy = (ctypes.POINTER(vq_weight_t) * 1)(ctypes.pointer(w)), (ctypes.c_void_p * 1)(P)
+    calls = (vq_gemv_call_t * n)()
+    for c in calls:
+        c.w, c.x, c.y, c.count = ctypes.cast(ptr, type(c.w)), ctypes.cast(xy, type(c.x)), ctypes.cast(xy, type(c.y)), 1
+    assert internal("_ZN2vq14gemv_lut_worthEPK14vq_gemv_call_ti", calls, n) == table
