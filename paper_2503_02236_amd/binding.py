@@ -130,9 +130,16 @@ def status_str(status: int) -> str:
     return lib().vq_status_str(int(status)).decode()
 
 
-def _stream() -> int:
-    """The current HIP stream of the current device, without building a stream object (1 us of a 10 us call)."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+def _stream_getter(torch_c):
+    """A function that returns the current HIP stream of the current device: without building a stream object (1 us of a
+    10 us call) where torch has the calls for that, which are not part of its documented interface."""
+    raw, device = getattr(torch_c, "_cuda_getCurrentRawStream", None), getattr(torch_c, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        return lambda: int(torch.cuda.current_stream().cuda_stream)
+    return lambda: raw(device())
+
+
+_stream = _stream_getter(torch._C)
 
 
 def _dev(t: Optional[torch.Tensor], name: str, dtype=None) -> Optional[int]:

@@ -558,3 +558,12 @@ def test_lists_take_the_table_kernel_where_it_is_ahead(n, N, K, R, table):
     for c in calls:
         c.w, c.x, c.y, c.count = ctypes.cast(ptr, type(c.w)), ctypes.cast(xy, type(c.x)), ctypes.cast(xy, type(c.y)), 1
     assert internal("_ZN2vq14gemv_lut_worthEPK14vq_gemv_call_ti", calls, n) == table
+
+
+def test_binding_finds_the_stream_without_the_undocumented_calls_of_torch(monkeypatch):
+    from types import SimpleNamespace as obj
+    from paper_2503_02236_amd import binding
+    monkeypatch.setattr(binding.torch.cuda, "current_stream", lambda: obj(cuda_stream=77))
+    assert binding._stream_getter(obj())() == 77
+    assert binding._stream_getter(obj(_cuda_getDevice=lambda: 3))() == 77
+    assert binding._stream_getter(obj(_cuda_getDevice=lambda: 3, _cuda_getCurrentRawStream=lambda device: 100 + device))() == 103
