@@ -944,9 +944,9 @@ def test_attn_small_full_compare(gpu_device, B, H, T, v, G, ragged):
     assert_close(run_attn(kv, gpu_device, sm), oracle_attn(kv, sm), f"attn B{B} H{H} T{T} v{v} G{G}")
 
 
-# Two items per workgroup, v = 4: one codebook per head with copies in LDS, and 32 codebooks; odd numbers of items and of token
+# v = 4: one codebook per head, and 32 codebooks with one (T 1500) and two items per workgroup; odd numbers of items and of token
 # ranges, one and two tokens past a 32-token unit, flat and sharp softmax (weights from 1 down to far below the smallest
-# half: on the matrix cores such weights would be lost), and a V codebook with an infinity and a NaN that some tokens use.
+# half), and a V codebook with an infinity that one token uses and a NaN that none does.
 @pytest.mark.parametrize("sharp", [1.0, 6.0])
 @pytest.mark.parametrize("B,H,T,G", [(13, 32, 33, 1), (16, 24, 290, 1), (3, 32, 1500, 32), (9, 32, 97, 32), (3, 32, 2050, 32)])
 def test_attn_matrix_core_values(gpu_device, B, H, T, G, sharp):
@@ -956,7 +956,7 @@ def test_attn_matrix_core_values(gpu_device, B, H, T, G, sharp):
     assert_close(run_attn(kv, gpu_device, sm), oracle_attn(kv, sm), f"attn B{B} H{H} T{T} G{G} x{sharp}")
 
 
-@pytest.mark.parametrize("B,H,T,G", [(16, 24, 290, 1), (3, 32, 1500, 32)])
+@pytest.mark.parametrize("B,H,T,G", [(16, 24, 290, 1), (3, 32, 1500, 32), (3, 32, 2050, 32), (16, 32, 4096, 1)])
 def test_attn_matrix_core_values_with_infinities(gpu_device, B, H, T, G):
     kv = wl.make_kv(B, H, 128, T, 4, 256, G, seed=5350 + T)
     kv.v_codes[kv.v_codes == 7] = 8
@@ -1007,8 +1007,8 @@ def test_attn_two_sequences_per_workgroup_odd_batch_and_empty_sequences(gpu_devi
     (2, 256, 77, 200, [77, 5]),              # fewer entries than 256, a single ragged tile
 ])
 def test_attn_replicated_codebooks(gpu_device, B, H, T, E, lens):
-    """One codebook per head and side, enough (head, sequence pair) workgroups for one per compute unit: the
-    kernel with 32 copies of every entry in LDS (no bank conflicts), two sequences per workgroup."""
+    """One codebook per head and side and enough workgroups for one per compute unit, but ranges too short for copies of the
+    codebook in LDS (those: the test below)."""
     kv = wl.make_kv(B, H, 128, T, 4, E, 1, seed=5300 + B + H)
     if lens is not None:
         kv.seq_lens = np.array(lens, dtype=np.int32)
