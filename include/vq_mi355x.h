@@ -307,9 +307,9 @@ void vq_gemv_pipeline_destroy(vq_gemv_pipeline_t *p);
  * dequantized tile fed to the fp16 matrix cores, fp32 accumulation.
  *   Y[m][n] = scale[n] * sum_k W[n][k] * X[m][k],   m < M
  * X: device fp16 [M][K]; Y: device fp16 [M][N]; M >= 1.
- * ws: vq_gemm_workspace(w, M) bytes.  For M > 256 that is N*K*2: the weight is dequantized once per
+ * ws: vq_gemm_workspace(w, M) bytes.  For M > 256 and K % 64 == 0 that is N*K*2: the weight is dequantized once per
  * call into ws (fp16, the same bits vq_dequant returns) and multiplied by a dense matrix-core kernel;
- * for smaller M the dequantization is fused into the matrix-core loop and no workspace is needed
+ * otherwise the dequantization is fused into the matrix-core loop and no workspace is needed
  * (a small product of more than 256 tokens may leave ws unused).
  */
 int vq_gemm(const vq_weight_t *w, const void *X, int M, void *Y,

@@ -97,7 +97,7 @@ __device__ __forceinline__ int kvq_wave_argmin(float d, int e) {
 // group's codebook in registers (entry lane + 64 k, straight from memory: nothing is staged, so a codebook that serves a
 // single sub-vector -- coupled quantization -- is read once and used once) and the sub-vectors come one after the other.
 // Bound: the latency of two dependent loads and, per sub-vector, four distances and one reduction over the lanes.  One
-// token of B3 H32 with 32 codebooks per head and side: 5.8 us, where staging both sides' codebooks in LDS took 14.7.
+// token of B3 H32 with 32 codebooks per head and side: 5.3 us, where staging both sides' codebooks in LDS took 14.7.
 template <int V>
 __global__ __launch_bounds__(512) void kv_quantize_scan_kernel(KvQuantArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, NW = blockDim.x >> 6;
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(256) void kv_quantize_lane_kernel(KvQuantArgs a) {
 //   own rounding, (V + 2) 2^-24 of d / 2, below 2^-20.6.  Two distances are ordered as their s are when these lie more than
 //   2^-16.4 apart: 2^-16 is used.  (The split is that good while |c|max^2 lies in [kQuantMinC2, kQuantMaxC2]; outside, every
 //   item is scanned.  The matrix cores of this chip take subnormal halves as they are.)
-// Bound: vector issue, about 230 instructions per 32 items and wavefront (112 for minima, 60 for the exact distances)
+// Bound: vector issue, 251 instructions per 32 items and wavefront as counted (112 for minima, 60 for the exact distances)
 // against 8 matrix instructions.  B2 H32, 2048 tokens, one codebook per head and side (4.2 M items per side): 112 us back to back,
 // where a scan of every pair took 546; 32 codebooks of v = 4: 163, 64 of v = 2: 324.
 constexpr int kQuantMfmaTokens = 128;        // tokens per workgroup
