@@ -25,11 +25,12 @@ import subprocess
 
 
 def _short(name: str) -> str:
+    name = name.replace("DF16_", "Dh")        # _Float16, which older demanglers do not know, as the half type they do
     try:
         name = subprocess.run(["c++filt", name], capture_output=True, text=True).stdout.strip() or name
     except OSError:
         pass
-    return name.split("(")[0][-90:]
+    return name.replace("(anonymous namespace)::", "").split("(")[0].strip()[-90:]
 
 
 def stats(args):
