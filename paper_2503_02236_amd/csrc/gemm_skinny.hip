@@ -381,7 +381,7 @@ __global__ __launch_bounds__(64 * skinny_max_waves(L2CB, RT, CT)) void gemm_skin
     }
 }
 
-// Elements of X of one launch: its kernel holds byte offsets into X in 32 bits.  At least 512 tokens (K <= 2^22), whole
+// Elements of X of one launch: its kernel holds byte offsets into X in 32 bits.  At least 384 tokens (K <= 2^22), whole
 // tiles of every kind.
 constexpr long kSkinnyMaxX = 1L << 31;
 int skinny_max_tokens(int K) { return (int)std::min(1L << 30, (kSkinnyMaxX - 1) / K / 128 * 128); }
