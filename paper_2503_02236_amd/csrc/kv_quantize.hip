@@ -218,18 +218,21 @@ __global__ __launch_bounds__(256) void kv_quantize_lane_kernel(KvQuantArgs a) {
 //   fp32.  E = 256 entries are 8 of these.
 //   s is not the definition's distance bit for bit, so it only narrows the search: a lane keeps the minimum of each group
 //   of eight entries (the group's number in the four low mantissa bits), the best group and the value of the second best.
-//   If the second best is further away than the error of s can bridge, the definition's winner is in the best group: the
-//   two lanes of the item compute its eight distances as the definition says, four each, and take the smaller (smaller
-//   index on a tie).  Otherwise -- a near tie between groups, or anything not finite, for which the comparison is
+//   If the second best is further away than the error of s can bridge, the definition's winner is in the best group, and
+//   that is looked at once more: by s in fp32 from |c|^2 / 2, which is enough unless two entries of the group are too close in
+//   their turn, or by the definition's distances (smaller index on a tie).  Otherwise -- a near tie between groups, or anything not finite, for which the comparison is
 //   false -- the whole codebook is scanned as the definition says.  So the codes are those of the definition, always.
 //   Error bound, in units of |x|^2 + |c|max^2, which bounds every |s|, term and partial sum: 17 products and sums to 2^-23
 //   each, 15 ulp of the packed bits 2^-19.1, h itself (V + 2) 2^-24 and its split 2^-22: below 2^-17.7; the definition's
 //   own rounding, (V + 2) 2^-24 of d / 2, below 2^-20.6.  Two distances are ordered as their s are when these lie more than
 //   2^-16.4 apart: 2^-16 is used.  (The split is that good while |c|max^2 lies in [kQuantMinC2, kQuantMaxC2]; outside, every
 //   item is scanned.  The matrix cores of this chip take subnormal halves as they are.)
-// Bound: vector issue, 251 instructions per 32 items and wavefront as counted (112 for minima, 60 for the exact distances)
-// against 8 matrix instructions.  B2 H32, 2048 tokens, one codebook per head and side (4.2 M items per side): 112 us back to back,
-// where a scan of every pair took 546; 32 codebooks of v = 4: 163, 64 of v = 2: 324.
+//   (That s: V + 1 roundings to 2^-24 and 15 ulp of packed bits, below 2^-18.4.)
+// Bound: vector issue, about 320 instructions per 64 items and wavefront (208 for minima, 32 + 20 for the group) against 16 matrix
+// instructions.  An iteration covers 64 items, so that loads, addresses, norms, the group and the store serve a whole wavefront (the
+// minima lie in two lanes per item, and one lane swap brings them to the item's own lane); with 32 items, two lanes each, and the
+// group by the definition it was 251 per 32.  B2 H32, 2048 tokens, one codebook per head and side (4.2 M items per side): 112 us with
+// 32 items, 92 now, where a scan of every pair took 546.
 constexpr int kQuantMfmaTokens = 128;        // tokens per workgroup
 // i / PG for the items of a workgroup (i < 128 PG, PG <= 128) by a 24-bit product and a shift: with m = ceil(2^21 / PG) the
 // excess i (m PG - 2^21) stays below 2^14 * 2^7 = 2^21, and the product below 2^29.
@@ -242,38 +245,33 @@ constexpr bool kvq_quotient_exact() {
     return true;
 }
 static_assert(kQuantMfmaTokens <= 128 && kvq_quotient_exact(), "");
+constexpr float kQuantBound = 1.52587890625e-5f;           // 2^-16
 constexpr float kQuantMinC2 = 1e-6f, kQuantMaxC2 = 1e9f;   // (the largest h that 2^15 of headroom takes is 2^30)
 
 // min(a, b) as the median with a minus infinity that the compiler does not see through: one instruction (fminf first
 // quiets operands that come straight from a matrix instruction, two more)
 __device__ __forceinline__ float min2f(float a, float b, float ninf) { return __builtin_amdgcn_fmed3f(a, b, ninf); }
 
-// {the lower half's value in every lane, the upper half's value in every lane}
-__device__ __forceinline__ void both_halves(unsigned v, unsigned &lower, unsigned &upper) {
-    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    lower = r[0];
-    upper = r[1];
-}
-__device__ __forceinline__ void both_halves(float v, float &lower, float &upper) {
-    unsigned l, u;
-    both_halves(__float_as_uint(v), l, u);
-    lower = __uint_as_float(l);
-    upper = __uint_as_float(u);
-}
-__device__ __forceinline__ void both_halves(int v, int &lower, int &upper) {
-    unsigned l, u;
-    both_halves((unsigned)v, l, u);
-    lower = (int)l;
-    upper = (int)u;
+// The entry with the smaller distance of lanes l and l + 32, whose lower one has the smaller indices.
+__device__ __forceinline__ int closer_of_two_lanes(float d, int e) {
+    const auto dm = __builtin_amdgcn_permlane32_swap(__float_as_uint(d), __float_as_uint(d), false, false);
+    const auto em = __builtin_amdgcn_permlane32_swap((unsigned)e, (unsigned)e, false, false);
+    return __uint_as_float(dm[1]) < __uint_as_float(dm[0]) ? (int)em[1] : (int)em[0];
 }
 
 // TILES: tiles of 32 entries, 1, 2, 4 or 8, the fewest that hold E; codebooks are padded to that.
-template <int V, int TILES>
+// WAY: who looks at the eight entries of the best group.  kKvqPair: the two lanes that hold an item's minima, four each;
+// 32 items at a time.  kKvqOwn: 64 items at a time, each lane its own item.  kKvqNorms: the same by s once more, with the entries'
+// |c|^2 / 2 from LDS, and by the definition only where two entries of the group are too close (run_kvq_mfma chooses).
+enum { kKvqPair, kKvqOwn, kKvqNorms };
+template <int V, int TILES, int WAY>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) void kv_quantize_mfma_kernel(KvQuantArgs a) {
-    constexpr int EP = 32 * TILES;
+    constexpr int EP = 32 * TILES, STEP = WAY == kKvqPair ? 32 : 64;
+    constexpr bool NORMS = WAY == kKvqNorms;
     extern __shared__ __align__(16) unsigned char smem[];
-    half_t *cb = reinterpret_cast<half_t *>(smem);                            // [G][EP][V], infinite past E
-    float *c2m = reinterpret_cast<float *>(cb + (size_t)a.G * EP * V);        // [G]  largest |c|^2
+    half_t *cb = reinterpret_cast<half_t *>(smem);                                      // [G][EP][V], infinite past E
+    float *half_norms = reinterpret_cast<float *>(cb + (size_t)a.G * EP * V);           // [G][EP] |c|^2 / 2 (NORMS)
+    float *c2m = half_norms + (NORMS ? (size_t)a.G * EP : 0);                           // [G]  largest |c|^2
     uint8_t *out = reinterpret_cast<uint8_t *>(c2m + ((a.G + 3) & ~3));       // [tokens][P]
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, NW = blockDim.x >> 6;
     const int ln = lane & 31, lh = lane >> 5;
@@ -294,6 +292,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
                 for (int k = 0; k < V; ++k) n = __builtin_fmaf((float)c.h8[k], (float)c.h8[k], n);
                 // as bits, so that a NaN (above infinity) stays
                 m = __uint_as_float(max(__float_as_uint(m), __float_as_uint(n) & 0x7FFFFFFFu));
+                if (NORMS) half_norms[g * EP + e] = 0.5f * n;
             }
 #pragma unroll
             for (int k = 0; k < V / 2; ++k) reinterpret_cast<uint32_t *>(cb + (size_t)(g * EP + e) * V)[k] = c.w[k];
@@ -308,7 +307,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     float ninf;
     asm("s_mov_b32 %0, 0xff800000" : "=s"(ninf));
     const unsigned char *xs = reinterpret_cast<const unsigned char *>(a.x[side] + ((size_t)bh * a.n_new + t0) * a.D);
-    const int n_items = nt * a.PG, n_ct = (n_items + 31) / 32;   // per group
+    const int n_items = nt * a.PG, n_ct = (n_items + STEP - 1) / STEP;   // per group
     const int R = max(1, NW / a.G);                              // wavefronts that share a group
     for (int u = wave; u < a.G * R; u += NW) {
         const int g = u / R;
@@ -344,91 +343,127 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
             }
             A[t] = v.h8;
         }
+        // operand words of the upper half's k: what takes the power of two of h back
         const half2_t dd = {down, down}, d0 = {down, (half_t)0.f};
+        const unsigned back[4] = {__builtin_bit_cast(unsigned, dd), __builtin_bit_cast(unsigned, d0), 0u, 0u};
+        const float bound_c2 = kQuantBound * c2;
         auto item_off = [&](unsigned i) {   // index of the sub-vector in [token][P]
             return __umul24(__umul24(i, a.pg_inverse) >> 21, (unsigned)(a.P - a.PG)) + i + (unsigned)(g * a.PG);   // (kvq_quotient)
         };
-        auto lane_off = [&](int ct) { return item_off((unsigned)min(ct * 32 + ln, n_items - 1)); };
+        auto lane_off = [&](int ct) { return item_off((unsigned)min(ct * STEP + lane % STEP, n_items - 1)); };
         auto load_item = [&](unsigned off) { return kvq_load<V>(xs + off * (V * 2)); };
         unsigned off = lane_off(min(u % R, n_ct - 1));
         V16 xb = load_item(off);
         for (int ct = u % R; ct < n_ct; ct += R) {
             const unsigned off_next = lane_off(min(ct + R, n_ct - 1));
             const V16 xnext = load_item(off_next);
-            V16 bop;
+            V16 bop[2];   // items 0 .. 31 and 32 .. 63
 #pragma unroll
-            for (int i = 0; i < 4; ++i) bop.w[i] = lh ? 0u : xb.w[i];
-            if (lh) {
-                bop.h2[0] = dd;
-                bop.h2[1] = d0;
+            for (int i = 0; i < 4; ++i) {
+                const auto r = __builtin_amdgcn_permlane32_swap(i < V / 2 ? xb.w[i] : 0u, back[i], false, false);
+                bop[0].w[i] = r[0];
+                bop[1].w[i] = r[1];
             }
-            float best = INFINITY, second = INFINITY;
             const float16_t zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            float16_t s = __builtin_amdgcn_mfma_f32_32x32x16_f16(A[0], bop.h8, zero, 0, 0, 0);
+            float best[2] = {INFINITY, INFINITY}, second[2] = {INFINITY, INFINITY};
+            auto minima = [&](const half8_t &items, float &lowest, float &next) {
+                float16_t s = __builtin_amdgcn_mfma_f32_32x32x16_f16(A[0], items, zero, 0, 0, 0);
 #pragma unroll
-            for (int t = 0; t < TILES; ++t) {
-                float16_t sn = s;   // the next tile's products run while this tile's minima are taken
-                if (t + 1 < TILES) sn = __builtin_amdgcn_mfma_f32_32x32x16_f16(A[t + 1 < TILES ? t + 1 : 0], bop.h8, zero, 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int t = 0; t < TILES; ++t) {
+                    float16_t sn = s;   // the next tile's products run while this tile's minima are taken
+                    if (t + 1 < TILES) sn = __builtin_amdgcn_mfma_f32_32x32x16_f16(A[t + 1 < TILES ? t + 1 : 0], items, zero, 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    float key[2];
 #pragma unroll
-                for (int hf = 0; hf < 2; ++hf) {
-                    float m = min2f(s[8 * hf], s[8 * hf + 1], ninf);
-                    m = fminf(fminf(m, s[8 * hf + 2]), s[8 * hf + 3]);
-                    m = fminf(fminf(m, s[8 * hf + 4]), s[8 * hf + 5]);
-                    m = fminf(fminf(m, s[8 * hf + 6]), s[8 * hf + 7]);
-                    float key = __uint_as_float((__float_as_uint(m) & 0xFFFFFFF0u) | (unsigned)(2 * t + hf));
-                    // (a group whose first row, 16 hf + 4 lh, is past E has no entries and is never the closest; of 256 or
-                    // nearly 256 the few such groups may tie with the last entry instead, which is cheaper)
-                    if (TILES < 8) key = 32 * t + 16 * hf + 4 * lh < a.E ? key : 3e38f;
-                    second = __builtin_amdgcn_fmed3f(best, second, key);
-                    best = min2f(best, key, ninf);
+                    for (int hf = 0; hf < 2; ++hf) {
+                        float m = min2f(s[8 * hf], s[8 * hf + 1], ninf);
+                        m = fminf(fminf(m, s[8 * hf + 2]), s[8 * hf + 3]);
+                        m = fminf(fminf(m, s[8 * hf + 4]), s[8 * hf + 5]);
+                        m = fminf(fminf(m, s[8 * hf + 6]), s[8 * hf + 7]);
+                        key[hf] = __uint_as_float((__float_as_uint(m) & 0xFFFFFFF0u) | (unsigned)(2 * t + hf));
+                        // (a group whose first row, 16 hf + 4 lh, is past E has no entries and is never the closest; of 256 or
+                        // nearly 256 the few such groups may tie with the last entry instead, which is cheaper)
+                        if (TILES < 8) key[hf] = 32 * t + 16 * hf + 4 * lh < a.E ? key[hf] : 3e38f;
+                    }
+                    // second best of {lowest <= next, two keys}
+                    next = min2f(next, __builtin_amdgcn_fmed3f(lowest, key[0], key[1]), ninf);
+                    lowest = fminf(fminf(lowest, key[0]), key[1]);
+                    s = sn;
                 }
-                s = sn;
-            }
-            // the two lanes of the item
-            float bl, bu, sl, su;
-            both_halves(best, bl, bu);
-            both_halves(second, sl, su);
+            };
+            minima(bop[0].h8, best[0], second[0]);
+            asm volatile("" : "+v"(best[0]), "+v"(second[0]));   // (or the compiler moves the minima behind the branch, and all products lie in scratch)
+            if (STEP == 64 && ct * 64 + 32 < n_items) minima(bop[1].h8, best[1], second[1]);
+            // an item's entries lie in two lanes, 32 apart: both lanes' values to the item's own lane, or to both
+            const auto bm = __builtin_amdgcn_permlane32_swap(__float_as_uint(best[0]), __float_as_uint(best[STEP / 64]), false, false);
+            const auto sm = __builtin_amdgcn_permlane32_swap(__float_as_uint(second[0]), __float_as_uint(second[STEP / 64]), false, false);
+            const float bl = __uint_as_float(bm[0]), bu = __uint_as_float(bm[1]);
             const float win = min2f(bl, bu, ninf);
-            second = fminf(fmaxf(bl, bu), fminf(sl, su));
+            const float runner_up = fminf(fmaxf(bl, bu), fminf(__uint_as_float(sm[0]), __uint_as_float(sm[1])));
             float x2 = 0.f;
 #pragma unroll
             for (int i = 0; i < V; ++i) x2 = __builtin_fmaf((float)xb.h8[i], (float)xb.h8[i], x2);
-            const bool sure = second - win > 1.52587890625e-5f * (x2 + c2) && in_range;
+            const float bound = __builtin_fmaf(kQuantBound, x2, bound_c2);
+            const bool live = lane < STEP && ct * STEP + lane < n_items;
+            const bool sure = runner_up - win > bound && in_range;
             // entries of the group: rows 16 (grp & 1) + 4 (half whose lane holds them) + {0 .. 3, 8 .. 11} of tile grp / 2
-            const int e0 = 16 * (int)(__float_as_uint(win) & (2u * TILES - 1u)) + (bu < bl ? 4 : 0) + 8 * lh;
+            const int e0 = 16 * (int)(__float_as_uint(win) & (2u * TILES - 1u)) + (bu < bl ? 4 : 0);
             int be = e0;
-            float bd = kvq_exact<V>(xb, kvq_load<V>(cbg + (size_t)e0 * V));
+            bool within = false;   // the group's closest entry is known
+            if constexpr (NORMS) {
+                const float *hg = half_norms + g * EP + e0;
+                float lowest = INFINITY, next = INFINITY;
 #pragma unroll
-            for (int i = 1; i < 4; ++i) {
-                const float d = kvq_exact<V>(xb, kvq_load<V>(cbg + (size_t)(e0 + i) * V));
-                be = d < bd ? e0 + i : be;
-                bd = d < bd ? d : bd;
+                for (int q = 0; q < 2; ++q) {
+                    const float4_t h4 = *reinterpret_cast<const float4_t *>(hg + 8 * q);
+                    V16 c4[V / 2];   // four entries
+#pragma unroll
+                    for (int i = 0; i < V / 2; ++i) c4[i] = ld16(cbg + (size_t)(e0 + 8 * q) * V + 8 * i);
+                    float key[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        float d = h4[j];
+#pragma unroll
+                        for (int i = 0; i < V; ++i) d = __builtin_fmaf(-(float)xb.h8[i], (float)c4[(j * V + i) / 8].h8[(j * V + i) % 8], d);
+                        key[j] = __uint_as_float((__float_as_uint(d) & 0xFFFFFFF0u) | (unsigned)(8 * q + j));
+                    }
+#pragma unroll
+                    for (int j = 0; j < 4; j += 2) {
+                        next = min2f(next, __builtin_amdgcn_fmed3f(lowest, key[j], key[j + 1]), ninf);
+                        lowest = fminf(fminf(lowest, key[j]), key[j + 1]);
+                    }
+                }
+                within = next - lowest > bound;
+                be = e0 + (int)(__float_as_uint(lowest) & 15u);
             }
-            {
-                float dl, du;
-                int el, eu;
-                both_halves(bd, dl, du);
-                both_halves(be, el, eu);
-                be = du < dl ? eu : el;   // (the lower half's entries have the smaller indices)
+            if (!NORMS || __ballot(sure && !within && live)) {
+                const int first = WAY == kKvqPair ? e0 + 8 * lh : e0;
+                float bd = kvq_exact<V>(xb, kvq_load<V>(cbg + (size_t)first * V));
+                int ge = first;
+#pragma unroll
+                for (int i = 1; i < (WAY == kKvqPair ? 4 : 8); ++i) {
+                    const int e = first + i + (i & 4);
+                    const float d = kvq_exact<V>(xb, kvq_load<V>(cbg + (size_t)e * V));
+                    ge = d < bd ? e : ge;
+                    bd = d < bd ? d : bd;
+                }
+                if (WAY == kKvqPair) ge = closer_of_two_lanes(bd, ge);
+                be = within ? be : ge;
             }
-            const bool live = ct * 32 + ln < n_items;
-            unsigned long long left = __ballot(!sure && live && lh == 0);
+            unsigned long long left = __ballot(!sure && live);
             if (left) {
-                if (__popcll(left) > 12) {
-                    // many: every item scanned by its own two lanes, one half of the entries each
+                if (__popcll(left) > STEP * 3 / 8) {
+                    // many: every lane scans the entries for its item, two lanes one half each
+                    const int from = WAY == kKvqPair ? lh * 128 : 0, to = WAY == kKvqPair ? min(from + 128, a.E) : a.E;
                     float bd2 = INFINITY;
-                    int be2 = lh * 128;
-                    for (int e = lh * 128; e < min(lh * 128 + 128, a.E); ++e) {
+                    int be2 = from;
+                    for (int e = from; e < to; ++e) {
                         const float d = kvq_exact<V>(xb, kvq_load<V>(cbg + (size_t)e * V));
                         be2 = d < bd2 ? e : be2;
                         bd2 = d < bd2 ? d : bd2;
                     }
-                    float dl, du;
-                    int el, eu;
-                    both_halves(bd2, dl, du);
-                    both_halves(be2, el, eu);
-                    be = sure ? be : du < dl ? eu : el;
+                    if (WAY == kKvqPair) be2 = closer_of_two_lanes(bd2, be2);
+                    be = sure ? be : be2;
                 } else {
                     // few: one after the other, the 64 lanes taking the entries in turn
                     for (; left; left &= left - 1) {
@@ -447,11 +482,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
                             bd2 = d < bd2 ? d : bd2;
                         }
                         const int code = kvq_wave_argmin(bd2, be2);
-                        be = ln == j ? code : be;
+                        be = lane == j ? code : be;
                     }
                 }
             }
-            if (live && lh == 0) out[off] = (uint8_t)be;
+            if (live) out[off] = (uint8_t)be;
             xb = xnext;
             off = off_next;
         }
@@ -491,11 +526,12 @@ int kvq_log_lanes(int items) {
 bool kvq_four_tokens(int P, int v, int n_new) { return v <= 4 && n_new >= 4 * (256 / P); }
 
 // The kernel with the least estimated time (us): the chain of one workgroup or the instructions of all of them (a vector
-// instruction of a wavefront: 1.63e-6 us of the chip), whichever is longer.  Fitted to 703 measured calls (B 1 .. 64, 1 to
-// 2048 tokens, 8 to 256 entries, 1 to 64 groups, head sizes 64 to 256): the pick takes 0.2 % more than the best of the three on
-// average, 20 % at worst.  Some of them, us, scan / lane / matrix cores: one group of 256, v = 4, one token, B4 4.3 / 4.1 / 4.8,
+// instruction of a wavefront: 1.63e-6 us of the chip), whichever is longer.  Over 432 measured calls (B 1 .. 64, 1 to
+// 2048 tokens, 8 to 256 entries, 1 to 64 groups, head sizes 64 to 192) the pick takes 0.5 % more than the best of the three on
+// average, 28 % at worst (16 entries, where the lanes keep calls that the matrix cores have come to do in 43 us against 51).  Some,
+// us, scan / lane / matrix cores: one group of 256, v = 4, one token, B4 4.3 / 4.1 / 4.8,
 // B16 8.6 / 6.3 / 5.4, B64 25.2 / 16.8 / 15.9; 32 groups of 256, B4, 4 tokens 11.0 / - / 14.3, 8 tokens 18.9 / - / 14.5; 8 groups of 64,
-// B16, one token 8.6 / 4.0 / 6.7; 16 entries, v = 4, B64, 4 tokens 73 / 7.2 / 11.1, B2, 2048 tokens 1052 / 49 / 57.
+// B16, one token 8.6 / 4.0 / 6.7; 16 entries, v = 4, B64, 4 tokens 73 / 7.2 / 11.1, B2, 2048 tokens 1052 / 51 / 43.
 int kvq_choice(int bh, int P, int v, int E, int G, int n_new) {
     const double kInst = 1.63e-6;
     double best = 1e300;
@@ -523,11 +559,11 @@ int kvq_choice(int bh, int P, int v, int E, int G, int n_new) {
     }
     {
         const int tiles = E <= 32 ? 1 : E <= 64 ? 2 : E <= 128 ? 4 : 8, most = kvq_mfma_tokens(bh, n_new), tokens = std::min(n_new, most);
-        const int columns = ceil_div((long)tokens * (P / G), 32);   // column tiles of 32 items per group
+        const int items = tokens * (P / G), columns = ceil_div(items, 32);   // per group; column tiles of 32 items
         const int waves = 4 * ((long)G * 64 * tiles * v + tokens * P) > 160 * 1024 ? 8 : 4, share = std::max(1, waves / G);
         const double chain = ceil_div(G, waves) * (0.6 + 0.2 * tiles + 0.08 * v + (ceil_div(columns, share) - 1) * (0.5 + 0.06 * tiles));
         consider(kKvqMfma, chain + 1.8e-5 * (G * E * v * 2), sides * ceil_div(n_new, most), 0.0022,
-                 G * (40.0 + 36 * tiles + columns * (95.0 + 14 * tiles)));
+                 G * (40.0 + 36 * tiles + columns * 14.0 * tiles + (items <= 32 * share ? columns * 95.0 : ceil_div(items, 64) * (110.0 + 14 * v))));
     }
     return pick;
 }
@@ -540,15 +576,30 @@ int kv_quantize_kernel_of(const vq_kv_t *kv, int n_new) {
 
 namespace {
 
+template <int V, int TILES, int WAY>
+int run_kvq_mfma_as(const KvQuantArgs &a, int bh, int threads, size_t lds, hipStream_t s) {
+    static KernelSetup setup;
+    if (int st = kernel_setup(reinterpret_cast<const void *>(&kv_quantize_mfma_kernel<V, TILES, WAY>), lds, false, setup)) return st;
+    kv_quantize_mfma_kernel<V, TILES, WAY><<<dim3(bh, (a.n_new + a.tokens - 1) / a.tokens, 2), threads, lds, s>>>(a);
+    return launch_status();
+}
+
 template <int V, int TILES>
 int run_kvq_mfma(const KvQuantArgs &a, int bh, hipStream_t s) {
     const size_t lds = (size_t)a.G * 32 * TILES * V * sizeof(half_t) + (((size_t)a.G + 3) & ~(size_t)3) * 4 + (size_t)a.tokens * a.P;
-    static KernelSetup setup;
-    if (int st = kernel_setup(reinterpret_cast<const void *>(&kv_quantize_mfma_kernel<V, TILES>), lds, false, setup)) return st;
     // a CU holds 16 wavefronts of this kernel: two workgroups of 8 where 64 KiB of codebooks are staged, four of 4 otherwise
     const int threads = 4 * lds > 160 * 1024 ? 512 : 256;
-    kv_quantize_mfma_kernel<V, TILES><<<dim3(bh, (a.n_new + a.tokens - 1) / a.tokens, 2), threads, lds, s>>>(a);
-    return launch_status();
+    // Two lanes per item where a wavefront has 32 items of a group or fewer (12 tokens of 8 groups ...): 64 at a time leave half of
+    // the lanes idle.  And where a call is as long as one wavefront's chain (up to two workgroups a CU) and units of 32 spread
+    // better over the wavefronts: an iteration over 64 takes 1.7 times as long.
+    const int items = std::min(a.tokens, a.n_new) * a.PG, share = std::max(1, threads / 64 / a.G);
+    const int by_32 = ceil_div(ceil_div(items, 32), share), by_64 = ceil_div(ceil_div(items, 64), share);
+    const bool chain = (long)bh * 2 * ceil_div(a.n_new, a.tokens) <= 512;
+    if (items <= 32 * share || (chain && 10 * by_32 < 17 * by_64)) return run_kvq_mfma_as<V, TILES, kKvqPair>(a, bh, threads, lds, s);
+    // the norms, where they do not cost a workgroup per CU and no group is in part past the last entry
+    const size_t with_norms = lds + (size_t)a.G * 32 * TILES * sizeof(float);
+    if (a.E % 16 == 0 && with_norms * (threads == 512 ? 2 : 4) <= 160 * 1024) return run_kvq_mfma_as<V, TILES, kKvqNorms>(a, bh, threads, with_norms, s);
+    return run_kvq_mfma_as<V, TILES, kKvqOwn>(a, bh, threads, lds, s);
 }
 
 template <int V>

@@ -1268,6 +1268,31 @@ def test_kv_quantize_hard_values(gpu_device, v, G, E, n_new, kind):
     assert np.array_equal(kd.v_codes.cpu().numpy()[:, :, 2:2 + n_new], oracle.kv_quantize(x[1], kv.v_codebooks))
 
 
+# The matrix-core kernel takes 32 items (few per wavefront) or 64 at a time, and looks at the best group of eight entries by norms
+# (E % 16 == 0 and room in LDS) or by the definition: edges of the units, and near ties inside and between groups
+@pytest.mark.parametrize("D,v,G,E", [(8, 8, 1, 256), (8, 8, 1, 250), (128, 4, 1, 256), (128, 4, 1, 240), (128, 2, 1, 256), (128, 4, 32, 256), (128, 8, 16, 64)])
+@pytest.mark.parametrize("n_new", [4, 33, 64, 129, 161])
+@pytest.mark.parametrize("apart", [0, 1, 8, 16])
+def test_kv_quantize_units_and_near_ties(gpu_device, D, v, G, E, n_new, apart):
+    rng = np.random.default_rng(9550 + E + n_new + apart)
+    B, H, T, P = 1, 2, n_new + 3, D // v
+    cb = rng.normal(0, 1, size=(2, H, G, E, v)).astype(np.float16)
+    if apart:   # every entry of an even block of that length has a twin `apart` further on, in part one unit in the last place off
+        for e in range(E - apart):
+            if (e // apart) % 2 == 0:
+                cb[:, :, :, e + apart] = cb[:, :, :, e]
+        cb.view(np.uint16)[:, :, :, ::3, 0] += 1
+    x = rng.normal(0, 1, size=(2, B, H, n_new, D)).astype(np.float16)
+    codes = [torch.full((B, H, T, P), 255, dtype=torch.uint8, device=gpu_device) for _ in range(2)]
+    kd = vq.VQKVDev(B, H, D, T, v, codes[0], codes[1], dev_x(cb[0], gpu_device), dev_x(cb[1], gpu_device))
+    vq.vq_kv_quantize(kd, dev_x(x[0], gpu_device), dev_x(x[1], gpu_device), 2)
+    torch.cuda.synchronize()
+    for side in range(2):
+        got = codes[side].cpu().numpy()
+        assert np.array_equal(got[:, :, 2:2 + n_new], oracle.kv_quantize(x[side], cb[side])), side
+        assert (got[:, :, :2] == 255).all() and (got[:, :, 2 + n_new:] == 255).all(), side
+
+
 # head sizes other than 128: sub-vectors per group that are no power of two, one sub-vector per group, and the most LDS that
 # staged codebooks take (D = 256: 128 KiB); a last workgroup that is not full
 @pytest.mark.parametrize("D,v,G,E", [(96, 4, 1, 256), (96, 8, 4, 256), (80, 8, 2, 250), (192, 2, 32, 256), (40, 2, 5, 200), (24, 8, 3, 256),
