@@ -150,6 +150,126 @@ int launch_dequant(const vq_weight_t *w, void *W, int out_fp32, hipStream_t s) {
     return launch_status();
 }
 
+// The fp16 weight in operand order (vq_common.h), the first stage of the prefill product; the same bits as above.
+struct OrderedArgs {
+    const void *codes;
+    const half_t *cb;
+    half_t *out;
+    int N, K, E;
+    int tile_n, tile_k, tiles_k;   // per-tile codebooks (tile_n 0: per tensor)
+};
+
+// UNITS groups of 8 k per thread.  A wavefront takes 16 rows (a strip); with 8 units a lane has 64 k of a row, four lanes a row's
+// 256, and reads its codes as whole words; every store of the wavefront is four runs of 256 bytes.  Eight lookups are in flight per
+// thread and codebook: what bounds it is one gather per code from L1 or L2, or the stores.  2 units: the same with a thread per 16
+// k and code by code, for small weights, which have too few wavefronts otherwise.
+template <typename CodeT, int V, int R, int UNITS>
+__global__ __launch_bounds__(256) void dequant_ordered_kernel(OrderedArgs a) {
+    constexpr int BITS = std::is_same<CodeT, Code12>::value ? 12 : 8 * (int)sizeof(typename std::conditional<std::is_same<CodeT, Code12>::value, char, CodeT>::type);
+    constexpr int H = 8 / V;                 // sub-vectors per unit
+    constexpr int WORDS = 64 / V * R * BITS / 32;   // code words of 64 k
+    const int lane = threadIdx.x & 63, ln = lane & 15, part = lane >> 4;
+    const int KC = a.K / 64, groups = UNITS == 8 ? (KC + 3) / 4 : KC;   // wavefronts per strip
+    const int id = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int strip = id / groups, chunk = UNITS == 8 ? (id - strip * groups) * 4 + part : id - strip * groups;
+    const int row = strip * 16 + ln, cols = min(a.N - strip * 16, 16);
+    if (row >= a.N || chunk >= KC) return;
+    const int u0 = UNITS == 8 ? 0 : part * UNITS;   // first unit of this thread in its 64 k
+    const size_t first = (size_t)row * (a.K / V) + (size_t)chunk * (64 / V);   // sub-vector (of 64 k)
+
+    unsigned code[UNITS * H * R];
+    if constexpr (UNITS == 8) {
+        uint32_t w[WORDS + 1];
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(reinterpret_cast<const unsigned char *>(a.codes) + first * R * BITS / 8);
+#pragma unroll
+        for (int i = 0; i < WORDS; ++i) w[i] = src[i];
+        w[WORDS] = 0;
+#pragma unroll
+        for (int i = 0; i < UNITS * H * R; ++i) {
+            const int b = i * BITS;
+            uint32_t c = w[b / 32] >> (b % 32);
+            if (b % 32 + BITS > 32) c = __builtin_amdgcn_alignbit(w[b / 32 + 1], w[b / 32], b % 32);
+            code[i] = c & ((1u << BITS) - 1u);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < UNITS * H * R; ++i) code[i] = read_code<CodeT>(a.codes, (first + u0 * H) * R + i);
+    }
+
+    typedef unsigned raw_t __attribute__((ext_vector_type(V / 2)));
+    const half_t *cb = a.cb;   // (a tile of codebooks is a multiple of 16 rows x 64 k: check_weight)
+    if (a.tile_n > 0) cb += ((size_t)(strip * 16 / a.tile_n) * a.tiles_k + (size_t)(chunk * 64 / a.tile_k)) * ((size_t)R * a.E * V);
+    auto look_up = [&](int i, int r) {   // i: sub-vector of this thread
+        return *reinterpret_cast<const raw_t *>(cb + ((unsigned)(r * a.E) + code[i * R + r]) * (unsigned)V);
+    };
+    constexpr int AT = R <= 2 ? UNITS : 2;   // units looked up together
+    half_t *out = a.out + (size_t)strip * 16 * a.K + (size_t)chunk * 64 * cols + ln * 8;
+#pragma unroll
+    for (int g = 0; g < UNITS; g += AT) {
+        raw_t e[R][AT * H];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int i = 0; i < AT * H; ++i) e[r][i] = look_up(g * H + i, r);
+        if constexpr (UNITS == 8) __builtin_amdgcn_sched_barrier(0);   // (or one lookup after the other, to save registers)
+#pragma unroll
+        for (int u = 0; u < AT; ++u) {
+            V16 o;
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+                typedef half_t half_v __attribute__((ext_vector_type(V)));
+                half_v sum = __builtin_bit_cast(half_v, e[0][u * H + h]);
+                if constexpr (R > 1) {   // RNE of the fp32 sum, r ascending
+                    float f[V];
+#pragma unroll
+                    for (int k = 0; k < V; ++k) f[k] = (float)sum[k];
+#pragma unroll
+                    for (int r = 1; r < R; ++r) {
+                        const half_v x = __builtin_bit_cast(half_v, e[r][u * H + h]);
+#pragma unroll
+                        for (int k = 0; k < V; ++k) f[k] += (float)x[k];
+                    }
+#pragma unroll
+                    for (int k = 0; k < V; ++k) sum[k] = (half_t)f[k];
+                }
+                const raw_t raw = __builtin_bit_cast(raw_t, sum);
+#pragma unroll
+                for (int k = 0; k < V / 2; ++k) o.w[h * (V / 2) + k] = raw[k];
+            }
+            *reinterpret_cast<uint4 *>(out + (size_t)(u0 + g + u) * 8 * cols) = o.u;
+        }
+    }
+}
+
+template <typename CodeT, int V, int R>
+static int run_dequant_ordered(const OrderedArgs &a, hipStream_t s) {
+    const long strips = (a.N + 15) / 16, KC = a.K / 64, waves8 = strips * ((KC + 3) / 4);
+    // below 2048 wavefronts of eight units a quarter of the work per thread
+    if (waves8 >= 2048)
+        dequant_ordered_kernel<CodeT, V, R, 8><<<(unsigned)((waves8 + 3) / 4), 256, 0, s>>>(a);
+    else
+        dequant_ordered_kernel<CodeT, V, R, 2><<<(unsigned)((strips * KC + 3) / 4), 256, 0, s>>>(a);
+    return launch_status();
+}
+
+template <typename CodeT, int V>
+static int run_dequant_ordered(const vq_weight_t *w, const OrderedArgs &a, hipStream_t s) {
+    switch (w->n_codebooks) {
+        case 1: return run_dequant_ordered<CodeT, V, 1>(a, s);
+        case 2: return run_dequant_ordered<CodeT, V, 2>(a, s);
+        case 3: return run_dequant_ordered<CodeT, V, 3>(a, s);
+        default: return run_dequant_ordered<CodeT, V, 4>(a, s);
+    }
+}
+
+int launch_dequant_ordered(const vq_weight_t *w, half_t *W, hipStream_t s) {
+    const OrderedArgs a = {w->codes, (const half_t *)w->codebooks, W, w->N, w->K, w->n_entries,
+                           w->cb_tile_n, w->cb_tile_n > 0 ? w->cb_tile_k : 1, w->cb_tile_n > 0 ? w->K / w->cb_tile_k : 1};
+    if (w->code_bits == 8) return w->v == 8 ? run_dequant_ordered<uint8_t, 8>(w, a, s) : run_dequant_ordered<uint8_t, 4>(w, a, s);
+    if (w->code_bits == 12) return w->v == 8 ? run_dequant_ordered<Code12, 8>(w, a, s) : run_dequant_ordered<Code12, 4>(w, a, s);
+    return w->v == 8 ? run_dequant_ordered<uint16_t, 8>(w, a, s) : run_dequant_ordered<uint16_t, 4>(w, a, s);
+}
+
 // One thread per (b, h, t, p): copies entry k/v_codebooks[h][g(p)][code] verbatim.
 __global__ __launch_bounds__(256) void kv_dequant_kernel(const uint8_t *__restrict__ codes,
                                                          const uint16_t *__restrict__ cb,

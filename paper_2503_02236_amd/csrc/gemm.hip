@@ -1,7 +1,7 @@
 // VQ-gemm for gfx950: Y[m][n] = scale[n] * sum_k W[n][k] X[m][k], W held as VQ codes, contraction on the fp16 matrix
 // cores with fp32 accumulation.  Operation: VQ-LLM (arXiv 2503.02236) Sec. III-C "VQ-gemm"; dequantization of Sec. II-A.
-// This file chooses between the two ways: dequantize once and multiply densely (dequant.hip, gemm_dense.hip), or look
-// entries up inside the product (gemm_skinny.hip).
+// This file chooses between the two ways: dequantize once and multiply densely (dequant.hip, gemm_tiles.hip; gemm_dense.hip
+// for a very long K), or look entries up inside the product (gemm_skinny.hip).
 #include "vq_common.h"
 
 namespace vq {
@@ -28,6 +28,12 @@ int launch_gemm(const vq_weight_t *w, const void *X, int M, void *Y, void *ws, h
     half_t *Yp = (half_t *)Y;
     if (gemm_one_pass(w, M)) return launch_gemm_skinny(w, X, M, Y, s);
     if (gemm_two_stage(w, M)) {
+        if (gemm_tiles_fits(w->K)) {
+            int pick;
+            gemm_tiles_time(M, w->N, w->K, &pick);
+            const int st = launch_dequant_ordered(w, (half_t *)ws, s);
+            return st != VQ_OK ? st : launch_gemm_tiles(Xp, (const half_t *)ws, (const half_t *)w->scale, Yp, M, w->N, w->K, pick, s);
+        }
         int st = launch_dequant(w, ws, /*out_fp32=*/0, s);
         if (st != VQ_OK) return st;
         return launch_gemm_dense(Xp, (const half_t *)ws, (const half_t *)w->scale, Yp, M, w->N, w->K, s);

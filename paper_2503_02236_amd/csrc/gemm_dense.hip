@@ -1,5 +1,5 @@
-// Second stage of the prefill VQ-gemm when M is large: Y = X * Wd^T with Wd the fp16
-// dequantized weight (written once per call into the workspace by the dequantization
+// Second stage of the prefill VQ-gemm when M is large and K beyond 2^22, where the 32-bit offsets of gemm_tiles.hip
+// do not reach (and that is faster everywhere else): Y = X * Wd^T with Wd the fp16 dequantized weight (written once per call into the workspace by the dequantization
 // kernel), on v_mfma_f32_32x32x16_f16 with fp32 accumulation.
 //
 // Why two stages (VQ-LLM, arXiv 2503.02236, Sec. VII-B notes that dequantization hurts the
@@ -11,7 +11,7 @@
 // of gathers.  The fp16 tile this kernel consumes is exactly the bit-exact tile of vq_dequant.
 //
 // Tile: BM x BN = 256 x 128 per workgroup (256 tiles for M = 2048, N = 4096: one per CU),
-// four wavefronts 2 x 2, each 128 x 64 = 4 x 2 MFMA tiles; 128 x 128 where that leaves CUs idle (gemm_dense_rounds).  K in blocks of 64; both operands
+// four wavefronts 2 x 2, each 128 x 64 = 4 x 2 MFMA tiles; 128 x 128 where that leaves CUs idle (gemm_dense_small).  K in blocks of 64; both operands
 // are K-contiguous, so a lane's MFMA operand (8 consecutive k) is one 128-bit LDS read.
 //
 // Data movement: global -> LDS directly (global_load_lds_dwordx4, no registers), three LDS
@@ -253,17 +253,15 @@ __global__ __launch_bounds__(256) void gemm_dense_kernel(DenseArgs a) {
     }
 }
 
-// Rounds of workgroups over 256 CUs, in units of a round of 256 x 128 tiles; *small: with 128 x 128 tiles, whose round is
-// counted as 0.75 of that (over 288 products, N 64 .. 11008, 257 .. 4096 tokens, K 512 and 4096, any value from 0.7 to 0.8 takes
+// Whether 128 x 128 tiles take fewer rounds of workgroups over 256 CUs than 256 x 128 ones, a round of theirs being
+// counted as 0.75 (over 288 products, N 64 .. 11008, 257 .. 4096 tokens, K 512 and 4096, any value from 0.7 to 0.8 takes
 // 0.03 % more than the better tile; 0.65 up to 9 % more).  A product of few tiles leaves CUs idle: M = 512, N = K = 4096 has 64 of the large ones (46.5 us) or 128
 // of the small (31.9); 600 x 11008 258 (two rounds, 102.9 us) or 430 (two rounds, 69.5); 1024 x 4096 52.4 / 39.7.  With as many
 // large rounds as would be full the large tile is ahead (2048 x 4096 68.6 / 81.4, 512 x 11008 55.0 / 66.7).
-double gemm_dense_rounds(int M, int N, bool *small) {
+static bool gemm_dense_small(int M, int N) {
     const long tn = ((long)N + 127) / 128;
     const long large = (((long)M + 255) / 256 * tn + 255) / 256, little = (((long)M + 127) / 128 * tn + 255) / 256;
-    const bool s = 0.75 * little < large;
-    if (small) *small = s;
-    return s ? 0.75 * little : (double)large;
+    return 0.75 * little < large;
 }
 
 template <int MT, int NT>
@@ -290,9 +288,7 @@ static int run_dense(const half_t *A, const half_t *B, const half_t *scale, half
 
 int launch_gemm_dense(const half_t *A, const half_t *B, const half_t *scale, half_t *C, int M, int N, int K,
                       hipStream_t s) {
-    bool small;
-    gemm_dense_rounds(M, N, &small);
-    return small ? run_dense<2, 2>(A, B, scale, C, M, N, K, s) : run_dense<4, 2>(A, B, scale, C, M, N, K, s);
+    return gemm_dense_small(M, N) ? run_dense<2, 2>(A, B, scale, C, M, N, K, s) : run_dense<4, 2>(A, B, scale, C, M, N, K, s);
 }
 
 }  // namespace vq

@@ -444,7 +444,7 @@ constexpr SkinnyTile kL2Tiles[] = {{1, 1}, {1, 2}, {1, 4}, {2, 4}, {1, 8}, {2, 8
 // The constants were fitted to 210 measured shapes (six formats, N 256 .. 11008, M 17 .. 256) x 6 tiles: the tile that
 // this picks takes 0.5 % more than the best one on average and 17 % more at worst.  Staging of the codebooks, the same for every
 // tile, counts only in the estimate (*clocks).
-int skinny_tile(const vq_weight_t *w, int M, bool l2, double staging = 0, double *clocks = nullptr) {
+int skinny_tile(const vq_weight_t *w, int M, bool l2, double staging = 0, double *us = nullptr) {
     int best = 0;
     double best_cost = 1e300;
     for (int i = 0; i < (l2 ? 6 : 5); ++i) {
@@ -458,9 +458,12 @@ int skinny_tile(const vq_weight_t *w, int M, bool l2, double staging = 0, double
         if (cost < best_cost) {
             best_cost = cost;
             best = i;
+            // (to compare with another kernel: fitted to 397 measured launches, 11 % off on average)
+            const double x = 16.0 * t.ct * w->K * 2 / 41;
+            if (us && l2) *us = rounds * (lookups * (w->v == 8 ? 2.88e-4 : 3.34e-4) + x * 5.7e-4 + 1.26) + 2.7;
+            if (us && !l2) *us = rounds * (lookups * (w->v == 8 ? 2.81e-4 : 1.83e-4) + x * 6.6e-4 + staging * 6.3e-4 + 2.26) + 1.4;
         }
     }
-    if (clocks) *clocks = best_cost;
     return best;
 }
 
@@ -522,22 +525,23 @@ bool gemm_skinny_supported(const vq_weight_t *w) {
     return entries_from_lds(w) || (w->cb_tile_n == 0 && R == 1 && w->code_bits == 16);
 }
 
-// More than 256 tokens: against the two-stage product, whose time is one round of tiles after another, however few tiles a
-// round has (256 x 128 tiles: about 20 K + 5500 clocks), after writing the weight once (0.0017 clocks an element + 3500).
-// Measured with two 256-entry codebooks, two-stage / here: N = 256, K = 1024, 1024 tokens 13.0 / 5.8 us; N = 1024,
-// K = 4096, 1024 tokens 35.7 / 20.0; N = K = 4096, 384 tokens 48.2 / 34.8, 1024 tokens 51.4 / 67.6; N = 11008, 272 tokens
-// 75.0 / 66.2, 384 tokens 75.7 / 83.5; 2^16 entries, N = 1024, 1024 tokens 36.9 / 31.8, N = 4096, 384 tokens 45.4 / 60.3.
-// Every workgroup stages the codebooks (41 bytes per clock): 4096 12-bit codes, N = 1000, K = 512, 1024 tokens 15.0 / 17.2.
-// The estimates are good to 20 %, so this one has to be that much lower: over 1056 measured calls (11 formats, 12 weights, 257 to
-// 2048 tokens) the pick takes 1.8 % more than the better of the two.  (A supported weight with K % 64 == 0.)
+// More than 256 tokens: against the two-stage product, which writes the weight once and multiplies it tile by tile.  Measured,
+// two-stage / here, us: two 256-entry codebooks, N = 256, K = 4096, 1024 tokens 18.7 / 9.1; N = 1024, K = 2048, 400 tokens 12.0 / 9.0,
+// 2048 tokens 18.0 / 21.2; N = K = 4096, 400 tokens 33.6 / 31.4, 700 tokens 41.5 / 48.5; N = 11008, K = 1024, 257 tokens 28.7 / 24.0; 2^16
+// entries, N = 64, K = 8192, 257 tokens 25.2 / 13.2.  Every workgroup stages the codebooks (41 bytes per clock).  The estimates are
+// good to about 10 %: over 397 measured calls (8 formats, 11 weights, 257 to 2048 tokens) the pick takes 1.9 % more than the
+// better of the two on average.  (A supported weight with K % 64 == 0.)
 bool gemm_skinny_wins(const vq_weight_t *w, int M) {
     if ((long)M * w->K >= kSkinnyMaxX) return false;
     double here;
     const bool l2 = !entries_from_lds(w);
     const size_t sets = w->cb_tile_n > 0 ? w->K / w->cb_tile_k : 1;
     skinny_tile(w, M, l2, l2 ? 0 : sets * w->n_codebooks * w->n_entries * w->v * 2 / 41.0, &here);
-    const double rounds = gemm_dense_rounds(M, w->N, nullptr);
-    return here < 0.8 * (rounds * (20.0 * w->K + 5500) + 0.0017 * w->N * w->K + 3500);
+    // dequantization: by the million elements, the first 16 of which are dearer (few wavefronts), and launches
+    const double m = 1e-6 * w->N * w->K, first = std::min(m, 16.0), rest = m - first;
+    const double two = 3.5 + 0.97 * gemm_tiles_time(M, w->N, w->K, nullptr) +
+                       (l2 ? w->v == 8 ? 1.33 * first + 0.62 * rest : 1.76 * first + 1.09 * rest : w->v == 8 ? 1.29 * first + 0.45 * rest : 1.26 * first + 0.57 * rest);
+    return (l2 ? 0.92 : 1.0) * here < two;
 }
 
 // Where vq_gemv (1 .. 16 tokens) runs here.

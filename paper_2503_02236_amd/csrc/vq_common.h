@@ -120,7 +120,14 @@ bool gemm_skinny_supported(const vq_weight_t *w);
 bool gemm_skinny_wins(const vq_weight_t *w, int M);
 bool gemm_skinny_for_gemv(const vq_weight_t *w, int bs);
 int launch_gemm_skinny(const vq_weight_t *w, const void *x, int M, void *y, hipStream_t s);
-double gemm_dense_rounds(int M, int N, bool *small);
+// Two stages (K % 64 == 0).  The second reads the dequantized weight in the order of its wavefronts' operands: strips of 16 columns
+// (the last of N may have fewer, c), in a strip fragments of 32 k, in a fragment four groups of 8 k, in a group the strip's columns,
+// 8 halves each.  Element (n, k) is half number 16 K (n / 16) + 32 c (k / 32) + 8 c (k % 32 / 8) + 8 (n % 16) + k % 8; N K in all.
+int launch_dequant_ordered(const vq_weight_t *w, half_t *W, hipStream_t s);
+bool gemm_tiles_fits(int K);
+double gemm_tiles_time(int M, int N, int K, int *pick);
+int launch_gemm_tiles(const half_t *X, const half_t *W, const half_t *scale, half_t *Y, int M, int N, int K, int pick, hipStream_t s);
+// ... or in rows (K too long for the 32-bit offsets of the above)
 int launch_gemm_dense(const half_t *A, const half_t *B, const half_t *scale, half_t *C, int M, int N, int K,
                       hipStream_t s);
 bool gemv_mfma_batch_supported(const vq_weight_t *const *w, int count);

@@ -824,6 +824,47 @@ def test_gemm_two_stage_ragged(gpu_device, M, N, K, v, bits, R):
     assert_close(Y, oracle.gemm(w.codes, w.codebooks, w.scale, X), f"gemm two-stage {M}x{N}x{K} R{R}")
 
 
+# The two stages by themselves: the weight in operand order (16-column strips, the last one narrower) holds the bits of vq_dequant,
+# every code format, with eight units of 8 k per thread (large) and with two (small)
+@pytest.mark.parametrize("N,K", [(1, 64), (37, 192), (130, 320), (2051, 4160), (2056, 4096)])
+@pytest.mark.parametrize("v,bits,R,E", [(8, 8, 1, 256), (8, 8, 2, 200), (4, 8, 2, 256), (4, 8, 4, 64), (8, 16, 1, 65536), (4, 16, 1, 5001), (4, 16, 3, 500),
+                                        (8, 12, 1, 4096), (8, 12, 2, 4096), (4, 12, 2, 2000), (8, 8, 3, 256)])
+def test_dequant_in_operand_order(gpu_device, N, K, v, bits, R, E):
+    w = vq.weight_to_device(wl.make_weight(N, K, v, bits, R, E, 0.05, seed=4780 + N), gpu_device)
+    rows = vq.vq_dequant(w, out_fp32=False).cpu().numpy()
+    got = torch.full((N * K + 64,), 7.0, dtype=torch.float16, device=gpu_device)
+    f = vq.lib()._ZN2vq22launch_dequant_orderedEPK11vq_weight_tPDF16_P12ihipStream_t
+    assert f(ctypes.byref(w.desc()), ctypes.c_void_p(got.data_ptr()), ctypes.c_void_p(0)) == 0
+    torch.cuda.synchronize()
+    n, k = np.arange(N)[:, None], np.arange(K)[None, :]
+    c = np.minimum(16, N - n // 16 * 16)
+    at = 16 * K * (n // 16) + 32 * c * (k // 32) + 8 * c * (k % 32 // 8) + 8 * (n % 16) + k % 8
+    got = got.cpu().numpy()
+    assert len(np.unique(at)) == N * K and np.array_equal(got[at].view(np.uint16), rows.view(np.uint16)) and (got[N * K:] == 7).all()
+
+
+# ... and every tile of the product, at the edges of tiles, strips, fragments and the ring of stages
+@pytest.mark.parametrize("M,N,K", [(1, 1, 64), (70, 37, 128), (129, 264, 192), (257, 72, 320), (300, 513, 448), (513, 200, 1024)])
+@pytest.mark.parametrize("pick", range(8))
+def test_gemm_tiles(gpu_device, M, N, K, pick):
+    g = torch.Generator(device=gpu_device).manual_seed(4790 + M + pick)
+    X = torch.randn((M, K), generator=g, device=gpu_device).to(torch.float16)
+    W = (torch.randn((N, K), generator=g, device=gpu_device) * 0.05).to(torch.float16)
+    scale = (torch.rand(N, generator=g, device=gpu_device) + 0.5).to(torch.float16) if pick % 2 or M == 513 else None
+    n, k = torch.arange(N, device=gpu_device)[:, None], torch.arange(K, device=gpu_device)[None, :]
+    c = torch.clamp(N - n // 16 * 16, max=16)
+    ordered = torch.empty(N * K, dtype=torch.float16, device=gpu_device)
+    ordered[16 * K * (n // 16) + 32 * c * (k // 32) + 8 * c * (k % 32 // 8) + 8 * (n % 16) + k % 8] = W
+    Y = torch.full((M + 1, N), 7.0, dtype=torch.float16, device=gpu_device)
+    ptr = lambda t: ctypes.c_void_p(0 if t is None else t.data_ptr())  # noqa: E731
+    torch.cuda.synchronize()
+    assert vq.lib()._ZN2vq17launch_gemm_tilesEPKDF16_S1_S1_PDF16_iiiiP12ihipStream_t(ptr(X), ptr(ordered), ptr(scale), ptr(Y), M, N, K, pick, ptr(None)) == 0
+    torch.cuda.synchronize()
+    want = X.double().cpu().numpy() @ W.double().cpu().numpy().T * (1 if scale is None else scale.double().cpu().numpy())
+    assert_close(Y[:M], want, f"tile {pick} {M}x{N}x{K}")
+    assert (Y[M] == 7).all()
+
+
 # One pass over the codes for 17 .. 256 tokens: every tile of the kernel ({weight rows} x {tokens} of a workgroup: 16 x 16,
 # 16 x 32, 32 x 32, 32 x 64, 64 x 64 from LDS; 16 x 16 .. 32 x 128 from L2) at ragged N, M and K, several iterations per
 # wavefront among them.  Codes are in range, so the bound is that of the other products (fp16 operands, fp32 sums).

@@ -97,6 +97,44 @@ def test_gemm_dense_ring_wait_matches_the_transfers_of_a_stage(tmp_path):
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
+def test_gemm_tiles_waits_match_the_loads_in_flight(tmp_path):
+    """Before the barrier of a stage the tile kernel waits until as many loads are in flight as are issued after the last load
+    of the next stage of X, not counting the weight loads right behind it; so in front of every such wait, in program order
+    (start, main loop, loop end), the transfers to LDS of that stage have to lie that far back."""
+    out = tmp_path / "gemm_tiles.s"
+    cmd = [HIPCC, "-O3", "-std=c++17", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang",
+           "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "--cuda-device-only", "-S",
+           os.path.join(CSRC, "gemm_tiles.hip"), "-o", str(out)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    kernels = re.findall(r"^_ZN2vq\S*gemm_tiles_kernelILi(\d+)ELi(\d+)E\S*:(.*?)^\.Lfunc_end", out.read_text(), re.S | re.M)
+    assert len(kernels) == 8
+    for BM, NF, text in kernels:
+        XL, WL = int(BM) // 32, 2 * int(NF)
+        lines = [l.strip() for l in text.splitlines()]
+        loads = [(i, " lds" in l) for i, l in enumerate(lines) if l.startswith("buffer_load_dwordx4")]
+        # the start, two copies of the stage in the main loop, one for an odd number of stages (whose weight loads nobody waits for)
+        assert sum(x for _, x in loads) == 6 * XL and sum(not x for _, x in loads) == 4 * WL, (BM, NF, len(loads))
+        assert not any(re.match(r"(global|flat|scratch)_load", l) for l in lines[loads[0][0]:loads[-1][0]]), (BM, NF)
+        order = [x for _, x in loads]
+        start = order[:3 * XL + 2 * WL]
+        assert start[:XL] == [True] * XL
+        for q in range(2):      # stages 1 and 2 of X with 0 and 1 of the weight, half a stage at a time
+            for s in range(2):
+                part = start[XL + (2 * q + s) * (XL + WL) // 2:XL + (2 * q + s + 1) * (XL + WL) // 2]
+                assert sum(part) == XL // 2, (BM, NF, q, s)
+        waits = [i for i, l in enumerate(lines) if l == f"s_waitcnt vmcnt({(XL + WL) * 3 // 2}) lgkmcnt(0)"]
+        assert len(waits) == 3 and all(lines[i + 1] == "s_barrier" for i in waits), (BM, NF)
+        # in the main loop each half stage is its transfers first, its weight loads last
+        body = [x for i, x in loads if i > loads[3 * XL + 2 * WL - 1][0]][:2 * (XL + WL)]
+        half = [True] * (XL // 2) + [False] * (WL // 2)
+        assert body == half * 4, (BM, NF)
+        for w in waits[:2]:     # each wait stands between the two halves of a stage
+            before = sum(1 for i, _ in loads[3 * XL + 2 * WL:] if i < w)
+            assert before % (XL + WL) == (XL + WL) // 2, (BM, NF)
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
 def test_attention_kernels_have_no_static_lds(tmp_path):
     """The attention kernel forms entry addresses as absolute LDS offsets, which needs its dynamic LDS to start
     at address 0, i.e. no static LDS in any build of it (the launcher checks the same at run time and returns
