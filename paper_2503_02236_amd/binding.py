@@ -1,4 +1,7 @@
-"""Thin ctypes binding over libvqmi.so (argument marshalling only).
+"""Thin binding over libvqmi.so (argument marshalling only).
+
+ctypes throughout; the calls that a decode step makes by the hundred go through ``_marshal`` (csrc/marshal.cpp), which does
+the same in native code for plain arguments and leaves every other call, and every error, to the code here.
 
 Every function here has the name and semantics of the C entry point it wraps
 (``include/vq_mi355x.h``); torch is used for device memory and the current HIP
@@ -59,6 +62,7 @@ class vq_side_streams_t(ctypes.Structure):
 
 
 _lib = None
+_marshal = None    # the native marshalling, once the library is loaded
 
 #: name -> (restype, argtypes); must list every symbol the header declares
 SYMBOLS = {
@@ -123,7 +127,21 @@ def lib() -> ctypes.CDLL:
             fn = getattr(l, name)
             fn.restype, fn.argtypes = res, args
         _lib = l
+        _load_marshal(l)
     return _lib
+
+
+def _load_marshal(l) -> None:
+    global _marshal
+    try:
+        from . import _marshal as native
+    except ImportError:     # (not built, or built for another torch: slower, not different)
+        return
+    address = lambda name: ctypes.cast(getattr(l, name), ctypes.c_void_p).value  # noqa: E731
+    native.init(tuple(address(n) for n in ("vq_gemv", "vq_gemv_workspace", "vq_gemv_batch", "vq_gemv_batch_workspace", "vq_gemm",
+                                           "vq_gemm_workspace", "vq_attn_decode", "vq_attn_decode_workspace", "vq_kv_quantize")),
+                VQWeightDev, VQKVDev, vq_gemv_pack_t, VQError)
+    _marshal = native
 
 
 def status_str(status: int) -> str:
@@ -301,6 +319,8 @@ def vq_gemv_workspace(w: VQWeightDev, bs: int) -> int:
 def vq_gemv(w: VQWeightDev, x: torch.Tensor, y: Optional[torch.Tensor] = None,
             ws: Optional[torch.Tensor] = None) -> torch.Tensor:
     """y[bs][N] = scale * (x[bs][K] @ dequant(W)^T) on the current stream."""
+    if _marshal is not None and (r := _marshal.gemv(w, x, y, ws)) is not NotImplemented:
+        return r
     bs = x.shape[0]
     if y is None:
         y = x.new_empty((bs, w.N))     # (x has to be fp16: checked below)
@@ -340,6 +360,8 @@ class GemvBatch:
 
 def vq_gemv_batch(ws_list, xs, ys=None, ws: Optional[torch.Tensor] = None):
     """Independent bs = 1 problems y_i = scale_i * (W_i x_i) in one call; returns the list of y_i."""
+    if _marshal is not None and (r := _marshal.gemv_batch(ws_list, xs, ys, ws)) is not NotImplemented:
+        return r
     if ys is None:
         ys = [torch.empty((1, w.N), dtype=torch.float16, device=x.device) for w, x in zip(ws_list, xs)]
     call = GemvBatch(ws_list, xs, ys)
@@ -449,6 +471,8 @@ def vq_gemm_workspace(w: VQWeightDev, M: int) -> int:
 def vq_gemm(w: VQWeightDev, X: torch.Tensor, Y: Optional[torch.Tensor] = None,
             ws: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Y[M][N] = scale * (X[M][K] @ dequant(W)^T) on the current stream (matrix cores)."""
+    if _marshal is not None and (r := _marshal.gemm(w, X, Y, ws)) is not NotImplemented:
+        return r
     M = X.shape[0]
     if Y is None:
         Y = X.new_empty((M, w.N))      # (X has to be fp16: checked below)
@@ -467,6 +491,8 @@ def vq_attn_decode_workspace(kv: VQKVDev) -> int:
 def vq_attn_decode(kv: VQKVDev, q: torch.Tensor, sm_scale: float, out: Optional[torch.Tensor] = None,
                    ws: Optional[torch.Tensor] = None) -> torch.Tensor:
     """out[B][H][D] = softmax(sm_scale * q K^T) V over the VQ cache, on the current stream."""
+    if _marshal is not None and (r := _marshal.attn_decode(kv, q, sm_scale, out, ws)) is not NotImplemented:
+        return r
     if out is None:
         out = torch.empty_like(q)
     d, l = ctypes.byref(kv.desc()), lib()
@@ -499,6 +525,8 @@ def vq_dequant(w: VQWeightDev, out_fp32: bool = True) -> torch.Tensor:
 
 def vq_kv_quantize(kv: VQKVDev, k_new: torch.Tensor, v_new: torch.Tensor, pos: int) -> None:
     """Quantize new tokens (fp16 [B][H][n][D] each) and store their codes at positions [pos, pos + n)."""
+    if _marshal is not None and _marshal.kv_quantize(kv, k_new, v_new, pos) is not NotImplemented:
+        return
     n = k_new.shape[2]
     d = kv.desc()
     _check(lib().vq_kv_quantize(ctypes.byref(d), _dev(k_new, "k_new", torch.float16),

@@ -1567,3 +1567,125 @@ def test_gemv_pipeline_small_codebook_list_as_replayed_graph(gpu_device):
         torch.cuda.synchronize()
     del g
     pipe.close()
+
+
+# ---------------------------------------------------------------- native marshalling of the Python calls
+
+def _both_ways(monkeypatch, f):
+    """f() as it is and with ctypes alone: (result or exception) of each."""
+    from paper_2503_02236_amd import binding
+    vq.lib()
+    assert binding._marshal is not None, "the native part of the binding is not built"
+    got = []
+    for native in (binding._marshal, None):
+        monkeypatch.setattr(binding, "_marshal", native)
+        try:
+            r = f()
+            torch.cuda.synchronize()
+        except Exception as e:  # noqa: BLE001
+            r = (type(e), str(e))
+        got.append(r)
+    monkeypatch.undo()
+    return got
+
+
+def _same(a, b):
+    if isinstance(a, (list, tuple)):
+        return type(a) is type(b) and len(a) == len(b) and all(_same(x, y) for x, y in zip(a, b))
+    if isinstance(a, torch.Tensor):
+        return a.dtype == b.dtype and a.shape == b.shape and a.stride() == b.stride() and a.device == b.device and torch.equal(a, b)
+    return a == b
+
+
+@pytest.mark.parametrize("fmt", ["u8x2", "u12x2", "u16", "pack", "tile"])
+def test_native_marshalling_gemv_gemm(gpu_device, monkeypatch, fmt):
+    v, bits, R, E = {"u8x2": (8, 8, 2, 256), "u12x2": (8, 12, 2, 4096), "u16": (8, 16, 1, 65536), "pack": (8, 16, 1, 65536), "tile": (4, 8, 1, 256)}[fmt]
+    if fmt == "tile":
+        wd = vq.weight_to_device(wl.gptvq_like_layer(0), gpu_device)
+    else:
+        w = wl.make_weight(512, 1024, v, bits, R, E, 0.02, seed=77, with_scale=fmt != "u16")
+        wd = vq.weight_to_device(w, gpu_device, prepack=fmt == "pack")
+    K = wd.K
+    x1, x5, X = (dev_x(wl.make_activations(n, K, seed=78 + n), gpu_device) for n in (1, 5, 300))
+    for f in (lambda: vq.vq_gemv(wd, x1), lambda: vq.vq_gemv(wd, x5), lambda: vq.vq_gemm(wd, X), lambda: vq.vq_gemm(wd, X=X[:40].contiguous()),
+              lambda: vq.vq_gemv_batch([wd, wd], [x1, x1]), lambda: vq.vq_gemv_batch((wd, wd), (x1, x1)),
+              # refused, or taken, alike: shapes, types, strides, scratch, host memory
+              lambda: vq.vq_gemv(wd, X), lambda: vq.vq_gemv(wd, x1.float()), lambda: vq.vq_gemv(wd, x5.t()), lambda: vq.vq_gemv(wd, x1.cpu()),
+              lambda: vq.vq_gemm(wd, X, ws=torch.empty(16, dtype=torch.uint8, device=gpu_device)), lambda: vq.vq_gemv(wd, x5[:0]),
+              lambda: vq.vq_gemv(wd, x1, y=torch.empty((1, wd.N), device=gpu_device)), lambda: vq.vq_gemv_batch([wd], [x1, x1]),
+              lambda: vq.vq_gemv_batch([], []), lambda: vq.vq_gemv(wd, x5[:, 1:]), lambda: vq.vq_gemv(wd, None)):
+        a, b = _both_ways(monkeypatch, f)
+        assert _same(a, b), (fmt, a, b)
+    y = torch.empty((5, wd.N), dtype=torch.float16, device=gpu_device)
+    assert vq.vq_gemv(wd, x5, y=y) is y and vq.vq_gemm(wd, X[:5].contiguous(), Y=y) is y
+    ys = [torch.empty((1, wd.N), dtype=torch.float16, device=gpu_device) for _ in range(2)]
+    assert vq.vq_gemv_batch([wd, wd], [x1, x1], ys) is ys
+    s = torch.cuda.Stream()
+    want = vq.vq_gemv(wd, x5)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        got = vq.vq_gemv(wd, x5)
+    s.synchronize()
+    assert torch.equal(got, want)
+
+
+def test_native_marshalling_attention(gpu_device, monkeypatch):
+    kv, q = wl.make_kv(2, 3, 128, 204, 4, 256, 1, seed=91), dev_x(wl.make_activations(6, 128, seed=92), gpu_device).view(2, 3, 128)
+    kd = vq.kv_to_device(kv, gpu_device)
+    new = torch.randn((2, 3, 4, 128), device=gpu_device).to(torch.float16)
+
+    def quantize(*args):
+        vq.vq_kv_quantize(kd, *args)
+        return kd.k_codes.clone(), kd.v_codes.clone()
+    for f in (lambda: vq.vq_attn_decode(kd, q, 0.09), lambda: vq.vq_attn_decode(kd, q, 1), lambda: vq.vq_attn_decode(kd, q.float(), 0.09),
+              lambda: vq.vq_attn_decode(kd, q.transpose(0, 1), 0.09), lambda: quantize(new, new * 0.5, 7), lambda: quantize(new, new, 199),
+              lambda: quantize(new, new.float(), 0), lambda: quantize(new, new, 3.0), lambda: quantize(new[:, :, :0], new, 0)):
+        a, b = _both_ways(monkeypatch, f)
+        assert _same(a, b), (a, b)
+    kd.seq_lens = torch.tensor([150, 3], dtype=torch.int32, device=gpu_device)
+    a, b = _both_ways(monkeypatch, lambda: vq.vq_attn_decode(kd, q, 0.09))
+    assert _same(a, b)
+    kd.seq_lens = torch.tensor([150, 3], device=gpu_device)      # int64: refused
+    a, b = _both_ways(monkeypatch, lambda: vq.vq_attn_decode(kd, q, 0.09))
+    assert a == b and a[0] is TypeError
+
+
+def test_native_marshalling_leaves_what_is_not_plain_to_python(gpu_device):
+    from paper_2503_02236_amd import binding
+    from torch.overrides import TorchFunctionMode
+    w, x = wl.config1_tiny()
+    wd, x = vq.weight_to_device(w, gpu_device), dev_x(x, gpu_device)
+    native = binding._marshal
+
+    class Sub(torch.Tensor):
+        pass
+
+    class SubWeight(vq.VQWeightDev):
+        pass
+
+    class Mode(TorchFunctionMode):
+        seen = 0
+
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            Mode.seen += "new_empty" in str(func)
+            return func(*args, **(kwargs or {}))
+    want = vq.vq_gemv(wd, x)
+    sub = SubWeight(**{f: getattr(wd, f) for f in wd.__dataclass_fields__})
+    assert native.gemv(wd, x, None, None) is not NotImplemented
+    assert native.gemv(wd, x.as_subclass(Sub), None, None) is NotImplemented and native.gemv(sub, x, None, None) is NotImplemented
+    assert torch.equal(vq.vq_gemv(sub, x), want)
+    with Mode():
+        assert native.gemv(wd, x, None, None) is NotImplemented
+        assert torch.equal(vq.vq_gemv(wd, x), want)
+    assert Mode.seen == 1
+    g = torch.cuda.CUDAGraph()          # captured like any other call
+    y = torch.zeros_like(want)
+    vq.vq_gemv(wd, x, y=y)
+    with torch.cuda.graph(g):
+        vq.vq_gemv(wd, x, y=y)
+    for _ in range(3):
+        y.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want)
