@@ -1569,6 +1569,36 @@ def test_gemv_pipeline_small_codebook_list_as_replayed_graph(gpu_device):
     pipe.close()
 
 
+# Long ranges with copies of the codebooks: weights without a running maximum where the scores are bounded, with one where they are
+# not (a large scale, or an entry that is infinite, used or not); empty, one-token and ragged sequences
+@pytest.mark.parametrize("kind", ["bounded", "near_the_bound", "large_scale", "infinite_entry_unused", "nan_entry_unused", "negative_scale"])
+def test_attn_decode_bounded_scores(gpu_device, kind):
+    B, H, T, D, v, E = 16, 32, 4096, 128, 4, 256
+    from paper_2503_02236_amd.binding import vq_kv_t
+    g = torch.Generator(device=gpu_device).manual_seed(8800)
+    codes = [torch.randint(0, E - 1, (B, H, T, D // v), generator=g, device=gpu_device, dtype=torch.int32).to(torch.uint8) for _ in range(2)]
+    cb = [torch.randn((H, 1, E, v), generator=g, device=gpu_device).to(torch.float16) for _ in range(2)]
+    q = torch.randn((B, H, D), generator=g, device=gpu_device).to(torch.float16)
+    scale = {"near_the_bound": 0.16, "large_scale": 2.5, "negative_scale": -0.09}.get(kind, 0.088)
+    if "unused" in kind:    # (no code is E - 1)
+        cb[0][:, 0, E - 1, 1] = float("inf") if kind.startswith("inf") else float("nan")
+        cb[1][:, 0, E - 1, 0] = float("nan")
+    kv = vq.VQKVDev(B, H, D, T, v, codes[0], codes[1], cb[0], cb[1])
+    kv.seq_lens = torch.tensor([0, 1, 33, 4095] + [4096 - 300 * i for i in range(12)], dtype=torch.int32, device=gpu_device)
+    import ctypes as ct
+    d = kv.desc()
+    f = vq.lib()._ZN2vq15attn_replicatedEPK7vq_kv_t
+    f.restype = ct.c_bool
+    assert f(ct.byref(d)) and isinstance(d, vq_kv_t)
+    out = vq.vq_attn_decode(kv, q, scale).double().cpu()
+    assert (out[0] == 0).all()
+    for b, h in [(1, 0), (2, 31), (3, 7), (4, 0), (9, 16), (15, 31)]:
+        n = int(kv.seq_lens[b])
+        K, V = (cb[i][h, 0].double().cpu()[codes[i][b, h, :n].long().cpu()].reshape(n, D) for i in range(2))
+        p = torch.softmax(scale * (K @ q[b, h].double().cpu()), 0)
+        assert_close(out[b, h], (p @ V).numpy(), f"{kind} b{b} h{h}")
+
+
 # ---------------------------------------------------------------- native marshalling of the Python calls
 
 def _both_ways(monkeypatch, f):
