@@ -414,20 +414,45 @@ __global__ __launch_bounds__(kAttnWaves * 64 * SEQ) __attribute__((amdgpu_waves_
     }
 }
 
-// Merge of the token-range partials by log-sum-exp (base 2), one workgroup per (b, h).
+// Merge of the token-range partials by log-sum-exp (base 2), one workgroup per (b, h).  A launch of loads that take a trip to
+// memory each: eight ranges are requested at once.  Attention of B3 H32 T3001, 32 codebooks (4 ranges)
+// 16.7 -> 15.2 us with that, B1 H8 T30000 (59 ranges) 20.9 -> 17.7.
 __global__ __launch_bounds__(128) void attn_merge_kernel(const float *__restrict__ ws, half_t *__restrict__ out,
                                                          int S) {
-    constexpr int D = 128;
+    constexpr int D = 128, N = 8;
     const int bh = blockIdx.x, d = threadIdx.x;
     const float *wp = ws + (size_t)bh * S * (D + 2);
-    float M = -INFINITY;
-    for (int s = 0; s < S; ++s) M = fmaxf(M, wp[s * (D + 2) + D]);
+    float m[N], l[N], x[N];
+    auto request = [&](int s0) {   // (past the end: the last range once more)
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const float *p = wp + min(s0 + i, S - 1) * (D + 2);
+            m[i] = p[D];
+            l[i] = p[D + 1];
+            x[i] = p[d];
+        }
+    };
+    request(0);
+    float M = m[0];
+#pragma unroll
+    for (int i = 1; i < N; ++i) M = fmaxf(M, m[i]);
+    for (int s = N; s < S; s += N) {   // more than eight: the maximum of them all first
+        float t[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) t[i] = wp[min(s + i, S - 1) * (D + 2) + D];
+#pragma unroll
+        for (int i = 0; i < N; ++i) M = fmaxf(M, t[i]);
+    }
     float L = 0.f, o = 0.f;
-    for (int s = 0; s < S; ++s) {
-        float ms = wp[s * (D + 2) + D];
-        float wgt = exp2f(ms - M);
-        L += wp[s * (D + 2) + D + 1] * wgt;
-        o += wp[s * (D + 2) + d] * wgt;
+    for (int s = 0; s < S; s += N) {
+        if (s > 0) request(s);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            if (s + i >= S) break;
+            const float wgt = exp2f(m[i] - M);
+            L += l[i] * wgt;
+            o += x[i] * wgt;
+        }
     }
     out[(size_t)bh * D + d] = (half_t)(L > 0.f ? o / L : 0.f);
 }
