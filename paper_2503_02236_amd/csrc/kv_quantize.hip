@@ -26,6 +26,7 @@ struct KvQuantArgs {
     int PG;                // sub-vectors per group of the codebook
     unsigned pg_inverse;   // kvq_inverse(PG) (matrix-core kernel)
     int log_lanes;         // lanes that share an item (kv_quantize_lane_kernel)
+    int share;             // workgroups that share a token range (kv_quantize_scan_kernel)
 };
 
 // A sub-vector (V halves, aligned) in the low halves of 16 bytes, the rest zero.
@@ -98,17 +99,20 @@ __device__ __forceinline__ int kvq_wave_argmin(float d, int e) {
 // single sub-vector -- coupled quantization -- is read once and used once) and the sub-vectors come one after the other.
 // Bound: the latency of two dependent loads and, per sub-vector, four distances and one reduction over the lanes.  One
 // token of B3 H32 with 32 codebooks per head and side: 5.3 us, where staging both sides' codebooks in LDS took 14.7.
-template <int V>
+// SHARED: several workgroups share a token range.
+template <int V, bool SHARED>
 __global__ __launch_bounds__(512) void kv_quantize_scan_kernel(KvQuantArgs a) {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, NW = blockDim.x >> 6;
-    const int bh = blockIdx.x, h = bh % a.H, side = blockIdx.z;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    constexpr int NW = 8;
+    const int bh = blockIdx.x, h = bh % a.H, side = SHARED ? blockIdx.z & 1 : blockIdx.z;
     const int t0 = blockIdx.y * a.tokens, nt = min(a.tokens, a.n_new - t0);
     const half_t *src = a.cb[side] + (size_t)h * a.G * a.E * V;
     const half_t *xs = a.x[side] + ((size_t)bh * a.n_new + t0) * a.D;
     uint8_t *dst = a.codes[side] + ((size_t)bh * a.T + a.pos + t0) * a.P;
     const int n_items = nt * a.PG;                // per group
-    const int R = max(1, NW / a.G);               // wavefronts that share a group
-    for (int u = wave; u < a.G * R; u += NW) {
+    const int all = SHARED ? NW * a.share : NW;   // wavefronts of the workgroups that share these tokens
+    const int R = max(1, all / a.G);              // wavefronts that share a group
+    for (int u = (SHARED ? NW * (blockIdx.z >> 1) : 0) + wave; u < a.G * R; u += all) {
         const int g = u / R;
         V16 c[4];
 #pragma unroll
@@ -623,7 +627,17 @@ int run_kvq(KvQuantArgs &a, int bh, hipStream_t s) {
     if (kernel == kKvqLane) return run_kvq_lane<V>(a, bh, s);
     if (kernel == kKvqScan) {
         a.tokens = std::min(a.n_new, kQuantScanTokens);
-        kv_quantize_scan_kernel<V><<<dim3(bh, (a.n_new + a.tokens - 1) / a.tokens, 2), 512, 0, s>>>(a);
+        // Workgroups that share the items of a token range, up to four: a wavefront takes its groups and items one after the other,
+        // each a trip to memory or a reduction, so few sequences are spread over the chip.  32 codebooks of v = 4 per head and side,
+        // H32, one token: B1 5.0 -> 3.0 us, B3 5.0 -> 4.4, four tokens 10.7 -> 7.3; beyond 768 workgroups only long chains gain (B8, one
+        // token 6.6 / 6.7; 64 codebooks of v = 2, six tokens 34.5 -> 29.3).
+        const int ranges = ceil_div(a.n_new, a.tokens);
+        a.share = 1;
+        while (a.share < 4 && 16 * a.share <= a.tokens * a.P && (long)bh * 4 * ranges * a.share <= (a.tokens * a.P >= 128 * a.share ? 1024 : 768)) a.share *= 2;
+        if (a.share > 1)
+            kv_quantize_scan_kernel<V, true><<<dim3(bh, ranges, 2 * a.share), 512, 0, s>>>(a);
+        else
+            kv_quantize_scan_kernel<V, false><<<dim3(bh, ranges, 2), 512, 0, s>>>(a);
         return launch_status();
     }
     a.pg_inverse = kvq_inverse(a.PG);
