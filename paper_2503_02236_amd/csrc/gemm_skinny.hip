@@ -101,284 +101,15 @@ constexpr int skinny_depth(int epi, int u, bool l2, int rt, int ct) {
 // L2CB: entries are gathered from global memory (L2); otherwise the codebooks are staged in LDS.
 template <typename CodeT, int V, int R, bool L2CB, int RT, int CT>
 __global__ __launch_bounds__(64 * skinny_max_waves(L2CB, RT, CT)) void gemm_skinny_kernel(SkinnyArgs a) {
-    constexpr int BITS = SkinnyShape<CodeT, V, R>::BITS, LB = SkinnyShape<CodeT, V, R>::LB;
-    constexpr int CPO = 8 / V;                         // entries side by side in an operand
-    constexpr int MPI = LB * 8 / (BITS * R * CPO);     // operands per lane and iteration
-    static_assert(MPI * BITS * R * CPO == LB * 8, "whole operands per code load");
-    static_assert(R <= 2, "operands are summed in fp16 (one rounding)");
-    constexpr bool TR = LB != 12 && BITS * R * CPO <= 32;   // whole operands per dword: transpose
-    constexpr int NS = TR ? LB / 4 : 1, OPD = MPI / NS;     // steps per iteration, operands per step
-    // X goes through LDS in units of U operands (32 U k) x 16 tokens, private to the wavefront.  D units per lane are
-    // in flight in registers.
-    constexpr int U = skinny_unit(MPI, OPD), NU = MPI / U, SEGS = 4 * U, EPI = NU * CT;
-    constexpr int D = skinny_depth(EPI, U, L2CB, RT, CT);
-    static_assert(D <= EPI && MPI % U == 0 && EPI % D == 0 && (!L2CB || NU % 2 == 0), "slots are the same in every iteration");
-
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, nwaves = blockDim.x >> 6;
-    const int r = lane & 15, g = lane >> 4;
-    const int n0 = (blockIdx.x / a.groups_m) * 16 * RT, m0 = (blockIdx.x % a.groups_m) * 16 * CT;
-    const int row_bytes = a.ops * CPO * R * BITS / 8;
-    const int slot = !TR || NS == 4 ? g : ((g & 1) << 1) | (g >> 1);   // (two dwords: one swap, lanes 1 and 2 of a row change places)
-
-    const unsigned char *cbase = reinterpret_cast<const unsigned char *>(a.codes) + (size_t)n0 * row_bytes;
-    uint32_t crow[RT];
-#pragma unroll
-    for (int t = 0; t < RT; ++t)   // rows past the end are computed and dropped
-        crow[t] = (uint32_t)(min(n0 + 16 * t + r, a.N - 1) - n0) * (uint32_t)row_bytes;
-    // X loads: instruction j of a unit covers 64 / SEGS tokens, whole contiguous rows of SEGS 16-byte segments
-    const int xseg = lane % SEGS, xtok = lane / SEGS;
-    uint32_t xrow[CT][U];   // byte offsets (kSkinnyMaxX)
-#pragma unroll
-    for (int c = 0; c < CT; ++c)
-#pragma unroll
-        for (int j = 0; j < U; ++j) xrow[c][j] = (uint32_t)min(m0 + 16 * c + j * (64 / SEGS) + xtok, a.M - 1) * (uint32_t)(a.K * 2);
-
-    // Loads carry no condition: a lane past the end of its row reads the row's last bytes, and what it makes of them
-    // is zeroed (both operands: an infinity there must not meet a zero).
-    auto load_codes = [&](int it, int t, V16 &cd) {
-        const unsigned char *p = cbase + (crow[t] + (uint32_t)min((it * 4 + g) * LB, row_bytes - LB));
-        if (LB == 16) {
-            cd = ld16(p);
-        } else if (LB == 12) {
-            const uint32_t *c3 = reinterpret_cast<const uint32_t *>(p);
-            cd.w[0] = c3[0];
-            cd.w[1] = c3[1];
-            cd.w[2] = c3[2];
-            cd.w[3] = 0;
-        } else {
-            const V8 c8 = ld8(p);
-            cd.w[0] = c8.w[0];
-            cd.w[1] = c8.w[1];
-            cd.w[2] = cd.w[3] = 0;
-        }
-    };
-    auto transpose = [&](V16 &cd) {
-        if (TR && NS == 4) {
-            swap32(cd.w[0], cd.w[2]);
-            swap32(cd.w[1], cd.w[3]);
-            swap16(cd.w[0], cd.w[1]);
-            swap16(cd.w[2], cd.w[3]);
-        } else if (TR && NS == 2) {
-            swap32(cd.w[0], cd.w[1]);
-        }
-    };
-    // position (in operands) of this lane's operand o of an iteration
-    auto op_index = [&](int it, int o) { return it * 4 * MPI + ((o / OPD) * 4 + slot) * OPD + o % OPD; };
-    const int cb_bytes = L2CB ? 0 : (R * a.E * V * 2 * a.tiles_k + 15) & ~15;
-    unsigned char *stage = smem + cb_bytes + wave * (U * 1024);
-    // slot of 16-byte segment `seg` of token `tok` of a unit: the 16 tokens of a pass over the banks get different ones
-    auto stage_off = [&](int tok, int seg) {
-        const int swz = U == 2 ? (tok ^ (tok >> 3)) & 7 : tok & (SEGS < 16 ? SEGS - 1 : 15);
-        return tok * (SEGS * 16) + ((seg ^ swz) << 4);
-    };
-    // A unit is whole steps of the four lanes of a row (their operands lie side by side), or a part of one step (U of the OPD
-    // operands of each of the four lanes).
-    constexpr bool PART = U < OPD;
-    static_assert(PART ? OPD % U == 0 : U % OPD == 0, "units and steps");
-    const int xlane = PART ? (xseg / U) * OPD + xseg % U : xseg;
-    auto load_x = [&](int it, int e, V16 (&xb)[U]) {   // unit e / CT, token tile e % CT
-        const int u = e / CT, first = PART ? u * U / OPD * (4 * OPD) + u * U % OPD : u * SEGS;
-        const uint32_t k = min(it * (4 * MPI) + first + xlane, a.ops - 1) * 16;
-#pragma unroll
-        for (int j = 0; j < U; ++j) xb[j] = ld16(reinterpret_cast<const unsigned char *>(a.x) + (xrow[e % CT][j] + k));
-    };
-    // registers -> LDS -> operands (a wavefront's LDS operations are carried out in order: one buffer is enough)
-    auto stage_x = [&](const V16 (&xb)[U], half8_t (&xo)[U]) {
-#pragma unroll
-        for (int j = 0; j < U; ++j) *reinterpret_cast<uint4 *>(stage + stage_off(j * (64 / SEGS) + xtok, xseg)) = xb[j].u;
-#pragma unroll
-        for (int q = 0; q < U; ++q)
-            xo[q] = *reinterpret_cast<const half8_t *>(stage + stage_off(r, PART ? slot * U + q : ((q / OPD) * 4 + slot) * OPD + q % OPD));
-    };
-    const half_t *cbl = reinterpret_cast<const half_t *>(smem);
-    const int set_halves = R * a.E * V;
-    auto entry = [&](unsigned idx, int set) {   // entry idx of the concatenated codebooks (LDS) or of the codebook (L2)
-        V16 e;
-        e.u = make_uint4(0, 0, 0, 0);
-        if (L2CB) {
-            const unsigned char *p = reinterpret_cast<const unsigned char *>(a.cb) + idx * (unsigned)(V * 2);
-            if (V == 8) {
-                e = ld16(p);
-            } else {
-                const V8 t = ld8(p);
-                e.w[0] = t.w[0];
-                e.w[1] = t.w[1];
-            }
-        } else {
-            const half_t *p = cbl + set + idx * V;
-            if (V == 8) {
-                e = ld16(p);
-            } else {
-                const V8 t = ld8(p);
-                e.w[0] = t.w[0];
-                e.w[1] = t.w[1];
-            }
-        }
-        return e;
-    };
-    auto load_entries = [&](int it, int u, const V16 (&cd)[RT], V16 (&ev)[U][RT][CPO][R]) {
-#pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const int o = u * U + q;
-            int set = 0;
-            if (!L2CB && a.tiles_k > 1) set = min(op_index(it, o) / a.tile_ops, a.tiles_k - 1) * set_halves;
-#pragma unroll
-            for (int t = 0; t < RT; ++t)
-#pragma unroll
-                for (int h = 0; h < CPO; ++h)
-#pragma unroll
-                    for (int rr = 0; rr < R; ++rr)
-                        ev[q][t][h][rr] = entry(rr * a.E + skinny_code<CodeT>(cd[t], (o * CPO + h) * R + rr), set);
-        }
-    };
-
-    // codes of this iteration, of the next one and of the one after that (a wavefront whose iterations have run out
-    // repeats the last one and does not use it)
-    V16 cd[RT], cn[RT], cf[RT];
-    V16 xr[D][U];
-    V16 er[L2CB ? 2 : 1][U][RT][CPO][R];
-    const int first = min(wave, a.nit - 1);
-#pragma unroll
-    for (int t = 0; t < RT; ++t) load_codes(first, t, cd[t]);
-#pragma unroll
-    for (int t = 0; t < RT; ++t) load_codes(min(wave + nwaves, a.nit - 1), t, cn[t]);
-#pragma unroll
-    for (int e = 0; e < D; ++e) load_x(first, e, xr[e]);
-    // scales of the rows that this lane writes at the end, as raw halves (row tile wave % RT; else read there)
-    half_t sc4[4];
-    {
-        const half_t *sp = a.scale ? a.scale : a.x;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) sc4[i] = sp[a.scale ? min(n0 + 16 * (wave % RT) + 4 * g + i, a.N - 1) : 0];
-    }
-    if (!L2CB) {
-        const half_t *src = a.cb + (a.tile_n > 0 ? (size_t)(n0 / a.tile_n) * a.tiles_k * set_halves : 0);
-        const int n16 = set_halves * a.tiles_k / 8;
-        for (int i = tid; i < n16; i += blockDim.x) reinterpret_cast<uint4 *>(smem)[i] = reinterpret_cast<const uint4 *>(src)[i];
-        __syncthreads();
-    }
-#pragma unroll
-    for (int t = 0; t < RT; ++t) transpose(cd[t]);
-    if (L2CB) load_entries(first, 0, cd, er[0]);
-
-    float4v_t acc[RT][CT];
-#pragma unroll
-    for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int c = 0; c < CT; ++c) acc[t][c] = float4v_t{0.f, 0.f, 0.f, 0.f};
-
-    half8_t xo[U];
-    {   // element 0 is staged ahead, and so is every next element before the current one is multiplied
-        stage_x(xr[0], xo);
-        load_x(D < EPI ? first : min(first + nwaves, a.nit - 1), D % EPI, xr[0]);
-    }
-    for (int it = wave; it < a.nit; it += nwaves) {
-        const int nx = min(it + nwaves, a.nit - 1);
-        const bool tail = (it + 1) * 4 * MPI > a.ops;   // some lanes of this iteration are past the end of the row
-#pragma unroll
-        for (int t = 0; t < RT; ++t) load_codes(min(it + 2 * nwaves, a.nit - 1), t, cf[t]);
-#pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            if (L2CB) {
-                if (u + 1 == NU) {
-#pragma unroll
-                    for (int t = 0; t < RT; ++t) {
-                        cd[t] = cn[t];
-                        transpose(cd[t]);
-                    }
-                }
-                load_entries(u + 1 < NU ? it : nx, (u + 1) % NU, cd, er[(u + 1) & 1]);
-            } else {
-                load_entries(it, u, cd, er[0]);
-            }
-            // the operands: one entry, or the fp16 sum of two (one rounding, that of their fp32 sum)
-            V16 op[U][RT];
-#pragma unroll
-            for (int q = 0; q < U; ++q) {
-#pragma unroll
-                for (int t = 0; t < RT; ++t) {
-                    const V16 (&e)[CPO][R] = er[L2CB ? u & 1 : 0][q][t];
-#pragma unroll
-                    for (int h = 0; h < CPO; ++h) {
-#pragma unroll
-                        for (int p = 0; p < V / 2; ++p) {
-                            half2_t s = e[h][0].h2[p];
-                            if (R == 2) s += e[h][R - 1].h2[p];
-                            op[q][t].h2[h * (V / 2) + p] = s;
-                        }
-                    }
-                }
-            }
-            if (tail) {
-#pragma unroll
-                for (int q = 0; q < U; ++q)
-                    if (op_index(it, u * U + q) >= a.ops) {
-#pragma unroll
-                        for (int t = 0; t < RT; ++t) op[q][t].u = make_uint4(0, 0, 0, 0);
-                    }
-            }
-#pragma unroll
-            for (int c = 0; c < CT; ++c) {
-                const int e = u * CT + c;
-                half8_t xc[U];
-#pragma unroll
-                for (int q = 0; q < U; ++q) xc[q] = xo[q];
-                stage_x(xr[(e + 1) % D], xo);
-                {
-                    const int f = e + 1 + D;   // element f of this iteration, or of one of the next two
-                    load_x(f < EPI ? it : f < 2 * EPI ? nx : min(it + 2 * nwaves, a.nit - 1), f % EPI, xr[(e + 1) % D]);
-                }
-                if (tail) {
-#pragma unroll
-                    for (int q = 0; q < U; ++q)
-                        if (op_index(it, u * U + q) >= a.ops) xc[q] = half8_t{0, 0, 0, 0, 0, 0, 0, 0};
-                }
-#pragma unroll
-                for (int q = 0; q < U; ++q)
-#pragma unroll
-                    for (int t = 0; t < RT; ++t) acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(op[q][t].h8, xc[q], acc[t][c], 0, 0, 0);
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < RT; ++t) {
-            if (!L2CB) {
-                cd[t] = cn[t];
-                transpose(cd[t]);
-            }
-            cn[t] = cf[t];
-        }
-    }
-
-    // partial tiles -> LDS [tile][wavefront][lane] (over the codebooks), added in wavefront order, tile t by wavefront t
-    // mod the wavefronts.  Lane (r, g) of a tile holds token r, rows 4 g + 0..3.
-    float4v_t *red = reinterpret_cast<float4v_t *>(smem);
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < CT; ++c)
-#pragma unroll
-        for (int t = 0; t < RT; ++t) red[((c * RT + t) * nwaves + wave) * 64 + lane] = acc[t][c];
-    __syncthreads();
-    for (int i = wave; i < RT * CT; i += nwaves) {
-        float4v_t sum = red[(i * nwaves) * 64 + lane];
-        for (int w = 1; w < nwaves; ++w) sum += red[(i * nwaves + w) * 64 + lane];
-        const int t = i % RT, m = m0 + 16 * (i / RT) + r, n = n0 + 16 * t + 4 * g;
-        if (m >= a.M) continue;
-        half4_t o;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float sc = !a.scale ? 1.f : t == wave % RT ? (float)sc4[j] : (float)a.scale[min(n + j, a.N - 1)];
-            o[j] = (half_t)(sum[j] * sc);
-        }
-        half_t *yp = a.y + (size_t)m * a.N + n;
-        if ((a.N & 3) == 0) {
-            if (n < a.N) *reinterpret_cast<half4_t *>(yp) = o;
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (n + j < a.N) yp[j] = o[j];
-        }
-    }
+#include "gemm_skinny_body.inc"
+}
+// 48 tokens: what X costs a workgroup is by the token, and one of 33 to 48, or two of 65 to 96, read a quarter less than with 64.
+// 4096 x 4096, two 256-entry codebooks, 77 tokens 12.8 -> 11.3 us, 48 tokens 10.4 -> 9.2; one, K = 11008, 80 tokens 23.1 -> 18.3.
+template <typename CodeT, int V, int R, int RT>
+__global__ __launch_bounds__(64 * skinny_max_waves(false, RT, 3)) void gemm_skinny_48_kernel(SkinnyArgs a) {
+    constexpr bool L2CB = false;
+    constexpr int CT = 3;
+#include "gemm_skinny_body.inc"
 }
 
 // Elements of X of one launch: its kernel holds byte offsets into X in 32 bits.  At least 384 tokens (K <= 2^22), whole
@@ -428,14 +159,19 @@ int run_tile(const vq_weight_t *w, const half_t *x, int M, half_t *y, hipStream_
         if (lds_of(n) <= kSkinnyLds && (grid <= 256 || per_cu(n) == per_cu(waves))) waves = n;
     const size_t lds = lds_of(waves);
     static KernelSetup setup;
-    if (int st = kernel_setup(reinterpret_cast<const void *>(&gemm_skinny_kernel<CodeT, V, R, L2CB, RT, CT>), lds, false, setup)) return st;
-    gemm_skinny_kernel<CodeT, V, R, L2CB, RT, CT><<<(int)grid, waves * 64, lds, s>>>(a);
+    void (*kernel)(SkinnyArgs);
+    if constexpr (CT == 3)
+        kernel = &gemm_skinny_48_kernel<CodeT, V, R, RT>;
+    else
+        kernel = &gemm_skinny_kernel<CodeT, V, R, L2CB, RT, CT>;
+    if (int st = kernel_setup(reinterpret_cast<const void *>(kernel), lds, false, setup)) return st;
+    kernel<<<(int)grid, waves * 64, lds, s>>>(a);
     return launch_status();
 }
 
 // The tiles that are built, {RT, CT}.
 struct SkinnyTile { int rt, ct; };
-constexpr SkinnyTile kLdsTiles[] = {{1, 1}, {1, 2}, {2, 2}, {2, 4}, {4, 4}};   // ({1, 4} was never the best)
+constexpr SkinnyTile kLdsTiles[] = {{1, 1}, {1, 2}, {2, 2}, {2, 4}, {4, 4}, {2, 3}, {1, 3}};   // ({1, 4} was never the best)
 constexpr SkinnyTile kL2Tiles[] = {{1, 1}, {1, 2}, {1, 4}, {2, 4}, {1, 8}, {2, 8}};
 
 // Estimated clocks of a launch: a workgroup's lookups (3.5 per clock from LDS, 0.35 from L2) and X (41 bytes per clock)
@@ -447,9 +183,10 @@ constexpr SkinnyTile kL2Tiles[] = {{1, 1}, {1, 2}, {1, 4}, {2, 4}, {1, 8}, {2, 8
 int skinny_tile(const vq_weight_t *w, int M, bool l2, double staging = 0, double *us = nullptr) {
     int best = 0;
     double best_cost = 1e300;
-    for (int i = 0; i < (l2 ? 6 : 5); ++i) {
+    for (int i = 0; i < (l2 ? 6 : 7); ++i) {
         const SkinnyTile t = l2 ? kL2Tiles[i] : kLdsTiles[i];
         if (w->cb_tile_n > 0 && w->cb_tile_n % (16 * t.rt) != 0) continue;
+        if (t.ct == 3 && M > 256) continue;   // (X no longer fits a die's L2, and more workgroups that read it lose: N = 256, K = 4096, 700 tokens 10.1 -> 11.7)
         if (w->code_bits == 12 && t.rt == 4) continue;   // (four operands per lane and unit: does not fit the registers)
         const double r = (double)(((long)w->N + 16 * t.rt - 1) / (16 * t.rt)) * ((M + 16 * t.ct - 1) / (16 * t.ct)) / 256;
         const double rounds = l2 ? (r <= 1 ? std::max(0.7, r) : r + 0.3) : r <= 1 ? 1.0 : r <= 2 ? 2.0 : r + 0.3;
@@ -474,6 +211,8 @@ int run_lds(int tile, const vq_weight_t *w, const half_t *x, int M, half_t *y, h
         case 1: return run_tile<CodeT, V, R, false, 1, 2>(w, x, M, y, s);
         case 2: return run_tile<CodeT, V, R, false, 2, 2>(w, x, M, y, s);
         case 3: return run_tile<CodeT, V, R, false, 2, 4>(w, x, M, y, s);
+        case 5: return run_tile<CodeT, V, R, false, 2, 3>(w, x, M, y, s);
+        case 6: return run_tile<CodeT, V, R, false, 1, 3>(w, x, M, y, s);
         default:
             if constexpr (!std::is_same<CodeT, Code12>::value) return run_tile<CodeT, V, R, false, 4, 4>(w, x, M, y, s);
             return VQ_ERR_UNSUPPORTED;

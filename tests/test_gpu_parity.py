@@ -900,6 +900,16 @@ def test_gemm_skinny_many_tokens_half_a_block_of_k(gpu_device, N, K, M, v, bits,
     assert_close(Y, oracle.gemm(ocodes(w), w.codebooks, w.scale, X), f"skinny gemm {M}x{N}x{K} v{v} b{bits} R{R}")
 
 
+# tiles of 48 tokens, with one and with two row tiles: their edges, ragged N and K, every format
+@pytest.mark.parametrize("N,K,M", [(33, 192, 33), (4100, 192, 48), (4100, 1216, 65), (2051, 320, 96), (1000, 2304, 140), (8200, 448, 47)])
+@pytest.mark.parametrize("v,bits,R,E", [(8, 8, 1, 256), (8, 8, 2, 200), (4, 8, 1, 256), (4, 8, 2, 100), (8, 12, 2, 1000), (8, 12, 1, 4096), (8, 16, 1, 4096), (4, 16, 2, 900)])
+def test_gemm_skinny_48_tokens(gpu_device, N, K, M, v, bits, R, E):
+    w = wl.make_weight(N, K, v, bits, R, E, 0.02 / R, seed=4990 + N + M)
+    X = wl.make_activations(M, K, seed=4991 + M)
+    Y = vq.vq_gemm(vq.weight_to_device(w, gpu_device), dev_x(X, gpu_device))
+    assert_close(Y, oracle.gemm(ocodes(w), w.codebooks, w.scale, X), f"skinny gemm {M}x{N}x{K} v{v} b{bits} R{R}")
+
+
 def test_gemm_skinny_x_beyond_32_bit_offsets(gpu_device):
     # 513 tokens of K = 2^22 - 32: byte offsets into X fit 32 bits for 512 tokens, so the last one goes in a second launch
     N, K, M = 16, (1 << 22) - 32, 513

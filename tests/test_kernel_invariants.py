@@ -225,6 +225,18 @@ def test_gemm_skinny_keeps_its_operands_in_registers(tmp_path):
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
+def test_gemm_skinny_tiles_of_48_tokens_keep_their_registers(tmp_path):
+    out = tmp_path / "gemm_skinny.s"
+    cmd = [HIPCC, "-O3", "-std=c++17", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang",
+           "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "--cuda-device-only", "-S",
+           os.path.join(CSRC, "gemm_skinny.hip"), "-o", str(out)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    scratch = re.findall(r"\.amdhsa_kernel \S*gemm_skinny_48_kernel\S*\n.*?\.amdhsa_private_segment_fixed_size (\d+)", out.read_text(), re.S)
+    assert scratch == ["0"] * (12 * 2)     # one and two row tiles of every format
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
 def test_gemv_lut_keeps_its_ring_of_requests_in_flight(tmp_path):
     """The table-lookup kernel requests codes eight steps ahead with ordinary loads: none by asm (whose registers the compiler
     would take as written at once), and in front of each of the eight steps a wait that leaves the seven younger requests (two
