@@ -47,12 +47,12 @@ __global__ __launch_bounds__(256) void dequant_kernel(const void *__restrict__ c
     }
 }
 
-// The fp16 tile of one or two per-tensor codebooks, the first stage of the prefill product: kDequantUnroll sub-vectors per
+// The fp16 tile of one or two per-tensor codebooks in row order (vq_dequant, and the product of a K beyond 2^22): kDequantUnroll sub-vectors per
 // thread, 256 apart, so that every load and store is coalesced.  What bounds it is one gather per code from L1 or L2, and
 // for that many gathers have to be in flight: with one sub-vector per thread a thread waits for its code (a trip to memory),
 // then for its entry, and is gone.  N = 11008, K = 4096: two 256-entry codebooks 27.0 -> 19.1 us, 12-bit codes 44.0 -> 38.8,
-// 2^16 entries 30.3 -> 30.1 (gathers from L2 alone 24); with 2048 tokens the whole product 221.7 -> 214.4.  Non-temporal
-// stores are 2 us faster here, but the dense kernel then finds less of the tile in L2 and loses more than that.  Below 512
+// 2^16 entries 30.3 -> 30.1 (gathers from L2 alone 24).  Non-temporal
+// stores are 2 us faster here, but a product behind it then finds less of the tile in L2 and loses more than that.  Below 512
 // workgroups the plain kernel has more wavefronts: N = 300, K = 1024 2.4 us, here 3.3.
 constexpr int kDequantUnroll = 8;
 template <typename CodeT, int V, int R>

@@ -98,8 +98,8 @@ __device__ __forceinline__ int kvq_wave_argmin(float d, int e) {
 // group's codebook in registers (entry lane + 64 k, straight from memory: nothing is staged, so a codebook that serves a
 // single sub-vector -- coupled quantization -- is read once and used once) and the sub-vectors come one after the other.
 // Bound: the latency of two dependent loads and, per sub-vector, four distances and one reduction over the lanes.  One
-// token of B3 H32 with 32 codebooks per head and side: 5.3 us, where staging both sides' codebooks in LDS took 14.7.
-// SHARED: several workgroups share a token range.
+// token of B3 H32 with 32 codebooks per head and side: 4.4 us (5.3 with a workgroup per
+// token range), where staging both sides' codebooks in LDS took 14.7.  SHARED: several workgroups share a token range.
 template <int V, bool SHARED>
 __global__ __launch_bounds__(512) void kv_quantize_scan_kernel(KvQuantArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
