@@ -151,8 +151,7 @@ __device__ __forceinline__ void gemv_mfma_body(const GemvMfmaArgs &a, const int 
     // all codebooks (with per-tile codebooks: the sets of the tiles this workgroup's 16 rows cross), or (HOT,
     // one codebook) its first n_hot entries
     const half_t *cb_src = a.cb + (a.tile_n > 0 ? (size_t)(n0 / a.tile_n) * a.tiles_k * set_halves : 0);
-    for (int i = tid; i < cb_bytes / 16; i += blockDim.x)
-        reinterpret_cast<uint4 *>(cbl)[i] = reinterpret_cast<const uint4 *>(cb_src)[i];
+    stage_lds(cb_src, smem, cb_bytes / 16, __builtin_amdgcn_readfirstlane(wave), nwaves, lane);
     __syncthreads();
 
     float4v_t acc[RT];

@@ -608,25 +608,6 @@ __device__ __forceinline__ float unit_sum(uint32_t (&q)[PF][2], gbyte_t *gbase, 
     return (acc.a[0] + acc.a[1]) + acc.a[2];
 }
 
-// Direct global -> LDS transfers (no registers).  M0 is written and used inside one asm statement only; it is a
-// reserved register that the compiler neither allocates nor accepts in a clobber list, and nothing else in
-// these kernels uses it.
-typedef __attribute__((address_space(3))) unsigned char lds_byte_t;
-// 64 lanes x 16 bytes -> dst_wave_base + 16 lane
-__device__ __forceinline__ void dma_1k(const uint4 *src_lane, unsigned char *dst_wave_base) {
-    const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_byte_t *)dst_wave_base);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(m0), "v"(src_lane) : "memory");
-}
-// a contiguous 4 KiB: four such transfers 1 KiB apart in both address spaces, one M0 write
-__device__ __forceinline__ void dma_4k(const uint4 *src_lane, unsigned char *dst_wave_base) {
-    const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_byte_t *)dst_wave_base);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-                 "global_load_lds_dwordx4 %1, off\n\t"
-                 "global_load_lds_dwordx4 %1, off offset:1024\n\t"
-                 "global_load_lds_dwordx4 %1, off offset:2048\n\t"
-                 "global_load_lds_dwordx4 %1, off offset:3072" ::"s"(m0), "v"(src_lane) : "memory");
-}
-
 // Workgroup number -> (codebook slice, row block).  Workgroups are dealt round-robin to the 8 compute dies, each
 // with its own L2.  All row blocks of one codebook slice run on the same die, so a slice is fetched from memory
 // by one L2 only (otherwise every die pulls the whole 1 MiB codebook: 8 MiB per launch).

@@ -64,6 +64,44 @@ __device__ __forceinline__ float wave_max(float x) {
     return x;
 }
 
+// Direct global -> LDS transfers (no registers).  M0 is written and used inside one asm statement only; it is a
+// reserved register that the compiler neither allocates nor accepts in a clobber list, and nothing else in
+// these kernels uses it.
+typedef __attribute__((address_space(3))) unsigned char lds_byte_t;
+// 64 lanes x 16 bytes -> dst_wave_base + 16 lane
+__device__ __forceinline__ void dma_1k(const uint4 *src_lane, unsigned char *dst_wave_base) {
+    const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_byte_t *)dst_wave_base);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(m0), "v"(src_lane) : "memory");
+}
+// a contiguous 4 KiB: four such transfers 1 KiB apart in both address spaces, one M0 write
+__device__ __forceinline__ void dma_4k(const uint4 *src_lane, unsigned char *dst_wave_base) {
+    const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_byte_t *)dst_wave_base);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %1, off\n\t"
+                 "global_load_lds_dwordx4 %1, off offset:1024\n\t"
+                 "global_load_lds_dwordx4 %1, off offset:2048\n\t"
+                 "global_load_lds_dwordx4 %1, off offset:3072" ::"s"(m0), "v"(src_lane) : "memory");
+}
+
+// n16 units of 16 bytes from src to LDS at dst by all wavefronts of a workgroup, complete for the calling wavefront.  One
+// per thread and more: direct transfers, all requested before the first is waited for.  (In a loop of loads and LDS writes every round
+// waits out its own trip to L2, and the first one everything that was requested before it: 128 KiB by 1024 threads are eight such
+// rounds.)  The gemv of two 12-bit codebooks, us, loop / transfers: N = K = 4096 7.9 / 6.6, 11008 x 4096 with 16 tokens 22.4 / 18.4; 32 KiB of
+// per-tile codebooks, 11008 x 4096 11.0 / 9.8; 256 x 256 (two rounds of 128 threads) 2.7 / 2.4.  Less than one per thread: a single
+// load and write is ahead of a transfer (4 KiB, N = K = 4096 4.56 / 4.82; 8 KiB, 8 tokens 6.3 / 6.9).
+__device__ __forceinline__ void stage_lds(const void *src, unsigned char *dst, int n16, int wave, int nwaves, int lane) {
+    const uint4 *s = reinterpret_cast<const uint4 *>(src) + lane;
+    if (n16 < nwaves * 64) {
+        if (wave * 64 + lane < n16) reinterpret_cast<uint4 *>(dst)[wave * 64 + lane] = s[wave * 64];
+        return;
+    }
+    int c = 0;   // rounds of 4 KiB per wavefront, then pieces of 1 KiB
+    for (; c + nwaves <= n16 >> 8; c += nwaves) dma_4k(s + (c + wave) * 256, dst + (c + wave) * 4096);
+    for (int t = c * 4 + wave; t * 64 < n16; t += nwaves)
+        if (t * 64 + lane < n16) dma_1k(s + t * 64, dst + t * 1024);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the compiler does not count these transfers)
+}
+
 // Tag type for packed 12-bit codes (VQ-LLM Sec. VII-B: VQ<8,12,2> has an unaligned 12-bit storage format).
 // Reading of the layout: one little-endian bit string, code i in bits [12 i, 12 i + 12), i.e. two codes in
 // three bytes, in the canonical order [N][K/v][R].

@@ -128,6 +128,18 @@ def test_gemv_shapes_and_edges(gpu_device, N, K, v, bits, R, E, bs, scale):
     assert_close(run_gemv(w, x, gpu_device), oracle.gemv(w.codes, w.codebooks, w.scale, x), f"{N}x{K} v{v} R{R} bs{bs}")
 
 
+# The codebooks on their way to LDS, where the number of 16-byte units is less than, as many as or more than the threads (K = 64: one
+# wavefront, 1024: four), and around whole rounds of 4 KiB and pieces of 1 KiB; the last entries are looked up.
+@pytest.mark.parametrize("v,R,E", [(8, 1, 1), (8, 1, 63), (8, 1, 64), (8, 1, 65), (8, 1, 255), (8, 1, 256), (8, 1, 257), (8, 1, 1023),
+                                   (8, 1, 1024), (8, 1, 1025), (8, 1, 1300), (8, 1, 8192), (8, 2, 511), (4, 1, 514), (4, 2, 2047), (8, 4, 2000)])
+@pytest.mark.parametrize("K", [64, 1024])
+def test_gemv_codebooks_of_every_length(gpu_device, v, R, E, K):
+    w = wl.make_weight(37, K, v, 16, R, E, 0.02, seed=1700 + E + K)
+    w.codes[:, -4:, :] = E - 1 - np.arange(4)[:, None] % E
+    x = wl.make_activations(2, K, seed=1800 + E)
+    assert_close(run_gemv(w, x, gpu_device), oracle.gemv(w.codes, w.codebooks, w.scale, x), f"K {K} v {v} R {R} E {E}")
+
+
 @pytest.mark.parametrize("v,bits,R,E,sigma", [
     (8, 8, 1, 256, 0.02),       # entries verbatim
     (8, 8, 2, 256, 0.01),       # one fp16 addition = the fp32 sum rounded once
