@@ -87,18 +87,26 @@ __device__ __forceinline__ void dma_4k(const uint4 *src_lane, unsigned char *dst
 // per thread and more: direct transfers, all requested before the first is waited for.  (In a loop of loads and LDS writes every round
 // waits out its own trip to L2, and the first one everything that was requested before it: 128 KiB by 1024 threads are eight such
 // rounds.)  The gemv of two 12-bit codebooks, us, loop / transfers: N = K = 4096 7.9 / 6.6, 11008 x 4096 with 16 tokens 22.4 / 18.4; 32 KiB of
-// per-tile codebooks, 11008 x 4096 11.0 / 9.8; 256 x 256 (two rounds of 128 threads) 2.7 / 2.4.  Less than one per thread: a single
+// per-tile codebooks, 11008 x 4096 11.0 / 9.8; 256 x 256 (two rounds of 128 threads) 2.7 / 2.4.  The one-pass product of
+// 11008 x 4096, 64 tokens 31.1 / 27.3.  Less than one per thread: a single
 // load and write is ahead of a transfer (4 KiB, N = K = 4096 4.56 / 4.82; 8 KiB, 8 tokens 6.3 / 6.9).
 __device__ __forceinline__ void stage_lds(const void *src, unsigned char *dst, int n16, int wave, int nwaves, int lane) {
-    const uint4 *s = reinterpret_cast<const uint4 *>(src) + lane;
     if (n16 < nwaves * 64) {
-        if (wave * 64 + lane < n16) reinterpret_cast<uint4 *>(dst)[wave * 64 + lane] = s[wave * 64];
+        if (wave * 64 + lane < n16) reinterpret_cast<uint4 *>(dst)[wave * 64 + lane] = reinterpret_cast<const uint4 *>(src)[wave * 64 + lane];
         return;
     }
+    const unsigned char *s = reinterpret_cast<const unsigned char *>(src);   // (a scalar base and one offset per lane: few registers)
+    const uint32_t to = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_byte_t *)dst), at = lane * 16;
     int c = 0;   // rounds of 4 KiB per wavefront, then pieces of 1 KiB
-    for (; c + nwaves <= n16 >> 8; c += nwaves) dma_4k(s + (c + wave) * 256, dst + (c + wave) * 4096);
+    for (; c + nwaves <= n16 >> 8; c += nwaves)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                     "global_load_lds_dwordx4 %1, %2\n\t"
+                     "global_load_lds_dwordx4 %1, %2 offset:1024\n\t"
+                     "global_load_lds_dwordx4 %1, %2 offset:2048\n\t"
+                     "global_load_lds_dwordx4 %1, %2 offset:3072" ::"s"(to + (c + wave) * 4096), "v"(at), "s"(s + (c + wave) * 4096) : "memory");
     for (int t = c * 4 + wave; t * 64 < n16; t += nwaves)
-        if (t * 64 + lane < n16) dma_1k(s + t * 64, dst + t * 1024);
+        if (lane < n16 - t * 64)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to + t * 1024), "v"(at), "s"(s + t * 1024) : "memory");
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the compiler does not count these transfers)
 }
 
