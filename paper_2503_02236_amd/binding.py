@@ -11,7 +11,9 @@ or a call fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
+import sys
 from dataclasses import dataclass
 from typing import Optional
 
@@ -131,11 +133,20 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+def marshal_built_for() -> tuple:
+    """What the native marshalling has to have been built for: torch (whose tensors it reads by inlined accessors, so that a
+    module for another build can load and read the wrong fields), Python, and the structs that it fills."""
+    return ("torch %s %s hip %s python %s" % (torch.__version__, torch.version.git_version, torch.version.hip, sys.implementation.cache_tag),
+            ctypes.sizeof(vq_weight_t), ctypes.sizeof(vq_kv_t), ctypes.sizeof(vq_gemv_pack_t))
+
+
 def _load_marshal(l) -> None:
     global _marshal
     try:
-        from . import _marshal as native
-    except ImportError:     # (not built, or built for another torch: slower, not different)
+        native = importlib.import_module("._marshal", __package__)
+    except ImportError:     # (not built: slower, not different)
+        return
+    if getattr(native, "built_for", None) != marshal_built_for():   # (the same)
         return
     address = lambda name: ctypes.cast(getattr(l, name), ctypes.c_void_p).value  # noqa: E731
     native.init(tuple(address(n) for n in ("vq_gemv", "vq_gemv_workspace", "vq_gemv_batch", "vq_gemv_batch_workspace", "vq_gemm",

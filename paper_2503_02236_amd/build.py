@@ -1,4 +1,4 @@
-"""Build libvqmi.so (the C-ABI library of hand-written gfx950 kernels) in-tree with hipcc, and _marshal.so (the native part
+"""Build libvqmi.so (the C-ABI library of hand-written gfx950 kernels) in-tree with hipcc, and _marshal (the native part
 of the Python binding) with the host compiler.
 
 hipcc cross-compiles for gfx950 without a GPU, so this runs on the CPU build host;
@@ -9,6 +9,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -16,7 +17,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libvqmi.so")
-MARSHAL = os.path.join(PKG, "_marshal.so")
+MARSHAL = os.path.join(PKG, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))   # (another Python does not load it)
 SOURCES = ["api.hip", "dequant.hip", "gemv.hip", "gemv_packed.hip", "gemv_mfma.hip", "gemv_replica.hip", "gemv_lut.hip", "gemm.hip", "gemm_skinny.hip", "gemm_dense.hip", "gemm_tiles.hip", "attn.hip", "attn_channel.hip", "kv_quantize.hip", "reorder.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Wall", "-Wno-unused-function",
@@ -38,14 +39,15 @@ def _compile(src: str, extra) -> str:
 
 
 def _build_marshal() -> None:
-    import sysconfig
-
     import torch
+
+    from .binding import marshal_built_for
     base = os.path.dirname(torch.__file__)
     rocm = os.path.dirname(os.path.dirname(HIPCC))
     tmp = MARSHAL + ".tmp.%d" % os.getpid()
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I", os.path.join(ROOT, "include"),
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), '-DVQ_BUILT_FOR="%s"' % marshal_built_for()[0],
+           "-I", os.path.join(ROOT, "include"),
            *(f"-isystem{p}" for p in (os.path.join(base, "include"), os.path.join(base, "include", "torch", "csrc", "api", "include"),
                                       os.path.join(rocm, "include"), sysconfig.get_paths()["include"])),
            os.path.join(CSRC, "marshal.cpp"), "-o", tmp, "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]

@@ -395,5 +395,13 @@ PyMODINIT_FUNC PyInit__marshal() {
                  {&s_k_codes, "k_codes"}, {&s_v_codes, "v_codes"}, {&s_k_codebooks, "k_codebooks"}, {&s_v_codebooks, "v_codebooks"}, {&s_seq_lens, "seq_lens"}};
     for (const auto &n : names)
         if (!(*n.at = PyUnicode_InternFromString(n.name))) return nullptr;
-    return PyModule_Create(&module);
+    PyObject *m = PyModule_Create(&module);
+    // binding.py compares this with what it runs under before it calls init
+    PyObject *built_for = m ? Py_BuildValue("(snnn)", VQ_BUILT_FOR, (Py_ssize_t)sizeof(vq_weight_t), (Py_ssize_t)sizeof(vq_kv_t), (Py_ssize_t)sizeof(vq_gemv_pack_t)) : nullptr;
+    if (!built_for || PyModule_AddObject(m, "built_for", built_for) != 0) {
+        Py_XDECREF(built_for);
+        Py_XDECREF(m);
+        return nullptr;
+    }
+    return m;
 }

@@ -567,3 +567,25 @@ def test_binding_finds_the_stream_without_the_undocumented_calls_of_torch(monkey
     assert binding._stream_getter(obj())() == 77
     assert binding._stream_getter(obj(_cuda_getDevice=lambda: 3))() == 77
     assert binding._stream_getter(obj(_cuda_getDevice=lambda: 3, _cuda_getCurrentRawStream=lambda device: 100 + device))() == 103
+
+
+def test_native_marshalling_is_used_only_where_it_was_built_for(monkeypatch):
+    """Its tensor accessors are inlined from torch's headers: a module for another torch, Python or struct layout is left alone, however
+    well it loads."""
+    import importlib
+    import sysconfig
+    import types
+    from paper_2503_02236_amd import binding
+    l = vq.lib()
+    built = importlib.import_module("paper_2503_02236_amd._marshal")
+    assert built.built_for == binding.marshal_built_for() and built.__file__.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    for version in (binding.marshal_built_for(), None, ("torch 0",) + binding.marshal_built_for()[1:], binding.marshal_built_for()[:3] + (0,)):
+        calls = []
+        fake = types.SimpleNamespace(init=lambda *a: calls.append(a))
+        if version:
+            fake.built_for = version
+        monkeypatch.setattr(binding, "_marshal", None)
+        monkeypatch.setitem(sys.modules, "paper_2503_02236_amd._marshal", fake)
+        binding._load_marshal(l)
+        right = version == binding.marshal_built_for()
+        assert len(calls) == right and (binding._marshal is fake) == right
