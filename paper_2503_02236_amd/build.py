@@ -57,10 +57,21 @@ def _build_marshal() -> None:
     os.replace(tmp, MARSHAL)
 
 
+def _build_marshal_if_possible() -> None:
+    """The library does not need it, and neither does the binding: where it cannot be built (no torch or its headers, no host
+    compiler) that is said, and calls are marshalled by ctypes."""
+    try:
+        _build_marshal()
+    except Exception as e:  # noqa: BLE001
+        sys.stderr.write("the native part of the binding was not built: %s\n" % e)
+        if os.path.exists(MARSHAL):
+            os.remove(MARSHAL)      # (that of an earlier build)
+
+
 def build(extra_flags=(), jobs: int = 7) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
-        marshal = ex.submit(_build_marshal)
+        marshal = ex.submit(_build_marshal_if_possible)
         objs = list(ex.map(lambda s: _compile(s, list(extra_flags)), SOURCES))
         marshal.result()
     tmp = LIB + ".tmp.%d" % os.getpid()

@@ -589,3 +589,22 @@ def test_native_marshalling_is_used_only_where_it_was_built_for(monkeypatch):
         binding._load_marshal(l)
         right = version == binding.marshal_built_for()
         assert len(calls) == right and (binding._marshal is fake) == right
+
+
+@pytest.mark.skipif(not os.path.exists("/opt/rocm/bin/hipcc"), reason="hipcc not available")
+def test_library_is_built_without_the_native_marshalling(tmp_path, monkeypatch, capsys):
+    """The C library needs hipcc alone: without a host compiler for the binding's native part it is linked all the same, and a native
+    part of an earlier build does not stay beside it."""
+    from paper_2503_02236_amd import build
+
+    def compile_one(src, extra):
+        obj = str(tmp_path / (src + ".o"))
+        subprocess.run([build.HIPCC, "-fPIC", "-x", "c", "-c", "/dev/null", "-o", obj], check=True)
+        return obj
+    stale = tmp_path / "_marshal.so"
+    stale.write_text("stale")
+    for name, value in (("SOURCES", ["one.hip"]), ("_compile", compile_one), ("OBJ", str(tmp_path)), ("LIB", str(tmp_path / "lib.so")), ("MARSHAL", str(stale))):
+        monkeypatch.setattr(build, name, value)
+    monkeypatch.setenv("CXX", "/bin/false")
+    assert build.build() == str(tmp_path / "lib.so") and (tmp_path / "lib.so").exists() and not stale.exists()
+    assert "marshal.cpp" in capsys.readouterr().err
