@@ -7,6 +7,7 @@ the resulting shared object travels with the source tree to the GPU machine.
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -43,7 +44,7 @@ def _build_marshal() -> None:
 
     from .binding import marshal_built_for
     base = os.path.dirname(torch.__file__)
-    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(shutil.which(HIPCC) or HIPCC)))   # (HIPCC may be a name on PATH, or a link)
     tmp = MARSHAL + ".tmp.%d" % os.getpid()
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), '-DVQ_BUILT_FOR="%s"' % marshal_built_for()[0],

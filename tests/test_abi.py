@@ -608,3 +608,24 @@ def test_library_is_built_without_the_native_marshalling(tmp_path, monkeypatch, 
     monkeypatch.setenv("CXX", "/bin/false")
     assert build.build() == str(tmp_path / "lib.so") and (tmp_path / "lib.so").exists() and not stale.exists()
     assert "marshal.cpp" in capsys.readouterr().err
+
+
+@pytest.mark.skipif(not os.path.exists("/opt/rocm/bin/hipcc"), reason="hipcc not available")
+@pytest.mark.parametrize("how", ["path", "name", "link"])
+def test_native_marshalling_finds_the_headers_beside_the_compiler(tmp_path, monkeypatch, how):
+    """HIPCC may be a path, a name on PATH, or a link to the compiler: the HIP headers are those beside the compiler itself."""
+    from paper_2503_02236_amd import build
+    hipcc = "/opt/rocm/bin/hipcc"
+    if how == "link":
+        os.symlink(hipcc, tmp_path / "hipcc")
+        hipcc = str(tmp_path / "hipcc")
+    monkeypatch.setattr(build, "HIPCC", "hipcc" if how == "name" else hipcc)
+    monkeypatch.setenv("PATH", "/opt/rocm/bin" + os.pathsep + os.environ["PATH"])
+    monkeypatch.setattr(build, "MARSHAL", str(tmp_path / "_marshal.so"))
+    script = tmp_path / "cxx"
+    script.write_text("#!/bin/sh\nfor a in \"$@\"; do case $a in -isystem*) [ -f \"${a#-isystem}/hip/hip_runtime.h\" ] && echo found > \"%s\";; esac; done\nexit 1\n" % (tmp_path / "seen"))
+    script.chmod(0o755)
+    monkeypatch.setenv("CXX", str(script))
+    with pytest.raises(RuntimeError):
+        build._build_marshal()
+    assert (tmp_path / "seen").exists()
