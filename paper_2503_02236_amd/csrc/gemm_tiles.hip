@@ -175,8 +175,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tile_waves(
         stage(kt + 1, std::integral_constant<int, 1>{});
     }
     if (kt < KT) stage(kt, std::integral_constant<int, 0>{});
-    // (the nops: the compiler does not know that the accumulators come from matrix instructions that may still be under way)
+    // The nops: the compiler does not know that the accumulators come from matrix instructions that may still be under way.  Every
+    // accumulator then passes through an (empty) statement that cannot change places with this one, so that nothing reads it earlier.
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int j = 0; j < NF; ++j) asm volatile("" : "+a"(acc[i][j]));
 
     // An accumulator holds Y^T: lane (ln, lk), register r is row m = ln, column n = 4 lk + r of its 16 x 16 block.  Scaled and
     // rounded, blocks of kRows rows go through a private LDS region of the wavefront (rows padded by 16 bytes) and leave as 16

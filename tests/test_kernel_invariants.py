@@ -135,6 +135,30 @@ def test_gemm_tiles_waits_match_the_loads_in_flight(tmp_path):
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
+def test_gemm_tiles_reads_its_accumulators_behind_the_wait_for_them(tmp_path):
+    """The matrix instructions are asm, so the compiler does not know when their results are there: behind the last of them stands a wait
+    by s_nops, and every accumulator passes through a statement of its own behind that, in front of its first use."""
+    out = tmp_path / "gemm_tiles.s"
+    cmd = [HIPCC, "-O3", "-std=c++17", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang",
+           "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "--cuda-device-only", "-S",
+           os.path.join(CSRC, "gemm_tiles.hip"), "-o", str(out)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    kernels = re.findall(r"^_ZN2vq\S*gemm_tiles_kernelILi(\d+)ELi(\d+)E\S*:(.*?)^\.Lfunc_end", out.read_text(), re.S | re.M)
+    assert len(kernels) == 8
+    for BM, NF, text in kernels:
+        lines = [l.strip() for l in text.splitlines()]
+        names_acc = lambda l: not l.startswith(";") and re.search(r"[ ,]a(\d|\[)", l)  # noqa: E731
+        last = max(i for i, l in enumerate(lines) if l.startswith("v_mfma"))
+        nops = [i for i, l in enumerate(lines) if l == "s_nop 15"]
+        assert len(nops) == 2 and last < nops[0] and nops[1] == nops[0] + 1, (BM, NF)
+        assert not any(names_acc(l) for l in lines[last + 1:nops[1]]), (BM, NF)
+        first = min(i for i, l in enumerate(lines) if i > nops[1] and names_acc(l))
+        ties = sum(lines[i] == ";;#ASMSTART" and lines[i + 1] == ";;#ASMEND" for i in range(nops[1], first))
+        assert ties == int(BM) // 16 * int(NF), (BM, NF, ties)
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
 def test_attention_kernels_have_no_static_lds(tmp_path):
     """The attention kernel forms entry addresses as absolute LDS offsets, which needs its dynamic LDS to start
     at address 0, i.e. no static LDS in any build of it (the launcher checks the same at run time and returns
