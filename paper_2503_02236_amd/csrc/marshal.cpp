@@ -266,6 +266,19 @@ PyObject *gemm(PyObject *, PyObject *const *args, Py_ssize_t n) {
     return guarded([&] { return product(args, n, lib.gemm, lib.gemm_workspace, "vq_gemm"); });
 }
 
+// References to what the caller's lists held: another thread may change the lists while a call runs without the interpreter's lock.
+struct Held {
+    std::vector<PyObject *> all;
+    PyObject *add(PyObject *o) {
+        all.push_back(o);
+        Py_INCREF(o);
+        return o;
+    }
+    ~Held() {
+        for (PyObject *o : all) Py_DECREF(o);
+    }
+};
+
 // (list of w, list of x, list of y or None, ws or None)
 PyObject *gemv_batch(PyObject *, PyObject *const *args, Py_ssize_t n) {
     return guarded([&]() -> PyObject * {
@@ -274,25 +287,26 @@ PyObject *gemv_batch(PyObject *, PyObject *const *args, Py_ssize_t n) {
         constexpr Py_ssize_t kMost = 16;   // (the entry point takes four)
         const Py_ssize_t count = PyList_GET_SIZE(args[0]);
         if (count < 1 || count > kMost || PyList_GET_SIZE(args[1]) != count || (args[2] != Py_None && PyList_GET_SIZE(args[2]) != count)) throw NotPlain();
+        Held held;
         std::vector<std::unique_ptr<Weight>> w;
         const vq_weight_t *wp[kMost];
         const void *xp[kMost];
         void *yp[kMost];
         std::vector<at::Tensor> own;
         for (Py_ssize_t i = 0; i < count; ++i) {
-            w.emplace_back(new Weight(PyList_GET_ITEM(args[0], i)));
+            w.emplace_back(new Weight(held.add(PyList_GET_ITEM(args[0], i))));
             wp[i] = &w.back()->d;
-            PyObject *x = PyList_GET_ITEM(args[1], i);
+            PyObject *x = held.add(PyList_GET_ITEM(args[1], i));
             xp[i] = data(x, at::kHalf);
             if (args[2] == Py_None) {
                 if (wp[i]->N < 0) throw NotPlain();
                 own.push_back(at::empty({1, (int64_t)wp[i]->N}, THPVariable_Unpack(x).options()));
                 yp[i] = own.back().data_ptr();
             } else {
-                yp[i] = data(PyList_GET_ITEM(args[2], i), at::kHalf);
+                yp[i] = data(held.add(PyList_GET_ITEM(args[2], i)), at::kHalf);
             }
         }
-        Workspace ws(args[3], THPVariable_Unpack(PyList_GET_ITEM(args[1], 0)).device(), [&] { return lib.gemv_batch_workspace(wp, (int)count); });
+        Workspace ws(args[3], THPVariable_Unpack(held.all[1]).device(), [&] { return lib.gemv_batch_workspace(wp, (int)count); });
         void *s = stream();
         int status;
         VQ_WITHOUT_GIL(status, lib.gemv_batch(wp, xp, yp, (int)count, ws.p, ws.bytes, s));

@@ -1702,6 +1702,35 @@ def test_native_marshalling_attention(gpu_device, monkeypatch):
     assert a == b and a[0] is TypeError
 
 
+def test_native_marshalling_holds_what_the_lists_of_a_batch_held(gpu_device):
+    """The interpreter's lock is released around the entry point, so another thread may change the caller's lists meanwhile: here the
+    entry point is a stand-in that does so, and all weights, inputs and outputs have to be there still."""
+    import weakref
+    from paper_2503_02236_amd import binding
+    l, native = vq.lib(), binding._marshal
+    names = ("vq_gemv", "vq_gemv_workspace", "vq_gemv_batch", "vq_gemv_batch_workspace", "vq_gemm", "vq_gemm_workspace", "vq_attn_decode",
+             "vq_attn_decode_workspace", "vq_kv_quantize")
+    address = [ctypes.cast(getattr(l, n), ctypes.c_void_p).value for n in names]
+    types = (vq.VQWeightDev, vq.VQKVDev, binding.vq_gemv_pack_t, vq.VQError)
+    w, _ = wl.config1_tiny()
+    ws = [vq.weight_to_device(w, gpu_device) for _ in range(3)]
+    xs = [torch.zeros((1, w.K), dtype=torch.float16, device=gpu_device) for _ in range(3)]
+    ys = [torch.zeros((1, w.N), dtype=torch.float16, device=gpu_device) for _ in range(3)]
+    refs, alive = [weakref.ref(o) for o in ws + xs + ys], []
+
+    def entry(*args):
+        ws.clear(), xs.clear(), ys.clear()
+        alive.append(all(r() is not None for r in refs))
+        return 0
+    stand_in = ctypes.CFUNCTYPE(ctypes.c_int, *l.vq_gemv_batch.argtypes)(entry)
+    try:
+        native.init(tuple(address[:2] + [ctypes.cast(stand_in, ctypes.c_void_p).value] + address[3:]), *types)
+        assert native.gemv_batch(ws, xs, ys, None) is ys
+    finally:
+        native.init(tuple(address), *types)
+    assert alive == [True] and not any(r() for r in refs)
+
+
 def test_native_marshalling_leaves_what_is_not_plain_to_python(gpu_device):
     from paper_2503_02236_amd import binding
     from torch.overrides import TorchFunctionMode
