@@ -24,6 +24,7 @@
 // entries, 32 tokens 160 -> 14.7, 256 tokens 175 -> 32; N = 11008, 8 tokens 62.5 -> 30.5 (two passes of gathers before,
 // one now: 0.37 per clock and CU).
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "vq_common.h"
@@ -195,10 +196,10 @@ int skinny_tile(const vq_weight_t *w, int M, bool l2, double staging = 0, double
         if (cost < best_cost) {
             best_cost = cost;
             best = i;
-            // (to compare with another kernel: fitted to 397 measured launches, 11 % off on average)
-            const double x = 16.0 * t.ct * w->K * 2 / 41;
-            if (us && l2) *us = rounds * (lookups * (w->v == 8 ? 2.88e-4 : 3.34e-4) + x * 5.7e-4 + 1.26) + 2.7;
-            if (us && !l2) *us = rounds * (lookups * (w->v == 8 ? 2.81e-4 : 1.83e-4) + x * 6.6e-4 + staging * 6.3e-4 + 2.26) + 1.4;
+            // (to compare with another kernel: constants by the formats' entries, and the start and end of a workgroup by its tile)
+            const double x = 16.0 * t.ct * w->K * 2 / 41, ends = t.rt * t.ct * (r <= 1 ? 0.1 : r <= 2 ? 0.24 : 0.25 * (0.7 * std::ceil(r) + 0.3 * r));
+            if (us && l2) *us = rounds * (lookups * (w->v == 8 ? 2.88e-4 : 3.34e-4) + x * 5.7e-4 + 1.26) + ends + 2.7;
+            if (us && !l2) *us = rounds * (lookups * (w->v == 8 ? 2.81e-4 : 1.83e-4) + x * 6.6e-4 + staging * 6.3e-4 + 2.26) + ends + 1.4;
         }
     }
     return best;
@@ -266,21 +267,25 @@ bool gemm_skinny_supported(const vq_weight_t *w) {
 
 // More than 256 tokens: against the two-stage product, which writes the weight once and multiplies it tile by tile.  Measured,
 // two-stage / here, us: two 256-entry codebooks, N = 256, K = 4096, 1024 tokens 18.7 / 9.1; N = 1024, K = 2048, 400 tokens 12.0 / 9.0,
-// 2048 tokens 18.0 / 21.2; N = K = 4096, 400 tokens 33.6 / 31.4, 700 tokens 41.5 / 48.5; N = 11008, K = 1024, 257 tokens 28.7 / 24.0; 2^16
-// entries, N = 64, K = 8192, 257 tokens 25.2 / 13.2.  Every workgroup stages the codebooks (41 bytes per clock).  The estimates are
-// good to about 10 %: over 397 measured calls (8 formats, 11 weights, 257 to 2048 tokens) the pick takes 1.9 % more than the
-// better of the two on average.  (A supported weight with K % 64 == 0.)
+// 2048 tokens 18.0 / 21.2; N = K = 4096, 400 tokens 33.6 / 31.4, 700 tokens 41.5 / 48.5; N = 11008, K = 2112, 327 tokens 38.5 / 63.5; two
+// of 4096 entries, N = 11008, K = 10560, 317 tokens 230 / 149; 2^16 entries, N = 64, K = 8192, 257 tokens 25.2 / 13.2.  Every workgroup
+// stages the codebooks (41 bytes per clock).  What the estimates have to know: here, that a workgroup of a large tile takes longer to start
+// and to end, and that rounds are mostly whole ones; of the two stages, that the output is written (element by element where N % 8 != 0),
+// that lookups are dearer the less of the codebooks a CU's L1 holds, and that a weight of more than 64 M elements does not stay in the
+// Infinity Cache.  Over 8372 measured calls (15 formats, N 16 .. 11008, K 256 .. 11008, 257 to 4096 tokens) the pick takes 0.7 % more
+// than the better of the two on average, 23 % or more in the worst hundredth.  (A supported weight with K % 64 == 0.)
 bool gemm_skinny_wins(const vq_weight_t *w, int M) {
     if ((long)M * w->K >= kSkinnyMaxX) return false;
     double here;
     const bool l2 = !entries_from_lds(w);
-    const size_t sets = w->cb_tile_n > 0 ? w->K / w->cb_tile_k : 1;
-    skinny_tile(w, M, l2, l2 ? 0 : sets * w->n_codebooks * w->n_entries * w->v * 2 / 41.0, &here);
-    // dequantization: by the million elements, the first 16 of which are dearer (few wavefronts), and launches
-    const double m = 1e-6 * w->N * w->K, first = std::min(m, 16.0), rest = m - first;
-    const double two = 3.5 + 0.97 * gemm_tiles_time(M, w->N, w->K, nullptr) +
-                       (l2 ? w->v == 8 ? 1.33 * first + 0.62 * rest : 1.76 * first + 1.09 * rest : w->v == 8 ? 1.29 * first + 0.45 * rest : 1.26 * first + 0.57 * rest);
-    return (l2 ? 0.92 : 1.0) * here < two;
+    const size_t sets = w->cb_tile_n > 0 ? w->K / w->cb_tile_k : 1, set = (size_t)w->n_codebooks * w->n_entries * w->v * 2;
+    skinny_tile(w, M, l2, l2 ? 0 : sets * set / 41.0, &here);
+    // in millions: the weight's elements (the first 16 of which are dearer: few wavefronts), lookups, outputs
+    const double m = 1e-6 * w->N * w->K, first = std::min(m, 16.0), rest = m - first, far = std::max(m - 64, 0.0);
+    const double lookup = m / w->v * w->n_codebooks, out = 1e-6 * w->N * M;
+    const double two = 4.0 + 1.05 * gemm_tiles_time(M, w->N, w->K, nullptr) + 0.76 * first + 0.14 * rest + 0.79 * far +
+                       lookup * (set > 128 * 1024 ? 2.92 : set > 32 * 1024 ? 1.63 : 0.71) + out * (w->N % 8 != 0 ? 1.96 : 0.3);
+    return here < two;
 }
 
 // Where vq_gemv (1 .. 16 tokens) runs here.

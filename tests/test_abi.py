@@ -530,6 +530,21 @@ def test_staging_of_large_codebooks_counts_in_the_choice_of_the_product():
     assert one_pass(1024, N=1000, K=512, n_codebooks=2) and not one_pass(1024, N=1000, K=512, **big) and one_pass(257, N=1000, K=512, **big)
 
 
+# measured, one pass / two stages, us
+@pytest.mark.parametrize("kw,M,one", [
+    # more than one round of large tiles: 63.5 / 38.5, 56.5 / 42.0, 63.2 / 42.5 (per-tile codebooks)
+    (dict(N=11008, K=2112, n_codebooks=2), 327, False), (dict(N=11008, K=1408), 507, False),
+    (dict(N=4096, K=4608, n_codebooks=2, cb_tile_n=256, cb_tile_k=512), 528, False),
+    # many lookups of codebooks that no L1 holds, a weight beyond the caches: 149 / 230, 167 / 232; 41.4 / 58.8 with few rows
+    (dict(N=11008, K=10560, n_codebooks=2, code_bits=16, n_entries=4096), 317, True), (dict(N=11008, K=11008, n_codebooks=2, code_bits=16, n_entries=4096), 275, True),
+    (dict(N=554, K=11008, v=4, n_codebooks=2, code_bits=16, n_entries=1000), 1517, True),
+    # the two stages write an odd number of rows element by element: 39.4 / 48.6
+    (dict(N=645, K=11008, v=4, n_codebooks=2), 981, True),
+])
+def test_more_than_256_tokens_take_the_faster_of_the_two_products(kw, M, one):
+    assert internal("_ZN2vq13gemm_one_passEPK11vq_weight_ti", ctypes.byref(weight(**kw)), M) == one
+
+
 @pytest.mark.parametrize("kw,copies", [
     (dict(B=16, H=32, T=4096), True), (dict(B=8, H=32, T=8192), True), (dict(B=33, H=30, T=4096), True),   # whole rounds of long ranges
     (dict(B=3, H=32, T=1500), False),        # 160 workgroups (pairs of batch entries would be 192)
