@@ -192,6 +192,9 @@ int skinny_tile(const vq_weight_t *w, int M, bool l2, double staging = 0, double
         const double r = (double)(((long)w->N + 16 * t.rt - 1) / (16 * t.rt)) * ((M + 16 * t.ct - 1) / (16 * t.ct)) / 256;
         const double rounds = l2 ? (r <= 1 ? std::max(0.7, r) : r + 0.3) : r <= 1 ? 1.0 : r <= 2 ? 2.0 : r + 0.3;
         const double lookups = 16.0 * t.rt * (w->K / w->v) * w->n_codebooks / (l2 ? 0.35 : 3.5);
+        // (16 rows x 48 tokens of one codebook of v = 4, whose lookups are few, read too much of X where K is long: 4096 x 11008, 46 tokens 15.8 -> 16.5,
+        // 585 x 10688, 219 tokens 15.4 -> 16.7)
+        if (t.ct == 3 && t.rt == 1 && w->v == 4 && w->n_codebooks == 1 && w->K > 8192) continue;
         const double cost = rounds * (lookups + 16.0 * t.ct * w->K * 2 / 41 + 2000 + staging);
         if (cost < best_cost) {
             best_cost = cost;
@@ -263,6 +266,13 @@ bool gemm_skinny_supported(const vq_weight_t *w) {
     const long row_bits = (long)(w->K / w->v) * R * w->code_bits;
     if (w->K <= 0 || w->K % 8 != 0 || w->N <= 0 || w->N > (1 << 26) || row_bits % (lb * 8) != 0 || w->K > (1 << 22)) return false;   // (256 tokens: byte offsets into X of 32 bits)
     return entries_from_lds(w) || (w->cb_tile_n == 0 && R == 1 && w->code_bits == 16);
+}
+
+// The tile of a launch of M tokens, 16 {weight rows} + {tokens} in sixteens (for tests).
+int gemm_skinny_tile_of(const vq_weight_t *w, int M) {
+    const bool l2 = !entries_from_lds(w);
+    const SkinnyTile t = (l2 ? kL2Tiles : kLdsTiles)[skinny_tile(w, M, l2)];
+    return 16 * t.rt + t.ct;
 }
 
 // More than 256 tokens: against the two-stage product, which writes the weight once and multiplies it tile by tile.  Measured,

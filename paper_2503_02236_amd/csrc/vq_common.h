@@ -164,6 +164,7 @@ size_t gemm_workspace(const vq_weight_t *w, int M);
 // a few to a few hundred tokens in one pass over the codes (gemm_skinny.hip)
 bool gemm_skinny_supported(const vq_weight_t *w);
 bool gemm_skinny_wins(const vq_weight_t *w, int M);
+int gemm_skinny_tile_of(const vq_weight_t *w, int M);
 bool gemm_skinny_for_gemv(const vq_weight_t *w, int bs);
 int launch_gemm_skinny(const vq_weight_t *w, const void *x, int M, void *y, hipStream_t s);
 // Two stages (K % 64 == 0).  The second reads the dequantized weight in the order of its wavefronts' operands: strips of 16 columns

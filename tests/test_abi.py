@@ -530,6 +530,17 @@ def test_staging_of_large_codebooks_counts_in_the_choice_of_the_product():
     assert one_pass(1024, N=1000, K=512, n_codebooks=2) and not one_pass(1024, N=1000, K=512, **big) and one_pass(257, N=1000, K=512, **big)
 
 
+# measured, tiles of 48 tokens / the other, us
+@pytest.mark.parametrize("kw,M,tile", [
+    (dict(N=4096, K=4096, n_codebooks=2), 77, (2, 3)), (dict(N=4096, K=4096, n_codebooks=2), 48, (1, 3)),                # 11.3 / 12.8, 9.2 / 10.4
+    (dict(N=4096, K=11008, v=4), 46, (2, 2)), (dict(N=1322, K=11008, v=4), 105, (2, 2)),   # 16.5 / 15.8, 16.3 / 15.4
+    (dict(N=4096, K=11008, v=4, n_codebooks=2), 46, (1, 3)),
+])
+def test_one_pass_product_takes_48_tokens_where_that_is_faster(kw, M, tile):
+    f = vq.lib()._ZN2vq19gemm_skinny_tile_ofEPK11vq_weight_ti
+    assert divmod(f(ctypes.byref(weight(**kw)), M), 16) == tile
+
+
 # measured, one pass / two stages, us
 @pytest.mark.parametrize("kw,M,one", [
     # more than one round of large tiles: 63.5 / 38.5, 56.5 / 42.0, 63.2 / 42.5 (per-tile codebooks)
