@@ -529,6 +529,17 @@ int kvq_log_lanes(int items) {
 // 28.0 with four; v = 4 34.3 / 30.3).
 bool kvq_four_tokens(int P, int v, int n_new) { return v <= 4 && n_new >= 4 * (256 / P); }
 
+// Workgroups of the scan that share the items of a token range, up to four: a wavefront takes its groups and items one after the other,
+// each a trip to memory or a reduction, so few sequences are spread over the chip.  32 codebooks of v = 4 per head and side,
+// H32, one token: B1 5.0 -> 3.0 us, B3 5.0 -> 4.4, four tokens 10.7 -> 7.3; beyond 768 workgroups only long chains gain (B8, one
+// token 6.6 / 6.7; 64 codebooks of v = 2, six tokens 34.5 -> 29.3), and beyond 256 none with fewer than 32 items a workgroup (16 items: 64
+// sequence-heads 4.1 -> 3.2, 88 3.18 / 3.47, 74 3.37 / 3.66).
+int kvq_share(long bh, int ranges, int items) {
+    int share = 1;
+    while (share < 4 && 16 * share <= items && bh * 4 * ranges * share <= (items >= 128 * share ? 1024 : items >= 32 * share ? 768 : 256)) share *= 2;
+    return share;
+}
+
 // The kernel with the least estimated time (us): the chain of one workgroup or the instructions of all of them (a vector
 // instruction of a wavefront: 1.63e-6 us of the chip), whichever is longer.  Over 432 measured calls (B 1 .. 64, 1 to
 // 2048 tokens, 8 to 256 entries, 1 to 64 groups, head sizes 64 to 192) the pick takes 0.5 % more than the best of the three on
@@ -580,30 +591,50 @@ int kv_quantize_kernel_of(const vq_kv_t *kv, int n_new) {
 
 namespace {
 
+// A launch of the matrix-core kernel.
+struct KvqMfmaPlan {
+    int tokens, threads, way;
+    size_t lds;
+};
+KvqMfmaPlan kvq_mfma_plan(int bh, int P, int v, int E, int G, int n_new) {
+    const int tiles = E <= 32 ? 1 : E <= 64 ? 2 : E <= 128 ? 4 : 8;
+    KvqMfmaPlan p;
+    p.tokens = kvq_mfma_tokens(bh, n_new);
+    p.lds = (size_t)G * 32 * tiles * v * sizeof(half_t) + (((size_t)G + 3) & ~(size_t)3) * 4 + (size_t)p.tokens * P;
+    // a CU holds 16 wavefronts of this kernel: two workgroups of 8 where 64 KiB of codebooks are staged, four of 4 otherwise
+    p.threads = 4 * p.lds > 160 * 1024 ? 512 : 256;
+    // Two lanes per item where a wavefront has 32 items of a group or fewer (12 tokens of 8 groups ...): 64 at a time leave half of
+    // the lanes idle.  And where a call is as long as one wavefront's chain (up to two workgroups a CU) and units of 32 spread
+    // better over the wavefronts: an iteration over 64 takes 1.7 times as long.
+    const int items = std::min(p.tokens, n_new) * (P / G), share = std::max(1, p.threads / 64 / G);
+    const int by_32 = ceil_div(ceil_div(items, 32), share), by_64 = ceil_div(ceil_div(items, 64), share);
+    const bool chain = (long)bh * 2 * ceil_div(n_new, p.tokens) <= 512;
+    // the norms, where they do not cost a workgroup per CU and no group is in part past the last entry
+    const size_t with_norms = p.lds + (size_t)G * 32 * tiles * sizeof(float);
+    if (items <= 32 * share || (chain && 10 * by_32 < 17 * by_64)) {
+        p.way = kKvqPair;
+    } else if (E % 16 == 0 && with_norms * (p.threads == 512 ? 2 : 4) <= 160 * 1024) {
+        p.way = kKvqNorms;
+        p.lds = with_norms;
+    } else {
+        p.way = kKvqOwn;
+    }
+    return p;
+}
+
 template <int V, int TILES, int WAY>
-int run_kvq_mfma_as(const KvQuantArgs &a, int bh, int threads, size_t lds, hipStream_t s) {
+int run_kvq_mfma_as(const KvQuantArgs &a, int bh, const KvqMfmaPlan &p, hipStream_t s) {
     static KernelSetup setup;
-    if (int st = kernel_setup(reinterpret_cast<const void *>(&kv_quantize_mfma_kernel<V, TILES, WAY>), lds, false, setup)) return st;
-    kv_quantize_mfma_kernel<V, TILES, WAY><<<dim3(bh, (a.n_new + a.tokens - 1) / a.tokens, 2), threads, lds, s>>>(a);
+    if (int st = kernel_setup(reinterpret_cast<const void *>(&kv_quantize_mfma_kernel<V, TILES, WAY>), p.lds, false, setup)) return st;
+    kv_quantize_mfma_kernel<V, TILES, WAY><<<dim3(bh, (a.n_new + a.tokens - 1) / a.tokens, 2), p.threads, p.lds, s>>>(a);
     return launch_status();
 }
 
 template <int V, int TILES>
-int run_kvq_mfma(const KvQuantArgs &a, int bh, hipStream_t s) {
-    const size_t lds = (size_t)a.G * 32 * TILES * V * sizeof(half_t) + (((size_t)a.G + 3) & ~(size_t)3) * 4 + (size_t)a.tokens * a.P;
-    // a CU holds 16 wavefronts of this kernel: two workgroups of 8 where 64 KiB of codebooks are staged, four of 4 otherwise
-    const int threads = 4 * lds > 160 * 1024 ? 512 : 256;
-    // Two lanes per item where a wavefront has 32 items of a group or fewer (12 tokens of 8 groups ...): 64 at a time leave half of
-    // the lanes idle.  And where a call is as long as one wavefront's chain (up to two workgroups a CU) and units of 32 spread
-    // better over the wavefronts: an iteration over 64 takes 1.7 times as long.
-    const int items = std::min(a.tokens, a.n_new) * a.PG, share = std::max(1, threads / 64 / a.G);
-    const int by_32 = ceil_div(ceil_div(items, 32), share), by_64 = ceil_div(ceil_div(items, 64), share);
-    const bool chain = (long)bh * 2 * ceil_div(a.n_new, a.tokens) <= 512;
-    if (items <= 32 * share || (chain && 10 * by_32 < 17 * by_64)) return run_kvq_mfma_as<V, TILES, kKvqPair>(a, bh, threads, lds, s);
-    // the norms, where they do not cost a workgroup per CU and no group is in part past the last entry
-    const size_t with_norms = lds + (size_t)a.G * 32 * TILES * sizeof(float);
-    if (a.E % 16 == 0 && with_norms * (threads == 512 ? 2 : 4) <= 160 * 1024) return run_kvq_mfma_as<V, TILES, kKvqNorms>(a, bh, threads, with_norms, s);
-    return run_kvq_mfma_as<V, TILES, kKvqOwn>(a, bh, threads, lds, s);
+int run_kvq_mfma(const KvQuantArgs &a, int bh, const KvqMfmaPlan &p, hipStream_t s) {
+    if (p.way == kKvqPair) return run_kvq_mfma_as<V, TILES, kKvqPair>(a, bh, p, s);
+    if (p.way == kKvqNorms) return run_kvq_mfma_as<V, TILES, kKvqNorms>(a, bh, p, s);
+    return run_kvq_mfma_as<V, TILES, kKvqOwn>(a, bh, p, s);
 }
 
 template <int V>
@@ -627,13 +658,8 @@ int run_kvq(KvQuantArgs &a, int bh, hipStream_t s) {
     if (kernel == kKvqLane) return run_kvq_lane<V>(a, bh, s);
     if (kernel == kKvqScan) {
         a.tokens = std::min(a.n_new, kQuantScanTokens);
-        // Workgroups that share the items of a token range, up to four: a wavefront takes its groups and items one after the other,
-        // each a trip to memory or a reduction, so few sequences are spread over the chip.  32 codebooks of v = 4 per head and side,
-        // H32, one token: B1 5.0 -> 3.0 us, B3 5.0 -> 4.4, four tokens 10.7 -> 7.3; beyond 768 workgroups only long chains gain (B8, one
-        // token 6.6 / 6.7; 64 codebooks of v = 2, six tokens 34.5 -> 29.3).
         const int ranges = ceil_div(a.n_new, a.tokens);
-        a.share = 1;
-        while (a.share < 4 && 16 * a.share <= a.tokens * a.P && (long)bh * 4 * ranges * a.share <= (a.tokens * a.P >= 128 * a.share ? 1024 : 768)) a.share *= 2;
+        a.share = kvq_share(bh, ranges, a.tokens * a.P);
         if (a.share > 1)
             kv_quantize_scan_kernel<V, true><<<dim3(bh, ranges, 2 * a.share), 512, 0, s>>>(a);
         else
@@ -641,14 +667,31 @@ int run_kvq(KvQuantArgs &a, int bh, hipStream_t s) {
         return launch_status();
     }
     a.pg_inverse = kvq_inverse(a.PG);
-    a.tokens = kvq_mfma_tokens(bh, a.n_new);
-    if (a.E <= 32) return run_kvq_mfma<V, 1>(a, bh, s);
-    if (a.E <= 64) return run_kvq_mfma<V, 2>(a, bh, s);
-    if (a.E <= 128) return run_kvq_mfma<V, 4>(a, bh, s);
-    return run_kvq_mfma<V, 8>(a, bh, s);
+    const KvqMfmaPlan p = kvq_mfma_plan(bh, a.P, V, a.E, a.G, a.n_new);
+    a.tokens = p.tokens;
+    if (a.E <= 32) return run_kvq_mfma<V, 1>(a, bh, p, s);
+    if (a.E <= 64) return run_kvq_mfma<V, 2>(a, bh, p, s);
+    if (a.E <= 128) return run_kvq_mfma<V, 4>(a, bh, p, s);
+    return run_kvq_mfma<V, 8>(a, bh, p, s);
 }
 
 }  // namespace
+
+// What a call does (for tests): kernel, its variant (matrix cores), tokens per workgroup, threads, workgroups that share a token range.
+void kv_quantize_plan_of(const vq_kv_t *kv, int n_new, int out[5]) {
+    const int bh = kv->B * kv->H, P = kv->D / kv->v;
+    out[0] = kv_quantize_kernel_of(kv, n_new);
+    out[1] = 0;
+    out[2] = std::min(n_new, out[0] == kKvqScan ? kQuantScanTokens : kQuantLaneTokens);
+    out[3] = out[0] == kKvqScan ? 512 : 256;
+    out[4] = out[0] == kKvqScan ? kvq_share(bh, ceil_div(n_new, out[2]), out[2] * P) : 1;
+    if (out[0] == kKvqMfma) {
+        const KvqMfmaPlan p = kvq_mfma_plan(bh, P, kv->v, kv->n_entries, kv->cb_groups, n_new);
+        out[1] = p.way;
+        out[2] = p.tokens;
+        out[3] = p.threads;
+    }
+}
 
 int launch_kv_quantize(const vq_kv_t *kv, const void *k_new, const void *v_new, int n_new, int pos, hipStream_t s) {
     const size_t cb_bytes = (size_t)kv->cb_groups * kv->n_entries * kv->v * sizeof(half_t);

@@ -515,6 +515,23 @@ def test_kv_quantize_kernel_follows_the_amount_of_work(kw, n_new, kernel):
     assert f(ctypes.byref(kvdesc(**{**dict(T=4096), **kw})), n_new) == ("scan", "lane", "matrix").index(kernel)
 
 
+def kv_plan(kw, n_new):
+    out = (ctypes.c_int * 5)()
+    vq.lib()._ZN2vq19kv_quantize_plan_ofEPK7vq_kv_tiPi(ctypes.byref(kvdesc(**{**dict(T=4096, D=128), **kw})), n_new, out)
+    return out
+
+
+# measured, us: one workgroup per token range / the shared one
+@pytest.mark.parametrize("kw,n_new,share", [
+    (dict(B=1, H=88, D=64, v=4, cb_groups=4), 1, 1), (dict(B=1, H=74, D=64, v=8), 2, 1), (dict(B=1, H=128, v=8), 1, 1),           # 3.18 / 3.47, 3.37 / 3.66, 3.46 / 3.66
+    (dict(B=1, H=28, D=64, v=4), 1, 2), (dict(B=1, H=32, v=4, cb_groups=32), 1, 4), (dict(B=3, H=32, v=4, cb_groups=32), 1, 2),    # 5.0 / 3.0, 5.0 / 4.4
+    (dict(B=8, H=32, v=4, cb_groups=32), 1, 1),                                                                                   # 6.6 / 6.7
+])
+def test_kv_quantize_shares_a_token_range_where_that_is_faster(kw, n_new, share):
+    out = kv_plan(kw, n_new)
+    assert out[0] == 0 and out[4] == share
+
+
 def test_gemv_takes_the_faster_of_two_kernels_at_the_lines_between_them():
     """Routes on both sides of a line; each was measured as the faster one there."""
     for_gemv = lambda bs, **kw: internal("_ZN2vq20gemm_skinny_for_gemvEPK11vq_weight_ti", ctypes.byref(weight(**kw)), bs)  # noqa: E731
