@@ -541,12 +541,14 @@ int kvq_share(long bh, int ranges, int items) {
 }
 
 // The kernel with the least estimated time (us): the chain of one workgroup or the instructions of all of them (a vector
-// instruction of a wavefront: 1.63e-6 us of the chip), whichever is longer.  Over 432 measured calls (B 1 .. 64, 1 to
-// 2048 tokens, 8 to 256 entries, 1 to 64 groups, head sizes 64 to 192) the pick takes 0.5 % more than the best of the three on
-// average, 28 % at worst (16 entries, where the lanes keep calls that the matrix cores have come to do in 43 us against 51).  Some,
+// instruction of a wavefront: 1.63e-6 us of the chip), whichever is longer.  Over 10815 measured calls (B 1 .. 64, 1 to
+// 2048 tokens, 8 to 256 entries, 1 to 64 groups, head sizes 64 to 256) the pick takes 1.5 % more than the best of the three on
+// average and 25 % or more in the worst hundredth (6 % and 80 % while the scan counted as if no workgroups shared it).  Some,
 // us, scan / lane / matrix cores: one group of 256, v = 4, one token, B4 4.3 / 4.1 / 4.8,
-// B16 8.6 / 6.3 / 5.4, B64 25.2 / 16.8 / 15.9; 32 groups of 256, B4, 4 tokens 11.0 / - / 14.3, 8 tokens 18.9 / - / 14.5; 8 groups of 64,
-// B16, one token 8.6 / 4.0 / 6.7; 16 entries, v = 4, B64, 4 tokens 73 / 7.2 / 11.1, B2, 2048 tokens 1052 / 51 / 43.
+// B16 8.6 / 6.3 / 5.4, B64 25.2 / 16.8 / 15.9; 32 groups of 256, B4, 4 tokens 11.0 / - / 14.3, 22 sequence-heads, 6 tokens 5.1 / - / 13.4, 4, 10 tokens 6.6 / - / 13.1;
+// 8 groups of 64, B16, one token 8.6 / 4.0 / 6.7; 16 entries, v = 4, B64, 4 tokens 73 / 7.2 / 11.1, B2, 2048 tokens 1052 / 51 / 43.
+// Workgroups that share a chain are in each other's way: it takes up to 1.7 times what its part of the items would, and longer the more
+// instructions there are (without that, 104 sequence-heads, 15 tokens, 64 groups of 128, v = 2 came to the scan, 33.0 / - / 24.5).
 int kvq_choice(int bh, int P, int v, int E, int G, int n_new) {
     const double kInst = 1.63e-6;
     double best = 1e300;
@@ -559,9 +561,12 @@ int kvq_choice(int bh, int P, int v, int E, int G, int n_new) {
         }
     };
     const double sides = 2.0 * bh;
-    {   // a wavefront of eight takes one item after the other
-        const int tokens = std::min(n_new, kQuantScanTokens), items = tokens * P;
-        consider(kKvqScan, ceil_div(items, 8) * (0.33 + 0.045 * v), sides * ceil_div(n_new, tokens), 0.0022, items * (52.0 + 9 * v));
+    {   // a wavefront takes one item after the other
+        const int tokens = std::min(n_new, kQuantScanTokens), items = tokens * P, ranges = ceil_div(n_new, tokens), share = kvq_share(bh, ranges, items);
+        const double item = 0.33 + 0.045 * v, inst = items * (52.0 + 9 * v);
+        double chain = ceil_div(items, 8) * item;
+        if (share > 1) chain = std::min(chain, 1.6 * ceil_div(items, 8 * share) * item + 0.5 * sides * ranges * inst * kInst);
+        consider(kKvqScan, chain, sides * ranges, 0.0022 * share, inst);
     }
     if (G * E * v * 2 <= kQuantLaneBytes) {
         const int tokens = std::min(n_new, kQuantLaneTokens), items = tokens * P, log_lanes = kvq_log_lanes(items);

@@ -532,6 +532,17 @@ def test_kv_quantize_shares_a_token_range_where_that_is_faster(kw, n_new, share)
     assert out[0] == 0 and out[4] == share
 
 
+# measured, us: matrix cores or lanes / the scan that workgroups share
+@pytest.mark.parametrize("kw,n_new,kernel", [
+    (dict(B=1, H=22, v=4, cb_groups=32), 6, "scan"), (dict(B=1, H=32, v=2, cb_groups=64, n_entries=128), 9, "scan"),   # 13.4 / 5.1, 24.0 / 9.9
+    (dict(B=1, H=4, v=4, cb_groups=32), 10, "scan"), (dict(B=1, H=6, v=8), 2, "scan"),                                 # 13.1 / 6.6, 4.3 / 2.7
+    (dict(B=8, H=32, v=4, cb_groups=32), 16, "matrix"),                                                                # more workgroups than the chip holds at once
+])
+def test_kv_quantize_takes_the_fastest_kernel(kw, n_new, kernel):
+    f = vq.lib()._ZN2vq21kv_quantize_kernel_ofEPK7vq_kv_ti
+    assert f(ctypes.byref(kvdesc(**{**dict(T=4096, D=128), **kw})), n_new) == ("scan", "lane", "matrix").index(kernel)
+
+
 def test_gemv_takes_the_faster_of_two_kernels_at_the_lines_between_them():
     """Routes on both sides of a line; each was measured as the faster one there."""
     for_gemv = lambda bs, **kw: internal("_ZN2vq20gemm_skinny_for_gemvEPK11vq_weight_ti", ctypes.byref(weight(**kw)), bs)  # noqa: E731
