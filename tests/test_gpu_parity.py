@@ -1331,8 +1331,8 @@ def test_kv_quantize_hard_values(gpu_device, v, G, E, n_new, kind):
     assert np.array_equal(kd.v_codes.cpu().numpy()[:, :, 2:2 + n_new], oracle.kv_quantize(x[1], kv.v_codebooks))
 
 
-# The matrix-core kernel takes 32 items (few per wavefront) or 64 at a time, and looks at the best group of eight entries by norms
-# (E % 16 == 0 and room in LDS) or by the definition: edges of the units, and near ties inside and between groups
+# Few sequences: the scan (D = 8, and few tokens) and the matrix cores with 16 tokens per workgroup, 32 items at a time or 64 with norms:
+# edges of the units, and near ties inside and between groups of eight entries (more tokens per workgroup: the test after this one)
 @pytest.mark.parametrize("D,v,G,E", [(8, 8, 1, 256), (8, 8, 1, 250), (128, 4, 1, 256), (128, 4, 1, 240), (128, 2, 1, 256), (128, 4, 32, 256), (128, 8, 16, 64)])
 @pytest.mark.parametrize("n_new", [4, 33, 64, 129, 161])
 @pytest.mark.parametrize("apart", [0, 1, 8, 16])
@@ -1428,6 +1428,49 @@ def _random_weight_case(rng):
 
 
 @pytest.mark.parametrize("N,K,v,bits,R,E,tile,bs", [
+def kv_plan(kd, n_new):
+    """(kernel, way, tokens per workgroup, threads) of a call: what the library itself goes by."""
+    out = (ctypes.c_int * 5)()
+    vq.lib()._ZN2vq19kv_quantize_plan_ofEPK7vq_kv_tiPi(ctypes.byref(kd.desc()), n_new, out)
+    return ("scan", "lane", "matrix")[out[0]], ("pair", "own", "norms")[out[1]], out[2], out[3]
+
+
+# The matrix-core kernel by every way of looking at the best group of entries (two lanes per item, each lane its own item by the
+# definition's distances, the same by norms), every number of tiles of entries, up to 128 tokens per workgroup with one that is not full,
+# and both numbers of wavefronts; what is meant is asserted.  With twins of entries 8 further on, and without.
+@pytest.mark.parametrize("apart", [0, 8])
+@pytest.mark.parametrize("B,H,D,v,G,E,n_new,way,tokens,threads", [
+    (2, 32, 128, 4, 1, 256, 1025, "norms", 128, 256), (2, 32, 128, 4, 1, 240, 1090, "norms", 128, 256), (2, 32, 128, 2, 1, 256, 1027, "norms", 128, 256),
+    (2, 32, 128, 4, 1, 250, 1100, "own", 128, 256), (2, 32, 128, 8, 1, 256, 1033, "norms", 128, 256), (4, 32, 64, 8, 1, 201, 640, "own", 128, 256),
+    (2, 32, 128, 4, 32, 256, 1031, "own", 128, 512), (2, 32, 128, 2, 64, 256, 1026, "own", 128, 512), (2, 32, 128, 8, 16, 256, 1040, "own", 128, 512),
+    (2, 32, 256, 4, 1, 256, 1030, "norms", 128, 256), (2, 32, 128, 4, 1, 250, 513, "own", 64, 256), (1, 2, 128, 4, 1, 250, 33, "own", 16, 256),
+    (1, 2, 128, 4, 1, 250, 129, "own", 16, 256), (2, 32, 128, 4, 1, 128, 1025, "norms", 128, 256), (2, 32, 128, 4, 1, 100, 1025, "own", 128, 256),
+    (2, 32, 128, 4, 1, 64, 1025, "norms", 128, 256), (2, 32, 128, 4, 1, 50, 1025, "own", 128, 256), (16, 32, 64, 8, 8, 32, 300, "norms", 128, 256),
+    (2, 32, 128, 8, 16, 64, 600, "norms", 64, 256), (1, 2, 128, 4, 32, 250, 33, "pair", 16, 512), (1, 8, 128, 8, 16, 100, 40, "pair", 16, 256), (2, 32, 128, 8, 1, 32, 1029, "norms", 128, 256),
+])
+def test_kv_quantize_prompts_by_every_way(gpu_device, B, H, D, v, G, E, n_new, way, tokens, threads, apart):
+    rng = np.random.default_rng(9560 + E + n_new + apart)
+    T, P = n_new + 3, D // v
+    cb = rng.normal(0, 1, size=(2, H, G, E, v)).astype(np.float16)
+    if apart:
+        for e in range(E - apart):
+            if (e // apart) % 2 == 0:
+                cb[:, :, :, e + apart] = cb[:, :, :, e]
+        cb.view(np.uint16)[:, :, :, ::3, 0] += 1
+    g = torch.Generator(device=gpu_device).manual_seed(9570 + n_new)
+    x = [torch.randn((B, H, n_new, D), generator=g, device=gpu_device).to(torch.float16) for _ in range(2)]
+    codes = [torch.full((B, H, T, P), 255, dtype=torch.uint8, device=gpu_device) for _ in range(2)]
+    kd = vq.VQKVDev(B, H, D, T, v, codes[0], codes[1], dev_x(cb[0], gpu_device), dev_x(cb[1], gpu_device))
+    assert kv_plan(kd, n_new) == ("matrix", way, tokens, threads)
+    vq.vq_kv_quantize(kd, x[0], x[1], 2)
+    torch.cuda.synchronize()
+    heads = [0, H // 2, H - 1]      # (the oracle takes its time)
+    for side in range(2):
+        got, xs = codes[side].cpu().numpy(), x[side][:, heads].contiguous().cpu().numpy()
+        assert np.array_equal(got[:, heads, 2:2 + n_new], oracle.kv_quantize(xs, np.ascontiguousarray(cb[side][heads]))), side
+        assert (got[:, :, :2] == 255).all() and (got[:, :, 2 + n_new:] == 255).all(), side
+
+
     (8200, 512, 8, 8, 2, 256, None, 16),        # 257 workgroups of 32 rows, the last one with 8 rows
     (8192, 1024, 4, 8, 1, 256, None, 11),       # v = 4, batch not a power of two
     (8192, 512, 8, 12, 2, 4096, None, 16),      # packed 12-bit codes, two 64 KiB codebooks
