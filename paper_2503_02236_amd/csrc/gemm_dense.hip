@@ -258,7 +258,7 @@ __global__ __launch_bounds__(256) void gemm_dense_kernel(DenseArgs a) {
 // 0.03 % more than the better tile; 0.65 up to 9 % more).  A product of few tiles leaves CUs idle: M = 512, N = K = 4096 has 64 of the large ones (46.5 us) or 128
 // of the small (31.9); 600 x 11008 258 (two rounds, 102.9 us) or 430 (two rounds, 69.5); 1024 x 4096 52.4 / 39.7.  With as many
 // large rounds as would be full the large tile is ahead (2048 x 4096 68.6 / 81.4, 512 x 11008 55.0 / 66.7).
-static bool gemm_dense_small(int M, int N) {
+bool gemm_dense_small(int M, int N) {
     const long tn = ((long)N + 127) / 128;
     const long large = (((long)M + 255) / 256 * tn + 255) / 256, little = (((long)M + 127) / 128 * tn + 255) / 256;
     return 0.75 * little < large;

@@ -174,7 +174,8 @@ int launch_dequant_ordered(const vq_weight_t *w, half_t *W, hipStream_t s);
 bool gemm_tiles_fits(int K);
 double gemm_tiles_time(int M, int N, int K, int *pick);
 int launch_gemm_tiles(const half_t *X, const half_t *W, const half_t *scale, half_t *Y, int M, int N, int K, int pick, hipStream_t s);
-// ... or in rows (K too long for the 32-bit offsets of the above)
+// ... or in rows (K too long for the 32-bit offsets of the above); small: by 128 x 128 tiles, not 256 x 128
+bool gemm_dense_small(int M, int N);
 int launch_gemm_dense(const half_t *A, const half_t *B, const half_t *scale, half_t *C, int M, int N, int K,
                       hipStream_t s);
 bool gemv_mfma_batch_supported(const vq_weight_t *const *w, int count);

@@ -826,7 +826,7 @@ def test_gemm_config4_full_size_sampled_columns(gpu_device, N, v):
 
 
 # The two-stage product at ragged sizes: three and four codebooks always take it, at any size (one K block, N of one and
-# of two tiles, rows of Y 16-byte aligned and not, two to five M tiles; the last two sizes take the larger tile).
+# of two tiles, rows of Y 16-byte aligned and not, several M tiles; the tile is chosen by estimated time, test_gemm_tiles runs every one).
 @pytest.mark.parametrize("M,N,K,v,bits,R", [(300, 130, 256, 8, 8, 4), (1025, 64, 64, 8, 8, 4), (700, 200, 320, 8, 8, 3), (257, 136, 128, 4, 8, 4),
                                             (257, 520, 256, 4, 16, 3), (1990, 3013, 64, 8, 8, 3), (1990, 3016, 192, 8, 8, 4)])
 def test_gemm_two_stage_ragged(gpu_device, M, N, K, v, bits, R):
@@ -874,6 +874,78 @@ def test_gemm_tiles(gpu_device, M, N, K, pick):
     torch.cuda.synchronize()
     want = X.double().cpu().numpy() @ W.double().cpu().numpy().T * (1 if scale is None else scale.double().cpu().numpy())
     assert_close(Y[:M], want, f"tile {pick} {M}x{N}x{K}")
+    assert (Y[M] == 7).all()
+
+
+# The second stage for a K beyond 2^22 by itself, at the edges of its two tiles (128 x 128, and 256 x 128 where the last sizes fill the chip
+# with them), with one stage of K, with as many as its ring has and with more; rows of Y 16-byte aligned and not
+@pytest.mark.parametrize("M,N,K,small", [(1, 1, 64, True), (129, 37, 128, True), (257, 136, 192, True), (300, 513, 448, True), (128, 128, 320, True),
+                                         (1990, 3013, 64, False), (1990, 3016, 320, False), (2048, 4096, 192, False)])
+@pytest.mark.parametrize("scaled", [False, True])
+def test_gemm_dense(gpu_device, M, N, K, small, scaled):
+    l = vq.lib()
+    l._ZN2vq16gemm_dense_smallEii.restype = ctypes.c_bool
+    assert l._ZN2vq16gemm_dense_smallEii(M, N) == small
+    g = torch.Generator(device=gpu_device).manual_seed(4795 + M + K)
+    X = torch.randn((M, K), generator=g, device=gpu_device).to(torch.float16)
+    W = (torch.randn((N, K), generator=g, device=gpu_device) * 0.05).to(torch.float16)
+    scale = (torch.rand(N, generator=g, device=gpu_device) + 0.5).to(torch.float16) if scaled else None
+    Y = torch.full((M + 1, N), 7.0, dtype=torch.float16, device=gpu_device)
+    ptr = lambda t: ctypes.c_void_p(0 if t is None else t.data_ptr())  # noqa: E731
+    torch.cuda.synchronize()
+    assert l._ZN2vq17launch_gemm_denseEPKDF16_S1_S1_PDF16_iiiP12ihipStream_t(ptr(X), ptr(W), ptr(scale), ptr(Y), M, N, K, ptr(None)) == 0
+    torch.cuda.synchronize()
+    want = X.double().cpu().numpy() @ W.double().cpu().numpy().T * (1 if scale is None else scale.double().cpu().numpy())
+    assert_close(Y[:M], want, f"dense {M}x{N}x{K}")
+    assert (Y[M] == 7).all()
+
+
+def _product_in_pieces(X, W, scale):
+    """X W^T in 64 bits on the GPU, over pieces of a very long K."""
+    want = torch.zeros((X.shape[0], W.shape[0]), dtype=torch.float64, device=X.device)
+    for k in range(0, X.shape[1], 1 << 18):
+        want += X[:, k:k + (1 << 18)].double() @ W[:, k:k + (1 << 18)].double().t()
+    return (want if scale is None else want * scale.double()).cpu().numpy()
+
+
+# Both sides of K = 2^22, up to which the second stage has 32-bit offsets in a tile (256 rows of X are 2 GiB there), every kind of
+# dequantization; 24 columns are a whole strip of the ordered weight and a narrower one.  (One or two codebooks take one pass up to 2^22.)
+@pytest.mark.parametrize("K,v,bits,R,E", [(1 << 22, 8, 8, 3, 256), (1 << 22, 4, 16, 3, 300), ((1 << 22) + 64, 8, 8, 3, 256), ((1 << 22) + 64, 8, 16, 1, 5001),
+                                          ((1 << 22) + 64, 4, 8, 2, 200)])
+def test_gemm_two_stage_at_the_limit_of_its_offsets(gpu_device, K, v, bits, R, E):
+    M, N = 257, 24
+    one_pass = vq.lib()._ZN2vq13gemm_one_passEPK11vq_weight_ti
+    one_pass.restype = ctypes.c_bool
+    fits = vq.lib()._ZN2vq15gemm_tiles_fitsEi
+    fits.restype = ctypes.c_bool
+    g = torch.Generator(device=gpu_device).manual_seed(4797 + v)
+    codes = torch.randint(0, E, (N, K // v, R), generator=g, device=gpu_device, dtype=torch.int32).to(torch.uint16 if bits == 16 else torch.uint8)
+    w = vq.VQWeightDev(N, K, v, bits, codes, (torch.randn((R, E, v), generator=g, device=gpu_device) * 0.02).to(torch.float16),
+                       (torch.rand(N, generator=g, device=gpu_device) + 0.5).to(torch.float16))
+    assert not one_pass(ctypes.byref(w.desc()), M) and fits(K) == (K <= 1 << 22) and vq.vq_gemm_workspace(w, M) == N * K * 2
+    X = torch.randn((M, K), generator=g, device=gpu_device, dtype=torch.float16)
+    Y = vq.vq_gemm(w, X)
+    assert_close(Y, _product_in_pieces(X, vq.vq_dequant(w, out_fp32=False), w.scale), f"K {K} v {v} R {R}")
+
+
+# ... and the tiles with the longest offsets: 256 rows of X, and 256 columns of the weight
+@pytest.mark.parametrize("pick,M,N", [(0, 256, 24), (1, 300, 72), (2, 128, 250)])
+def test_gemm_tiles_at_the_limit_of_their_offsets(gpu_device, pick, M, N):
+    K = 1 << 22
+    g = torch.Generator(device=gpu_device).manual_seed(4799 + pick)
+    X = torch.randn((M, K), generator=g, device=gpu_device, dtype=torch.float16)
+    W = torch.randn((N, K), generator=g, device=gpu_device, dtype=torch.float16) * 0.02
+    pieces = []     # operand order: strips of 16 columns, fragments of 32 k, groups of 8
+    for n in range(0, N, 16):
+        strip = W[n:n + 16]
+        pieces.append(strip.view(strip.shape[0], K // 8, 8).transpose(0, 1).reshape(-1))
+    ordered = torch.cat(pieces)
+    Y = torch.full((M + 1, N), 7.0, dtype=torch.float16, device=gpu_device)
+    ptr = lambda t: ctypes.c_void_p(0 if t is None else t.data_ptr())  # noqa: E731
+    torch.cuda.synchronize()
+    assert vq.lib()._ZN2vq17launch_gemm_tilesEPKDF16_S1_S1_PDF16_iiiiP12ihipStream_t(ptr(X), ptr(ordered), ptr(None), ptr(Y), M, N, K, pick, ptr(None)) == 0
+    torch.cuda.synchronize()
+    assert_close(Y[:M], _product_in_pieces(X, W, None), f"tile {pick} {M}x{N}x{K}")
     assert (Y[M] == 7).all()
 
 
@@ -1356,6 +1428,49 @@ def test_kv_quantize_units_and_near_ties(gpu_device, D, v, G, E, n_new, apart):
         assert (got[:, :, :2] == 255).all() and (got[:, :, 2 + n_new:] == 255).all(), side
 
 
+def kv_plan(kd, n_new):
+    """(kernel, way, tokens per workgroup, threads) of a call: what the library itself goes by."""
+    out = (ctypes.c_int * 5)()
+    vq.lib()._ZN2vq19kv_quantize_plan_ofEPK7vq_kv_tiPi(ctypes.byref(kd.desc()), n_new, out)
+    return ("scan", "lane", "matrix")[out[0]], ("pair", "own", "norms")[out[1]], out[2], out[3]
+
+
+# The matrix-core kernel by every way of looking at the best group of entries (two lanes per item, each lane its own item by the
+# definition's distances, the same by norms), every number of tiles of entries, up to 128 tokens per workgroup with one that is not full,
+# and both numbers of wavefronts; what is meant is asserted.  With twins of entries 8 further on, and without.
+@pytest.mark.parametrize("apart", [0, 8])
+@pytest.mark.parametrize("B,H,D,v,G,E,n_new,way,tokens,threads", [
+    (2, 32, 128, 4, 1, 256, 1025, "norms", 128, 256), (2, 32, 128, 4, 1, 240, 1090, "norms", 128, 256), (2, 32, 128, 2, 1, 256, 1027, "norms", 128, 256),
+    (2, 32, 128, 4, 1, 250, 1100, "own", 128, 256), (2, 32, 128, 8, 1, 256, 1033, "norms", 128, 256), (4, 32, 64, 8, 1, 201, 640, "own", 128, 256),
+    (2, 32, 128, 4, 32, 256, 1031, "own", 128, 512), (2, 32, 128, 2, 64, 256, 1026, "own", 128, 512), (2, 32, 128, 8, 16, 256, 1040, "own", 128, 512),
+    (2, 32, 256, 4, 1, 256, 1030, "norms", 128, 256), (2, 32, 128, 4, 1, 250, 513, "own", 64, 256), (1, 2, 128, 4, 1, 250, 33, "own", 16, 256),
+    (1, 2, 128, 4, 1, 250, 129, "own", 16, 256), (2, 32, 128, 4, 1, 128, 1025, "norms", 128, 256), (2, 32, 128, 4, 1, 100, 1025, "own", 128, 256),
+    (2, 32, 128, 4, 1, 64, 1025, "norms", 128, 256), (2, 32, 128, 4, 1, 50, 1025, "own", 128, 256), (16, 32, 64, 8, 8, 32, 300, "norms", 128, 256),
+    (2, 32, 128, 8, 16, 64, 600, "norms", 64, 256), (1, 2, 128, 4, 32, 250, 33, "pair", 16, 512), (1, 8, 128, 8, 16, 100, 40, "pair", 16, 256), (2, 32, 128, 8, 1, 32, 1029, "norms", 128, 256),
+])
+def test_kv_quantize_prompts_by_every_way(gpu_device, B, H, D, v, G, E, n_new, way, tokens, threads, apart):
+    rng = np.random.default_rng(9560 + E + n_new + apart)
+    T, P = n_new + 3, D // v
+    cb = rng.normal(0, 1, size=(2, H, G, E, v)).astype(np.float16)
+    if apart:
+        for e in range(E - apart):
+            if (e // apart) % 2 == 0:
+                cb[:, :, :, e + apart] = cb[:, :, :, e]
+        cb.view(np.uint16)[:, :, :, ::3, 0] += 1
+    g = torch.Generator(device=gpu_device).manual_seed(9570 + n_new)
+    x = [torch.randn((B, H, n_new, D), generator=g, device=gpu_device).to(torch.float16) for _ in range(2)]
+    codes = [torch.full((B, H, T, P), 255, dtype=torch.uint8, device=gpu_device) for _ in range(2)]
+    kd = vq.VQKVDev(B, H, D, T, v, codes[0], codes[1], dev_x(cb[0], gpu_device), dev_x(cb[1], gpu_device))
+    assert kv_plan(kd, n_new) == ("matrix", way, tokens, threads)
+    vq.vq_kv_quantize(kd, x[0], x[1], 2)
+    torch.cuda.synchronize()
+    heads = [0, H // 2, H - 1]      # (the oracle takes its time)
+    for side in range(2):
+        got, xs = codes[side].cpu().numpy(), x[side][:, heads].contiguous().cpu().numpy()
+        assert np.array_equal(got[:, heads, 2:2 + n_new], oracle.kv_quantize(xs, np.ascontiguousarray(cb[side][heads]))), side
+        assert (got[:, :, :2] == 255).all() and (got[:, :, 2 + n_new:] == 255).all(), side
+
+
 # head sizes other than 128: sub-vectors per group that are no power of two, one sub-vector per group, and the most LDS that
 # staged codebooks take (D = 256: 128 KiB); a last workgroup that is not full
 @pytest.mark.parametrize("D,v,G,E", [(96, 4, 1, 256), (96, 8, 4, 256), (80, 8, 2, 250), (192, 2, 32, 256), (40, 2, 5, 200), (24, 8, 3, 256),
@@ -1428,49 +1543,6 @@ def _random_weight_case(rng):
 
 
 @pytest.mark.parametrize("N,K,v,bits,R,E,tile,bs", [
-def kv_plan(kd, n_new):
-    """(kernel, way, tokens per workgroup, threads) of a call: what the library itself goes by."""
-    out = (ctypes.c_int * 5)()
-    vq.lib()._ZN2vq19kv_quantize_plan_ofEPK7vq_kv_tiPi(ctypes.byref(kd.desc()), n_new, out)
-    return ("scan", "lane", "matrix")[out[0]], ("pair", "own", "norms")[out[1]], out[2], out[3]
-
-
-# The matrix-core kernel by every way of looking at the best group of entries (two lanes per item, each lane its own item by the
-# definition's distances, the same by norms), every number of tiles of entries, up to 128 tokens per workgroup with one that is not full,
-# and both numbers of wavefronts; what is meant is asserted.  With twins of entries 8 further on, and without.
-@pytest.mark.parametrize("apart", [0, 8])
-@pytest.mark.parametrize("B,H,D,v,G,E,n_new,way,tokens,threads", [
-    (2, 32, 128, 4, 1, 256, 1025, "norms", 128, 256), (2, 32, 128, 4, 1, 240, 1090, "norms", 128, 256), (2, 32, 128, 2, 1, 256, 1027, "norms", 128, 256),
-    (2, 32, 128, 4, 1, 250, 1100, "own", 128, 256), (2, 32, 128, 8, 1, 256, 1033, "norms", 128, 256), (4, 32, 64, 8, 1, 201, 640, "own", 128, 256),
-    (2, 32, 128, 4, 32, 256, 1031, "own", 128, 512), (2, 32, 128, 2, 64, 256, 1026, "own", 128, 512), (2, 32, 128, 8, 16, 256, 1040, "own", 128, 512),
-    (2, 32, 256, 4, 1, 256, 1030, "norms", 128, 256), (2, 32, 128, 4, 1, 250, 513, "own", 64, 256), (1, 2, 128, 4, 1, 250, 33, "own", 16, 256),
-    (1, 2, 128, 4, 1, 250, 129, "own", 16, 256), (2, 32, 128, 4, 1, 128, 1025, "norms", 128, 256), (2, 32, 128, 4, 1, 100, 1025, "own", 128, 256),
-    (2, 32, 128, 4, 1, 64, 1025, "norms", 128, 256), (2, 32, 128, 4, 1, 50, 1025, "own", 128, 256), (16, 32, 64, 8, 8, 32, 300, "norms", 128, 256),
-    (2, 32, 128, 8, 16, 64, 600, "norms", 64, 256), (1, 2, 128, 4, 32, 250, 33, "pair", 16, 512), (1, 8, 128, 8, 16, 100, 40, "pair", 16, 256), (2, 32, 128, 8, 1, 32, 1029, "norms", 128, 256),
-])
-def test_kv_quantize_prompts_by_every_way(gpu_device, B, H, D, v, G, E, n_new, way, tokens, threads, apart):
-    rng = np.random.default_rng(9560 + E + n_new + apart)
-    T, P = n_new + 3, D // v
-    cb = rng.normal(0, 1, size=(2, H, G, E, v)).astype(np.float16)
-    if apart:
-        for e in range(E - apart):
-            if (e // apart) % 2 == 0:
-                cb[:, :, :, e + apart] = cb[:, :, :, e]
-        cb.view(np.uint16)[:, :, :, ::3, 0] += 1
-    g = torch.Generator(device=gpu_device).manual_seed(9570 + n_new)
-    x = [torch.randn((B, H, n_new, D), generator=g, device=gpu_device).to(torch.float16) for _ in range(2)]
-    codes = [torch.full((B, H, T, P), 255, dtype=torch.uint8, device=gpu_device) for _ in range(2)]
-    kd = vq.VQKVDev(B, H, D, T, v, codes[0], codes[1], dev_x(cb[0], gpu_device), dev_x(cb[1], gpu_device))
-    assert kv_plan(kd, n_new) == ("matrix", way, tokens, threads)
-    vq.vq_kv_quantize(kd, x[0], x[1], 2)
-    torch.cuda.synchronize()
-    heads = [0, H // 2, H - 1]      # (the oracle takes its time)
-    for side in range(2):
-        got, xs = codes[side].cpu().numpy(), x[side][:, heads].contiguous().cpu().numpy()
-        assert np.array_equal(got[:, heads, 2:2 + n_new], oracle.kv_quantize(xs, np.ascontiguousarray(cb[side][heads]))), side
-        assert (got[:, :, :2] == 255).all() and (got[:, :, 2 + n_new:] == 255).all(), side
-
-
     (8200, 512, 8, 8, 2, 256, None, 16),        # 257 workgroups of 32 rows, the last one with 8 rows
     (8192, 1024, 4, 8, 1, 256, None, 11),       # v = 4, batch not a power of two
     (8192, 512, 8, 12, 2, 4096, None, 16),      # packed 12-bit codes, two 64 KiB codebooks
