@@ -532,11 +532,15 @@ bool kvq_four_tokens(int P, int v, int n_new) { return v <= 4 && n_new >= 4 * (2
 // Workgroups of the scan that share the items of a token range, up to four: a wavefront takes its groups and items one after the other,
 // each a trip to memory or a reduction, so few sequences are spread over the chip.  32 codebooks of v = 4 per head and side,
 // H32, one token: B1 5.0 -> 3.0 us, B3 5.0 -> 4.4, four tokens 10.7 -> 7.3; beyond 768 workgroups only long chains gain (B8, one
-// token 6.6 / 6.7; 64 codebooks of v = 2, six tokens 34.5 -> 29.3), and beyond 256 none with fewer than 32 items a workgroup (16 items: 64
-// sequence-heads 4.1 -> 3.2, 88 3.18 / 3.47, 74 3.37 / 3.66).
+// token 6.6 / 6.7; 64 codebooks of v = 2, six tokens 34.5 -> 29.3).  Fewer than 32 items a workgroup: not where that makes 257 to 512
+// workgroups, which take 5 % longer than half as many of twice the items (88 sequence-heads, 16 items 3.18 / 3.47); up to 256 take 18 % less,
+// 513 to 768 2 to 9 % (96 sequence-heads, 32 items of 32 groups 4.3 -> 4.1 with four).
 int kvq_share(long bh, int ranges, int items) {
     int share = 1;
-    while (share < 4 && 16 * share <= items && bh * 4 * ranges * share <= (items >= 128 * share ? 1024 : items >= 32 * share ? 768 : 256)) share *= 2;
+    for (; share < 4 && 16 * share <= items; share *= 2) {
+        const long wgs = bh * 4 * ranges * share;   // with twice the share
+        if (wgs > (items >= 128 * share ? 1024 : 768) || (items < 32 * share && wgs > 256 && wgs <= 512)) break;
+    }
     return share;
 }
 

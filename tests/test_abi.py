@@ -524,7 +524,7 @@ def kv_plan(kw, n_new):
 # measured, us: one workgroup per token range / the shared one
 @pytest.mark.parametrize("kw,n_new,share", [
     (dict(B=1, H=88, D=64, v=4, cb_groups=4), 1, 1), (dict(B=1, H=74, D=64, v=8), 2, 1), (dict(B=1, H=128, v=8), 1, 1),           # 3.18 / 3.47, 3.37 / 3.66, 3.46 / 3.66
-    (dict(B=1, H=28, D=64, v=4), 1, 2), (dict(B=1, H=32, v=4, cb_groups=32), 1, 4), (dict(B=3, H=32, v=4, cb_groups=32), 1, 2),    # 5.0 / 3.0, 5.0 / 4.4
+    (dict(B=1, H=28, D=64, v=4), 1, 2), (dict(B=1, H=32, v=4, cb_groups=32), 1, 4), (dict(B=3, H=32, v=4, cb_groups=32), 1, 4),    # 5.0 / 3.0, 5.0 / 4.1 (shared by two 4.3)
     (dict(B=8, H=32, v=4, cb_groups=32), 1, 1),                                                                                   # 6.6 / 6.7
 ])
 def test_kv_quantize_shares_a_token_range_where_that_is_faster(kw, n_new, share):
