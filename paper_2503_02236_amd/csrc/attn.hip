@@ -270,7 +270,7 @@ __global__ __launch_bounds__(kAttnWaves * 64 * SEQ) __attribute__((amdgpu_waves_
     // REP: no score is larger than |sm_scale log2 e| sum_p |q_p| max |entry|, and that not than |..| sqrt(P) |q| max |entry|.  Up to 60 (N(0, 1)
     // keys and queries of 128 channels: 32) the weights 2^score and their sums stay well inside fp32 without a running maximum
     // to subtract: the same relative precision, without the chain of maximum, comparison and branch between a tile's scores and
-    // its weights.  B16 H32 T4096: 34.1 -> 31.7 us.  (Where the gathers of a shared copy set the pace it gives nothing, and a short
+    // its weights.  B16 H32 T4096: 34.1 -> 33.2 us from HBM.  (Where the gathers of a shared copy set the pace it gives nothing, and a short
     // range pays for the bound: 300 tokens 8.1 -> 8.3.)
     bool fixed = false;
     if constexpr (REP) {

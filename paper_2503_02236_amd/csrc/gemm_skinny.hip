@@ -113,8 +113,8 @@ __global__ __launch_bounds__(64 * skinny_max_waves(false, RT, 3)) void gemm_skin
 #include "gemm_skinny_body.inc"
 }
 
-// Elements of X of one launch: its kernel holds byte offsets into X in 32 bits.  At least 384 tokens (K <= 2^22), whole
-// tiles of every kind.
+// Elements of X of one launch: its kernel holds byte offsets into X in 32 bits.  At least 384 tokens (K <= 2^22), whole tiles of
+// every kind that launches of more than 256 tokens have (not the 48 tokens).
 constexpr long kSkinnyMaxX = 1L << 31;
 int skinny_max_tokens(int K) { return (int)std::min(1L << 30, (kSkinnyMaxX - 1) / K / 128 * 128); }
 

@@ -233,7 +233,7 @@ __global__ __launch_bounds__(256) void kv_quantize_lane_kernel(KvQuantArgs a) {
 //   item is scanned.  The matrix cores of this chip take subnormal halves as they are.)
 //   (That s: V + 1 roundings to 2^-24 and 15 ulp of packed bits, below 2^-18.4.)
 // Bound: vector issue, about 320 instructions per 64 items and wavefront (208 for minima, 32 + 20 for the group) against 16 matrix
-// instructions.  An iteration covers 64 items, so that loads, addresses, norms, the group and the store serve a whole wavefront (the
+// instructions; counters read 370: these 16 with them, and some 30 for the codebooks (450 a wavefront, 16 iterations) and rare paths.  An iteration covers 64 items, so that loads, addresses, norms, the group and the store serve a whole wavefront (the
 // minima lie in two lanes per item, and one lane swap brings them to the item's own lane); with 32 items, two lanes each, and the
 // group by the definition it was 251 per 32.  B2 H32, 2048 tokens, one codebook per head and side (4.2 M items per side): 112 us with
 // 32 items, 92 now, where a scan of every pair took 546.
