@@ -262,7 +262,9 @@ bool gemm_tiles_fits(int K) { return K % 64 == 0 && K <= (1 << 22); }
 // Estimated time in us and the tile with the least, by measurement of all eight over 156 products (N 256 .. 11008, K 512 .. 11008,
 // 257 .. 4096 tokens): a workgroup alone on its CU takes kAlone[0] per 4096 k and kAlone[1] besides; with more of the 256 CUs busy the
 // chip clocks down, to 0.87 of that speed when all are; more than one workgroup a CU, where two or more fit, overlap a
-// little (kOverlap).  The tile picked takes 0.2 % more than the best on average, 8 % at most.
+// little (kOverlap).  Over 2850 other products (N 64 .. 11008, K 256 .. 11008, 257 .. 4096 tokens) the tile picked takes 1.1 % more than the best
+// on average and 16 % or more in the worst hundredth: below K = 512, where the output counts, and for weights of more than 64 M elements,
+// which a tile of few columns reads from memory too often (11008 x 11008, 677 tokens 167 / 224); elsewhere 0.7 % and 10 %.
 double gemm_tiles_time(int M, int N, int K, int *pick) {
     static const int kTile[8][2] = {{256, 256}, {256, 192}, {128, 256}, {128, 192}, {128, 128}, {128, 64}, {64, 128}, {64, 64}};
     static const double kAlone[8][2] = {{65, 7}, {55, 6}, {37, 3.2}, {30, 3.2}, {22.5, 1.6}, {17.5, 1.8}, {15.5, 1.8}, {11.8, 1.6}};
