@@ -180,8 +180,8 @@ constexpr SkinnyTile kL2Tiles[] = {{1, 1}, {1, 2}, {1, 4}, {2, 4}, {1, 8}, {2, 8
 // ones fill in; from L2 all workgroups share the dies' L2s, so fewer than 256 of them are not that much faster.
 // The constants were fitted to 210 measured shapes (six formats, N 256 .. 11008, M 17 .. 256) x 6 tiles; over 1950 others (15
 // formats, N 16 .. 11008, K 256 .. 11008) the tile that this picks takes 2.7 % more than the best one on average and 43 % or more in the
-// worst hundredth, mostly below K = 512 (8.9 %), where a workgroup has fewer wavefronts than its tile could feed; K > 2048 1.1 %.  Staging of the codebooks, the same for every
-// tile, counts only in the estimate (*clocks).
+// worst hundredth, mostly below K = 512 (8.9 %), where a workgroup has fewer wavefronts than its tile could feed; K > 2048 1.1 %.  Staging
+// of the codebooks, the same for every tile, counts only in the estimate (*us).
 int skinny_tile(const vq_weight_t *w, int M, bool l2, double staging = 0, double *us = nullptr) {
     int best = 0;
     double best_cost = 1e300;
